@@ -27,9 +27,6 @@ void free_ws(AtreeWs &w)
     hipFree(w.slots);
     hipFree(w.mp);
     hipFree(w.lo);
-    hipFree(w.binom);
-    hipFree(w.binom16);
-    hipFree(w.binom32);
     hipFree(w.mp2);
     hipFree(w.lo2);
     hipFree(w.adj);
@@ -264,21 +261,6 @@ int ensure_ws(fmm_atree *t, int p, int precision)
         return rc;
     }
     w.coef_cap = coef;
-    auto pascal = [](int nb) {
-        std::vector<double> b((size_t)nb * nb, 0.0);
-        for (int a = 0; a < nb; ++a) {
-            b[(size_t)a * nb] = 1.0;
-            for (int k = 1; k <= a; ++k)
-                b[(size_t)a * nb + k] = b[(size_t)(a - 1) * nb + k - 1] + (k < a ? b[(size_t)(a - 1) * nb + k] : 0.0);
-        }
-        return b;
-    };
-    if ((rc = upload(&w.binom, pascal(2 * p + 1), "binomial table")) ||
-        (rc = upload(&w.binom16, pascal(33), "binomial table")) ||
-        (rc = upload(&w.binom32, pascal(65), "binomial table"))) {
-        free_ws(w);
-        return rc;
-    }
     w.p = p;
     w.precision = precision;
     return FMM_OK;
@@ -366,12 +348,12 @@ int choose_occupancy(const fmm_atree *t, int precision, bool concurrent)
     return (ratio >= 0.4 && ratio <= 1.6) ? 5 : 6;
 }
 
-// Up to 16 terms the M2L runs on MFMA with the shared operator tables and the tree's M2L
-// plan (made on the first such call, synchronising s); tabs stays NULL otherwise.
+// The translations' operator tables (shared) and the tree's M2L plan (made on the first
+// call, synchronising s); a tree without expansions needs neither (tabs NULL).
 int ensure_m2l_plan(fmm_atree *t, int p, hipStream_t s, const Tables *&tabs)
 {
     tabs = nullptr;
-    if (p > 16 || t->sizes[FMM_AT_DEEPEST] < 2) return FMM_OK;
+    if (t->sizes[FMM_AT_DEEPEST] < 2) return FMM_OK;
     std::string err;
     const Tables *tb = nullptr;
     int rc = shared_tables(t->device, p, &tb, err);

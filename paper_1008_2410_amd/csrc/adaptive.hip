@@ -8,6 +8,7 @@
 // Complex charge c_j = -i Gamma_j / (2 pi); conjugate velocity W = u - i v.
 #include "adaptive_internal.h"
 #include "device_common.h"
+#include "translate.h"
 
 #include <cmath>
 
@@ -132,237 +133,12 @@ __global__ __launch_bounds__(64) void at_p2m_kernel(const int *__restrict__ cell
             if (m < p) mp[(int64_t)k * p + m] = acc[m];
 }
 
-// M2M (stage 5) into the split cells of one level, one thread per (cell, m):
-//   A_m = sum_children sum_{k<=m} C(m,k) d^(m-k) 2^-k a_k,  d = (c_child - c_parent)/w_parent.
-__global__ __launch_bounds__(256) void at_m2m_kernel(const int *__restrict__ cells, int ncells,
-                                                      const int4 *__restrict__ child, const double *__restrict__ binom,
-                                                      int nb, int p, double2 *__restrict__ mp)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ncells * p) return;
-    const int k = cells[t / p], m = t % p;
-    const int4 ch = child[k];
-    const int cq[4] = {ch.x, ch.y, ch.z, ch.w};
-    double2 acc = make_double2(0.0, 0.0);
-    for (int q = 0; q < 4; ++q) {
-        const int c = cq[q];
-        if (c < 0) continue;
-        const double2 d = make_double2(((q & 1) - 0.5) * 0.5, ((q >> 1) - 0.5) * 0.5);
-        double2 pw = make_double2(1.0, 0.0);
-        for (int kk = m; kk >= 0; --kk) {
-            const double f = binom[m * nb + kk] * ldexp(1.0, -kk);
-            const double2 a = mp[(int64_t)c * p + kk];
-            const double2 term = cmul<double>(a, pw);
-            acc.x = fma(f, term.x, acc.x);
-            acc.y = fma(f, term.y, acc.y);
-            pw = cmul<double>(pw, d);
-        }
-    }
-    mp[(int64_t)k * p + m] = acc;
-}
-
-// Stage 6 for every cell of level >= 2 in one launch (its sources need only the
-// multipoles, complete after the upward pass), one thread per cell, PMAX terms
-// (coefficients m >= p enter as zero; the binomial table is sized for PMAX):
-// M2L from V, with u = 1/delta, delta = (c - c_S)/w and a~_m = u^m a_m(S),
-//   b_l = sum_S (-1)^l u^(l+1) sum_m C(l+m,m) a~_m;
-// P2L from X,  b_l += -sum_{j in A} c_j u_j^(l+1),  u_j = w/(z_j - c).
-// Up to 16 terms the cell's locals, the scaled source coefficients and the loads in flight
-// fit in 168 VGPRs with a 40-byte spill: 3 wavefronts per SIMD instead of 2 hide more of
-// the gather latency (clustered tree, 2^24 particles: 6.02 against 6.18 ms per evaluation).
-template <int PMAX, bool CPLX>
-__global__ __launch_bounds__(64, PMAX <= 16 ? 3 : 1) void at_m2l_kernel(int first, int ncells, const int4 *__restrict__ cell,
-                                                     const int *__restrict__ v_off, const int *__restrict__ v_idx,
-                                                     const int *__restrict__ x_off, const int *__restrict__ x_idx,
-                                                     const int2 *__restrict__ range, const double2 *__restrict__ xy,
-                                                     const double *__restrict__ gamma, const double2 *__restrict__ q,
-                                                     double x0, double y0, double side,
-                                                     const double *__restrict__ binom, int p,
-                                                     const double2 *__restrict__ mp, double2 *__restrict__ lo)
-{
-    constexpr int NB = 2 * PMAX + 1;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ncells) return;
-    const int k = first + t;
-    const int4 c = cell[k];
-    double2 b[PMAX];
-#pragma unroll
-    for (int l = 0; l < PMAX; ++l) b[l] = make_double2(0.0, 0.0);
-    for (int e = v_off[k]; e < v_off[k + 1]; ++e) {
-        const int S = v_idx[e];
-        const int4 cs = cell[S];
-        const double2 u = cinv(make_double2((double)(c.y - cs.y), (double)(c.z - cs.z)));
-        const double2 *a = mp + (int64_t)S * p;
-        double2 at[PMAX];
-        double2 pw = make_double2(1.0, 0.0);
-#pragma unroll
-        for (int m = 0; m < PMAX; ++m) {
-            const double2 am = m < p ? a[m] : make_double2(0.0, 0.0);
-            at[m] = cmul<double>(am, pw);
-            pw = cmul<double>(pw, u);
-        }
-        double2 ul = u;
-#pragma unroll
-        for (int l = 0; l < PMAX; ++l) {
-            double2 sum = make_double2(0.0, 0.0);
-#pragma unroll
-            for (int m = 0; m < PMAX; ++m) {
-                const double cb = binom[(l + m) * NB + m];
-                sum.x = fma(cb, at[m].x, sum.x);
-                sum.y = fma(cb, at[m].y, sum.y);
-            }
-            const double2 tv = cmul<double>(ul, sum);
-            const double sg = (l & 1) ? -1.0 : 1.0;
-            b[l].x = fma(sg, tv.x, b[l].x);
-            b[l].y = fma(sg, tv.y, b[l].y);
-            ul = cmul<double>(ul, u);
-        }
-    }
-    if (x_off[k] < x_off[k + 1]) {
-        const double rw = 1.0 / ldexp(side, -c.x);
-        const double2 ctr = cell_centre(x0, y0, side, c);
-        for (int e = x_off[k]; e < x_off[k + 1]; ++e) {
-            const int2 r = range[x_idx[e]];
-            for (int j = r.x; j < r.x + r.y; ++j) {
-                const double2 z = xy[j];
-                const double2 u = cinv(make_double2((z.x - ctr.x) * rw, (z.y - ctr.y) * rw));
-                const double2 cj = charge<CPLX>(gamma, q, j);
-                double2 ul = cmul<double>(cj, u);  // c_j u^(l+1)
-#pragma unroll
-                for (int l = 0; l < PMAX; ++l) {
-                    b[l].x -= ul.x;
-                    b[l].y -= ul.y;
-                    ul = cmul<double>(ul, u);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int l = 0; l < PMAX; ++l)
-        if (l < p) lo[(int64_t)k * p + l] = b[l];
-}
-
-// Stages 5-7 on v_mfma_f64_16x16x4f64 for p <= 16.  With radius-scaled coefficients
-// every translation is a fixed 2p x 2p real operator per offset, shared with the uniform
-// tree (its tables and interaction entries):
-//  - mode 0 (stages 6 + 7) over the cells of one level, grouped by parity class q: the
-//    M2L from V, whose cells sit at the class's 27 interaction offsets (vslot: the source
-//    cell per offset, -1 where V has none), plus the L2L from the parent's locals (levels
-//    >= 3), added to the P2L sums of the cells with an X list (written before);
-//  - mode 1 (stage 5) over the split cells of one level: the M2M from the four children.
-// A wavefront takes 16 targets; per operator it gathers their 16 source rows (a zero row
-// where a target has no source; an operator no target of the tile uses is skipped).
-// Operand layouts as for the uniform tree's FP64 gather-GEMM:
-//   A: lane l holds A[row l%16][k l/16]     B: lane l holds B[k l/16][col l%16]
-//   D: lane l, register r holds D[l/16 + 4r][l%16]
-// with K permuted so that step s uses k = 8(l/16) + s.
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-struct AtGemm {
-    const int *targets;          // the launch's targets, by class (mode 0) or one list (mode 1)
-    int cstart[4], clen[4], cwave0[4];
-    int nwaves, mode, first, p;
-    const int *vslot;            // mode 0: 27 source cells per cell of level >= 2 (index - first)
-    const int *x_off;            // mode 0: cells with an X list start from their P2L sums
-    const int *parent;           // mode 0: the L2L source (with par)
-    const int4 *child;           // mode 1: the four children
-    const int4 *entries;         // {dx, dy, slot, kind}: 4 x 28 M2L/L2L, then 4 M2M
-    const double *src;           // multipoles (M2L and M2M sources)
-    const double *par;           // mode 0: locals of the parents' level, NULL at level 2
-    double *out;                 // locals (mode 0) or multipoles (mode 1)
-    const double *tab, *zero;
-};
-
-__global__ __launch_bounds__(256, 4) void at_gemm_kernel(AtGemm a)
-{
-    const int lane = threadIdx.x & 63;
-    const int row = lane & 15, kq = lane >> 4;
-    const int two_p = 2 * a.p;
-    const int k0 = 8 * kq;
-    const int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-    if (wave >= a.nwaves) return;  // whole wavefronts
-    int q = 0;
-    for (int c = 1; c < 4; ++c)
-        if (wave >= a.cwave0[c]) q = c;
-    const int cs = a.cstart[q], cl = a.clen[q];
-    const int base = (wave - a.cwave0[q]) * 16;
-    const int li = base + row;
-    const bool tvalid = li < cl;
-    const int tcell = tvalid ? a.targets[cs + li] : -1;
-    doublex4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-    if (a.mode == 0) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int o = base + kq + 4 * r;
-            if (o < cl) {
-                const int k = a.targets[cs + o];
-                if (a.x_off[k] < a.x_off[k + 1]) {
-                    const double *b = a.out + (size_t)k * two_p;
-                    if (row < two_p) acc0[r] = b[row];
-                    if (16 + row < two_p) acc1[r] = b[16 + row];
-                }
-            }
-        }
-    }
-    const int ne = a.mode == 0 ? 28 : 4;
-    for (int e = 0; e < ne; ++e) {
-        int S = -1, en_idx;
-        const double *sbase = a.src;
-        if (a.mode == 1) {
-            en_idx = 112 + e;
-            if (tvalid) {
-                const int4 ch = a.child[tcell];
-                S = e == 0 ? ch.x : e == 1 ? ch.y : e == 2 ? ch.z : ch.w;
-            }
-        } else if (e < 27) {
-            en_idx = 28 * q + e;
-            if (tvalid) S = a.vslot[(int64_t)(tcell - a.first) * 27 + e];
-        } else {
-            en_idx = 28 * q + 27;  // L2L from the parent (child quadrant q)
-            sbase = a.par;
-            if (tvalid && a.par) S = a.parent[tcell];
-        }
-        if (!__any(S >= 0)) continue;  // wavefront-uniform
-        const int4 en = a.entries[en_idx];
-        const double *b0p = a.tab + (((size_t)en.z * 4 + kq) * 32 + row) * 8;
-        const double *b1p = b0p + 16 * 8;
-        double av[8], b0[8], b1[8];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const double2 u0 = ((const double2 *)b0p)[v], u1 = ((const double2 *)b1p)[v];
-            b0[2 * v] = u0.x;
-            b0[2 * v + 1] = u0.y;
-            b1[2 * v] = u1.x;
-            b1[2 * v + 1] = u1.y;
-        }
-        // rows carry a tail pad and absent sources read the zero row: the 8 reads stay inside
-        const double *src = S >= 0 ? sbase + (size_t)S * two_p + k0 : a.zero + k0;
-#pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            const double v = src[st];
-            av[st] = (k0 + st < two_p) ? v : 0.0;
-        }
-#pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[st], b0[st], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[st], b1[st], acc1, 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int o = base + kq + 4 * r;
-        if (o < cl) {
-            double *out = a.out + (size_t)a.targets[cs + o] * two_p;
-            if (row < two_p) out[row] = acc0[r];
-            if (16 + row < two_p) out[16 + row] = acc1[r];
-        }
-    }
-}
-
-// P2L from X before the MFMA translations, one thread per cell with a non-empty X list,
-// written to its locals (the level's gather-GEMM adds M2L and L2L to them):
-//   b_l = -sum_{j in A} c_j u_j^(l+1),  u_j = w/(z_j - c).
-template <int PMAX, bool CPLX>
+// P2L from X, written to the locals of the cells with a non-empty X list before the M2L
+// adds to them, G lanes per cell (64/G cells per wavefront):
+//   b_l = -sum_{j in A} c_j u_j^(l+1),  u_j = w/(z_j - c),
+// the G lanes over the particles of a source leaf, then a butterfly over the G lanes per
+// coefficient.  (One thread per cell was a serial chain over the list's particles.)
+template <int PMAX, bool CPLX, int G>
 __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const int4 *__restrict__ cell,
                                                      const int *__restrict__ x_off, const int *__restrict__ x_idx,
                                                      const int2 *__restrict__ range, const double2 *__restrict__ xy,
@@ -370,19 +146,20 @@ __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const
                                                      const double2 *__restrict__ q, double x0, double y0,
                                                      double side, int p, double2 *__restrict__ lo)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ncells) return;
-    const int k = first + t;
-    if (x_off[k] == x_off[k + 1]) return;
+    const int lane = threadIdx.x, g = lane % G;
+    const int t = blockIdx.x * (64 / G) + lane / G;
+    const int k = first + min(t, ncells - 1);
+    const int e0 = x_off[k], e1 = t < ncells ? x_off[k + 1] : e0;
+    if (!__any(e0 < e1)) return;  // a group without a list idles (its shuffles stay inside it)
     const int4 c = cell[k];
     double2 b[PMAX];
 #pragma unroll
     for (int l = 0; l < PMAX; ++l) b[l] = make_double2(0.0, 0.0);
     const double rw = 1.0 / ldexp(side, -c.x);
     const double2 ctr = cell_centre(x0, y0, side, c);
-    for (int e = x_off[k]; e < x_off[k + 1]; ++e) {
+    for (int e = e0; e < e1; ++e) {
         const int2 r = range[x_idx[e]];
-        for (int j = r.x; j < r.x + r.y; ++j) {
+        for (int j = r.x + g; j < r.x + r.y; j += G) {
             const double2 z = xy[j];
             const double2 u = cinv(make_double2((z.x - ctr.x) * rw, (z.y - ctr.y) * rw));
             const double2 cj = charge<CPLX>(gamma, q, j);
@@ -396,36 +173,11 @@ __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const
         }
     }
 #pragma unroll
-    for (int l = 0; l < PMAX; ++l)
-        if (l < p) lo[(int64_t)k * p + l] = b[l];
-}
-
-// Stage 7 into the cells of one level l >= 3 (parents of level >= 2), one thread per
-// (cell, k), by Horner in d = (c - c_parent)/w_parent:
-//   b_k += 2^-(k+1) sum_{j>=k} C(j,k) d^(j-k) b_j(parent).
-__global__ __launch_bounds__(256) void at_l2l_kernel(int first, int ncells, const int4 *__restrict__ cell,
-                                                      const int *__restrict__ parent,
-                                                      const double *__restrict__ binom, int nb, int p,
-                                                      double2 *__restrict__ lo)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ncells * p) return;
-    const int k = first + t / p, kk = t % p;
-    const int4 c = cell[k];
-    const double2 *bp = lo + (int64_t)parent[k] * p;
-    const double2 d = make_double2(((c.y & 1) - 0.5) * 0.5, ((c.z & 1) - 0.5) * 0.5);
-    const double c0 = binom[(p - 1) * nb + kk];
-    double2 acc = make_double2(c0 * bp[p - 1].x, c0 * bp[p - 1].y);
-    for (int j = p - 2; j >= kk; --j) {
-        acc = cmul<double>(acc, d);
-        const double cj = binom[j * nb + kk];
-        acc.x = fma(cj, bp[j].x, acc.x);
-        acc.y = fma(cj, bp[j].y, acc.y);
-    }
-    const double f = ldexp(1.0, -(kk + 1));
-    double2 &out = lo[(int64_t)k * p + kk];
-    out.x = fma(f, acc.x, out.x);
-    out.y = fma(f, acc.y, out.y);
+    for (int o = G / 2; o >= 1; o >>= 1) butterfly_step<PMAX>(b, o);
+    if (e0 < e1 && g == 0)
+#pragma unroll
+        for (int l = 0; l < PMAX; ++l)
+            if (l < p) lo[(int64_t)k * p + l] = b[l];
 }
 
 // Near field (stage 9) over U.  One wavefront per work entry:
@@ -825,28 +577,14 @@ void launch_atree_coords(const fmm_atree *t, int is_double, void *pos, hipStream
                                                                t->side, (float2 *)pos);
 }
 
-// One gather-GEMM launch over up to four target lists (classes).
-void at_gemm_launch(AtGemm a, const int *seg_off, int nlists, hipStream_t s)
-{
-    a.nwaves = 0;
-    for (int k = 0; k < 4; ++k) {
-        a.cstart[k] = k < nlists ? seg_off[k] : 0;
-        a.clen[k] = k < nlists ? seg_off[k + 1] - seg_off[k] : 0;
-        a.cwave0[k] = a.nwaves;
-        a.nwaves += (a.clen[k] + 15) / 16;
-    }
-    if (a.nwaves > 0) at_gemm_kernel<<<(unsigned)((a.nwaves + 3) / 4), 256, 0, s>>>(a);
-}
-
 template <bool CPLX>
 void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
 {
     const fmm_atree *t = c.t;
     const int deepest = (int)t->sizes[6];
     if (deepest < 2) return;
-    const int p = c.p, nb = 2 * p + 1;
+    const int p = c.p;
     const double2 *q = t->wsp->adj;
-    const bool gemm = c.tabs && t->m2l_plan;  // p <= 16: stages 5-7 on MFMA
     if (t->np2m > 0) {
         // 16 lanes per leaf, four leaves per wavefront
         const int np = (int)t->np2m;
@@ -858,68 +596,50 @@ void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
             at_p2m_kernel<32, CPLX, 16><<<g, 64, 0, s>>>(t->d.p2m_cells, np, t->d.cell, t->d.range, t->d.xy,
                                                          t->wsp->gamma, q, t->x0, t->y0, t->side, p, mp);
     }
-    AtGemm a{};
-    if (gemm) {
-        a.first = t->level_off[2];
-        a.p = p;
-        a.vslot = t->d.vslot;
-        a.x_off = t->d.x_off;
-        a.parent = t->d.parent;
-        a.child = t->d.child;
-        a.entries = c.tabs->mfma_entries;
-        a.src = (const double *)mp;
-        a.tab = c.tabs->mfma_d;
-        a.zero = c.tabs->zero_row;
-    }
+    TransArgs a{};
+    a.p = p;
+    a.no_lds = c.near_occ > 0;
+    a.entries = c.tabs->mfma_entries;
+    a.tab = c.tabs->mfma_d;
+    a.zero = c.tabs->zero_row;
+    a.first = t->level_off[2];
+    a.child = t->d.child;
+    a.parent = t->d.parent;
+    a.vslot = t->d.vslot;
+    a.x_off = t->d.x_off;
+    // stage 5 level by level upward
+    a.targets = t->d.inner;
+    a.src = a.out = mp;
+    a.nseg = 1;
     for (int l = deepest - 1; l >= 2; --l) {
-        const int cnt = t->inner_off[l + 1] - t->inner_off[l];
-        if (cnt == 0) continue;
-        if (gemm) {
-            a.mode = 1;
-            a.targets = t->d.inner + t->inner_off[l];
-            a.out = (double *)mp;
-            const int one[2] = {0, cnt};
-            at_gemm_launch(a, one, 1, s);
-        } else {
-            at_m2m_kernel<<<blocks((int64_t)cnt * p, 256), 256, 0, s>>>(t->d.inner + t->inner_off[l], cnt,
-                                                                        t->d.child, t->wsp->binom, nb, p, mp);
-        }
+        a.seg[0] = TransSeg{0, t->inner_off[l], t->inner_off[l + 1] - t->inner_off[l], l};
+        launch_trans64(a, Trans::M2M, true, s);
     }
-    const int first = t->level_off[2], cnt = t->level_off[deepest + 1] - first;
-    if (cnt > 0 && gemm) {
-        // P2L into the locals of the cells with an X list, then level by level the M2L
-        // from V and the L2L from the parent added to them
-        if (t->sizes[5] > 0)  // |X|
-            at_p2l_kernel<16, CPLX><<<blocks(cnt, 64), 64, 0, s>>>(first, cnt, t->d.cell, t->d.x_off, t->d.x_idx,
-                                                                   t->d.range, t->d.xy, t->wsp->gamma, q, t->x0,
-                                                                   t->y0, t->side, p, lo);
-        a.mode = 0;
-        a.targets = t->d.m2l_targets;
-        a.out = (double *)lo;
-        for (int l = 2; l <= deepest; ++l) {
-            a.par = l >= 3 ? (const double *)lo : nullptr;
-            at_gemm_launch(a, &t->m2l_seg_off[4 * (l - 2)], 4, s);
-        }
-        return;
+    const int cnt = t->level_off[deepest + 1] - a.first;
+    if (cnt <= 0) return;
+    // P2L into the locals of the cells with an X list, then the M2L from V of every level
+    // added to them, then the L2L level by level downward
+    if (t->sizes[5] > 0) {  // |X|
+        auto k = p <= 16 ? at_p2l_kernel<16, CPLX, 16> : at_p2l_kernel<32, CPLX, 16>;
+        k<<<blocks(cnt, 4), 64, 0, s>>>(a.first, cnt, t->d.cell, t->d.x_off, t->d.x_idx, t->d.range, t->d.xy,
+                                         t->wsp->gamma, q, t->x0, t->y0, t->side, p, lo);
     }
-    // M2L + P2L for every cell of level >= 2 at once, then L2L level by level
-    if (cnt > 0) {
-        if (p <= 16)
-            at_m2l_kernel<16, CPLX><<<blocks(cnt, 64), 64, 0, s>>>(first, cnt, t->d.cell, t->d.v_off, t->d.v_idx,
-                                                                   t->d.x_off, t->d.x_idx, t->d.range, t->d.xy,
-                                                                   t->wsp->gamma, q, t->x0, t->y0, t->side,
-                                                                   t->wsp->binom16, p, mp, lo);
-        else
-            at_m2l_kernel<32, CPLX><<<blocks(cnt, 64), 64, 0, s>>>(first, cnt, t->d.cell, t->d.v_off, t->d.v_idx,
-                                                                   t->d.x_off, t->d.x_idx, t->d.range, t->d.xy,
-                                                                   t->wsp->gamma, q, t->x0, t->y0, t->side,
-                                                                   t->wsp->binom32, p, mp, lo);
-    }
+    a.targets = t->d.m2l_targets;
+    a.out = lo;
+    auto level_segs = [&](int l0, int l1) {
+        a.nseg = 0;
+        for (int l = l0; l <= l1; ++l)
+            for (int k = 0; k < 4; ++k) {
+                const int *off = &t->m2l_seg_off[4 * (l - 2) + k];
+                a.seg[a.nseg++] = TransSeg{0, off[0], off[1] - off[0], l};
+            }
+    };
+    level_segs(2, deepest);
+    launch_trans64(a, Trans::M2L, true, s);
+    a.src = lo;
     for (int l = 3; l <= deepest; ++l) {
-        const int f = t->level_off[l], nc = t->level_off[l + 1] - f;
-        if (nc == 0) continue;
-        at_l2l_kernel<<<blocks((int64_t)nc * p, 256), 256, 0, s>>>(f, nc, t->d.cell, t->d.parent, t->wsp->binom, nb, p,
-                                                                   lo);
+        level_segs(l, l);
+        launch_trans64(a, Trans::L2L, true, s);
     }
 }
 

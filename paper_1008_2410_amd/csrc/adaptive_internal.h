@@ -107,9 +107,6 @@ struct AtreeWs {
     void *qt = nullptr;
     double4 *pa = nullptr, *psrc = nullptr;
     double *pb = nullptr;
-    double *binom = nullptr;    // C(a, k), a, k <= 2p, row-major (2p + 1)^2
-    double *binom16 = nullptr;  // the same for a, k <= 32 (33 x 33), and for a, k <= 64 (65 x 65):
-    double *binom32 = nullptr;  // the M2L kernel runs 16 or 32 terms whatever p
 };
 
 }  // namespace fmm
@@ -149,7 +146,7 @@ struct AtreeCall {
     int is_double;
     double alpha;   // record scale (as for the uniform tree)
     int near_occ = 0;  // forward near field: wavefronts per SIMD it may hold (0: no cap)
-    const Tables *tabs = nullptr;  // with the M2L plan (p <= 16): the MFMA operators
+    const Tables *tabs = nullptr;  // the translation operators (NULL: no expansions)
 };
 
 // Stages 1-3 on the device (adaptive_build.hip): fills t->d and the host facts of t

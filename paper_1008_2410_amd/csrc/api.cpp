@@ -93,10 +93,13 @@ void free_tree(fmm_tree *t)
 // The mutual form is used when its plan has items; else the target-centric units alone.
 bool use_mutual(const fmm_tree *t) { return t->near_mutual && t->nmut > 0; }
 
-int effective_lc(const fmm_tree *t) { return std::min(t->lc, t->depth); }
-
-// Last FP64 level: every level in FP64 precision; in mixed precision the coarse levels.
-int split_level(const fmm_tree *t, int precision) { return precision == FMM_FP64 ? t->depth : effective_lc(t); }
+// Last FP64 level: every level in FP64 precision; in the mixed form the coarse levels, and
+// always levels 2..5, whose few cells cost nothing in FP64 (their passes run in one launch).
+constexpr int kMinSplit = 5;
+int split_level(const fmm_tree *t, int precision)
+{
+    return precision == FMM_FP64 ? t->depth : std::min(std::max(t->lc, kMinSplit), t->depth);
+}
 
 // A workspace last used by another tree (a rebuild's hand-over, or a tree sharing it):
 // multipoles of cells that are empty in this tree must read as zero (the M2L kernels
@@ -233,7 +236,6 @@ FarArgs far_args(const fmm_tree *t, const Workspace &ws, int p, int precision, b
     a.t = t;
     a.p = p;
     a.split = ws.split;
-    a.lc = effective_lc(t);
     a.mp_d = adjoint ? ws.mp2_d : ws.mp_d;
     a.lo_d = adjoint ? ws.lo2_d : ws.lo_d;
     a.mp_f = adjoint ? ws.mp2_f : ws.mp_f;
@@ -246,13 +248,20 @@ FarArgs far_args(const fmm_tree *t, const Workspace &ws, int p, int precision, b
     return a;
 }
 
-// Stage costs of the mixed form (p = 16) on one MI355X, in ms, fitted by the cost-model
-// sweep of uniform particles (the complexity terms of section "Complexity Estimates"
-// with the counts a launch pays for):
+// Stage costs of the mixed form (p = 16) on one MI355X, in ms: the near field's constants
+// fitted by the cost-model sweep of uniform particles (the complexity terms of section
+// "Complexity Estimates" with the counts a launch pays for), the far chain's set to its
+// launches (one per fine level each way, P2M, the coarse passes) and its time per cell:
 //   T_near = kNear0 + kNearPair pairs + kNearVisit 9 N_leaves,
 //   T_far  = kFar0 + kFarCell C_fine + kFarCoarse C_coarse + kFarLevel (L - L_c).
 constexpr double kNear0 = 0.070, kNearPair = 1.95e-10, kNearVisit = 1.74e-7;
-constexpr double kFar0 = 0.268, kFarCell = 1.32e-6, kFarCoarse = 4.87e-5, kFarLevel = 0.00216;
+constexpr double kFar0 = 0.060, kFarCell = 0.9e-6, kFarCoarse = 1.9e-6, kFarLevel = 0.012;
+
+// The part of T_near that grows with the tree.
+double near_work_ms(const fmm_tree *t)
+{
+    return kNearPair * (double)t->p2p_pairs + kNearVisit * 9.0 * (double)t->nonempty_leaves;
+}
 
 // Predicted far-field / near-field time of the tree (the model above).
 double far_near_ratio(const fmm_tree *t)
@@ -260,34 +269,28 @@ double far_near_ratio(const fmm_tree *t)
     const int lc = std::min(t->lc, t->depth);
     double fine = 0, coarse = 0;
     for (int l = 2; l <= t->depth; ++l) (l <= lc ? coarse : fine) += (double)t->list_len[l];
-    const double near = kNear0 + kNearPair * (double)t->p2p_pairs + kNearVisit * 9.0 * (double)t->nonempty_leaves;
+    const double near = kNear0 + near_work_ms(t);
     const double far = kFar0 + kFarCell * fine + kFarCoarse * coarse + kFarLevel * (t->depth - lc);
     return far / near;
 }
 
 // Whether a call runs the far chain beside the near field (FMM_OPT_SCHEDULE 0), after it
-// (1), or by the model (2, the default): both are throughput work on the same CUs.  In the
-// mixed form, with the near field capped as below, overlapping measured faster than
-// serialising up to a predicted far/near ratio of about 2.5 (uniform 2^18-2^22 particles,
-// ratios 1.2-2.2: -7% to -15%; ratio 3.0: +2%), so only calls beyond it are serialised.
-// FP64 calls overlap (the FP64 near field leaves issue slots that the far chain uses).
-constexpr double kSerialRatio = 2.5;
+// (1), or by the model (2, the default): both are throughput work on the same CUs.
+//  - A near field of less than kSerialNear ms of work is not worth the second stream: the
+//    events between the streams cost about 25 us (uniform 4096 particles, depth 4: 53 us
+//    serialised against 75-86 overlapped; 50021, depth 6: 81 against 91-95).
+//  - In the mixed form calls beyond a far/near ratio of kSerialRatio are serialised; below
+//    it overlapping measured no slower (uniform 2^22 particles at depth 10, r = 0.8: 3.5
+//    against 3.9 ms; patches 10^6 at depth 8, r = 0.36: 0.41 against 0.47 ms).
+//  - FP64 calls overlap (the FP64 near field leaves issue slots that the far chain uses).
+constexpr double kSerialRatio = 2.5, kSerialNear = 0.012;
 bool call_overlaps(const fmm_tree *t, int precision)
 {
     if (t->schedule != 2) return t->schedule == 0;
-    if (precision == FMM_FP64 || t->depth < 2) return true;
-    return far_near_ratio(t) <= kSerialRatio;
+    if (t->depth < 2) return true;
+    if (near_work_ms(t) < kSerialNear) return false;
+    return precision == FMM_FP64 || far_near_ratio(t) <= kSerialRatio;
 }
-
-// In an overlapped call whose far chain is predicted clearly longer than the near field
-// (r >= 1.4), the near field starts once P2M is done: beside the near field's workgroups
-// P2M gets few slots, and the whole far chain waits for it (the 1024^2 lattice, depth 8,
-// p = 12, coarse levels <= 5, r = 2.2: FP64 0.730 -> 0.705 ms, mixed 0.597 -> 0.573; uniform
-// 2^20 particles at depths 7-9, r = 1.45-2.25: 0.23 ms less over the 12 points).  Nearer
-// r = 1, P2M beside the near field costs less than the delay (uniform 2^22 particles at
-// depth 10, r = 1.22: 3.65 against 3.88 ms with the wait), and far below it much less
-// (2^24 patches, depth 10: 8.17 against 8.34 ms).
-bool p2m_first(const fmm_tree *t) { return t->depth >= 2 && far_near_ratio(t) >= 1.4; }
 
 // Near-field occupancy cap of a call (FMM_OPT_NEAR_OCCUPANCY), automatic from the tree:
 //  - mixed, leaves of more than ~2500 near-field pairs per particle and a work list of at
@@ -296,23 +299,25 @@ bool p2m_first(const fmm_tree *t) { return t->depth >= 2 && far_near_ratio(t) >=
 //    uncapped; 2^23: 8.1 against 9.1).  With fewer entries the cap idles the chip (uniform
 //    2^22 particles at depth 6, 20K entries: 9.5 ms at cap 3 against 7.6 uncapped);
 //  - mixed, by the predicted far/near ratio r (the far chain takes the slots the cap
-//    leaves): r < 0.12 none, r < 0.9 six (2^24 patches at depth 10: 8.13 ms against 8.40
-//    at five and 8.61 uncapped), 0.9 <= r <= 1.1 five, above four (uniform 2^20-2^22
-//    particles at depths 7-10: four within 0.01 ms of the fastest cap);
-//  - FP64 (at most 5 wavefronts per SIMD): 2 when the far field is the longer part (r >= 1:
-//    the 1024^2 lattice, depth 8, p = 12, coarse levels <= 5 took 0.78 ms against 0.90
-//    uncapped or serialised), else none.
+//    leaves): r < 0.07 none, r < 0.3 six (2^24 patches at depth 10: 6.9 ms against 7.2 at
+//    five and 7.1 uncapped; 2^22 at depth 9: 1.58 against 1.64 and 1.72), r < 0.85 five
+//    (uniform 2^22 at depth 10: 3.50 against 3.53 at four and 3.72 at six), above four;
+//  - FP64 (at most 5 wavefronts per SIMD): four, or three from r = 0.3 on (1024^2 lattice,
+//    depth 8, p = 12: 0.468 ms against 0.500 at four and 0.499 uncapped; 7 10^5 patch
+//    particles at depth 8: 0.59 against 0.64 and 0.66);
+//  - a work list of less than 4096 entries leaves slots free by itself: no cap.
 int choose_occupancy(const fmm_tree *t, int precision, bool overlap)
 {
     if (!overlap || t->depth < 2) return 0;
     if (t->near_occupancy >= 0) return t->near_occupancy;
-    const double r = far_near_ratio(t);
-    if (precision == FMM_FP64) return r >= 1.0 ? 2 : 0;
     const int64_t entries = use_mutual(t) ? t->nnear_work : t->nunits;
+    if (entries < 4096) return 0;
+    const double r = far_near_ratio(t);
+    if (precision == FMM_FP64) return r < 0.07 ? 0 : r < 0.3 ? 4 : 3;
     if ((double)t->p2p_pairs >= 2500.0 * (double)t->n && entries >= 65536) return 3;
-    if (r < 0.12) return 0;
-    if (r < 0.9) return 6;
-    if (r <= 1.1) return 5;
+    if (r < 0.07) return 0;
+    if (r < 0.3) return 6;
+    if (r < 0.85) return 5;
     return 4;
 }
 
@@ -430,8 +435,7 @@ int run_forward(fmm_tree *t, const double *gamma, double sigma, int p, int preci
     a.pos = pos;
     a.gam = nullptr;  // P2M starts before the circulations are gathered: it reads the staging array
     t->occupancy_in_use = choose_occupancy(t, precision, overlap);
-    // beside a capped near field the coarse kernel must fit in one wavefront per SIMD
-    if (overlap && t->occupancy_in_use > 0) a.coarse_threads = 256;
+    a.no_lds = t->occupancy_in_use > 0;
     Timing tm;
     if (!noalloc && (rc = tm.init(t))) return rc;
 
@@ -444,16 +448,7 @@ int run_forward(fmm_tree *t, const double *gamma, double sigma, int p, int preci
     launch_pack(t, is_double, ws.gam, ms);
     tm.mark(1, ms);
     tm.mark(2, ss);
-    if (overlap && p2m_first(t)) {
-        // the far chain is the longer part: P2M, its first and widest kernel, runs beside
-        // pack alone instead of being starved by the near field's workgroups
-        launch_p2m(a, ss);
-        HIP_TRY(hipEventRecord(t->ev_fork, ss));
-        launch_far_chain(a, ss, false);
-        HIP_TRY(hipStreamWaitEvent(ms, t->ev_fork, 0));
-    } else {
-        launch_far_chain(a, ss);
-    }
+    launch_far_chain(a, ss);
     tm.mark(3, ss);
     if (overlap) HIP_TRY(hipEventRecord(t->ev_join, ss));
     void *slots = use_mutual(t) ? ws.slots : nullptr;

@@ -24,23 +24,21 @@ constexpr int kNumEvents = 8;
 
 // ---------------------------------------------------------------------------------
 // Device-side tables for one expansion order p (radius-scaled operators, level
-// independent).  All complex arrays are interleaved (re, im).
-//   m2m[q][m][k]  = C(m,k) d_q^(m-k) 2^-k                 (k <= m, else 0)
-//   l2l[q][k][l]  = C(l,k) d_q^(l-k) 2^-(k+1)             (l >= k, else 0)
-//   m2l[o][m][l]  = (-1)^l C(l+m,m) delta^-(l+m+1), delta = (dx, dy) of offset o = (dx+3)*7 + (dy+3)
-// with d_q = (c_child - c_parent)/w_parent = ((q&1) - 1/2)/2 + i((q>>1) - 1/2)/2.
+// independent):
+//   M2M: A_m = sum_{k<=m} C(m,k) d_q^(m-k) 2^-k a_k
+//   L2L: b_k = sum_{l>=k} C(l,k) d_q^(l-k) 2^-(k+1) b_l
+//   M2L: b_l = sum_m (-1)^l C(l+m,m) delta^-(l+m+1) a_m,  delta = (dx, dy)
+// with d_q = (c_child - c_parent)/w_parent = ((q&1) - 1/2)/2 + i((q>>1) - 1/2)/2, as
+// 2p x 2p real matrices (complex entries embedded with interleaved (re, im) rows and
+// columns, zero-padded) in the operand order of the matrix instructions,
+// [slot][k / steps][column][k % steps] (translate.h gives the steps and columns of p):
+// slots 0..48 the M2L offsets (index (dx+3)*7 + (dy+3)), 49..52 the L2L parities, 53..56
+// the M2M children.
 // ---------------------------------------------------------------------------------
-// mfma_f: the M2L and L2L operators as 2p x 2p real matrices (complex entries embedded
-// with interleaved (re, im) rows and columns, zero-padded to 32 x 32) in the operand
-// order of the MFMA M2L kernel: [slot][k / 16][column][k % 16], slots 0..48 the M2L
-// offsets (index (dx+3)*7 + (dy+3)), 49..52 the L2L parities, 53..56 the M2M children.
-// Built for p <= 16.
 struct Tables {
     int p = 0;
-    double2 *m2m_d = nullptr, *l2l_d = nullptr, *m2l_d = nullptr;
-    float2 *m2m_f = nullptr, *l2l_f = nullptr, *m2l_f = nullptr;
     float *mfma_f = nullptr;
-    double *mfma_d = nullptr;      // FP64 MFMA operand order: [slot][k / 8][column][k % 8]
+    double *mfma_d = nullptr;
     int4 *mfma_entries = nullptr;  // {dx, dy, slot, kind}: 4 x 28 M2L/L2L entries, then 4 M2M entries
     double *zero_row = nullptr;    // 128 zero doubles: the row read for absent source cells
 };
@@ -182,7 +180,6 @@ struct FarArgs {
     const fmm_tree *t;
     int p;
     int split;                 // last FP64 level
-    int lc;                    // coarse cutoff actually used (<= depth)
     double2 *mp_d, *lo_d;      // FP64 storage (levels 0..split)
     float2 *mp_f, *lo_f;       // FP32 storage (levels split+1..L)
     const void *pos;           // the tree's leaf-unit coordinates in the records' precision (or null)
@@ -190,7 +187,7 @@ struct FarArgs {
     int rec_is_double;
     int charge_kind;           // 0: real Gamma in rec.z -> c = -i Gamma/(2 pi); 1: complex q from adj array
     const double2 *adj;        // complex charges in sorted order (charge_kind 1)
-    int coarse_threads = 1024; // workgroup size of the coarse-level kernel (256 or 1024)
+    bool no_lds = false;       // beside a capped near field, which holds the LDS: kernels without any
 };
 
 // Launchers (kernels.hip).  All are asynchronous on `s`.

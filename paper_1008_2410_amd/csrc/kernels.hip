@@ -11,6 +11,7 @@
 //  - Complex numbers are interleaved (re, im) float2 / double2.
 #include "fmm_internal.h"
 #include "device_common.h"
+#include "translate.h"
 
 #include <algorithm>
 #include <climits>
@@ -340,449 +341,6 @@ __global__ __launch_bounds__(64) void p2m_kernel(const int *__restrict__ leaves,
 }
 
 // ---------------------------------------------------------------------------------
-// Stage 5, M2M: coefficient m of parent P from its non-empty children,
-//   A_m = sum_q sum_{k<=m} C(m,k) d_q^(m-k) 2^-k a_k(child q)      (scaled form)
-// ---------------------------------------------------------------------------------
-template <typename TC, typename TP>
-__device__ __forceinline__ void m2m_one(int P, int m, int p, const int *__restrict__ child_count,
-                                        const c2<TC> *__restrict__ child, c2<TP> *__restrict__ parent,
-                                        const c2<TP> *__restrict__ tab)
-{
-    c2<TP> acc = mk<TP>(0, 0);
-    for (int q = 0; q < 4; ++q) {
-        const int ch = 4 * P + q;
-        if (child_count[ch] == 0) continue;
-        const c2<TC> *a = child + (int64_t)ch * p;
-        const c2<TP> *row = tab + (q * p + m) * p;
-        for (int k = 0; k <= m; ++k) acc = cmac<TP>(acc, row[k], cvt<TP, TC>(a[k]));
-    }
-    parent[(int64_t)P * p + m] = acc;
-}
-
-// ---------------------------------------------------------------------------------
-// Stages 6 + 7 fused per cell: local coefficient l of cell T at level `level`,
-//   b_l(T) = sum_{S in IL(T), S non-empty} sum_m (-1)^l C(l+m,m) delta^-(l+m+1) a_m(S)
-//          + sum_{k>=l} C(k,l) d_q^(k-l) 2^-(l+1) b_k(parent(T))   (levels >= 3)
-// IL(T) = children of the parent's neighbours that are not neighbours of T: for the
-// parity class (qx, qy) = (tx & 1, ty & 1) the source offsets are
-// dx in [-2-qx, 3-qx], dy in [-2-qy, 3-qy] minus the 3x3 block (27 cells).
-// ---------------------------------------------------------------------------------
-template <typename T, typename TPar>
-__device__ __forceinline__ void m2l_one(int Tm, int lo, int p, int level, const int *__restrict__ count_l,
-                                        const c2<T> *__restrict__ mp_l, c2<T> *__restrict__ lo_l,
-                                        const c2<T> *__restrict__ m2l_tab, const c2<TPar> *__restrict__ loc_par,
-                                        const c2<TPar> *__restrict__ l2l_tab)
-{
-    const int tx = (int)morton_x((uint32_t)Tm), ty = (int)morton_y((uint32_t)Tm);
-    const int qx = tx & 1, qy = ty & 1;
-    const int nside = 1 << level;
-    c2<T> acc = mk<T>(0, 0);
-    for (int dy = -2 - qy; dy <= 3 - qy; ++dy) {
-        const int sy = ty + dy;
-        if (sy < 0 || sy >= nside) continue;
-        for (int dx = -2 - qx; dx <= 3 - qx; ++dx) {
-            if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1) continue;
-            const int sx = tx + dx;
-            if (sx < 0 || sx >= nside) continue;
-            const uint32_t S = morton_encode((uint32_t)sx, (uint32_t)sy);
-            if (count_l[S] == 0) continue;
-            const c2<T> *a = mp_l + (int64_t)S * p;
-            // delta = (c_T - c_S)/w = (-dx, -dy)
-            const c2<T> *tab = m2l_tab + ((3 - dx) * 7 + (3 - dy)) * p * p + lo;
-            for (int m = 0; m < p; ++m) acc = cmac<T>(acc, tab[m * p], a[m]);
-        }
-    }
-    if (loc_par) {
-        const int P = Tm >> 2, q = Tm & 3;
-        const c2<TPar> *b = loc_par + (int64_t)P * p;
-        const c2<TPar> *row = l2l_tab + (q * p + lo) * p;
-        c2<TPar> acc2 = mk<TPar>(0, 0);
-        for (int k = lo; k < p; ++k) acc2 = cmac<TPar>(acc2, row[k], b[k]);
-        acc.x += (T)acc2.x;
-        acc.y += (T)acc2.y;
-    }
-    lo_l[(int64_t)Tm * p + lo] = acc;
-}
-
-// ---------------------------------------------------------------------------------
-// Stages 6 + 7 on MFMA (FP32, p <= 16).  For a target cell T of parity class q the
-// local expansion is a sum of 28 dense products of 2p-vectors with 2p x 2p real
-// matrices (the complex operators embedded with interleaved (re, im) rows/columns):
-//   L(T) = sum_{o in IL offsets of q} M(T + o) R_o  +  L(parent(T)) R^{L2L}_q.
-// All targets of one parity class share the 28 matrices, so each wavefront takes 4
-// tiles of 32 same-class targets and accumulates 32 x 32 output tiles with
-// v_mfma_f32_32x32x2f32 (16 instructions per offset and tile, K = 32).  Empty and
-// out-of-domain source cells contribute zero rows (multipoles of empty cells are
-// kept at zero).  Operand layouts of the 32x32x2 instruction:
-//   A: lane l holds A[row l%32][k l/32]     B: lane l holds B[k l/32][col l%32]
-//   D: lane l, register r holds D[8(r/4) + 4(l/32) + r%4][l%32]
-// K is permuted so that step s uses k = 16(l/32) + s: a lane then reads 16
-// contiguous floats of its row, and the table stores B as [slot][l/32][col][s].
-// ---------------------------------------------------------------------------------
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-
-// a[s] = row[k0 + s] for k0 + s < two_p, else 0.  Every coefficient array carries a
-// tail pad of 64 elements and absent sources read a zero row, so the 16 reads of a
-// half row never leave their allocation.
-__device__ __forceinline__ void load_half_row(float (&a)[16], const float *row, int k0, int two_p)
-{
-    const float *r = row + k0;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        const float v = r[s];
-        a[s] = (k0 + s < two_p) ? v : 0.0f;
-    }
-}
-__device__ __forceinline__ void load_half_row(float (&a)[16], const double *row, int k0, int two_p)
-{
-    const double *r = row + k0;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        const double v = r[s];
-        a[s] = (k0 + s < two_p) ? (float)v : 0.0f;
-    }
-}
-
-// One 32-target tile per wavefront: the 28 (M2L) or 4 (M2M) products of a tile run as
-// one chain of 16-instruction groups.  Entries {dx, dy, slot, kind} of a class:
-//   kind 0: M2L source cell (tx + dx, ty + dy) of the same level (skipped if outside)
-//   kind 1: L2L from the parent's local expansion
-//   kind 2: M2M from child dx (cell 4 T + dx of the next finer level)
-// Operands of one gather-GEMM entry {dx, dy, slot, kind} for this lane: b = the 16
-// table values of column `row`, half kh; a = 16 values of the source row.
-template <typename TPar>
-__device__ __forceinline__ void gemm_load_entry(int4 en, int kh, int row, int tx, int ty, int tcell, bool tvalid,
-                                                int nside, int k0, int two_p, int p,
-                                                const float *__restrict__ src_same,
-                                                const float *__restrict__ src_child,
-                                                const c2<TPar> *__restrict__ loc_par, const float *__restrict__ tab,
-                                                const double *__restrict__ zero, float (&a)[16], float (&b)[16])
-{
-    const float4 *bsrc = (const float4 *)(tab + ((size_t)(en.z * 2 + kh) * 32 + row) * 16);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const float4 t4 = bsrc[v];
-        b[4 * v] = t4.x;
-        b[4 * v + 1] = t4.y;
-        b[4 * v + 2] = t4.z;
-        b[4 * v + 3] = t4.w;
-    }
-    if (en.w == 1) {
-        load_half_row(a, (tvalid && loc_par) ? (const TPar *)(loc_par + (size_t)(tcell >> 2) * p) : (const TPar *)zero,
-                      k0, two_p);
-    } else {
-        const float *src = (const float *)zero;
-        if (en.w == 0) {
-            const int sx = tx + en.x, sy = ty + en.y;
-            if (tvalid && sx >= 0 && sy >= 0 && sx < nside && sy < nside)
-                src = src_same + (size_t)morton_encode((uint32_t)sx, (uint32_t)sy) * two_p;
-        } else if (tvalid) {
-            src = src_child + (size_t)(4 * tcell + en.x) * two_p;
-        }
-        load_half_row(a, src, k0, two_p);
-    }
-}
-
-template <typename TPar, typename TOut>
-__global__ __launch_bounds__(256, 4) void gather_gemm_kernel(
-    const int *__restrict__ targets, int4 class_start, int4 class_len, int4 class_wave0, int4 class_entry,
-    int4 class_nentry, int nwaves, int p, int level, const int4 *__restrict__ entries, const float *__restrict__ src_same,
-    const float *__restrict__ src_child, const c2<TPar> *__restrict__ loc_par, TOut *__restrict__ out,
-    const float *__restrict__ tab, const double *__restrict__ zero)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave_step = (int)((gridDim.x * blockDim.x) >> 6);
-    for (int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6); wave < nwaves; wave += wave_step) {
-    const int q = wave >= class_wave0.w ? 3 : wave >= class_wave0.z ? 2 : wave >= class_wave0.y ? 1 : 0;
-    const int cstart = q == 0 ? class_start.x : q == 1 ? class_start.y : q == 2 ? class_start.z : class_start.w;
-    const int clen = q == 0 ? class_len.x : q == 1 ? class_len.y : q == 2 ? class_len.z : class_len.w;
-    const int cw0 = q == 0 ? class_wave0.x : q == 1 ? class_wave0.y : q == 2 ? class_wave0.z : class_wave0.w;
-    const int e0 = q == 0 ? class_entry.x : q == 1 ? class_entry.y : q == 2 ? class_entry.z : class_entry.w;
-    const int ne = q == 0 ? class_nentry.x : q == 1 ? class_nentry.y : q == 2 ? class_nentry.z : class_nentry.w;
-    const int base = (wave - cw0) * 32;
-    const int row = lane & 31, kh = lane >> 5;
-    const int two_p = 2 * p;
-    const int nside = 1 << level;
-    const int k0 = 16 * kh;
-
-    const int li = base + row;
-    const bool tvalid = li < clen;
-    const int tcell = tvalid ? targets[cstart + li] : 0;
-    const int tx = (int)morton_x((uint32_t)tcell), ty = (int)morton_y((uint32_t)tcell);
-
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-    for (int e = 0; e < ne; ++e) {
-        float a[16], b[16];
-        gemm_load_entry<TPar>(entries[e0 + e], kh, row, tx, ty, tcell, tvalid, nside, k0, two_p, p, src_same,
-                              src_child, loc_par, tab, zero, a, b);
-#pragma unroll
-        for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0);
-    }
-    // Store: lane holds column `row` of rows 8(r/4) + 4 kh + r%4; the cell of output row
-    // o is the target of lane o.
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int orow = 8 * (r >> 2) + 4 * kh + (r & 3);
-        const int cell = __shfl(tcell, orow);
-        if (row < two_p && base + orow < clen) out[(size_t)cell * two_p + row] = (TOut)acc[r];
-    }
-    }
-}
-
-// ---------------------------------------------------------------------------------
-// The same gather-GEMM in FP64 on v_mfma_f64_16x16x4f64 (tiles of 16 targets, two
-// 16-column output blocks).  Operand layouts of the 16x16x4 instruction:
-//   A: lane l holds A[row l%16][k l/16]     B: lane l holds B[k l/16][col l%16]
-//   D: lane l, register r holds D[l/16 + 4r][l%16]
-// K is permuted so that step s uses k = 8(l/16) + s; the table stores B as
-// [slot][l/16][column][s].
-// ---------------------------------------------------------------------------------
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-// a[s] = row[k0 + s] for k0 + s < two_p, else 0 (rows padded as for load_half_row).
-__device__ __forceinline__ void load_row8(double (&a)[8], const double *row, int k0, int two_p)
-{
-    const double *r = row + k0;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const double v = r[s];
-        a[s] = (k0 + s < two_p) ? v : 0.0;
-    }
-}
-
-// One wavefront: the 16 targets tlist[base .. base + 15] (clen entries valid).
-__device__ __forceinline__ void gemm_tile_f64(const int *__restrict__ tlist, int clen, int base,
-                                              const int4 *__restrict__ ents, int ne, int p, int level,
-                                              const double *__restrict__ src_same,
-                                              const double *__restrict__ src_child,
-                                              const double *__restrict__ loc_par, double *__restrict__ out,
-                                              const double *__restrict__ tab, const double *__restrict__ zero)
-{
-    const int lane = threadIdx.x & 63;
-    const int row = lane & 15, kq = lane >> 4;
-    const int two_p = 2 * p;
-    const int k0 = 8 * kq;
-    const int nside = 1 << level;
-    const int li = base + row;
-    const bool tvalid = li < clen;
-    const int tcell = tvalid ? tlist[li] : 0;
-    const int tx = (int)morton_x((uint32_t)tcell), ty = (int)morton_y((uint32_t)tcell);
-    doublex4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-    for (int e = 0; e < ne; ++e) {
-        const int4 en = ents[e];
-        const double *b0p = tab + (((size_t)en.z * 4 + kq) * 32 + row) * 8;
-        const double *b1p = b0p + 16 * 8;
-        double a[8], b0[8], b1[8];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const double2 u0 = ((const double2 *)b0p)[v], u1 = ((const double2 *)b1p)[v];
-            b0[2 * v] = u0.x;
-            b0[2 * v + 1] = u0.y;
-            b1[2 * v] = u1.x;
-            b1[2 * v + 1] = u1.y;
-        }
-        const double *src = zero;
-        if (en.w == 0) {
-            const int sx = tx + en.x, sy = ty + en.y;
-            if (tvalid && sx >= 0 && sy >= 0 && sx < nside && sy < nside)
-                src = src_same + (size_t)morton_encode((uint32_t)sx, (uint32_t)sy) * two_p;
-        } else if (en.w == 1) {
-            if (tvalid && loc_par) src = loc_par + (size_t)(tcell >> 2) * two_p;
-        } else {
-            if (tvalid) src = src_child + (size_t)(4 * tcell + en.x) * two_p;
-        }
-        load_row8(a, src, k0, two_p);
-#pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[st], b0[st], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[st], b1[st], acc1, 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int lo = base + kq + 4 * r;
-        if (lo < clen) {
-            double *o = out + (size_t)tlist[lo] * two_p;
-            if (row < two_p) o[row] = acc0[r];
-            if (16 + row < two_p) o[16 + row] = acc1[r];
-        }
-    }
-}
-
-// Out-of-line copy for the coarse kernel, which calls it from two loops.
-__device__ __noinline__ void gemm_tile_f64_call(const int *__restrict__ tlist, int clen, int base,
-                                                const int4 *__restrict__ ents, int ne, int p, int level,
-                                                const double *__restrict__ src_same,
-                                                const double *__restrict__ src_child,
-                                                const double *__restrict__ loc_par, double *__restrict__ out,
-                                                const double *__restrict__ tab, const double *__restrict__ zero)
-{
-    gemm_tile_f64(tlist, clen, base, ents, ne, p, level, src_same, src_child, loc_par, out, tab, zero);
-}
-
-struct LevelClasses {
-    int start[4], len[4], wave0[4];
-    int waves;
-};
-
-// Wide FP64 launch over one level: wavefront w takes tile w of its class.
-__global__ __launch_bounds__(256, 4) void gather_gemm_f64_kernel(const int *__restrict__ targets, LevelClasses lc,
-                                                              int4 class_entry, int ne_l2l, int ne_m2m, int mode,
-                                                              int p, int level, const int4 *__restrict__ entries,
-                                                              const double *__restrict__ src_same,
-                                                              const double *__restrict__ src_child,
-                                                              const double *__restrict__ loc_par,
-                                                              double *__restrict__ out, const double *__restrict__ tab,
-                                                              const double *__restrict__ zero)
-{
-    const int wave_step = (int)((gridDim.x * blockDim.x) >> 6);
-    for (int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6); wave < lc.waves; wave += wave_step) {
-        int q = 0;
-        for (int c = 1; c < 4; ++c)
-            if (wave >= lc.wave0[c]) q = c;
-        const int e0 = q == 0 ? class_entry.x : q == 1 ? class_entry.y : q == 2 ? class_entry.z : class_entry.w;
-        const int ne = mode == 2 ? ne_m2m : ne_l2l;
-        gemm_tile_f64(targets + lc.start[q], lc.len[q], (wave - lc.wave0[q]) * 16, entries + e0, ne, p, level,
-                      src_same, src_child, loc_par, out, tab, zero);
-    }
-}
-
-template <typename TC, typename TP>
-__global__ __launch_bounds__(256) void m2m_kernel(const int *__restrict__ parents, int nparents, int p,
-                                                   const int *__restrict__ child_count,
-                                                   const c2<TC> *__restrict__ child, c2<TP> *__restrict__ parent,
-                                                   const c2<TP> *__restrict__ tab)
-{
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t cell = g / p;
-    if (cell >= nparents) return;
-    const int m = (int)(g - cell * p);
-    m2m_one<TC, TP>(parents[cell], m, p, child_count, child, parent, tab);
-}
-
-template <typename T, typename TPar>
-__global__ __launch_bounds__(256) void m2l_kernel(const int *__restrict__ targets, int ntargets, int p, int level,
-                                                   const int *__restrict__ count_l, const c2<T> *__restrict__ mp_l,
-                                                   c2<T> *__restrict__ lo_l, const c2<T> *__restrict__ m2l_tab,
-                                                   const c2<TPar> *__restrict__ loc_par,
-                                                   const c2<TPar> *__restrict__ l2l_tab)
-{
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t cell = g / p;
-    if (cell >= ntargets) return;
-    const int lo = (int)(g - cell * p);
-    m2l_one<T, TPar>(targets[cell], lo, p, level, count_l, mp_l, lo_l, m2l_tab, loc_par, l2l_tab);
-}
-
-// ---------------------------------------------------------------------------------
-// Coarse levels (<= L_c) in one workgroup: M2M into levels L_c-1..2, then M2L + L2L
-// for levels 2..L_c, in FP64 on MFMA (16 wavefronts, one 16-target tile each per
-// pass).  These levels hold too few cells to fill the chip; the paper assigns them to
-// a single thread group and covers their latency with the near-field work (section
-// "Concurrency").
-// ---------------------------------------------------------------------------------
-// One workgroup of up to 16 wavefronts (four per SIMD of its CU): each level's tiles are
-// dealt to the wavefronts, so a level of 1024 cells takes four rounds of gathers with 16
-// wavefronts instead of 16 rounds with 4.  Beside a near field capped below the full
-// occupancy only one wavefront per SIMD fits in the registers it leaves, so the kernel is
-// then launched with 4 (FarArgs::coarse_threads).
-constexpr int kCoarseThreads = 1024;
-constexpr int kCoarseMaxLevel = 4;
-
-struct CoarseArgs {
-    int p, lc;
-    const int *lists;
-    int64_t list_off[kMaxDepth + 1];
-    int64_t list_len[kMaxDepth + 1];
-    int64_t class_off[4 * (kMaxDepth + 1)];
-    double2 *mp, *lo;   // FP64 storage from level 0
-    const int4 *entries;
-    const double *tab;
-    const double *zero;
-};
-
-__global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(CoarseArgs a)
-{
-    const int p = a.p;
-    const int wave = threadIdx.x >> 6;
-    const int nw = blockDim.x >> 6;
-    for (int l = a.lc - 1; l >= 2; --l) {
-        const int n = (int)a.list_len[l];
-        const int *lst = a.lists + a.list_off[l];
-        for (int tile = wave; tile * 16 < n; tile += nw)
-            gemm_tile_f64_call(lst, n, tile * 16, a.entries + 112, 4, p, l, nullptr,
-                          (const double *)(a.mp + level_base(l + 1) * p), nullptr,
-                          (double *)(a.mp + level_base(l) * p), a.tab, a.zero);
-        __syncthreads();
-    }
-    for (int l = 2; l <= a.lc; ++l) {
-        const int n = (int)a.list_len[l];
-        const int *lst = a.lists + a.list_off[l];
-        const int64_t *co = &a.class_off[4 * l];
-        // tiles of the four parity classes, numbered consecutively
-        int ntile[4], tot = 0;
-        for (int q = 0; q < 4; ++q) {
-            const int len = (int)((q < 3 ? co[q + 1] : n) - co[q]);
-            ntile[q] = (len + 15) / 16;
-            tot += ntile[q];
-        }
-        for (int tile = wave; tile < tot; tile += nw) {
-            int q = 0, tq = tile;
-            while (tq >= ntile[q]) {
-                tq -= ntile[q];
-                ++q;
-            }
-            const int len = (int)((q < 3 ? co[q + 1] : n) - co[q]);
-            gemm_tile_f64_call(lst + co[q], len, tq * 16, a.entries + 28 * q, l >= 3 ? 28 : 27, p, l,
-                          (const double *)(a.mp + level_base(l) * p), nullptr,
-                          l >= 3 ? (const double *)(a.lo + level_base(l - 1) * p) : nullptr,
-                          (double *)(a.lo + level_base(l) * p), a.tab, a.zero);
-        }
-        __syncthreads();
-    }
-}
-
-// VALU form of the coarse-level kernel for p > 16 (no MFMA tables).
-struct CoarseValuArgs {
-    int p, lc;
-    const int *counts;  // global cell index
-    const int *lists;
-    int64_t list_off[kMaxDepth + 1];
-    int64_t list_len[kMaxDepth + 1];
-    double2 *mp, *lo;   // FP64 storage from level 0
-    const double2 *m2m_tab, *m2l_tab, *l2l_tab;
-};
-
-__global__ __launch_bounds__(1024) void coarse_valu_kernel(CoarseValuArgs a)
-{
-    const int p = a.p;
-    for (int l = a.lc - 1; l >= 2; --l) {
-        const int n = (int)a.list_len[l];
-        const int *lst = a.lists + a.list_off[l];
-        for (int g = threadIdx.x; g < n * p; g += blockDim.x) {
-            const int c = g / p, m = g - c * p;
-            m2m_one<double, double>(lst[c], m, p, a.counts + level_base(l + 1), a.mp + level_base(l + 1) * p,
-                                    a.mp + level_base(l) * p, a.m2m_tab);
-        }
-        __syncthreads();
-    }
-    for (int l = 2; l <= a.lc; ++l) {
-        const int n = (int)a.list_len[l];
-        const int *lst = a.lists + a.list_off[l];
-        for (int g = threadIdx.x; g < n * p; g += blockDim.x) {
-            const int c = g / p, lo = g - c * p;
-            m2l_one<double, double>(lst[c], lo, p, l, a.counts + level_base(l), a.mp + level_base(l) * p,
-                                    a.lo + level_base(l) * p, a.m2l_tab,
-                                    l >= 3 ? a.lo + level_base(l - 1) * p : nullptr, a.l2l_tab);
-        }
-        __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------------
 // Stages 8 + 10: L2P from the leaf's local expansion (Horner in xi = (z - c)/w_L,
 // W_far = (1/w_L) sum_l b_l xi^l), plus the near field, scattered to user order:
 // (u, v) = (u_near + Re W_far, v_near - Im W_far).  (A two-pass scatter through a
@@ -902,118 +460,6 @@ void p2m_launch(const FarArgs &a, hipStream_t s)
     else
         p2m_kernel<TR, TC, 32><<<g, 64, 0, s>>>(level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos,
                                                 t->d_gpos2, t->d_st1, gam, a.adj, t->x0, t->y0, w, a.p, out, nxcd);
-}
-
-template <typename TC, typename TP>
-void m2m_launch(const FarArgs &a, int l, const c2<TP> *tab, hipStream_t s)
-{
-    const fmm_tree *t = a.t;
-    const int64_t n = t->list_len[l];
-    if (n == 0) return;
-    m2m_kernel<TC, TP><<<blocks_for(n * a.p, 256), 256, 0, s>>>(
-        level_list(t, l), (int)n, a.p, t->d_counts + level_base(l + 1), level_ptr<TC>(a, l + 1, false),
-        level_ptr<TP>(a, l, false), tab);
-}
-
-// Split a level list into up to four classes of 32-target tiles (one wavefront each).
-struct ClassTiles {
-    int start[4], len[4], wave0[4], waves;
-};
-
-ClassTiles class_tiles(const int64_t *class_off, int64_t n, int nclass)
-{
-    ClassTiles c{};
-    for (int q = 0; q < 4; ++q) {
-        if (q < nclass) {
-            c.start[q] = (int)class_off[q];
-            c.len[q] = (int)((q + 1 < nclass ? class_off[q + 1] : n) - class_off[q]);
-        } else {
-            c.start[q] = (int)n;
-            c.len[q] = 0;
-        }
-        c.wave0[q] = c.waves;
-        c.waves += (c.len[q] + 31) / 32;
-    }
-    return c;
-}
-
-inline int4 i4(const int (&v)[4]) { return make_int4(v[0], v[1], v[2], v[3]); }
-
-// Stages 6 + 7 at level l on MFMA: local expansions of the non-empty cells.
-template <typename TPar>
-void m2l_mfma_launch(const FarArgs &a, int l, hipStream_t s)
-{
-    const fmm_tree *t = a.t;
-    const int64_t n = t->list_len[l];
-    if (n == 0) return;
-    const ClassTiles c = class_tiles(&t->class_off[4 * l], n, 4);
-    const c2<TPar> *par = l >= 3 ? level_ptr<TPar>(a, l - 1, true) : nullptr;
-    const int ne = par ? 28 : 27;  // the L2L entry is last in each class
-    gather_gemm_kernel<TPar, float><<<blocks_for(c.waves, 4), 256, 0, s>>>(
-        level_list(t, l), i4(c.start), i4(c.len), i4(c.wave0), make_int4(0, 28, 56, 84), make_int4(ne, ne, ne, ne),
-        c.waves, a.p, l, t->tabs->mfma_entries, (const float *)level_ptr<float>(a, l, false), nullptr, par,
-        (float *)level_ptr<float>(a, l, true), t->tabs->mfma_f, t->tabs->zero_row);
-}
-
-// Stage 5 into level l on MFMA from the FP32 child level l + 1.
-template <typename TP>
-void m2m_mfma_launch(const FarArgs &a, int l, hipStream_t s)
-{
-    const fmm_tree *t = a.t;
-    const int64_t n = t->list_len[l];
-    if (n == 0) return;
-    const int64_t one_class[1] = {0};
-    const ClassTiles c = class_tiles(one_class, n, 1);
-    gather_gemm_kernel<float, TP><<<blocks_for(c.waves, 4), 256, 0, s>>>(
-        level_list(t, l), i4(c.start), i4(c.len), i4(c.wave0), make_int4(112, 112, 112, 112), make_int4(4, 0, 0, 0),
-        c.waves, a.p, l, t->tabs->mfma_entries, nullptr, (const float *)level_ptr<float>(a, l + 1, false), nullptr,
-        (TP *)level_ptr<TP>(a, l, false), t->tabs->mfma_f, t->tabs->zero_row);
-}
-
-LevelClasses level_classes(const int64_t *class_off, int64_t n, int nclass)
-{
-    LevelClasses c{};
-    for (int q = 0; q < 4; ++q) {
-        if (q < nclass) {
-            c.start[q] = (int)class_off[q];
-            c.len[q] = (int)((q + 1 < nclass ? class_off[q + 1] : n) - class_off[q]);
-        } else {
-            c.start[q] = (int)n;
-            c.len[q] = 0;
-        }
-        c.wave0[q] = c.waves;
-        c.waves += (c.len[q] + 15) / 16;
-    }
-    return c;
-}
-
-// FP64 stages 6 + 7 (mode 0) or stage 5 (mode 2) at level l on MFMA.
-void gemm_f64_launch(const FarArgs &a, int l, int mode, hipStream_t s)
-{
-    const fmm_tree *t = a.t;
-    const int64_t n = t->list_len[l];
-    if (n == 0) return;
-    const int64_t one_class[1] = {0};
-    const LevelClasses c = mode == 2 ? level_classes(one_class, n, 1) : level_classes(&t->class_off[4 * l], n, 4);
-    const int p = a.p;
-    gather_gemm_f64_kernel<<<blocks_for(c.waves, 4), 256, 0, s>>>(
-        level_list(t, l), c, mode == 2 ? make_int4(112, 112, 112, 112) : make_int4(0, 28, 56, 84), l >= 3 ? 28 : 27, 4,
-        mode, p, l, t->tabs->mfma_entries, mode == 0 ? (const double *)(a.mp_d + level_base(l) * p) : nullptr,
-        mode == 2 ? (const double *)(a.mp_d + level_base(l + 1) * p) : nullptr,
-        (mode == 0 && l >= 3) ? (const double *)(a.lo_d + level_base(l - 1) * p) : nullptr,
-        (double *)((mode == 0 ? a.lo_d : a.mp_d) + level_base(l) * p), t->tabs->mfma_d, t->tabs->zero_row);
-}
-
-template <typename T, typename TPar>
-void m2l_launch(const FarArgs &a, int l, const c2<T> *m2l_tab, const c2<TPar> *l2l_tab, hipStream_t s)
-{
-    const fmm_tree *t = a.t;
-    const int64_t n = t->list_len[l];
-    if (n == 0) return;
-    const c2<TPar> *par = l >= 3 ? level_ptr<TPar>(a, l - 1, true) : nullptr;
-    m2l_kernel<T, TPar><<<blocks_for(n * a.p, 256), 256, 0, s>>>(
-        level_list(t, l), (int)n, a.p, l, t->d_counts + level_base(l), level_ptr<T>(a, l, false),
-        level_ptr<T>(a, l, true), m2l_tab, par, l2l_tab);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1423,75 +869,141 @@ void launch_p2m(const FarArgs &a, hipStream_t s)
     }
 }
 
+namespace {
+
+// The target segments of levels l0..l1 for one launch: the four parity classes of each.
+void class_segs(TransArgs &a, const fmm_tree *t, int l0, int l1)
+{
+    a.nseg = 0;
+    for (int l = l0; l <= l1; ++l)
+        for (int q = 0; q < 4; ++q) {
+            const int64_t *co = &t->class_off[4 * l];
+            TransSeg &g = a.seg[a.nseg++];
+            g.start = (int)(t->list_off[l] + co[q]);
+            g.len = (int)((q < 3 ? co[q + 1] : t->list_len[l]) - co[q]);
+            g.level = l;
+        }
+}
+
+}  // namespace
+
+// Stage 5 up to level 2, stage 6 (M2L) for every level but the widest at once (one launch
+// per precision), stage 7 down, with the M2L of the widest levels.  FP64 levels that a 1024-workgroup grid covers run three to a launch
+// (launch_subtree); the rest one level to a launch.
 void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
 {
     const fmm_tree *t = a.t;
     const int L = t->depth;
     if (L < 2) return;
     const Tables &tb = *t->tabs;
-    const bool fine_is_double = a.split >= L;  // FP64 precision: every level double
-    // Stage 4: P2M into the leaf level.
-    if (with_p2m) launch_p2m(a, s);
-    // Levels <= lw run in the one-workgroup coarse kernel: the coarse levels up to 256
-    // cells (level 4), one round of gathers for its 16 wavefronts.  Coarse levels above that
-    // (L_c = 5: 1024 cells, 64 tiles) keep FP64 and the side stream but run as wide launches
-    // like the fine levels: on one CU their MFMA work alone takes longer than the near field.
-    const int lw = std::min(a.lc, kCoarseMaxLevel);
-    // Stage 5 on the fine levels: parents L-1 .. max(lw, 2).
-    for (int l = L - 1; l >= 2 && l >= lw; --l) {
-        const bool child_d = (l + 1) <= a.split, parent_d = l <= a.split;
-        if (child_d && parent_d && a.p <= 16) gemm_f64_launch(a, l, 2, s);
-        else if (child_d && parent_d) m2m_launch<double, double>(a, l, tb.m2m_d, s);
-        else if (a.p <= 16 && parent_d) m2m_mfma_launch<double>(a, l, s);
-        else if (a.p <= 16) m2m_mfma_launch<float>(a, l, s);
-        else if (parent_d) m2m_launch<float, double>(a, l, tb.m2m_d, s);
-        else m2m_launch<float, float>(a, l, tb.m2m_f, s);
-    }
-    // Coarse levels 2..lw in one workgroup (stages 5, 6, 7 there).
-    if (lw >= 2 && a.p > 16) {
-        CoarseValuArgs c{};
-        c.p = a.p;
-        c.lc = lw;
-        c.counts = t->d_counts;
-        c.lists = t->d_lists;
-        for (int l = 0; l <= kMaxDepth; ++l) {
-            c.list_off[l] = l <= L ? t->list_off[l] : 0;
-            c.list_len[l] = l <= L ? t->list_len[l] : 0;
+    if (with_p2m) launch_p2m(a, s);  // stage 4
+    const int S = std::min(L, a.split);  // last FP64 level
+    const int64_t fbase = level_base(a.split + 1);
+
+    TransArgs g{};
+    g.p = a.p;
+    g.no_lds = a.no_lds;
+    g.targets = t->d_lists;
+    g.entries = tb.mfma_entries;
+    g.zero = tb.zero_row;
+    SubtreeArgs st{};
+    st.p = a.p;
+    st.deepest = S;
+    st.counts = t->d_counts;
+    st.tab = tb.mfma_d;
+
+    // the group of three levels a subtree launch covers: bases 2 and 5 (16 and 1024 workgroups)
+    auto group = [](int rank) { return 2 + 3 * (rank / 3); };
+
+    for (int l = L - 1; l >= 2;) {
+        g.nseg = 1;
+        g.seg[0] = TransSeg{0, (int)t->list_off[l], (int)t->list_len[l], l};
+        if (l >= a.split) {  // FP32 children
+            g.tab = tb.mfma_f;
+            g.src = a.mp_f;
+            g.src_off = fbase;
+            g.out = l == a.split ? (void *)a.mp_d : (void *)a.mp_f;
+            g.out_off = l == a.split ? 0 : fbase;
+            launch_trans32(g, Trans::M2M, false, l == a.split, s);
+            --l;
+            continue;
         }
-        c.mp = a.mp_d;
-        c.lo = a.lo_d;
-        c.m2m_tab = tb.m2m_d;
-        c.m2l_tab = tb.m2l_d;
-        c.l2l_tab = tb.l2l_d;
-        coarse_valu_kernel<<<1, 1024, 0, s>>>(c);
-    } else if (lw >= 2) {
-        CoarseArgs c{};
-        c.p = a.p;
-        c.lc = lw;
-        c.lists = t->d_lists;
-        for (int l = 0; l <= kMaxDepth; ++l) {
-            c.list_off[l] = l <= L ? t->list_off[l] : 0;
-            c.list_len[l] = l <= L ? t->list_len[l] : 0;
-            for (int q = 0; q < 4; ++q) c.class_off[4 * l + q] = l <= L ? t->class_off[4 * l + q] : 0;
+        const int b = group(l - 2);
+        if (b == 2 || (b == 5 && l > 5)) {
+            st.base = b;
+            st.rows = (double *)a.mp_d;
+            st.deepest = l + 1;
+            launch_subtree(st, true, s);
+            l = b - 1;
+            continue;
         }
-        c.mp = a.mp_d;
-        c.lo = a.lo_d;
-        c.entries = tb.mfma_entries;
-        c.tab = tb.mfma_d;
-        c.zero = tb.zero_row;
-        coarse_kernel<<<1, a.coarse_threads, 0, s>>>(c);
+        g.tab = tb.mfma_d;
+        g.src = g.out = a.mp_d;
+        g.src_off = g.out_off = 0;
+        launch_trans64(g, Trans::M2M, false, s);
+        --l;
     }
-    // Stages 6 + 7 on the fine levels.
-    for (int l = (lw + 1 > 2 ? lw + 1 : 2); l <= L; ++l) {
-        const bool here_d = l <= a.split, par_d = (l - 1) <= a.split;
-        if (here_d && a.p <= 16) gemm_f64_launch(a, l, 0, s);
-        else if (here_d) m2l_launch<double, double>(a, l, tb.m2l_d, tb.l2l_d, s);
-        else if (a.p <= 16 && par_d) m2l_mfma_launch<double>(a, l, s);
-        else if (a.p <= 16) m2l_mfma_launch<float>(a, l, s);
-        else if (par_d) m2l_launch<float, double>(a, l, tb.m2l_f, tb.l2l_d, s);
-        else m2l_launch<float, float>(a, l, tb.m2l_f, tb.l2l_f, s);
+
+    // levels from wide on (the finest, where the tree has cells enough) take M2L and L2L together
+    int wide = L + 1;
+    while (wide > 3 && (wide - 1 > S ? wide_level32(t->list_len[wide - 1], a.p) : wide_level64(t->list_len[wide - 1], a.p)))
+        --wide;
+    class_segs(g, t, 2, std::min(S, wide - 1));
+    g.tab = tb.mfma_d;
+    g.src = a.mp_d;
+    g.out = a.lo_d;
+    g.src_off = g.out_off = 0;
+    launch_trans64(g, Trans::M2L, false, s);
+    if (wide - 1 > S) {
+        class_segs(g, t, S + 1, wide - 1);
+        g.tab = tb.mfma_f;
+        g.src = a.mp_f;
+        g.out = a.lo_f;
+        g.src_off = g.out_off = fbase;
+        launch_trans32(g, Trans::M2L, false, false, s);
     }
-    (void)fine_is_double;
+
+    for (int l = 3; l <= L;) {
+        if (l >= wide) {
+            class_segs(g, t, l, l);
+            g.par = l - 1 <= S ? (const void *)a.lo_d : (const void *)a.lo_f;
+            g.par_off = l - 1 <= S ? 0 : fbase;
+            g.tab = l <= S ? (const void *)tb.mfma_d : (const void *)tb.mfma_f;
+            g.src = l <= S ? (const void *)a.mp_d : (const void *)a.mp_f;
+            g.out = l <= S ? (void *)a.lo_d : (void *)a.lo_f;
+            g.src_off = g.out_off = l <= S ? 0 : fbase;
+            if (l <= S) launch_trans64(g, Trans::M2L, false, s);
+            else launch_trans32(g, Trans::M2L, l - 1 <= S, false, s);
+            ++l;
+            continue;
+        }
+        if (l > S) {  // FP32 targets
+            class_segs(g, t, l, l);
+            g.tab = tb.mfma_f;
+            g.src = l - 1 <= S ? (const void *)a.lo_d : (const void *)a.lo_f;
+            g.src_off = l - 1 <= S ? 0 : fbase;
+            g.out = a.lo_f;
+            g.out_off = fbase;
+            launch_trans32(g, Trans::L2L, l - 1 <= S, false, s);
+            ++l;
+            continue;
+        }
+        const int b = group(l - 3), last = std::min({S, b + 3, wide - 1});
+        if (b == 2 || (b == 5 && last > 6)) {
+            st.base = b;
+            st.rows = (double *)a.lo_d;
+            st.deepest = last;
+            launch_subtree(st, false, s);
+            l = last + 1;
+            continue;
+        }
+        class_segs(g, t, l, l);
+        g.tab = tb.mfma_d;
+        g.src = g.out = a.lo_d;
+        g.src_off = g.out_off = 0;
+        launch_trans64(g, Trans::L2L, false, s);
+        ++l;
+    }
 }
 
 void launch_finalize(const fmm_tree *t, const FarArgs &a, const double2 *near, const void *slots, int slots_double,

@@ -1,0 +1,564 @@
+// gfx950 kernels of the translations M2M, M2L and L2L (stages 5-7 of Fig. fmmStages of
+// Knepley, arXiv:1008.2410), shared by the uniform and the adaptive tree.
+//
+// With radius-scaled coefficients every translation of one offset is the same 2p x 2p real
+// operator (complex entries embedded with interleaved (re, im) rows and columns), so a tile
+// of 16 (FP64) or 32 (FP32) targets of one parity class is a chain of small dense products
+//   out(T) += sum_e row(source_e(T)) R_e
+// on the matrix cores.  Absent sources read a zero row.
+//
+// A tree has few cells at most levels: the time of a chain of launches is the latency of a
+// tile, not its arithmetic.  So the M2L of all levels, which needs only the multipoles, is
+// one launch after the upward pass, and the downward pass is L2L alone, one operator per
+// level, added to the locals the M2L wrote.  (With M2L + L2L fused per level, each level
+// waited for the 28 gathered operands of the level above: 23-45 us a level whatever its
+// size, and 77-135 us for the levels <= 3 in one workgroup.)
+//
+// Operand layouts (lane l):
+//   FP64 16x16x4: A[row l%16][k l/16], B[k l/16][col l%16], D register r: [l/16 + 4r][l%16]
+//   FP32 32x32x2: A[row l%32][k l/32], B[k l/32][col l%32], D register r:
+//                 [8(r/4) + 4(l/32) + r%4][l%32]
+// K is permuted so that a lane's steps are consecutive: step s of group g = l/16 (l/32) is
+// k = KS g + s, so a lane reads KS contiguous values of its row; the tables hold B as
+// [slot][g][col][s].
+#include "translate.h"
+
+#include <algorithm>
+
+#include "device_common.h"
+
+namespace fmm {
+namespace {
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ int find_seg(const TransArgs &a, int tile)
+{
+    int sg = 0;
+    for (int k = 1; k < a.nseg; ++k)
+        if (tile >= a.seg[k].tile0) sg = k;
+    return sg;
+}
+
+// KS values of a row from k0 on, zero from two_p on (the reads past a row's end stay inside
+// the array's tail pad or the zero row).
+template <int KS>
+__device__ __forceinline__ void load_row(double (&a)[KS], const double *row, int k0, int two_p)
+{
+    const double2 *r = (const double2 *)(row + k0);
+#pragma unroll
+    for (int v = 0; v < KS / 2; ++v) {
+        const double2 t = r[v];
+        a[2 * v] = t.x;
+        a[2 * v + 1] = t.y;
+    }
+    if (4 * KS != two_p) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) a[s] = k0 + s < two_p ? a[s] : 0.0;
+    }
+}
+
+template <int KS> __device__ __forceinline__ void load_op(double (&b)[KS], const double *tab)
+{
+    const double2 *t = (const double2 *)tab;
+#pragma unroll
+    for (int v = 0; v < KS / 2; ++v) {
+        const double2 u = t[v];
+        b[2 * v] = u.x;
+        b[2 * v + 1] = u.y;
+    }
+}
+
+// Blocks of 16 output columns.
+template <int KS> constexpr int col_blocks() { return (4 * KS + 15) / 16; }
+
+// ---------------------------------------------------------------------------------
+// FP64.  A workgroup takes one tile of 16 RB targets; wavefront w has the column block
+// w % NB and, of the tile's operators, every KG-th from w / NB on.  The KG partial sums
+// meet in LDS, added in a fixed order; with SEQ one wavefront per column block makes them
+// one after the other and adds them in that order, without LDS and to the same bits.
+// Bound: the matrix cores (64 cycles per 16x16x4 product) where the tiles fill the chip,
+// the latency of the gathered rows where they do not; hence the operands of the next
+// operator are loaded ahead of the products of the current one, and few tiles are split
+// further (KG).
+// ---------------------------------------------------------------------------------
+template <int KS, int RB, int KG, bool SEQ, Trans MODE, bool ADAPT>
+__global__ __launch_bounds__(64 * col_blocks<KS>() * (SEQ ? 1 : KG)) void trans64_kernel(TransArgs a)
+{
+    constexpr int NB = col_blocks<KS>(), NC = 16 * NB;
+    constexpr int NE = MODE == Trans::M2L ? 27 : MODE == Trans::M2M ? 4 : 1;
+    const int tile = xcd_block(kXcds);
+    if (tile >= a.ntiles) return;  // the whole workgroup
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int cb = wave % NB, kg = wave / NB;
+    const int row = lane & 15, kq = lane >> 4;
+    const int two_p = 2 * a.p, k0 = KS * kq;
+    const int sg = find_seg(a, tile);
+    const TransSeg seg = a.seg[sg];
+    const int q = sg & 3;
+    const int base = (tile - seg.tile0) * 16 * RB;
+    const int *tl = a.targets + seg.start;
+
+    int tcell[RB], tx[RB], ty[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        const int li = base + 16 * b + row;
+        tcell[b] = li < seg.len ? tl[li] : -1;
+        if constexpr (!ADAPT && MODE == Trans::M2L) {
+            tx[b] = (int)morton_x((uint32_t)tcell[b]);
+            ty[b] = (int)morton_y((uint32_t)tcell[b]);
+        }
+    }
+    const int64_t here = ADAPT ? 0 : level_base(seg.level) - a.out_off;
+    const int64_t from =
+        ADAPT ? 0 : level_base(seg.level + (MODE == Trans::M2M ? 1 : MODE == Trans::L2L ? -1 : 0)) - a.src_off;
+    const double *src = (const double *)a.src;
+    double *out = (double *)a.out;
+
+    // the source row of target block b for operator e, or the zero row
+    auto source = [&](int b, int e, int4 en) -> const double * {
+        int64_t S = -1;
+        if constexpr (MODE == Trans::M2L && !ADAPT) {
+            if (e == 27)  // L2L (with par)
+                return tcell[b] >= 0 ? (const double *)a.par + (level_base(seg.level - 1) - a.par_off + (tcell[b] >> 2)) * two_p
+                                     : a.zero;
+            const int sx = tx[b] + en.x, sy = ty[b] + en.y, nside = 1 << seg.level;
+            if (tcell[b] >= 0 && sx >= 0 && sy >= 0 && sx < nside && sy < nside)
+                S = from + morton_encode((uint32_t)sx, (uint32_t)sy);
+        } else if constexpr (MODE == Trans::M2M && !ADAPT) {
+            if (tcell[b] >= 0) S = from + 4 * (int64_t)tcell[b] + e;
+        } else if constexpr (MODE == Trans::L2L && !ADAPT) {
+            if (tcell[b] >= 0) S = from + (tcell[b] >> 2);
+        } else if constexpr (MODE == Trans::M2L) {
+            if (tcell[b] >= 0) S = a.vslot[(int64_t)(tcell[b] - a.first) * 27 + e];
+        } else if constexpr (MODE == Trans::M2M) {
+            if (tcell[b] >= 0) {
+                const int4 ch = a.child[tcell[b]];
+                S = e == 0 ? ch.x : e == 1 ? ch.y : e == 2 ? ch.z : ch.w;
+            }
+        } else {
+            if (tcell[b] >= 0) S = a.parent[tcell[b]];
+        }
+        return S >= 0 ? src + S * two_p : a.zero;
+    };
+    const int e0 = MODE == Trans::M2L ? 28 * q : MODE == Trans::M2M ? 112 : 28 * q + 27;
+
+    // operators this wavefront applies, as a bit mask (adaptive M2L: those some target uses)
+    uint32_t used = (1u << NE) - 1u;
+    if (MODE == Trans::M2L && !ADAPT && a.par) used |= 1u << 27;
+    if constexpr (ADAPT && MODE == Trans::M2L) {
+        used = 0;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            bool any = false;
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+                any = any || (tcell[b] >= 0 && a.vslot[(int64_t)(tcell[b] - a.first) * 27 + e] >= 0);
+            if (__any(any)) used |= 1u << e;
+        }
+    }
+    // every KG-th of them, from number g on
+    auto share = [](uint32_t all, int g) {
+        uint32_t mine = 0;
+        for (int k = 0; all; ++k) {
+            const uint32_t low = all & -all;
+            if (k % KG == g) mine |= low;
+            all ^= low;
+        }
+        return mine;
+    };
+    used = (uint32_t)__builtin_amdgcn_readfirstlane((int)used);
+
+    doublex4 acc[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[b][r] = 0.0;
+    const int col = 16 * cb + row;
+    if ((MODE == Trans::L2L || (ADAPT && MODE == Trans::M2L)) && kg == 0) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int o = base + 16 * b + kq + 4 * r;
+                if (o < seg.len && col < two_p) {
+                    const int k = tl[o];
+                    // L2L adds to the M2L sums; the adaptive M2L to the P2L sums, where there are any
+                    if (MODE == Trans::L2L || a.x_off[k] < a.x_off[k + 1]) acc[b][r] = out[(here + k) * two_p + col];
+                }
+            }
+    }
+
+    const double *tab = (const double *)a.tab;
+    double av[2][RB][KS], bv[2][KS];
+    auto fetch = [&](int slot, uint32_t m) {
+        const int e = __builtin_ctz(m);
+        const int4 en = a.entries[e0 + e];
+        load_op<KS>(bv[slot], tab + (((size_t)en.z * 4 + kq) * NC + col) * KS);
+#pragma unroll
+        for (int b = 0; b < RB; ++b) load_row<KS>(av[slot][b], source(b, e, en), k0, two_p);
+    };
+    auto products = [&](int slot) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[slot][b][s], bv[slot][s], acc[b], 0, 0, 0);
+    };
+    auto apply = [&](uint32_t m) {  // m wavefront-uniform
+        if (m) fetch(0, m);
+        while (m) {
+            m &= m - 1;
+            if (m) fetch(1, m);
+            products(0);
+            if (!m) break;
+            m &= m - 1;
+            if (m) fetch(0, m);
+            products(1);
+        }
+    };
+    if constexpr (KG == 1) {
+        apply(used);
+    } else if constexpr (SEQ) {
+        doublex4 sum[RB];
+        for (int g = 0; g < KG; ++g) {
+            apply(share(used, g));
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    sum[b][r] = g == 0 ? acc[b][r] : sum[b][r] + acc[b][r];
+                    acc[b][r] = 0.0;
+                }
+        }
+#pragma unroll
+        for (int b = 0; b < RB; ++b) acc[b] = sum[b];
+    } else {
+        apply(share(used, kg));
+    }
+
+    if constexpr (KG > 1 && !SEQ) {
+        __shared__ double part[KG - 1][NB][RB][4][64];
+        if (kg > 0)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) part[kg - 1][cb][b][r][lane] = acc[b][r];
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[b][r] += part[g][cb][b][r][lane];
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int o = base + 16 * b + kq + 4 * r;
+            if (o < seg.len && col < two_p) out[(here + tl[o]) * two_p + col] = acc[b][r];
+        }
+}
+
+// ---------------------------------------------------------------------------------
+// The coarse end of the upward and downward passes: one workgroup per cell of level `base`
+// takes its subtree's next three levels in sequence, every cell of them (rows of empty
+// cells stay zero going up, and are not read going down).  A level is at most one 16-row
+// tile of parents going up (a wavefront per column block) and one per parity class going
+// down (a wavefront per class), so three levels cost three tile latencies and one launch.
+// ---------------------------------------------------------------------------------
+template <int KS>
+__global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(SubtreeArgs a)
+{
+    constexpr int NB = col_blocks<KS>(), NC = 16 * NB;
+    const int cell0 = blockIdx.x;
+    if (a.counts[level_base(a.base) + cell0] == 0) return;
+    const int lane = threadIdx.x & 63, cb = threadIdx.x >> 6;
+    const int row = lane & 15, kq = lane >> 4;
+    const int two_p = 2 * a.p, k0 = KS * kq, col = 16 * cb + row;
+    for (int l = min(a.deepest - 1, a.base + 2); l >= a.base; --l) {
+        const int n = 1 << (2 * (l - a.base));
+        const double *child = a.rows + (level_base(l + 1) + 4 * ((int64_t)cell0 * n + min(row, n - 1))) * two_p;
+        double av[4][KS], bv[4][KS];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            load_row<KS>(av[e], child + e * two_p, k0, two_p);
+            load_op<KS>(bv[e], a.tab + (((size_t)(53 + e) * 4 + kq) * NC + col) * KS);
+        }
+        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[e][s], bv[e][s], acc, 0, 0, 0);
+        double *out = a.rows + (level_base(l) + (int64_t)cell0 * n) * two_p;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (kq + 4 * r < n && col < two_p) out[(kq + 4 * r) * two_p + col] = acc[r];
+        __syncthreads();  // the next level reads these rows
+    }
+}
+
+template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(SubtreeArgs a)
+{
+    constexpr int NB = col_blocks<KS>(), NC = 16 * NB;
+    const int cell0 = blockIdx.x;
+    if (a.counts[level_base(a.base) + cell0] == 0) return;
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;  // wavefront: parity class of the targets
+    const int row = lane & 15, kq = lane >> 4;
+    const int two_p = 2 * a.p, k0 = KS * kq;
+    double bv[NB][KS];  // the class's operator, the same at every level
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+        load_op<KS>(bv[c], a.tab + (((size_t)(49 + q) * 4 + kq) * NC + 16 * c + row) * KS);
+    for (int l = a.base + 1; l <= min(a.deepest, a.base + 3); ++l) {
+        const int n = 1 << (2 * (l - a.base - 1));  // parents in the subtree, one target each per class
+        const double *par = a.rows + (level_base(l - 1) + (int64_t)cell0 * n) * two_p;
+        double *out = a.rows + (level_base(l) + 4 * (int64_t)cell0 * n + q) * two_p;  // target of parent k: row 4 k
+        double av[KS];
+        load_row<KS>(av, par + (int64_t)min(row, n - 1) * two_p, k0, two_p);
+        doublex4 acc[NB];
+#pragma unroll
+        for (int c = 0; c < NB; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int o = kq + 4 * r;
+                acc[c][r] = o < n && 16 * c + row < two_p ? out[(int64_t)4 * o * two_p + 16 * c + row] : 0.0;
+            }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int c = 0; c < NB; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s], bv[c][s], acc[c], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < NB; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int o = kq + 4 * r;
+                if (o < n && 16 * c + row < two_p) out[(int64_t)4 * o * two_p + 16 * c + row] = acc[c][r];
+            }
+        __syncthreads();  // the next level reads these rows
+    }
+}
+
+// ---------------------------------------------------------------------------------
+// FP32 (the fine levels of the mixed form): one wavefront per tile of 32 targets and block
+// of 32 columns, the next operator's operands loaded ahead of the current one's products.
+// ---------------------------------------------------------------------------------
+template <int KF, typename T>
+__device__ __forceinline__ void load_row32(float (&a)[KF], const T *row, int k0, int two_p)
+{
+    const T *r = row + k0;
+#pragma unroll
+    for (int s = 0; s < KF; ++s) {
+        const T v = r[s];
+        a[s] = k0 + s < two_p ? (float)v : 0.0f;
+    }
+}
+
+template <int KF> constexpr int col_blocks32() { return KF <= 16 ? 1 : 2; }
+
+template <int KF, Trans MODE, typename TSrc, typename TOut, typename TPar = float>
+__global__ __launch_bounds__(256, KF <= 16 ? 4 : 2) void trans32_kernel(TransArgs a)
+{
+    constexpr int NB = col_blocks32<KF>(), NC = 32 * NB;
+    const int NE = MODE == Trans::M2L ? (a.par ? 28 : 27) : MODE == Trans::M2M ? 4 : 1;
+    const int lane = threadIdx.x & 63;
+    const int id = xcd_block(kXcds) * 4 + (threadIdx.x >> 6);
+    const int tile = id / NB, cb = id % NB;
+    if (tile >= a.ntiles) return;  // whole wavefronts; no barriers below
+    const int row = lane & 31, kh = lane >> 5;
+    const int two_p = 2 * a.p, k0 = KF * kh;
+    const int sg = find_seg(a, tile);
+    const TransSeg seg = a.seg[sg];
+    const int q = sg & 3;
+    const int base = (tile - seg.tile0) * 32;
+    const int *tl = a.targets + seg.start;
+    const int li = base + row;
+    const int tcell = li < seg.len ? tl[li] : -1;
+    const int tx = (int)morton_x((uint32_t)tcell), ty = (int)morton_y((uint32_t)tcell);
+    const int nside = 1 << seg.level;
+    const int64_t here = level_base(seg.level) - a.out_off;
+    const int64_t from = level_base(seg.level + (MODE == Trans::M2M ? 1 : MODE == Trans::L2L ? -1 : 0)) - a.src_off;
+    const TSrc *src = (const TSrc *)a.src;
+    TOut *out = (TOut *)a.out;
+    const float *tab = (const float *)a.tab;
+    const int e0 = MODE == Trans::M2L ? 28 * q : MODE == Trans::M2M ? 112 : 28 * q + 27;
+    const int col = 32 * cb + row;
+
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    if constexpr (MODE == Trans::L2L) {  // added to the M2L sums
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int cell = __shfl(tcell, 8 * (r >> 2) + 4 * kh + (r & 3));
+            if (cell >= 0 && col < two_p) acc[r] = (float)out[(here + cell) * two_p + col];
+        }
+    }
+    float av[2][KF], bv[2][KF];
+    auto fetch = [&](int slot, int e) {
+        const int4 en = a.entries[e0 + e];
+        const float4 *b = (const float4 *)(tab + (((size_t)en.z * 2 + kh) * NC + col) * KF);
+#pragma unroll
+        for (int v = 0; v < KF / 4; ++v) {
+            const float4 t = b[v];
+            bv[slot][4 * v] = t.x;
+            bv[slot][4 * v + 1] = t.y;
+            bv[slot][4 * v + 2] = t.z;
+            bv[slot][4 * v + 3] = t.w;
+        }
+        int64_t S = -1;
+        if constexpr (MODE == Trans::M2L) {
+            if (e == 27) {  // L2L (with par)
+                const int64_t P = level_base(seg.level - 1) - a.par_off + (tcell >> 2);
+                load_row32<KF, TPar>(av[slot], tcell >= 0 ? (const TPar *)a.par + P * two_p : (const TPar *)a.zero, k0,
+                                     two_p);
+                return;
+            }
+            const int sx = tx + en.x, sy = ty + en.y;
+            if (tcell >= 0 && sx >= 0 && sy >= 0 && sx < nside && sy < nside)
+                S = from + morton_encode((uint32_t)sx, (uint32_t)sy);
+        } else if constexpr (MODE == Trans::M2M) {
+            if (tcell >= 0) S = from + 4 * (int64_t)tcell + e;
+        } else {
+            if (tcell >= 0) S = from + (tcell >> 2);
+        }
+        load_row32<KF, TSrc>(av[slot], S >= 0 ? src + S * two_p : (const TSrc *)a.zero, k0, two_p);
+    };
+    auto products = [&](int slot) {
+#pragma unroll
+        for (int s = 0; s < KF; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[slot][s], bv[slot][s], acc, 0, 0, 0);
+    };
+    fetch(0, 0);
+    for (int e = 0; e < NE; e += 2) {
+        if (e + 1 < NE) fetch(1, e + 1);
+        products(0);
+        if (e + 1 < NE) {
+            if (e + 2 < NE) fetch(0, e + 2);
+            products(1);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int cell = __shfl(tcell, 8 * (r >> 2) + 4 * kh + (r & 3));
+        if (cell >= 0 && col < two_p) out[(here + cell) * two_p + col] = (TOut)acc[r];
+    }
+}
+
+// Number the tiles of the segments (of `rows` targets each).
+void number_tiles(TransArgs &a, int rows)
+{
+    a.ntiles = 0;
+    for (int k = 0; k < a.nseg; ++k) {
+        a.seg[k].tile0 = a.ntiles;
+        a.ntiles += (a.seg[k].len + rows - 1) / rows;
+    }
+}
+
+template <int KS, int RB, int KG, Trans MODE, bool ADAPT, bool SEQ = false> void go64(TransArgs &a, hipStream_t s)
+{
+    number_tiles(a, 16 * RB);
+    if (a.ntiles == 0) return;
+    trans64_kernel<KS, RB, KG, SEQ, MODE, ADAPT>
+        <<<xcd_grid(a.ntiles, 1, kXcds), 64 * col_blocks<KS>() * (SEQ ? 1 : KG), 0, s>>>(a);
+}
+
+// KG partial sums side by side, or one after the other where the LDS is held.
+template <int KS, int KG, bool ADAPT> void split64(TransArgs &a, hipStream_t s)
+{
+    if (a.no_lds) go64<KS, 1, KG, Trans::M2L, ADAPT, true>(a, s);
+    else go64<KS, 1, KG, Trans::M2L, ADAPT>(a, s);
+}
+
+// M2L: split the operators over more wavefronts while the tiles leave the chip's 1024 SIMDs
+// idle; once they fill it, tiles of 32 targets (up to 16 terms: the operands of two row
+// blocks fit the registers twice) read each operator half as often.  The split meets in
+// LDS, so beside a near field that holds the LDS it would wait for workgroups to retire
+// (2^24 patches: 3.4 ms for the 88 tiles of levels 2..5).
+template <int KS, bool ADAPT> void m2l64(TransArgs &a, hipStream_t s)
+{
+    constexpr int NB = col_blocks<KS>();
+    number_tiles(a, 16);
+    const int waves = a.ntiles * NB;
+    if constexpr (KS <= 8) {
+        if (waves <= 1024) split64<KS, 4, ADAPT>(a, s);
+        else if (waves <= 4096) go64<KS, 1, 1, Trans::M2L, ADAPT>(a, s);
+        else go64<KS, 2, 1, Trans::M2L, ADAPT>(a, s);
+    } else {
+        if (waves <= 1024) split64<KS, 2, ADAPT>(a, s);
+        else go64<KS, 1, 1, Trans::M2L, ADAPT>(a, s);
+    }
+}
+
+template <int KS> void trans64(TransArgs &a, Trans mode, bool adaptive, hipStream_t s)
+{
+    if (mode == Trans::M2L) adaptive ? m2l64<KS, true>(a, s) : m2l64<KS, false>(a, s);
+    else if (mode == Trans::M2M)
+        adaptive ? go64<KS, 1, 1, Trans::M2M, true>(a, s) : go64<KS, 1, 1, Trans::M2M, false>(a, s);
+    else adaptive ? go64<KS, 1, 1, Trans::L2L, true>(a, s) : go64<KS, 1, 1, Trans::L2L, false>(a, s);
+}
+
+template <int KF, Trans MODE, typename TSrc, typename TOut, typename TPar = float> void go32(TransArgs &a, hipStream_t s)
+{
+    trans32_kernel<KF, MODE, TSrc, TOut, TPar><<<xcd_grid((int64_t)a.ntiles * col_blocks32<KF>(), 4, kXcds), 256, 0, s>>>(a);
+}
+
+template <int KF> void trans32(TransArgs &a, Trans mode, bool src_double, bool out_double, hipStream_t s)
+{
+    if (mode == Trans::M2L)
+        src_double ? go32<KF, Trans::M2L, float, float, double>(a, s) : go32<KF, Trans::M2L, float, float>(a, s);
+    else if (mode == Trans::M2M)
+        out_double ? go32<KF, Trans::M2M, float, double>(a, s) : go32<KF, Trans::M2M, float, float>(a, s);
+    else src_double ? go32<KF, Trans::L2L, double, float>(a, s) : go32<KF, Trans::L2L, float, float>(a, s);
+}
+
+template <int KS> void subtree(const SubtreeArgs &a, bool up, hipStream_t s)
+{
+    const unsigned g = 1u << (2 * a.base);
+    if (up) subtree_up_kernel<KS><<<g, 64 * col_blocks<KS>(), 0, s>>>(a);
+    else subtree_down_kernel<KS><<<g, 256, 0, s>>>(a);
+}
+
+}  // namespace
+
+void launch_trans64(TransArgs a, Trans mode, bool adaptive, hipStream_t s)
+{
+    switch (trans_ks(a.p)) {
+    case 4: trans64<4>(a, mode, adaptive, s); break;
+    case 6: trans64<6>(a, mode, adaptive, s); break;
+    case 8: trans64<8>(a, mode, adaptive, s); break;
+    case 12: trans64<12>(a, mode, adaptive, s); break;
+    default: trans64<16>(a, mode, adaptive, s); break;
+    }
+}
+
+void launch_trans32(TransArgs a, Trans mode, bool src_double, bool out_double, hipStream_t s)
+{
+    number_tiles(a, 32);
+    if (a.ntiles == 0) return;
+    switch (trans_kf(a.p)) {
+    case 8: trans32<8>(a, mode, src_double, out_double, s); break;
+    case 12: trans32<12>(a, mode, src_double, out_double, s); break;
+    case 16: trans32<16>(a, mode, src_double, out_double, s); break;
+    case 24: trans32<24>(a, mode, src_double, out_double, s); break;
+    default: trans32<32>(a, mode, src_double, out_double, s); break;
+    }
+}
+
+void launch_subtree(const SubtreeArgs &a, bool up, hipStream_t s)
+{
+    switch (trans_ks(a.p)) {
+    case 4: subtree<4>(a, up, s); break;
+    case 6: subtree<6>(a, up, s); break;
+    case 8: subtree<8>(a, up, s); break;
+    case 12: subtree<12>(a, up, s); break;
+    default: subtree<16>(a, up, s); break;
+    }
+}
+
+}  // namespace fmm
