@@ -185,9 +185,9 @@ __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const
 //    evaluates each unordered pair once for both particles (the kernel is odd), as for
 //    the uniform tree, with that level's leaf width; sums go to the per-direction slots;
 //  - a target-centric unit {leaf A, first, count <= 64, log2 TP | 16 if dense} takes
-//    every source leaf S of U(A) (but the same-level dense ones when flagged) in
-//    64-particle tiles staged in LDS, the target moved into S's frame
-//    (alpha (z_i - c_S) = record_i + alpha (c_A - c_S)).  A source tile whose bounding box
+//    every source leaf S of U(A) (but the same-level dense ones when flagged), the leaves
+//    concatenated and staged 64 sources at a time, each moved into A's frame
+//    (alpha (z_j - c_A) = record_j + alpha (c_S - c_A)).  A source leaf whose bounding box
 //    is at least the cut from the unit's box skips the exponential (1 - e rounds to 1).
 template <typename T>
 __device__ __forceinline__ void at_target_unit(const int4 u, rec_t<T> *tile, const int4 *__restrict__ cell,
@@ -199,12 +199,9 @@ __device__ __forceinline__ void at_target_unit(const int4 u, rec_t<T> *tile, con
                                                double2 *__restrict__ near)
 {
     const int lane = threadIdx.x;
-    const int logtp = u.w & 15;
     const bool skip_dense = (u.w >> 4) != 0;
-    const int tp = 1 << logtp;
-    const int t = lane & (tp - 1);
-    const int k = lane >> logtp;
-    const int i = u.y + min(t, u.z - 1);
+    const UnitLanes ul(lane, u.z, u.w & 15);
+    const int i = u.y + min(ul.t, u.z - 1);
     const rec_t<T> ri = rec(i);
     const int A = u.x;
     const int4 cla = cell[A];
@@ -212,43 +209,59 @@ __device__ __forceinline__ void at_target_unit(const int4 u, rec_t<T> *tile, con
     const double4 tb = tile_box[tile_start[A] + ((u.y - range[A].x) >> 6)];
     const double a2 = alpha * alpha;
     double au = 0.0, av = 0.0;
-    for (int e = u_off[A]; e < u_off[A + 1]; ++e) {
-        const int S = u_idx[e];
-        const int4 cls = cell[S];
-        const int2 r = range[S];
-        if (skip_dense && cls.x == cla.x && r.y >= dense) continue;  // in a mutual item
-        const double2 cs = cell_centre(x0, y0, side, cls);
-        const T tx = ri.x + (T)(alpha * (ca.x - cs.x));
-        const T ty = ri.y + (T)(alpha * (ca.y - cs.y));
-        T fu = 0, fv = 0;
-        int tt = tile_start[S];
-        for (int base = r.x; base < r.x + r.y; base += 64, ++tt) {
-            const int len = min(64, r.x + r.y - base);
-            __syncthreads();
-            if (lane < len) tile[lane] = rec(base + lane);
-            const double4 sb = tile_box[tt];
-            const double gx = fmax(0.0, fmax(sb.x - tb.z, tb.x - sb.z));
-            const double gy = fmax(0.0, fmax(sb.y - tb.w, tb.y - sb.w));
-            const bool far = (gx * gx + gy * gy) * a2 >= cut;
-            __syncthreads();
-            switch (logtp) {
-            case 6: p2p_tile_any<T, 1>(tile, len, k, tx, ty, fu, fv, far); break;
-            case 5: p2p_tile_any<T, 2>(tile, len, k, tx, ty, fu, fv, far); break;
-            case 4: p2p_tile_any<T, 4>(tile, len, k, tx, ty, fu, fv, far); break;
-            case 3: p2p_tile_any<T, 8>(tile, len, k, tx, ty, fu, fv, far); break;
-            case 2: p2p_tile_any<T, 16>(tile, len, k, tx, ty, fu, fv, far); break;
-            case 1: p2p_tile_any<T, 32>(tile, len, k, tx, ty, fu, fv, far); break;
-            default: p2p_tile_any<T, 64>(tile, len, k, tx, ty, fu, fv, far); break;
+    const int eend = u_off[A + 1];
+    for (int e0 = u_off[A]; e0 < eend; e0 += 64) {
+        // lane k: the k-th source leaf of this group of U(A)
+        int s0 = 0, len = 0;
+        bool far = false;
+        T ox = 0, oy = 0;
+        if (e0 + lane < eend) {
+            const int S = u_idx[e0 + lane];
+            const int4 cls = cell[S];
+            const int2 r = range[S];
+            s0 = r.x;
+            len = skip_dense && cls.x == cla.x && r.y >= dense ? 0 : r.y;  // else in a mutual item
+            const double2 cs = cell_centre(x0, y0, side, cls);
+            ox = (T)(alpha * (cs.x - ca.x));  // moved into the frame of A
+            oy = (T)(alpha * (cs.y - ca.y));
+            if (len > 0 && len <= 64) {  // one tile (a larger leaf takes the general form)
+                const double4 sb = tile_box[tile_start[S]];
+                const double gx = fmax(0.0, fmax(sb.x - tb.z, tb.x - sb.z));
+                const double gy = fmax(0.0, fmax(sb.y - tb.w, tb.y - sb.w));
+                far = (gx * gx + gy * gy) * a2 >= cut;
             }
         }
-        au += (double)fu;
-        av += (double)fv;
+        auto stage = [&](int e, int j) {
+            const int from = __shfl(s0, e);
+            const T sx = __shfl(ox, e), sy = __shfl(oy, e);
+            rec_t<T> r;
+            r.x = r.y = r.z = r.w = (T)0;
+            if (j >= 0) {
+                r = rec(from + j);
+                r.x += sx;
+                r.y += sy;
+            }
+            tile[lane] = r;
+            r.z = (T)0;
+            tile[64 + lane] = r;
+        };
+        source_batches<64>(far ? 0 : len, stage, [&](int count) {
+            T fu = 0, fv = 0;
+            p2p_batch<T, false>(tile, count, ul.k, ul.K, ri.x, ri.y, fu, fv);
+            au += (double)fu;
+            av += (double)fv;
+        });
+        if (__any(far))
+            source_batches<64>(far ? len : 0, stage, [&](int count) {
+                T fu = 0, fv = 0;
+                p2p_batch<T, true>(tile, count, ul.k, ul.K, ri.x, ri.y, fu, fv);
+                au += (double)fu;
+                av += (double)fv;
+            });
     }
-    for (int o = tp; o < 64; o <<= 1) {
-        au += __shfl_xor(au, o);
-        av += __shfl_xor(av, o);
-    }
-    if (k == 0 && t < u.z) near[i] = make_double2(-scale * au, scale * av);
+    au = ul.reduce(au);
+    av = ul.reduce(av);
+    if (lane < u.z) near[i] = make_double2(-scale * au, scale * av);
 }
 
 template <typename T>
@@ -379,16 +392,84 @@ __device__ __forceinline__ void at_backward_unit(const int4 u, rec_t<T> *tile, c
     constexpr int NA = SRC ? 9 : 5;
     const int lane = threadIdx.x;
     const int logtp = u.w & 15;
-    const int tp = 1 << logtp;
-    const int t = lane & (tp - 1);
-    const int k = lane >> logtp;
-    const int i = u.y + min(t, u.z - 1);
-    const rec_t<T> ri = rec(i);
     const int A = u.x;
     const int4 cla = cell[A];
     const double2 ca = cell_centre(x0, y0, side, cla);
     const double4 tb = tile_box[tile_start[A] + ((u.y - range[A].x) >> 6)];
     const double a2 = alpha * alpha;
+    const int ebegin = u_off[A], eend = u_off[A + 1];
+    int longest = 0;
+    for (int e = ebegin + lane; e < eend; e += 64) longest = max(longest, range[u_idx[e]].y);
+    if (!__any(longest > 64)) {  // every source leaf is one tile: staged together, in A's frame
+        const UnitLanes ul(lane, u.z, logtp);
+        const int i = u.y + min(ul.t, u.z - 1);
+        const rec_t<T> ri = rec(i);
+        double sum[NA] = {};
+        auto fold = [&](const T(&acc)[NA]) {
+#pragma unroll
+            for (int c = 0; c < NA; ++c) sum[c] += (double)acc[c];
+        };
+        for (int e0 = ebegin; e0 < eend; e0 += 64) {
+            int s0 = 0, len = 0;
+            bool far = false;
+            T ox = 0, oy = 0;
+            if (e0 + lane < eend) {
+                const int S = u_idx[e0 + lane];
+                const int2 r = range[S];
+                s0 = r.x;
+                len = r.y;
+                const double2 cs = cell_centre(x0, y0, side, cell[S]);
+                ox = (T)(alpha * (cs.x - ca.x));
+                oy = (T)(alpha * (cs.y - ca.y));
+                const double4 sb = tile_box[tile_start[S]];
+                const double gx = fmax(0.0, fmax(sb.x - tb.z, tb.x - sb.z));
+                const double gy = fmax(0.0, fmax(sb.y - tb.w, tb.y - sb.w));
+                far = (gx * gx + gy * gy) * a2 >= cut;
+            }
+            auto stage = [&](int e, int j) {
+                const int from = __shfl(s0, e);
+                const T sx = __shfl(ox, e), sy = __shfl(oy, e);
+                rec_t<T> r;
+                r.x = r.y = r.z = r.w = (T)0;
+                c2<T> q = mk<T>(0, 0);
+                if (j >= 0) {
+                    r = rec(from + j);
+                    r.x += sx;
+                    r.y += sy;
+                    q = qt[from + j];
+                }
+                tile[lane] = r;
+                qtile[lane] = q;
+                r.z = (T)0;
+                tile[64 + lane] = r;
+                qtile[64 + lane] = mk<T>(0, 0);
+            };
+            source_batches<64>(far ? 0 : len, stage, [&](int count) {
+                T acc[NA] = {};
+                p2p_bwd_batch<T, false, SRC>(tile, qtile, count, ul.k, ul.K, ri.x, ri.y, lambda, acc);
+                fold(acc);
+            });
+            if (__any(far))
+                source_batches<64>(far ? len : 0, stage, [&](int count) {
+                    T acc[NA] = {};
+                    p2p_bwd_batch<T, true, SRC>(tile, qtile, count, ul.k, ul.K, ri.x, ri.y, lambda, acc);
+                    fold(acc);
+                });
+        }
+#pragma unroll
+        for (int c = 0; c < NA; ++c) sum[c] = ul.reduce(sum[c]);
+        if (lane < u.z) {
+            out_pa[i] = make_double4(sum[0], sum[1], sum[2], sum[3]);
+            out_b[i] = sum[4];
+            if constexpr (SRC) out_src[i] = make_double4(sum[5], sum[6], sum[7], sum[8]);
+        }
+        return;
+    }
+    const int tp = 1 << logtp;
+    const int t = lane & (tp - 1);
+    const int k = lane >> logtp;
+    const int i = u.y + min(t, u.z - 1);
+    const rec_t<T> ri = rec(i);
     double sum[NA] = {};
     for (int e = u_off[A]; e < u_off[A + 1]; ++e) {
         const int S = u_idx[e];
@@ -445,8 +526,8 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void at_bac
     const c2<T> *__restrict__ qt, double x0, double y0, double side, double alpha, double cut, T lambda,
     double4 *__restrict__ out_pa, double *__restrict__ out_b, double4 *__restrict__ out_src)
 {
-    __shared__ rec_t<T> tile[64];
-    __shared__ c2<T> qtile[64];
+    __shared__ rec_t<T> tile[128];
+    __shared__ c2<T> qtile[128];
     const SoaRec<T> rec{pos, gam, (T)alpha};
     at_backward_unit<T, SRC>(units[blockIdx.x], tile, qtile, cell, range, u_off, u_idx, tile_start, tile_box, rec, qt,
                              x0, y0, side, alpha, cut, lambda, out_pa, out_b, out_src);

@@ -196,6 +196,82 @@ __device__ __forceinline__ void p2p_tile_any(const rec_t<T> *tile, int len, int 
     else p2p_tile<T, K, false>(tile, len, k, tx, ty, fu, fv);
 }
 
+// ---------------------------------------------------------------------------------
+// Target-centric units over sparse source leaves.  Taken leaf by leaf, a 3x3 neighbourhood
+// of ~16-particle leaves is nine dependent loads and barriers for nine steps of work each
+// (1024^2 lattice, 16 per leaf, FP64: 0.40 ms; its pairs issue in 0.17 ms).  So the unit's
+// source ranges are concatenated and staged 64 sources at a time, each moved into the
+// frame of the target's leaf on the way into LDS.
+// ---------------------------------------------------------------------------------
+
+// How a unit's 64 lanes share its nt targets: lane = k tp + t takes target t and every K-th
+// source from k on.  From 9 targets on tp = nt, so that no lane is left over but 64 mod nt;
+// below, tp is a power of two, so that the partial sums meet in a butterfly.
+struct UnitLanes {
+    int tp, K, t, k;
+    bool pow2;
+    __device__ __forceinline__ UnitLanes(int lane, int nt, int logtp)
+    {
+        pow2 = nt <= 8 || nt > 32;
+        tp = pow2 ? 1 << logtp : nt;
+        k = pow2 ? lane >> logtp : (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)nt));
+        K = pow2 ? 64 >> logtp : 64 / nt;
+        t = lane - k * tp;
+        if (k >= K) k = 0;  // a lane left over repeats the first share; its sums are not read
+    }
+    // the K partial sums of target t, complete in the lanes k = 0
+    __device__ __forceinline__ double reduce(double v) const
+    {
+        if (pow2) {
+            for (int o = tp; o < 64; o <<= 1) v += __shfl_xor(v, o);
+            return v;
+        }
+        double r = v;
+        for (int j = 1; j < K; ++j) r += __shfl(v, t + j * tp);
+        return r;
+    }
+};
+
+// The concatenation of up to E <= 64 source ranges, lane e < E holding the length of range e
+// (lanes >= E zero), in batches of 64: stage(e, j) with this lane's source, the j-th of
+// range e (j < 0: none), between two barriers, then work(count) over the staged sources.
+template <int E, typename Stage, typename Work>
+__device__ __forceinline__ void source_batches(int len, Stage stage, Work work)
+{
+    const int lane = threadIdx.x;
+    int incl = len;
+#pragma unroll
+    for (int d = 1; d < E; d <<= 1) {
+        const int o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, E - 1);
+    const int excl = incl - len;
+    for (int b = 0; b < total; b += 64) {
+        const int g = b + lane;
+        int e = 0;  // the last range that starts at or before g
+#pragma unroll
+        for (int d = E / 2; d >= 1; d >>= 1)
+            if (__shfl(excl, e + d) <= g) e += d;
+        const int j = g - __shfl(excl, e);
+        __syncthreads();
+        stage(e, g < total ? j : -1);
+        __syncthreads();
+        work(min(64, total - b));
+    }
+}
+
+// Steps of one batch: lane share k of K over `count` staged sources (zero-charge records
+// follow the last one up to 64 + K).
+template <typename T, bool FAR>
+__device__ __forceinline__ void p2p_batch(const rec_t<T> *tile, int count, int k, int K, T tx, T ty, T &fu, T &fv)
+{
+    const int steps = (count + K - 1) / K;
+    const rec_t<T> *src = tile + k;
+#pragma unroll 4
+    for (int it = 0; it < steps; ++it, src += K) p2p_pair<T, FAR>(*src, tx, ty, fu, fv);
+}
+
 // Smallest squared distance between two boxes {xmin, ymin, xmax, ymax}, the first
 // shifted by (ox, oy).
 __device__ __forceinline__ float box_gap2(float4 a, float ox, float oy, float4 b)
@@ -542,6 +618,19 @@ __device__ __forceinline__ void p2p_bwd_tile_any(const rec_t<T> *tile, const c2<
     if (cls == 2) p2p_bwd_tile<T, K, true, SRC>(tile, qtile, len, k, tx, ty, lambda, acc);
     else if (K <= 2 && cls == 1) p2p_bwd_tile<T, K, false, SRC, false>(tile, qtile, len, k, tx, ty, lambda, acc);
     else p2p_bwd_tile<T, K, false, SRC>(tile, qtile, len, k, tx, ty, lambda, acc);
+}
+
+// Steps of one batch of the adjoint, as p2p_batch.
+template <typename T, bool FAR, bool SRC>
+__device__ __forceinline__ void p2p_bwd_batch(const rec_t<T> *tile, const c2<T> *qtile, int count, int k, int K, T tx,
+                                              T ty, T lambda, T (&acc)[SRC ? 9 : 5])
+{
+    const int steps = (count + K - 1) / K;
+    const rec_t<T> *src = tile + k;
+    const c2<T> *qsrc = qtile + k;
+#pragma unroll 2
+    for (int it = 0; it < steps; ++it, src += K, qsrc += K)
+        p2p_bwd_pair<T, FAR, SRC>(*src, *qsrc, tx, ty, lambda, acc);
 }
 
 // ---------------------------------------------------------------------------------

@@ -161,12 +161,69 @@ __device__ __forceinline__ void p2p_forward_unit(const int4 u, rec_t<T> *tile, c
     const int lane = threadIdx.x;
     const int logtp = u.w & 15;
     const bool skip_dense = (u.w >> 4) != 0;  // pairs with dense leaves go to the mutual form
+    const int ix = (int)morton_x((uint32_t)u.x), iy = (int)morton_y((uint32_t)u.x);
+    // lane d < 9: the range of neighbour leaf d
+    int s0 = 0, len = 0, ddx = 0, ddy = 0;
+    uint32_t S = 0;
+    if (lane < 9) {
+        ddx = lane % 3 - 1;
+        ddy = lane / 3 - 1;
+        const int nx = ix + ddx, ny = iy + ddy;
+        if (nx >= 0 && ny >= 0 && nx < nside && ny < nside) {
+            S = morton_encode((uint32_t)nx, (uint32_t)ny);
+            s0 = leaf_start[S];
+            len = leaf_start[S + 1] - s0;
+            if (skip_dense && len >= dense) len = 0;
+        }
+    }
+    if (!__any(len > 64)) {  // every source leaf is one tile
+        const UnitLanes ul(lane, u.z, logtp);
+        const int i = u.y + min(ul.t, u.z - 1);
+        const rec_t<T> ri = rec(i);
+        bool far = false;
+        if (cut_leaf2 < 8.0f && len > 0) {  // (no tile of the neighbourhood is sqrt(8) leaves away)
+            const float4 tbox = tile_box[tile_start[u.x] + ((u.y - leaf_start[u.x]) >> 6)];
+            far = box_gap2(tbox, (float)-ddx, (float)-ddy, tile_box[tile_start[S]]) >= cut_leaf2;
+        }
+        const T ox = (T)ddx * step, oy = (T)ddy * step;
+        double au = 0.0, av = 0.0;
+        auto stage = [&](int e, int j) {
+            const int from = __shfl(s0, e);
+            const T sx = __shfl(ox, e), sy = __shfl(oy, e);
+            rec_t<T> r;
+            r.x = r.y = r.z = r.w = (T)0;
+            if (j >= 0) {
+                r = rec(from + j);
+                r.x += sx;
+                r.y += sy;
+            }
+            tile[lane] = r;
+            r.z = (T)0;
+            tile[64 + lane] = r;
+        };
+        source_batches<16>(far ? 0 : len, stage, [&](int count) {
+            T fu = 0, fv = 0;
+            p2p_batch<T, false>(tile, count, ul.k, ul.K, ri.x, ri.y, fu, fv);
+            au += (double)fu;
+            av += (double)fv;
+        });
+        if (__any(far))
+            source_batches<16>(far ? len : 0, stage, [&](int count) {
+                T fu = 0, fv = 0;
+                p2p_batch<T, true>(tile, count, ul.k, ul.K, ri.x, ri.y, fu, fv);
+                au += (double)fu;
+                av += (double)fv;
+            });
+        au = ul.reduce(au);
+        av = ul.reduce(av);
+        if (lane < u.z) near[i] = make_double2(-scale * au, scale * av);
+        return;
+    }
     const int tp = 1 << logtp;
     const int t = lane & (tp - 1);
     const int k = lane >> logtp;
     const int i = u.y + min(t, u.z - 1);
     const rec_t<T> ri = rec(i);
-    const int ix = (int)morton_x((uint32_t)u.x), iy = (int)morton_y((uint32_t)u.x);
     const float4 tbox = tile_box[tile_start[u.x] + ((u.y - leaf_start[u.x]) >> 6)];
     double au = 0.0, av = 0.0;
     for (int dy = -1; dy <= 1; ++dy) {
@@ -248,11 +305,12 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 8 : 5) void p2p_near_kernel(
                   scale, dense, n, near, slots);
 }
 
-// Sum over the 64 lanes of each of NC values (NC = 32 or 64) by recursive halving: at
-// offset o a lane keeps the half of its values that its lane bit o selects and adds its
-// partner's copy of that half.  Returns the total of value lane >> 1 (NC = 32; lanes 2c
-// and 2c + 1 both hold it) or of value lane (NC = 64).  Shuffles only: no LDS, so the
-// kernel fits beside near-field workgroups that hold the LDS.
+// Sum over the lanes of a group of each of NC values (NC = 32 or 64) by recursive halving:
+// at offset o a lane keeps the half of its values that its lane bit o selects and adds its
+// partner's copy of that half.  Starting from O = G/2, lane g of a group of G ends with the
+// totals of values g NC/G on in v[0 .. NC/G) (G <= NC; with G = 2 NC both lanes of a pair
+// hold value g/2).  Shuffles only: no LDS, so the kernel fits beside near-field workgroups
+// that hold the LDS.
 template <typename TC, int NC, int W, int O>
 __device__ __forceinline__ void lane_halve(TC (&v)[NC], int lane)
 {
@@ -272,15 +330,12 @@ __device__ __forceinline__ void lane_halve(TC (&v)[NC], int lane)
         }
     }
 }
-template <typename TC, int NC>
-__device__ __forceinline__ TC lane_reduce_scatter(TC (&v)[NC], int lane)
-{
-    static_assert(NC == 32 || NC == 64, "32 or 64 values");
-    lane_halve<TC, NC, NC, 32>(v, lane);
-    return v[0];
-}
 
-template <typename TR, typename TC, int PMAX>
+// Stage 4, P2M: a_m / w^m = sum_j c_j xi_j^m, G lanes per leaf (64/G leaves per wavefront),
+// each over every G-th particle.  G follows the mean occupancy (p2m_launch): a wavefront
+// per sparse leaf idles most lanes and pays the whole reduction for a few particles (2^22
+// uniform particles in 2^20 leaves: 577 us).
+template <typename TR, typename TC, int PMAX, int G>
 __global__ __launch_bounds__(64) void p2m_kernel(const int *__restrict__ leaves, int nleaves,
                                                   const int *__restrict__ leaf_start,
                                                   const double2 *__restrict__ xy, const c2<TC> *__restrict__ pos,
@@ -290,18 +345,19 @@ __global__ __launch_bounds__(64) void p2m_kernel(const int *__restrict__ leaves,
                                                   int p, c2<TC> *__restrict__ out, int nxcd)
 {
     constexpr int NC = 2 * PMAX;             // partial sums per lane (re, im interleaved)
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x, g = lane % G;
     // each XCD takes a contiguous run of leaves, so the staging windows its circulation
     // reads fall in stay in its own L2
-    for (int li = xcd_block(nxcd); li < nleaves; li += gridDim.x) {
-    const uint32_t leaf = (uint32_t)leaves[li];
-    const int s0 = leaf_start[leaf], s1 = leaf_start[leaf + 1];
+    const int li = xcd_block(nxcd) * (64 / G) + lane / G;
+    const bool valid = li < nleaves;  // a group past the end idles (its shuffles stay inside it)
+    const uint32_t leaf = valid ? (uint32_t)leaves[li] : 0;
+    const int s0 = valid ? leaf_start[leaf] : 0, s1 = valid ? leaf_start[leaf + 1] : 0;
     const double cx = x0 + (morton_x(leaf) + 0.5) * w;
     const double cy = y0 + (morton_y(leaf) + 0.5) * w;
-    c2<TC> acc[PMAX];
+    TC v[NC];
 #pragma unroll
-    for (int m = 0; m < PMAX; ++m) acc[m] = mk<TC>(0, 0);
-    for (int j = s0 + lane; j < s1; j += 64) {
+    for (int m = 0; m < NC; ++m) v[m] = (TC)0;
+    for (int j = s0 + g; j < s1; j += G) {
         c2<TC> xi;
         if (pos) {
             xi = pos[j];  // the tree's leaf-unit coordinates, made by the same formula
@@ -322,21 +378,20 @@ __global__ __launch_bounds__(64) void p2m_kernel(const int *__restrict__ leaves,
 #pragma unroll
         for (int m = 0; m < PMAX; ++m) {
             if (m < p) {
-                acc[m].x += pw.x;
-                acc[m].y += pw.y;
+                v[2 * m] += pw.x;
+                v[2 * m + 1] += pw.y;
                 pw = cmul<TC>(pw, xi);
             }
         }
     }
-    TC v[NC];
+    lane_halve<TC, NC, NC, G / 2>(v, lane);
+    TC *o = (TC *)out + (int64_t)leaf * 2 * p;
+    if constexpr (G > NC) {
+        if (valid && (g & 1) == 0 && g / 2 < 2 * p) o[g / 2] = v[0];
+    } else {
 #pragma unroll
-    for (int m = 0; m < PMAX; ++m) {
-        v[2 * m] = acc[m].x;
-        v[2 * m + 1] = acc[m].y;
-    }
-    const TC sum = lane_reduce_scatter<TC, NC>(v, lane);
-    const int c = NC == 64 ? lane : lane >> 1;  // the value this lane holds
-    if ((NC == 64 || (lane & 1) == 0) && c < 2 * p) ((TC *)out)[(int64_t)leaf * 2 * p + c] = sum;
+        for (int k = 0; k < NC / G; ++k)
+            if (valid && g * (NC / G) + k < 2 * p) o[g * (NC / G) + k] = v[k];
     }
 }
 
@@ -447,19 +502,24 @@ void p2m_launch(const FarArgs &a, hipStream_t s)
     if (nl == 0) return;
     const double w = t->side / (double)(1 << L);
     c2<TC> *out = level_ptr<TC>(a, L, false);
-    // one leaf per workgroup, contiguous per XCD
-    const unsigned g = xcd_grid(nl, 1);
-    const int nxcd = kXcds;
     // the leaf-unit coordinates when they are in the precision of the expansions
     using TRs = typename RecScalar<TR>::type;
     const c2<TC> *pos = std::is_same<TRs, TC>::value ? (const c2<TC> *)a.pos : nullptr;
     const TRs *gam = (const TRs *)a.gam;
-    if (a.p <= 16)
-        p2m_kernel<TR, TC, 16><<<g, 64, 0, s>>>(level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos,
-                                                t->d_gpos2, t->d_st1, gam, a.adj, t->x0, t->y0, w, a.p, out, nxcd);
-    else
-        p2m_kernel<TR, TC, 32><<<g, 64, 0, s>>>(level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos,
-                                                t->d_gpos2, t->d_st1, gam, a.adj, t->x0, t->y0, w, a.p, out, nxcd);
+    auto go = [&](auto kernel, int per) {
+        kernel<<<xcd_grid(nl, per), 64, 0, s>>>(level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos, t->d_gpos2,
+                                                t->d_st1, gam, a.adj, t->x0, t->y0, w, a.p, out, kXcds);
+    };
+    // lanes per leaf by the mean occupancy
+    const double mean = (double)t->n / (double)nl;
+    if (a.p <= 16) {
+        if (mean <= 6) go(p2m_kernel<TR, TC, 16, 8>, 8);
+        else if (mean <= 32) go(p2m_kernel<TR, TC, 16, 16>, 4);
+        else go(p2m_kernel<TR, TC, 16, 64>, 1);
+    } else {
+        if (mean <= 32) go(p2m_kernel<TR, TC, 32, 16>, 4);
+        else go(p2m_kernel<TR, TC, 32, 64>, 1);
+    }
 }
 
 // ---------------------------------------------------------------------------------
@@ -507,12 +567,78 @@ __device__ __forceinline__ void p2p_backward_unit(const int4 u, rec_t<T> *tile, 
     constexpr int NA = SRC ? 9 : 5;
     const int lane = threadIdx.x;
     const int logtp = u.w;
+    const int ix = (int)morton_x((uint32_t)u.x), iy = (int)morton_y((uint32_t)u.x);
+    // lane d < 9: the range of neighbour leaf d
+    int s0 = 0, slen = 0, ddx = 0, ddy = 0;
+    uint32_t SL = 0;
+    if (lane < 9) {
+        ddx = lane % 3 - 1;
+        ddy = lane / 3 - 1;
+        const int nx = ix + ddx, ny = iy + ddy;
+        if (nx >= 0 && ny >= 0 && nx < nside && ny < nside) {
+            SL = morton_encode((uint32_t)nx, (uint32_t)ny);
+            s0 = leaf_start[SL];
+            slen = leaf_start[SL + 1] - s0;
+        }
+    }
+    if (!__any(slen > 64)) {  // every source leaf is one tile: staged together
+        const UnitLanes ul(lane, u.z, logtp);
+        const int i = u.y + min(ul.t, u.z - 1);
+        const rec_t<T> ri = rec(i);
+        bool far = false;
+        if (cut_leaf2 < 8.0f && slen > 0) {
+            const float4 tbox = tile_box[tile_start[u.x] + ((u.y - leaf_start[u.x]) >> 6)];
+            far = box_gap2(tbox, (float)-ddx, (float)-ddy, tile_box[tile_start[SL]]) >= cut_leaf2;
+        }
+        const T ox = (T)ddx * step, oy = (T)ddy * step;
+        double sum[NA] = {};
+        auto stage = [&](int e, int j) {
+            const int from = __shfl(s0, e);
+            const T sx = __shfl(ox, e), sy = __shfl(oy, e);
+            rec_t<T> r;
+            r.x = r.y = r.z = r.w = (T)0;
+            c2<T> q = mk<T>(0, 0);
+            if (j >= 0) {
+                r = rec(from + j);
+                r.x += sx;
+                r.y += sy;
+                q = qv[from + j];
+            }
+            tile[lane] = r;
+            qtile[lane] = q;
+            r.z = (T)0;
+            tile[64 + lane] = r;
+            qtile[64 + lane] = mk<T>(0, 0);
+        };
+        auto fold = [&](const T(&acc)[NA]) {
+#pragma unroll
+            for (int c = 0; c < NA; ++c) sum[c] += (double)acc[c];
+        };
+        source_batches<16>(far ? 0 : slen, stage, [&](int count) {
+            T acc[NA] = {};
+            p2p_bwd_batch<T, false, SRC>(tile, qtile, count, ul.k, ul.K, ri.x, ri.y, lambda, acc);
+            fold(acc);
+        });
+        if (__any(far))
+            source_batches<16>(far ? slen : 0, stage, [&](int count) {
+                T acc[NA] = {};
+                p2p_bwd_batch<T, true, SRC>(tile, qtile, count, ul.k, ul.K, ri.x, ri.y, lambda, acc);
+                fold(acc);
+            });
+#pragma unroll
+        for (int c = 0; c < NA; ++c) sum[c] = ul.reduce(sum[c]);
+        if (lane < u.z) {
+            out_pa[i] = make_double4(sum[0], sum[1], sum[2], sum[3]);
+            out_b[i] = sum[4];
+            if constexpr (SRC) out_src[i] = make_double4(sum[5], sum[6], sum[7], sum[8]);
+        }
+        return;
+    }
     const int tp = 1 << logtp;
     const int t = lane & (tp - 1);
     const int k = lane >> logtp;
     const int i = u.y + min(t, u.z - 1);
     const rec_t<T> ri = rec(i);
-    const int ix = (int)morton_x((uint32_t)u.x), iy = (int)morton_y((uint32_t)u.x);
     const float4 tbox = tile_box[tile_start[u.x] + ((u.y - leaf_start[u.x]) >> 6)];
     double sum[NA] = {};
     for (int dy = -1; dy <= 1; ++dy) {
@@ -569,8 +695,8 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void p2p_ba
     const float4 *__restrict__ tile_box, int nside, T step, float cut_leaf2, float series_leaf2, T lambda,
     double4 *__restrict__ out_pa, double *__restrict__ out_b, double4 *__restrict__ out_src)
 {
-    __shared__ rec_t<T> tile[64];
-    __shared__ c2<T> qtile[64];
+    __shared__ rec_t<T> tile[128];
+    __shared__ c2<T> qtile[128];
     const SoaRec<T> rec{pos, gam, step};
     p2p_backward_unit<T, SRC>(units[blockIdx.x], tile, qtile, rec, qv, leaf_start, tile_start, tile_box, nside, step,
                               cut_leaf2, series_leaf2, lambda, out_pa, out_b, out_src);
