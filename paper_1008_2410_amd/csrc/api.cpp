@@ -248,14 +248,14 @@ FarArgs far_args(const fmm_tree *t, const Workspace &ws, int p, int precision, b
     return a;
 }
 
-// Stage costs of the mixed form (p = 16) on one MI355X, in ms: the near field's constants
-// fitted by the cost-model sweep of uniform particles (the complexity terms of section
-// "Complexity Estimates" with the counts a launch pays for), the far chain's set to its
-// launches (one per fine level each way, P2M, the coarse passes) and its time per cell:
+// Stage costs of the mixed form (p = 12..16) on one MI355X, in ms, set to the stages of
+// serialised calls on uniform (2^18 to 2^22 particles, 4 and 16 per leaf) and patch trees
+// (10^6 to 2^24), within 25% of each (the complexity terms of section "Complexity Estimates"
+// with the counts a launch pays for):
 //   T_near = kNear0 + kNearPair pairs + kNearVisit 9 N_leaves,
-//   T_far  = kFar0 + kFarCell C_fine + kFarCoarse C_coarse + kFarLevel (L - L_c).
-constexpr double kNear0 = 0.070, kNearPair = 1.95e-10, kNearVisit = 1.74e-7;
-constexpr double kFar0 = 0.060, kFarCell = 0.9e-6, kFarCoarse = 1.9e-6, kFarLevel = 0.012;
+//   T_far  = kFar0 + kFarParticle n + kFarCell cells + kFarLevel L.
+constexpr double kNear0 = 0.020, kNearPair = 2.3e-10, kNearVisit = 4.5e-8;
+constexpr double kFar0 = 0.030, kFarParticle = 1.6e-8, kFarCell = 0.7e-6, kFarLevel = 0.006;
 
 // The part of T_near that grows with the tree.
 double near_work_ms(const fmm_tree *t)
@@ -266,24 +266,24 @@ double near_work_ms(const fmm_tree *t)
 // Predicted far-field / near-field time of the tree (the model above).
 double far_near_ratio(const fmm_tree *t)
 {
-    const int lc = std::min(t->lc, t->depth);
-    double fine = 0, coarse = 0;
-    for (int l = 2; l <= t->depth; ++l) (l <= lc ? coarse : fine) += (double)t->list_len[l];
+    double cells = 0;
+    for (int l = 2; l <= t->depth; ++l) cells += (double)t->list_len[l];
     const double near = kNear0 + near_work_ms(t);
-    const double far = kFar0 + kFarCell * fine + kFarCoarse * coarse + kFarLevel * (t->depth - lc);
+    const double far = kFar0 + kFarParticle * (double)t->n + kFarCell * cells + kFarLevel * t->depth;
     return far / near;
 }
 
 // Whether a call runs the far chain beside the near field (FMM_OPT_SCHEDULE 0), after it
 // (1), or by the model (2, the default): both are throughput work on the same CUs.
 //  - A near field of less than kSerialNear ms of work is not worth the second stream: the
-//    events between the streams cost about 25 us (uniform 4096 particles, depth 4: 53 us
-//    serialised against 75-86 overlapped; 50021, depth 6: 81 against 91-95).
-//  - In the mixed form calls beyond a far/near ratio of kSerialRatio are serialised; below
-//    it overlapping measured no slower (uniform 2^22 particles at depth 10, r = 0.8: 3.5
-//    against 3.9 ms; patches 10^6 at depth 8, r = 0.36: 0.41 against 0.47 ms).
-//  - FP64 calls overlap (the FP64 near field leaves issue slots that the far chain uses).
-constexpr double kSerialRatio = 2.5, kSerialNear = 0.012;
+//    events between the streams cost about 25 us (uniform 4096 particles, depth 4, FP64: 53 us
+//    serialised against 85-94 overlapped; 50021, depth 6: 77 against 94-100; 2^18, depth 7,
+//    mixed: 139 against 152-166).
+//  - In the mixed form calls beyond a far/near ratio of kSerialRatio are serialised: there is
+//    too little near field to run beside.  Up to 2.4 the best cap still gained (uniform 2^22,
+//    depth 10: 2.44 against 2.56 ms).
+//  - FP64 calls overlap (1024^2 lattice: 0.416 against 0.454 ms).
+constexpr double kSerialRatio = 4.0, kSerialNear = 0.020;
 bool call_overlaps(const fmm_tree *t, int precision)
 {
     if (t->schedule != 2) return t->schedule == 0;
@@ -299,12 +299,14 @@ bool call_overlaps(const fmm_tree *t, int precision)
 //    uncapped; 2^23: 8.1 against 9.1).  With fewer entries the cap idles the chip (uniform
 //    2^22 particles at depth 6, 20K entries: 9.5 ms at cap 3 against 7.6 uncapped);
 //  - mixed, by the predicted far/near ratio r (the far chain takes the slots the cap
-//    leaves): r < 0.07 none, r < 0.3 six (2^24 patches at depth 10: 6.9 ms against 7.2 at
-//    five and 7.1 uncapped; 2^22 at depth 9: 1.58 against 1.64 and 1.72), r < 0.85 five
-//    (uniform 2^22 at depth 10: 3.50 against 3.53 at four and 3.72 at six), above four;
-//  - FP64 (at most 5 wavefronts per SIMD): four, or three from r = 0.3 on (1024^2 lattice,
-//    depth 8, p = 12: 0.468 ms against 0.500 at four and 0.499 uncapped; 7 10^5 patch
-//    particles at depth 8: 0.59 against 0.64 and 0.66);
+//    leaves): r < 0.05 none, r < 0.3 six (2^24 patches at depth 10: 6.65 ms against 6.84 at
+//    five and 7.00 uncapped; 2^22 at depth 9: 1.50 against 1.56 and 1.70), r < 1 five (10^6
+//    patch particles at depth 8: four to six within 0.004 of 0.42 ms, 0.454 uncapped), above
+//    three (uniform 2^20 at depth 8: 0.274 ms against 0.294 at four and 0.308 uncapped; 2^22
+//    at depth 10: 2.44 against 2.55 and 2.53);
+//  - FP64 (at most 5 wavefronts per SIMD): r < 0.05 none, r < 0.3 four, r < 1 three (7 10^5
+//    patch particles at depth 8: 0.561 ms against 0.620 at four and 0.632 uncapped), above two
+//    (1024^2 lattice, depth 8, p = 12: 0.416 against 0.435 at three and 0.457 uncapped);
 //  - a work list of less than 4096 entries leaves slots free by itself: no cap.
 int choose_occupancy(const fmm_tree *t, int precision, bool overlap)
 {
@@ -313,12 +315,11 @@ int choose_occupancy(const fmm_tree *t, int precision, bool overlap)
     const int64_t entries = use_mutual(t) ? t->nnear_work : t->nunits;
     if (entries < 4096) return 0;
     const double r = far_near_ratio(t);
-    if (precision == FMM_FP64) return r < 0.07 ? 0 : r < 0.3 ? 4 : 3;
+    if (precision == FMM_FP64) return r < 0.05 ? 0 : r < 0.3 ? 4 : r < 1.0 ? 3 : 2;
     if ((double)t->p2p_pairs >= 2500.0 * (double)t->n && entries >= 65536) return 3;
-    if (r < 0.07) return 0;
+    if (r < 0.05) return 0;
     if (r < 0.3) return 6;
-    if (r < 0.85) return 5;
-    return 4;
+    return r < 1.0 ? 5 : 3;
 }
 
 struct Timing {

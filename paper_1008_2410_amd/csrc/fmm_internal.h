@@ -30,9 +30,8 @@ constexpr int kNumEvents = 8;
 //   M2L: b_l = sum_m (-1)^l C(l+m,m) delta^-(l+m+1) a_m,  delta = (dx, dy)
 // with d_q = (c_child - c_parent)/w_parent = ((q&1) - 1/2)/2 + i((q>>1) - 1/2)/2, as
 // 2p x 2p real matrices (complex entries embedded with interleaved (re, im) rows and
-// columns, zero-padded) in the operand order of the matrix instructions,
-// [slot][k / steps][column][k % steps] (translate.h gives the steps and columns of p):
-// slots 0..48 the M2L offsets (index (dx+3)*7 + (dy+3)), 49..52 the L2L parities, 53..56
+// columns, zero-padded) in the operand order of the matrix instructions
+// (translate.hip), slots 0..48 the M2L offsets (index (dx+3)*7 + (dy+3)), 49..52 the L2L parities, 53..56
 // the M2M children.
 // ---------------------------------------------------------------------------------
 struct Tables {

@@ -1072,7 +1072,8 @@ void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
 
     // levels from wide on (the finest, where the tree has cells enough) take M2L and L2L together
     int wide = L + 1;
-    while (wide > 3 && (wide - 1 > S ? wide_level32(t->list_len[wide - 1], a.p) : wide_level64(t->list_len[wide - 1], a.p)))
+    while (wide > 3 && wide - 1 != S + 1 &&  // (the parents in the level's own precision)
+           (wide - 1 > S ? wide_level32(t->list_len[wide - 1], a.p) : wide_level64(t->list_len[wide - 1], a.p)))
         --wide;
     class_segs(g, t, 2, std::min(S, wide - 1));
     g.tab = tb.mfma_d;
@@ -1092,14 +1093,15 @@ void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
     for (int l = 3; l <= L;) {
         if (l >= wide) {
             class_segs(g, t, l, l);
-            g.par = l - 1 <= S ? (const void *)a.lo_d : (const void *)a.lo_f;
-            g.par_off = l - 1 <= S ? 0 : fbase;
+            g.par = l <= S ? (const void *)a.lo_d : (const void *)a.lo_f;
+            g.par_off = l <= S ? 0 : fbase;
             g.tab = l <= S ? (const void *)tb.mfma_d : (const void *)tb.mfma_f;
             g.src = l <= S ? (const void *)a.mp_d : (const void *)a.mp_f;
             g.out = l <= S ? (void *)a.lo_d : (void *)a.lo_f;
             g.src_off = g.out_off = l <= S ? 0 : fbase;
             if (l <= S) launch_trans64(g, Trans::M2L, false, s);
-            else launch_trans32(g, Trans::M2L, l - 1 <= S, false, s);
+            else launch_trans32(g, Trans::M2L, false, false, s);
+            g.par = nullptr;
             ++l;
             continue;
         }

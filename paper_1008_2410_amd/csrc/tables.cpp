@@ -64,8 +64,12 @@ int upload_tables(Tables &tb, int p, std::string &err)
         const double r[2][2] = {{v.real(), v.imag()}, {-v.imag(), v.real()}};
         for (int i = 0; i < 2; ++i)
             for (int j = 0; j < 2; ++j) {
-                md[(((size_t)slot * 4 + k[i] / ks) * nc + c[j]) * ks + k[i] % ks] = r[i][j];
-                mf[(((size_t)slot * 2 + k[i] / kf) * nf + c[j]) * kf + k[i] % kf] = (float)r[i][j];
+                // lane and step of the element, and its place among the lane's vector loads
+                const size_t ld = k[i] / ks * 16 + c[j] % 16, sd = k[i] % ks;
+                const size_t lf = k[i] / kf * 32 + c[j] % 32, sf = k[i] % kf;
+                md[((((size_t)slot * (nc / 16) + c[j] / 16) * (ks / 2) + sd / 2) * 64 + ld) * 2 + sd % 2] = r[i][j];
+                mf[((((size_t)slot * (nf / 32) + c[j] / 32) * (kf / 4) + sf / 4) * 64 + lf) * 4 + sf % 4] =
+                    (float)r[i][j];
             }
     };
     for (int q = 0; q < 4; ++q) {

@@ -69,7 +69,7 @@ inline bool wide_level32(int64_t cells, int p) { return cells / 32 * (trans_cols
 void launch_trans64(TransArgs a, Trans mode, bool adaptive, hipStream_t s);
 // FP32 products (tiles of 32 targets) of the uniform tree: M2L on FP32 rows; M2M from FP32
 // children into FP32 or FP64 parents (out_double); L2L from FP32 or FP64 parents
-// (src_double) into FP32 children.  An M2L with `par` (FP64 rows when src_double) takes the
+// (src_double) into FP32 children.  An M2L with `par` (rows of its own precision) takes the
 // L2L along.
 void launch_trans32(TransArgs a, Trans mode, bool src_double, bool out_double, hipStream_t s);
 // Levels base + 2 .. base of the upward pass, or base + 1 .. base + 3 of the downward pass

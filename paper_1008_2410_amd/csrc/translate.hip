@@ -19,8 +19,10 @@
 //   FP32 32x32x2: A[row l%32][k l/32], B[k l/32][col l%32], D register r:
 //                 [8(r/4) + 4(l/32) + r%4][l%32]
 // K is permuted so that a lane's steps are consecutive: step s of group g = l/16 (l/32) is
-// k = KS g + s, so a lane reads KS contiguous values of its row; the tables hold B as
-// [slot][g][col][s].
+// k = KS g + s, so a lane reads KS contiguous values of its row.  The tables hold B as
+// [slot][column block][16-byte vector of the lane's steps][lane], so that a wavefront reads
+// an operator in whole cache lines (a lane's own steps in a row made each load touch four
+// times the lines: 1024^2 lattice FP64, M2L of the finest level 96 us).
 #include "translate.h"
 
 #include <algorithm>
@@ -41,10 +43,11 @@ __device__ __forceinline__ int find_seg(const TransArgs &a, int tile)
     return sg;
 }
 
-// KS values of a row from k0 on, zero from two_p on (the reads past a row's end stay inside
-// the array's tail pad or the zero row).
+// KS values of a row from k0 on; those from two_p on are not the row's (the reads stay inside
+// the array's tail pad or the zero row) and enter the products as zero (in_row).  The
+// selection waits until the value is used: at the load it would wait for memory there.
 template <int KS>
-__device__ __forceinline__ void load_row(double (&a)[KS], const double *row, int k0, int two_p)
+__device__ __forceinline__ void load_row(double (&a)[KS], const double *row, int k0)
 {
     const double2 *r = (const double2 *)(row + k0);
 #pragma unroll
@@ -53,18 +56,17 @@ __device__ __forceinline__ void load_row(double (&a)[KS], const double *row, int
         a[2 * v] = t.x;
         a[2 * v + 1] = t.y;
     }
-    if (4 * KS != two_p) {
-#pragma unroll
-        for (int s = 0; s < KS; ++s) a[s] = k0 + s < two_p ? a[s] : 0.0;
-    }
 }
+template <typename T> __device__ __forceinline__ T in_row(T v, int k, int two_p) { return k < two_p ? v : (T)0; }
 
-template <int KS> __device__ __forceinline__ void load_op(double (&b)[KS], const double *tab)
+// This lane's steps of column block cb of an operator.
+template <int KS, int NB>
+__device__ __forceinline__ void load_op(double (&b)[KS], const double *tab, int slot, int cb, int lane)
 {
-    const double2 *t = (const double2 *)tab;
+    const double2 *t = (const double2 *)tab + ((size_t)slot * NB + cb) * (KS / 2) * 64 + lane;
 #pragma unroll
     for (int v = 0; v < KS / 2; ++v) {
-        const double2 u = t[v];
+        const double2 u = t[v * 64];
         b[2 * v] = u.x;
         b[2 * v + 1] = u.y;
     }
@@ -86,11 +88,11 @@ template <int KS> constexpr int col_blocks() { return (4 * KS + 15) / 16; }
 template <int KS, int RB, int KG, bool SEQ, Trans MODE, bool ADAPT>
 __global__ __launch_bounds__(64 * col_blocks<KS>() * (SEQ ? 1 : KG)) void trans64_kernel(TransArgs a)
 {
-    constexpr int NB = col_blocks<KS>(), NC = 16 * NB;
+    constexpr int NB = col_blocks<KS>();
     constexpr int NE = MODE == Trans::M2L ? 27 : MODE == Trans::M2M ? 4 : 1;
     const int tile = xcd_block(kXcds);
     if (tile >= a.ntiles) return;  // the whole workgroup
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cb = wave % NB, kg = wave / NB;
     const int row = lane & 15, kq = lane >> 4;
     const int two_p = 2 * a.p, k0 = KS * kq;
@@ -116,31 +118,36 @@ __global__ __launch_bounds__(64 * col_blocks<KS>() * (SEQ ? 1 : KG)) void trans6
     const double *src = (const double *)a.src;
     double *out = (double *)a.out;
 
-    // the source row of target block b for operator e, or the zero row
+    // the source row of target block b for operator e, or the zero row: selected, not
+    // branched over, so that the loads of the next operator stay in flight
     auto source = [&](int b, int e, int4 en) -> const double * {
-        int64_t S = -1;
+        const int64_t c = max(tcell[b], 0);
+        bool ok = tcell[b] >= 0 && e >= 0;
+        e = max(e, 0);
+        int64_t S;
+        const double *rows = src;
         if constexpr (MODE == Trans::M2L && !ADAPT) {
-            if (e == 27)  // L2L (with par)
-                return tcell[b] >= 0 ? (const double *)a.par + (level_base(seg.level - 1) - a.par_off + (tcell[b] >> 2)) * two_p
-                                     : a.zero;
-            const int sx = tx[b] + en.x, sy = ty[b] + en.y, nside = 1 << seg.level;
-            if (tcell[b] >= 0 && sx >= 0 && sy >= 0 && sx < nside && sy < nside)
-                S = from + morton_encode((uint32_t)sx, (uint32_t)sy);
+            const uint32_t nside = 1u << seg.level;
+            const uint32_t sx = (uint32_t)(tx[b] + en.x), sy = (uint32_t)(ty[b] + en.y);
+            const bool l2l = e == 27;  // wavefront-uniform
+            ok = ok && (l2l || (sx < nside && sy < nside));
+            S = l2l ? level_base(seg.level - 1) - a.par_off + (c >> 2) : from + morton_encode(sx, sy);
+            rows = l2l ? (const double *)a.par : src;
         } else if constexpr (MODE == Trans::M2M && !ADAPT) {
-            if (tcell[b] >= 0) S = from + 4 * (int64_t)tcell[b] + e;
+            S = from + 4 * c + e;
         } else if constexpr (MODE == Trans::L2L && !ADAPT) {
-            if (tcell[b] >= 0) S = from + (tcell[b] >> 2);
+            S = from + (c >> 2);
         } else if constexpr (MODE == Trans::M2L) {
-            if (tcell[b] >= 0) S = a.vslot[(int64_t)(tcell[b] - a.first) * 27 + e];
+            S = a.vslot[(ok ? c - a.first : 0) * 27 + e];
+            ok = ok && S >= 0;
         } else if constexpr (MODE == Trans::M2M) {
-            if (tcell[b] >= 0) {
-                const int4 ch = a.child[tcell[b]];
-                S = e == 0 ? ch.x : e == 1 ? ch.y : e == 2 ? ch.z : ch.w;
-            }
+            S = ((const int *)(a.child + c))[e];
+            ok = ok && S >= 0;
         } else {
-            if (tcell[b] >= 0) S = a.parent[tcell[b]];
+            S = a.parent[c];
+            ok = ok && S >= 0;
         }
-        return S >= 0 ? src + S * two_p : a.zero;
+        return ok ? rows + S * two_p : a.zero;
     };
     const int e0 = MODE == Trans::M2L ? 28 * q : MODE == Trans::M2M ? 112 : 28 * q + 27;
 
@@ -192,30 +199,44 @@ __global__ __launch_bounds__(64 * col_blocks<KS>() * (SEQ ? 1 : KG)) void trans6
 
     const double *tab = (const double *)a.tab;
     double av[2][RB][KS], bv[2][KS];
-    auto fetch = [&](int slot, uint32_t m) {
-        const int e = __builtin_ctz(m);
-        const int4 en = a.entries[e0 + e];
-        load_op<KS>(bv[slot], tab + (((size_t)en.z * 4 + kq) * NC + col) * KS);
+    auto fetch = [&](int slot, int e) {  // e < 0: none (zero rows)
+        const int4 en = a.entries[e0 + max(e, 0)];
+        load_op<KS, NB>(bv[slot], tab, en.z, cb, lane);
 #pragma unroll
-        for (int b = 0; b < RB; ++b) load_row<KS>(av[slot][b], source(b, e, en), k0, two_p);
+        for (int b = 0; b < RB; ++b) load_row<KS>(av[slot][b], source(b, e, en), k0);
+        __builtin_amdgcn_sched_barrier(0);  // the loads go out before the products that follow
     };
     auto products = [&](int slot) {
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
             for (int b = 0; b < RB; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[slot][b][s], bv[slot][s], acc[b], 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row(av[slot][b][s], k0 + s, two_p), bv[slot][s], acc[b],
+                                                              0, 0, 0);
     };
-    auto apply = [&](uint32_t m) {  // m wavefront-uniform
-        if (m) fetch(0, m);
-        while (m) {
+    // the operators of m (wavefront-uniform) in order, the next one's operands loaded ahead of
+    // the products of the current one, without a branch between them (a load whose use is
+    // behind a branch moves down to it)
+    auto apply = [&](uint32_t m) {
+        auto next = [&m]() {
+            const int e = m ? __builtin_ctz(m) : -1;
             m &= m - 1;
-            if (m) fetch(1, m);
+            return e;
+        };
+        if constexpr (NE == 1) {
+            fetch(0, 0);
             products(0);
-            if (!m) break;
-            m &= m - 1;
-            if (m) fetch(0, m);
-            products(1);
+        } else {
+            int e = next();
+            if (e < 0) return;
+            fetch(0, e);
+            do {
+                fetch(1, next());
+                products(0);
+                e = next();
+                fetch(0, e);
+                products(1);
+            } while (e >= 0);
         }
     };
     if constexpr (KG == 1) {
@@ -273,7 +294,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>() * (SEQ ? 1 : KG)) void trans6
 template <int KS>
 __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(SubtreeArgs a)
 {
-    constexpr int NB = col_blocks<KS>(), NC = 16 * NB;
+    constexpr int NB = col_blocks<KS>();
     const int cell0 = blockIdx.x;
     if (a.counts[level_base(a.base) + cell0] == 0) return;
     const int lane = threadIdx.x & 63, cb = threadIdx.x >> 6;
@@ -285,15 +306,15 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(Subtr
         double av[4][KS], bv[4][KS];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            load_row<KS>(av[e], child + e * two_p, k0, two_p);
-            load_op<KS>(bv[e], a.tab + (((size_t)(53 + e) * 4 + kq) * NC + col) * KS);
+            load_row<KS>(av[e], child + e * two_p, k0);
+            load_op<KS, NB>(bv[e], a.tab, 53 + e, cb, lane);
         }
         doublex4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int s = 0; s < KS; ++s)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[e][s], bv[e][s], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row(av[e][s], k0 + s, two_p), bv[e][s], acc, 0, 0, 0);
         double *out = a.rows + (level_base(l) + (int64_t)cell0 * n) * two_p;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -304,7 +325,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(Subtr
 
 template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(SubtreeArgs a)
 {
-    constexpr int NB = col_blocks<KS>(), NC = 16 * NB;
+    constexpr int NB = col_blocks<KS>();
     const int cell0 = blockIdx.x;
     if (a.counts[level_base(a.base) + cell0] == 0) return;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;  // wavefront: parity class of the targets
@@ -313,13 +334,13 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(Sub
     double bv[NB][KS];  // the class's operator, the same at every level
 #pragma unroll
     for (int c = 0; c < NB; ++c)
-        load_op<KS>(bv[c], a.tab + (((size_t)(49 + q) * 4 + kq) * NC + 16 * c + row) * KS);
+        load_op<KS, NB>(bv[c], a.tab, 49 + q, c, lane);
     for (int l = a.base + 1; l <= min(a.deepest, a.base + 3); ++l) {
         const int n = 1 << (2 * (l - a.base - 1));  // parents in the subtree, one target each per class
         const double *par = a.rows + (level_base(l - 1) + (int64_t)cell0 * n) * two_p;
         double *out = a.rows + (level_base(l) + 4 * (int64_t)cell0 * n + q) * two_p;  // target of parent k: row 4 k
         double av[KS];
-        load_row<KS>(av, par + (int64_t)min(row, n - 1) * two_p, k0, two_p);
+        load_row<KS>(av, par + (int64_t)min(row, n - 1) * two_p, k0);
         doublex4 acc[NB];
 #pragma unroll
         for (int c = 0; c < NB; ++c)
@@ -332,7 +353,7 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(Sub
         for (int s = 0; s < KS; ++s)
 #pragma unroll
             for (int c = 0; c < NB; ++c)
-                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s], bv[c][s], acc[c], 0, 0, 0);
+                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row(av[s], k0 + s, two_p), bv[c][s], acc[c], 0, 0, 0);
 #pragma unroll
         for (int c = 0; c < NB; ++c)
 #pragma unroll
@@ -348,26 +369,29 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(Sub
 // FP32 (the fine levels of the mixed form): one wavefront per tile of 32 targets and block
 // of 32 columns, the next operator's operands loaded ahead of the current one's products.
 // ---------------------------------------------------------------------------------
-template <int KF, typename T>
-__device__ __forceinline__ void load_row32(float (&a)[KF], const T *row, int k0, int two_p)
+template <int KF>
+__device__ __forceinline__ void load_row32(float (&a)[KF], const float *row)
 {
-    const T *r = row + k0;
 #pragma unroll
-    for (int s = 0; s < KF; ++s) {
-        const T v = r[s];
-        a[s] = k0 + s < two_p ? (float)v : 0.0f;
-    }
+    for (int s = 0; s < KF; ++s) a[s] = row[s];
+}
+template <int KF>
+__device__ __forceinline__ void load_row32(float (&a)[KF], const double *row)
+{
+#pragma unroll
+    for (int s = 0; s < KF; ++s) a[s] = (float)row[s];
 }
 
 template <int KF> constexpr int col_blocks32() { return KF <= 16 ? 1 : 2; }
 
-template <int KF, Trans MODE, typename TSrc, typename TOut, typename TPar = float>
+template <int KF, Trans MODE, typename TSrc, typename TOut>
 __global__ __launch_bounds__(256, KF <= 16 ? 4 : 2) void trans32_kernel(TransArgs a)
 {
-    constexpr int NB = col_blocks32<KF>(), NC = 32 * NB;
-    const int NE = MODE == Trans::M2L ? (a.par ? 28 : 27) : MODE == Trans::M2M ? 4 : 1;
+    constexpr int NB = col_blocks32<KF>();
+    // M2L: the 28th is the L2L (with par), else nothing (zero rows)
+    constexpr int NE = MODE == Trans::M2L ? 28 : MODE == Trans::M2M ? 4 : 1;
     const int lane = threadIdx.x & 63;
-    const int id = xcd_block(kXcds) * 4 + (threadIdx.x >> 6);
+    const int id = xcd_block(kXcds) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = id / NB, cb = id % NB;
     if (tile >= a.ntiles) return;  // whole wavefronts; no barriers below
     const int row = lane & 31, kh = lane >> 5;
@@ -380,7 +404,6 @@ __global__ __launch_bounds__(256, KF <= 16 ? 4 : 2) void trans32_kernel(TransArg
     const int li = base + row;
     const int tcell = li < seg.len ? tl[li] : -1;
     const int tx = (int)morton_x((uint32_t)tcell), ty = (int)morton_y((uint32_t)tcell);
-    const int nside = 1 << seg.level;
     const int64_t here = level_base(seg.level) - a.out_off;
     const int64_t from = level_base(seg.level + (MODE == Trans::M2M ? 1 : MODE == Trans::L2L ? -1 : 0)) - a.src_off;
     const TSrc *src = (const TSrc *)a.src;
@@ -402,44 +425,47 @@ __global__ __launch_bounds__(256, KF <= 16 ? 4 : 2) void trans32_kernel(TransArg
     float av[2][KF], bv[2][KF];
     auto fetch = [&](int slot, int e) {
         const int4 en = a.entries[e0 + e];
-        const float4 *b = (const float4 *)(tab + (((size_t)en.z * 2 + kh) * NC + col) * KF);
+        const float4 *b = (const float4 *)tab + ((size_t)en.z * NB + cb) * (KF / 4) * 64 + lane;
 #pragma unroll
         for (int v = 0; v < KF / 4; ++v) {
-            const float4 t = b[v];
+            const float4 t = b[v * 64];
             bv[slot][4 * v] = t.x;
             bv[slot][4 * v + 1] = t.y;
             bv[slot][4 * v + 2] = t.z;
             bv[slot][4 * v + 3] = t.w;
         }
-        int64_t S = -1;
+        // selected, not branched over (see trans64_kernel)
+        const int64_t c = max(tcell, 0);
         if constexpr (MODE == Trans::M2L) {
-            if (e == 27) {  // L2L (with par)
-                const int64_t P = level_base(seg.level - 1) - a.par_off + (tcell >> 2);
-                load_row32<KF, TPar>(av[slot], tcell >= 0 ? (const TPar *)a.par + P * two_p : (const TPar *)a.zero, k0,
-                                     two_p);
-                return;
-            }
-            const int sx = tx + en.x, sy = ty + en.y;
-            if (tcell >= 0 && sx >= 0 && sy >= 0 && sx < nside && sy < nside)
-                S = from + morton_encode((uint32_t)sx, (uint32_t)sy);
-        } else if constexpr (MODE == Trans::M2M) {
-            if (tcell >= 0) S = from + 4 * (int64_t)tcell + e;
+            const uint32_t nside = 1u << seg.level;
+            const uint32_t sx = (uint32_t)(tx + en.x), sy = (uint32_t)(ty + en.y);
+            const int64_t S = from + morton_encode(sx, sy);
+            const bool l2l = e == 27 && a.par;  // wavefront-uniform
+            const int64_t P = level_base(seg.level - 1) - a.par_off + (c >> 2);
+            const float *r = (l2l ? (const float *)a.par : (const float *)src) + (l2l ? P : S) * two_p;
+            const bool ok = tcell >= 0 && (l2l || (e < 27 && sx < nside && sy < nside));
+            r = ok ? r : (const float *)a.zero;
+            load_row32<KF>(av[slot], r + k0);
         } else {
-            if (tcell >= 0) S = from + (tcell >> 2);
+            const int64_t S = from + (MODE == Trans::M2M ? 4 * c + e : c >> 2);
+            load_row32<KF>(av[slot], (tcell >= 0 ? src + S * two_p : (const TSrc *)a.zero) + k0);
         }
-        load_row32<KF, TSrc>(av[slot], S >= 0 ? src + S * two_p : (const TSrc *)a.zero, k0, two_p);
+        __builtin_amdgcn_sched_barrier(0);
     };
     auto products = [&](int slot) {
 #pragma unroll
         for (int s = 0; s < KF; ++s)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[slot][s], bv[slot][s], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in_row(av[slot][s], k0 + s, two_p), bv[slot][s], acc, 0, 0, 0);
     };
+    // the next operator's operands ahead of the current one's products (see trans64_kernel)
     fetch(0, 0);
-    for (int e = 0; e < NE; e += 2) {
-        if (e + 1 < NE) fetch(1, e + 1);
+    if constexpr (NE == 1) {
         products(0);
-        if (e + 1 < NE) {
-            if (e + 2 < NE) fetch(0, e + 2);
+    } else {
+        for (int e = 0; e < NE; e += 2) {
+            fetch(1, e + 1);
+            products(0);
+            fetch(0, min(e + 2, NE - 1));
             products(1);
         }
     }
@@ -503,15 +529,14 @@ template <int KS> void trans64(TransArgs &a, Trans mode, bool adaptive, hipStrea
     else adaptive ? go64<KS, 1, 1, Trans::L2L, true>(a, s) : go64<KS, 1, 1, Trans::L2L, false>(a, s);
 }
 
-template <int KF, Trans MODE, typename TSrc, typename TOut, typename TPar = float> void go32(TransArgs &a, hipStream_t s)
+template <int KF, Trans MODE, typename TSrc, typename TOut> void go32(TransArgs &a, hipStream_t s)
 {
-    trans32_kernel<KF, MODE, TSrc, TOut, TPar><<<xcd_grid((int64_t)a.ntiles * col_blocks32<KF>(), 4, kXcds), 256, 0, s>>>(a);
+    trans32_kernel<KF, MODE, TSrc, TOut><<<xcd_grid((int64_t)a.ntiles * col_blocks32<KF>(), 4, kXcds), 256, 0, s>>>(a);
 }
 
 template <int KF> void trans32(TransArgs &a, Trans mode, bool src_double, bool out_double, hipStream_t s)
 {
-    if (mode == Trans::M2L)
-        src_double ? go32<KF, Trans::M2L, float, float, double>(a, s) : go32<KF, Trans::M2L, float, float>(a, s);
+    if (mode == Trans::M2L) go32<KF, Trans::M2L, float, float>(a, s);
     else if (mode == Trans::M2M)
         out_double ? go32<KF, Trans::M2M, float, double>(a, s) : go32<KF, Trans::M2M, float, float>(a, s);
     else src_double ? go32<KF, Trans::L2L, double, float>(a, s) : go32<KF, Trans::L2L, float, float>(a, s);
