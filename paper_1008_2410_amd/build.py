@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfmm2d.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["kernels.hip", "translate.hip", "tree_build.hip", "adaptive.hip", "adaptive_build.hip", "tables.cpp", "api.cpp",
+SOURCES = ["kernels.hip", "translate.hip", "device_cache.cpp", "tree_build.hip", "adaptive.hip", "adaptive_build.hip", "tables.cpp", "api.cpp",
            "adaptive.cpp", "host_tree.cpp"]
 ARCH = "gfx950"
 

@@ -18,22 +18,12 @@ using namespace fmm;
 
 namespace {
 
+// Idle: the caller has finished the work that used it.
 void free_ws(AtreeWs &w)
 {
-    hipFree(w.gam);
-    hipFree(w.stage);
-    hipFree(w.gamma);
-    hipFree(w.near);
-    hipFree(w.slots);
-    hipFree(w.mp);
-    hipFree(w.lo);
-    hipFree(w.mp2);
-    hipFree(w.lo2);
-    hipFree(w.adj);
-    hipFree(w.qt);
-    hipFree(w.pa);
-    hipFree(w.pb);
-    hipFree(w.psrc);
+    for (void *p : {w.gam, (void *)w.stage, (void *)w.gamma, (void *)w.near, w.slots, (void *)w.mp, (void *)w.lo,
+                    (void *)w.mp2, (void *)w.lo2, (void *)w.adj, w.qt, (void *)w.pa, (void *)w.pb, (void *)w.psrc})
+        block_free(p);
     w = AtreeWs{};
 }
 
@@ -41,10 +31,8 @@ void free_atree(fmm_atree *t)
 {
     if (!t) return;
     AtreeDev &d = t->d;
-    // the device build's arrays and the adjoint units come from the stream-ordered pool
-    if (t->pooled || d.bwd_units || d.vslot) hipDeviceSynchronize();
-    for (void *p : {(void *)d.bwd_units, (void *)d.m2l_targets, (void *)d.vslot})
-        if (p) hipFreeAsync(p, nullptr);
+    hipDeviceSynchronize();  // blocks enter the cache idle
+    for (void *p : {(void *)d.bwd_units, (void *)d.m2l_targets, (void *)d.vslot, t->d_pos[0], t->d_pos[1]}) block_free(p);
     for (void *p : {(void *)d.perm, (void *)d.gpos1, (void *)d.gpos2, (void *)d.st1, (void *)d.leaf_of, (void *)d.xy, (void *)d.cell, (void *)d.range,
                     (void *)d.parent, (void *)d.child, (void *)d.u_off, (void *)d.u_idx, (void *)d.v_off,
                     (void *)d.v_idx, (void *)d.w_off, (void *)d.w_idx, (void *)d.x_off, (void *)d.x_idx,
@@ -52,17 +40,12 @@ void free_atree(fmm_atree *t)
                     (void *)d.work, (void *)d.leaf_start, (void *)d.leaf_tile, (void *)d.tile_box_leaf,
                     (void *)d.mask}) {
         if (!p) continue;
-        if (t->pooled)
-            hipFreeAsync(p, nullptr);
-        else
-            hipFree(p);
+        if (t->pooled) block_free(p);
+        else hipFree(p);
     }
     if (t->wsp.use_count() == 1) free_ws(*t->wsp);
-    for (void *q : t->d_pos) hipFree(q);
     if (t->d_flag) hipFree(t->d_flag);
-    if (t->ev_fork) hipEventDestroy(t->ev_fork);
-    if (t->ev_join) hipEventDestroy(t->ev_join);
-    if (t->own_side) hipStreamDestroy(t->own_side);
+    side_stream_give(t->device, t->aux);
     delete t;
 }
 
@@ -217,7 +200,7 @@ int ensure_coords(fmm_atree *t, int precision, hipStream_t s)
 {
     const int k = precision == FMM_FP64;
     if (t->d_pos[k]) return FMM_OK;
-    int rc = dev_alloc((char **)&t->d_pos[k], (size_t)t->n * (k ? sizeof(double2) : sizeof(float2)),
+    int rc = dev_alloc_block((char **)&t->d_pos[k], (size_t)t->n * (k ? sizeof(double2) : sizeof(float2)),
                        "leaf offsets of the particles");
     if (rc) return rc;
     launch_atree_coords(t, k, t->d_pos[k], s);
@@ -236,10 +219,10 @@ int ensure_ws(fmm_atree *t, int p, int precision)
         // a workspace handed over by fmm_atree_rebuild from a tree with fewer cells
         HIP_TRY(hipDeviceSynchronize());
         for (double2 **a : {&w.mp, &w.lo, &w.mp2, &w.lo2}) {
-            hipFree(*a);
+            block_free(*a);
             *a = nullptr;
         }
-        if ((rc = dev_alloc(&w.mp, coef, "multipoles")) || (rc = dev_alloc(&w.lo, coef, "locals"))) {
+        if ((rc = dev_alloc_block(&w.mp, coef, "multipoles")) || (rc = dev_alloc_block(&w.lo, coef, "locals"))) {
             free_ws(w);
             return rc;
         }
@@ -250,13 +233,13 @@ int ensure_ws(fmm_atree *t, int p, int precision)
         HIP_TRY(hipDeviceSynchronize());  // earlier calls may still read the old workspace
         free_ws(w);
     }
-    if ((rc = dev_alloc((char **)&w.gam, n * (precision == FMM_FP64 ? sizeof(double) : sizeof(float)),
+    if ((rc = dev_alloc_block((char **)&w.gam, n * (precision == FMM_FP64 ? sizeof(double) : sizeof(float)),
                         "circulations in the near field's precision")) ||
-        (rc = dev_alloc(&w.stage, n, "totals")) ||
-        (rc = dev_alloc(&w.gamma, n, "circulations")) || (rc = dev_alloc(&w.near, n, "near field")) ||
-        (rc = dev_alloc((char **)&w.slots, 9 * n * (precision == FMM_FP64 ? sizeof(double2) : sizeof(float2)),
+        (rc = dev_alloc_block(&w.stage, n, "totals")) ||
+        (rc = dev_alloc_block(&w.gamma, n, "circulations")) || (rc = dev_alloc_block(&w.near, n, "near field")) ||
+        (rc = dev_alloc_block((char **)&w.slots, 9 * n * (precision == FMM_FP64 ? sizeof(double2) : sizeof(float2)),
                         "mutual near-field slots")) ||
-        (rc = dev_alloc(&w.mp, coef, "multipoles")) || (rc = dev_alloc(&w.lo, coef, "locals"))) {
+        (rc = dev_alloc_block(&w.mp, coef, "multipoles")) || (rc = dev_alloc_block(&w.lo, coef, "locals"))) {
         free_ws(w);
         return rc;
     }
@@ -275,19 +258,19 @@ int ensure_ws_backward(fmm_atree *t, bool src)
     int rc = FMM_OK;
     // each group is allocated whole or not at all (a failed call leaves none of it)
     if (!w.mp2) {
-        if ((rc = dev_alloc(&w.mp2, w.coef_cap, "adjoint multipoles")) ||
-            (rc = dev_alloc(&w.lo2, w.coef_cap, "adjoint locals"))) {
-            hipFree(w.mp2);
+        if ((rc = dev_alloc_block(&w.mp2, w.coef_cap, "adjoint multipoles")) ||
+            (rc = dev_alloc_block(&w.lo2, w.coef_cap, "adjoint locals"))) {
+            block_free(w.mp2);
             w.mp2 = nullptr;
             return rc;
         }
     }
     if (!w.adj) {
-        if ((rc = dev_alloc(&w.adj, n, "adjoint charges")) ||
-            (rc = dev_alloc((char **)&w.qt, n * (w.precision == FMM_FP64 ? sizeof(double2) : sizeof(float2)),
+        if ((rc = dev_alloc_block(&w.adj, n, "adjoint charges")) ||
+            (rc = dev_alloc_block((char **)&w.qt, n * (w.precision == FMM_FP64 ? sizeof(double2) : sizeof(float2)),
                             "adjoint charges")) ||
-            (rc = dev_alloc(&w.pa, n, "adjoint near sums")) || (rc = dev_alloc(&w.pb, n, "adjoint near sums"))) {
-            for (void *q : {(void *)w.adj, w.qt, (void *)w.pa, (void *)w.pb}) hipFree(q);
+            (rc = dev_alloc_block(&w.pa, n, "adjoint near sums")) || (rc = dev_alloc_block(&w.pb, n, "adjoint near sums"))) {
+            for (void *q : {(void *)w.adj, w.qt, (void *)w.pa, (void *)w.pb}) block_free(q);
             w.adj = nullptr;
             w.qt = nullptr;
             w.pa = nullptr;
@@ -295,7 +278,7 @@ int ensure_ws_backward(fmm_atree *t, bool src)
             return rc;
         }
     }
-    if (src && !w.psrc && (rc = dev_alloc(&w.psrc, n, "adjoint source-position sums"))) return rc;
+    if (src && !w.psrc && (rc = dev_alloc_block(&w.psrc, n, "adjoint source-position sums"))) return rc;
     return FMM_OK;
 }
 
@@ -376,18 +359,18 @@ int run(fmm_atree *t, const double *gamma, double sigma, int p, int precision, v
     int rc = validate_inputs(t, gamma, nullptr, (hipStream_t)main_stream);
     hipStream_t ms = (hipStream_t)main_stream;
     if (rc || (rc = ensure_ws(t, p, precision)) || (rc = ensure_coords(t, precision, ms))) return rc;
-    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->own_side;
+    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
     const Tables *tabs = nullptr;
     if ((rc = ensure_m2l_plan(t, p, ms, tabs))) return rc;
     const AtreeCall c{t, p, precision == FMM_FP64, record_alpha(sigma, precision),
                       choose_occupancy(t, precision, ss != ms), tabs};
     launch_atree_pack(c, gamma, ms);
-    HIP_TRY(hipEventRecord(t->ev_fork, ms));
-    HIP_TRY(hipStreamWaitEvent(ss, t->ev_fork, 0));
+    HIP_TRY(hipEventRecord(t->aux.fork, ms));
+    HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
     launch_atree_far(c, ss);  // P2M, M2M, M2L + P2L + L2L
-    HIP_TRY(hipEventRecord(t->ev_join, ss));
+    HIP_TRY(hipEventRecord(t->aux.join, ss));
     launch_atree_near(c, ms);  // P2P over U, beside the far field
-    HIP_TRY(hipStreamWaitEvent(ms, t->ev_join, 0));
+    HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
     launch_atree_finalize(c, uv, uv_near, uv_far, base, h, ms);  // L2P + M2P + sum
     HIP_TRY(hipGetLastError());
     return FMM_OK;
@@ -407,7 +390,7 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     if (!guard.ok) return fail(FMM_ESTATE, "tree handle in use by another thread");
     HIP_TRY(hipSetDevice(t->device));
     hipStream_t ms = (hipStream_t)main_stream;
-    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->own_side;
+    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
     if ((rc = validate_inputs(t, gamma, dl_duv, ms))) return rc;
     if (t->nbwd_units < 0) {
         std::string err;
@@ -422,12 +405,12 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     launch_atree_pack_adjoint(c, dl_duv, scale, ms);
     // The two far chains run beside each other, then the near field (which holds every
     // wavefront slot, so that far kernels beside it would wait for it to drain).
-    HIP_TRY(hipEventRecord(t->ev_fork, ms));
-    HIP_TRY(hipStreamWaitEvent(ss, t->ev_fork, 0));
+    HIP_TRY(hipEventRecord(t->aux.fork, ms));
+    HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
     launch_atree_far(c, ss, true);   // the charges q: the transpose pass
     launch_atree_far(c, ms, false);  // the charges c: derivative W' at the particles
-    HIP_TRY(hipEventRecord(t->ev_join, ss));
-    HIP_TRY(hipStreamWaitEvent(ms, t->ev_join, 0));
+    HIP_TRY(hipEventRecord(t->aux.join, ss));
+    HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
     launch_atree_backward_near(c, src, ms);
     launch_atree_finalize_backward(c, out, ms);
     HIP_TRY(hipGetLastError());
@@ -465,9 +448,7 @@ int new_atree(const double *xy, int64_t n, int max_leaf, int max_depth, const do
 
 int finish_atree(fmm_atree *t)
 {
-    hipError_t e = hipStreamCreateWithFlags(&t->own_side, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&t->ev_fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&t->ev_join, hipEventDisableTiming);
+    const hipError_t e = side_stream_take(t->device, t->aux);
     return e != hipSuccess ? hip_fail(e, "creating the side stream") : FMM_OK;
 }
 
@@ -479,7 +460,6 @@ extern "C" int fmm_atree_build(const double *xy, int64_t n, int max_leaf, int ma
     fmm_atree *t = nullptr;
     int rc = new_atree(xy, n, max_leaf, max_depth, root_box, out, t);
     if (rc) return rc;
-    retain_pool(t->device);
     std::string err;
     int64_t bad = -1;
     rc = build_atree_device(t, xy, root_box, (hipStream_t)stream, err, bad);
@@ -489,11 +469,14 @@ extern "C" int fmm_atree_build(const double *xy, int64_t n, int max_leaf, int ma
     } else {
         rc = finish_atree(t);
     }
+    if (!rc) {
+        const hipError_t e = hipDeviceSynchronize();
+        if (e != hipSuccess) rc = hip_fail(e, "hipDeviceSynchronize");
+    }
     if (rc) {
         free_atree(t);
         return rc;
     }
-    trim_pool(t->device);  // the build's temporaries
     *out = t;
     return FMM_OK;
 }
@@ -938,5 +921,4 @@ extern "C" void fmm_atree_destroy(fmm_atree *t)
     hipSetDevice(t->device);
     const int dev = t->device;
     free_atree(t);
-    trim_pool(dev);
 }

@@ -437,35 +437,32 @@ __global__ __launch_bounds__(256) void ak_tile_box(const int *__restrict__ tile_
 }
 
 // Statistics gathered by the plan's counting pass.
-enum { kStPairs = 0, kStMutualPairs, kStMutualItems, kStUnits, kStMaxCost, kStCount };
+enum { kStPairs = 0, kStMutualPairs, kStMutualItems, kStUnits, kStCount };
 
 // Near-field plan, per leaf in sorted order: target-centric units (one per 64-particle
 // tile) when some of U is left to them, then for a dense leaf its mutual item with
 // itself and with each dense same-level leaf at (1, 0), (-1, 1), (0, 1), (1, 1); the slot
 // mask of every leaf.  Counting pass (NL + 1 counts, the last 0; statistics) and
-// filling pass (entries, costs, largest cost).
+// filling pass (entries, their order keys, and the identity to sort with them).
 template <bool FILL>
 __global__ __launch_bounds__(256) void ak_plan(const int *__restrict__ leaves, const int *__restrict__ leaf_index, int NL,
                                                 const int4 *__restrict__ cell, const int2 *__restrict__ range,
                                                 const int *__restrict__ coll, const int *__restrict__ u_off,
                                                 const int *__restrict__ u_idx, int D, uint32_t *__restrict__ cnt,
                                                 const int *__restrict__ off, int4 *__restrict__ work,
-                                                uint64_t *__restrict__ cost, uint16_t *__restrict__ mask,
-                                                unsigned long long *__restrict__ stats)
+                                                uint64_t *__restrict__ key, uint32_t *__restrict__ order,
+                                                uint16_t *__restrict__ mask, unsigned long long *__restrict__ stats)
 {
     const int li = blockIdx.x * blockDim.x + threadIdx.x;
-    if (li > NL) return;
-    if (li == NL) {
-        if (!FILL) cnt[NL] = 0;
-        return;
-    }
-    const int k = leaves[li];
+    if (FILL && li >= NL) return;
+    const bool valid = li < NL;  // the counting pass keeps its wavefronts whole for the sums
+    const int k = valid ? leaves[li] : 0;
     const int4 c = cell[k];
-    const int2 r = range[k];
+    const int2 r = valid ? range[k] : make_int2(0, 0);
     const bool dense = r.y >= D;
     uint32_t m = 0;
     int64_t nsrc = 0, usum = 0;
-    for (int u = u_off[k]; u < u_off[k + 1]; ++u) {
+    for (int u = valid ? u_off[k] : 0, ue = valid ? u_off[k + 1] : 0; u < ue; ++u) {
         const int S = u_idx[u];
         const int4 cs = cell[S];
         const int ns = range[S].y;
@@ -477,12 +474,11 @@ __global__ __launch_bounds__(256) void ak_plan(const int *__restrict__ leaves, c
     }
     int ne = 0;
     const int o = FILL ? off[li] : 0;
-    uint64_t cmax = 0;
     auto put = [&](int4 item, int64_t cst) {
         if (FILL) {
             work[o + ne] = item;
-            cost[o + ne] = (uint64_t)cst;
-            cmax = cmax > (uint64_t)cst ? cmax : (uint64_t)cst;
+            key[o + ne] = cost_order((uint64_t)cst);  // heaviest first
+            order[o + ne] = (uint32_t)(o + ne);
         }
         ++ne;
     };
@@ -510,26 +506,20 @@ __global__ __launch_bounds__(256) void ak_plan(const int *__restrict__ leaves, c
             mp += 2 * (int64_t)r.y * range[R].y;
         }
     }
-    if (!FILL) {
-        cnt[li] = (uint32_t)ne;
-        mask[k] = (uint16_t)m;
-        atomicAdd(&stats[kStPairs], (unsigned long long)((int64_t)r.y * usum - r.y));
-        if (mp) atomicAdd(&stats[kStMutualPairs], (unsigned long long)mp);
-        if (items) atomicAdd(&stats[kStMutualItems], (unsigned long long)items);
-        if (units) atomicAdd(&stats[kStUnits], (unsigned long long)units);
-    } else if (ne) {
-        atomicMax(&stats[kStMaxCost], (unsigned long long)cmax);
+    if constexpr (!FILL) {
+        if (li <= NL) cnt[li] = (uint32_t)ne;  // 0 at NL
+        if (valid) mask[k] = (uint16_t)m;
+        unsigned long long v[kStCount];
+        v[kStPairs] = (unsigned long long)((int64_t)r.y * usum - r.y);
+        v[kStMutualPairs] = (unsigned long long)mp;
+        v[kStMutualItems] = (unsigned long long)items;
+        v[kStUnits] = (unsigned long long)units;
+#pragma unroll
+        for (int q = 0; q < kStCount; ++q) {
+            for (int o2 = 32; o2 >= 1; o2 >>= 1) v[q] += __shfl_xor(v[q], o2);
+            if ((threadIdx.x & 63) == 0 && v[q]) atomicAdd(&stats[q], v[q]);
+        }
     }
-}
-
-// Sort keys of the plan: heaviest first, so key = largest cost - cost (ascending).
-__global__ __launch_bounds__(256) void ak_cost_keys(uint64_t *__restrict__ cost, int64_t nwork, uint64_t cmax,
-                                                     uint32_t *__restrict__ val)
-{
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= nwork) return;
-    cost[u] = cmax - cost[u];
-    val[u] = (uint32_t)u;
 }
 
 __global__ __launch_bounds__(256) void ak_gather_work(const int4 *__restrict__ src, const uint32_t *__restrict__ order,
@@ -569,8 +559,7 @@ __global__ __launch_bounds__(256) void ak_adj_units(const int *__restrict__ leaf
                                                      const int *__restrict__ leaf_tile, int NL,
                                                      const int2 *__restrict__ range, const int *__restrict__ u_off,
                                                      const int *__restrict__ u_idx, int4 *__restrict__ units,
-                                                     uint64_t *__restrict__ cost, uint32_t *__restrict__ order,
-                                                     unsigned long long *__restrict__ cmax)
+                                                     uint64_t *__restrict__ key, uint32_t *__restrict__ order)
 {
     const int li = blockIdx.x * blockDim.x + threadIdx.x;
     if (li >= NL) return;
@@ -578,23 +567,13 @@ __global__ __launch_bounds__(256) void ak_adj_units(const int *__restrict__ leaf
     const int2 r = range[k];
     int64_t usum = 0;
     for (int e = u_off[k]; e < u_off[k + 1]; ++e) usum += range[u_idx[e]].y;
-    uint64_t m = 0;
     int t = leaf_tile[li];
     for (int b = r.x; b < r.x + r.y; b += 64, ++t) {
         const int len = min(64, r.x + r.y - b);
         units[t] = make_int4(k, b, len, at_log2_lanes(len));
-        const uint64_t c = (uint64_t)at_unit_cost(usum, len);
-        cost[t] = c;
+        key[t] = cost_order((uint64_t)at_unit_cost(usum, len));  // heaviest first
         order[t] = (uint32_t)t;
-        m = m > c ? m : c;
     }
-    atomicMax(cmax, (unsigned long long)m);
-}
-
-__global__ __launch_bounds__(256) void ak_desc_keys(uint64_t *__restrict__ key, int64_t n, uint64_t cmax)
-{
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < n) key[u] = cmax - key[u];
 }
 
 // The per-cell arrays while the levels are made: grown by doubling, first `used`
@@ -608,22 +587,27 @@ struct CellStore {
     int64_t cap = 0;
     hipStream_t s = nullptr;
 
+    template <typename T> void drop(T *&p, int per) { build_free(p, (size_t)cap * per * sizeof(T), s); }
     ~CellStore()
     {
-        for (void *p : {(void *)cell, (void *)range, (void *)parent, (void *)child, (void *)coll})
-            if (p) (void)hipFreeAsync(p, s);
+        drop(cell, 1);
+        drop(range, 1);
+        drop(parent, 1);
+        drop(child, 1);
+        drop(coll, 8);
     }
     template <typename T>
     bool regrow(T *&p, int64_t ncap, int64_t used, int per, Status &st)
     {
         T *q = nullptr;
-        if (!st.check(hipMallocAsync((void **)&q, (size_t)ncap * per * sizeof(T), s), "adaptive tree cells")) return false;
+        const size_t bytes = (size_t)ncap * per * sizeof(T);
+        if (!st.check(build_alloc((void **)&q, bytes, s), "adaptive tree cells")) return false;
         if (used > 0 && !st.check(hipMemcpyAsync(q, p, (size_t)used * per * sizeof(T), hipMemcpyDeviceToDevice, s),
                                   "adaptive tree cells")) {
-            (void)hipFreeAsync(q, s);
+            build_free(q, bytes, s);
             return false;
         }
-        if (p) (void)hipFreeAsync(p, s);
+        drop(p, per);
         p = q;
         return true;
     }
@@ -642,7 +626,7 @@ struct CellStore {
 template <typename T>
 bool alloc_to(T *&p, int64_t count, hipStream_t s, Status &st, const char *what)
 {
-    return st.check(hipMallocAsync((void **)&p, (size_t)std::max<int64_t>(count, 1) * sizeof(T), s), what);
+    return st.check(build_alloc((void **)&p, (size_t)std::max<int64_t>(count, 1) * sizeof(T), s), what);
 }
 
 bool read_back(void *dst, const void *src, size_t bytes, hipStream_t s, Status &st)
@@ -675,6 +659,7 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
     const int smax = t->max_leaf;
     const double2 *xy2 = (const double2 *)xy;
     AtreeDev &d = t->d;
+    BuildScope scope(s);
 
     // Stage 1: root cell.
     if (root_box) {
@@ -719,7 +704,7 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
             return (hf & 2) ? FMM_EINVAL : FMM_ERANGE;
         }
     }
-    if (!radix_sort(key.p, val.p, n, 2 * L, s, st)) return failed();
+    if (!radix_sort(key, val, n, 2 * L, s, st)) return failed();
     if (!alloc_to(d.perm, n, s, st, "permutation") || !alloc_to(d.xy, n, s, st, "sorted positions") ||
         !alloc_to(d.leaf_of, n, s, st, "leaf of each particle"))
         return failed();
@@ -810,7 +795,7 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         ak_xcount<<<grid_for(nw, 256), 256, 0, s>>>(d.w_idx, nw, xcnt.p);
         ak_xkeys<<<grid_for(nw, 256), 256, 0, s>>>(d.w_idx, nw, xkey.p);
         if (!scan_exclusive(xcnt.p, xcnt.p, K + 1, nullptr, s, st) ||
-            !radix_sort(xkey.p, wown.p, nw, bits_for((uint64_t)K), s, st))
+            !radix_sort(xkey, wown, nw, bits_for((uint64_t)K), s, st))
             return failed();
         d.x_off = (int *)xcnt.release();
         d.x_idx = (int *)wown.release();
@@ -874,7 +859,8 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         return failed();
     ak_plan<false><<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, leaf_index.p, (int)NL, cs.cell, cs.range,
                                                                    cs.coll, d.u_off, d.u_idx, t->dense_leaf, pcnt.p,
-                                                                   nullptr, nullptr, nullptr, d.mask, stats.p);
+                                                                   nullptr, nullptr, nullptr, nullptr, d.mask,
+                                                                   stats.p);
     if (!scan_exclusive(pcnt.p, pcnt.p, (int64_t)NL + 1, &nwork, s, st)) return failed();
     Buf<int4> work;
     Buf<uint64_t> cost;
@@ -884,12 +870,12 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         return failed();
     ak_plan<true><<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, leaf_index.p, (int)NL, cs.cell, cs.range,
                                                                   cs.coll, d.u_off, d.u_idx, t->dense_leaf, nullptr,
-                                                                  (const int *)pcnt.p, work.p, cost.p, nullptr, stats.p);
+                                                                  (const int *)pcnt.p, work.p, cost.p, order.p, nullptr,
+                                                                  nullptr);
     unsigned long long hs[kStCount];
     if (!read_back(hs, stats.p, sizeof hs, s, st)) return failed();
     if (!alloc_to(d.work, nwork, s, st, "near-field work")) return failed();
-    ak_cost_keys<<<grid_for(nwork, 256), 256, 0, s>>>(cost.p, nwork, hs[kStMaxCost], order.p);
-    if (!radix_sort(cost.p, order.p, nwork, bits_for(hs[kStMaxCost]), s, st)) return failed();
+    if (!radix_sort(cost, order, nwork, 8, s, st)) return failed();
     ak_gather_work<<<grid_for(nwork, 256), 256, 0, s>>>(work.p, order.p, nwork, d.work);
 
     // Leaves and split cells of level >= 2, in cell order.
@@ -918,10 +904,10 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
     }
 
     // Staging slots of the two-pass permutations between user and sorted order.
-    if (!build_staging(d.perm, n, s, st, t->stage_shift, d.gpos1, d.gpos2, d.st1)) {
-        err = st.msg;
-        return st.code;
-    }
+    t->stage_shift = stage_shift_of(n);
+    if (!alloc_to(d.gpos1, n, s, st, "staging slots") || !alloc_to(d.gpos2, n, s, st, "staging slots") ||
+        !alloc_to(d.st1, n, s, st, "staging array") || !build_staging(d.perm, n, s, st, t->stage_shift, d.gpos1, d.gpos2))
+        return failed();
 
     // The cell arrays pass to the tree; the neighbour slots were the build's alone.
     d.cell = cs.cell;
@@ -948,35 +934,25 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
 int build_atree_adjoint_units(fmm_atree *t, hipStream_t s, std::string &err)
 {
     Status st;
+    BuildScope scope(s);
     const int64_t nt = t->ntiles;
     const int NL = (int)t->sizes[FMM_AT_LEAVES];
     Buf<int4> units;
     Buf<uint64_t> cost;
     Buf<uint32_t> order;
-    Buf<unsigned long long> cmax;
     int4 *out = nullptr;
     if (!st.check(units.alloc(nt, s), "adjoint units") || !st.check(cost.alloc(nt, s), "adjoint units") ||
-        !st.check(order.alloc(nt, s), "adjoint units") || !st.check(cmax.alloc(1, s), "adjoint units") ||
-        !st.check(hipMemsetAsync(cmax.p, 0, sizeof(unsigned long long), s), "adjoint units")) {
+        !st.check(order.alloc(nt, s), "adjoint units") || !alloc_to(out, nt, s, st, "adjoint units")) {
         err = st.msg;
         return st.code;
     }
     ak_adj_units<<<grid_for(NL, 256), 256, 0, s>>>(t->d.leaf_start, t->d.leaf_of, t->d.leaf_tile, NL, t->d.range,
-                                                   t->d.u_off, t->d.u_idx, units.p, cost.p, order.p, cmax.p);
-    unsigned long long hm = 0;
-    if (!read_back(&hm, cmax.p, sizeof hm, s, st)) {
-        err = st.msg;
-        return st.code;
-    }
-    ak_desc_keys<<<grid_for(nt, 256), 256, 0, s>>>(cost.p, nt, hm);
-    if (!radix_sort(cost.p, order.p, nt, bits_for(hm), s, st) ||
-        !st.check(hipMallocAsync((void **)&out, (size_t)std::max<int64_t>(nt, 1) * sizeof(int4), s), "adjoint units")) {
-        err = st.msg;
-        return st.code;
-    }
-    ak_gather_work<<<grid_for(nt, 256), 256, 0, s>>>(units.p, order.p, nt, out);
-    if (!st.check(hipGetLastError(), "adjoint units") || !st.check(hipStreamSynchronize(s), "adjoint units")) {
-        (void)hipFreeAsync(out, s);
+                                                   t->d.u_off, t->d.u_idx, units.p, cost.p, order.p);
+    const bool sorted = radix_sort(cost, order, nt, 8, s, st);
+    if (sorted) ak_gather_work<<<grid_for(nt, 256), 256, 0, s>>>(units.p, order.p, nt, out);
+    if (!sorted || !st.check(hipGetLastError(), "adjoint units") ||
+        !st.check(hipStreamSynchronize(s), "adjoint units")) {
+        build_free(out, (size_t)nt * sizeof(int4), s);
         err = st.msg;
         return st.code;
     }
@@ -1046,27 +1022,27 @@ int build_atree_m2l_plan(fmm_atree *t, const int4 *entries, hipStream_t s, std::
     }
     const int first = t->level_off[2], ncl = t->level_off[deepest + 1] - first;
     const int nseg = 4 * (deepest - 1);  // <= 56
+    BuildScope scope(s);
     Buf<uint64_t> key;
     Buf<uint32_t> val;
     Buf<unsigned int> cnt;
     int *targets = nullptr, *vslot = nullptr;
     auto failed = [&]() {
-        if (targets) (void)hipFreeAsync(targets, s);
-        if (vslot) (void)hipFreeAsync(vslot, s);
+        build_free(targets, (size_t)std::max(ncl, 1) * sizeof(int), s);
+        build_free(vslot, (size_t)std::max(ncl, 1) * 27 * sizeof(int), s);
         err = st.msg;
         return st.code;
     };
     if (!st.check(key.alloc(ncl, s), "M2L plan") || !st.check(val.alloc(ncl, s), "M2L plan") ||
         !st.check(cnt.alloc(nseg + 1, s), "M2L plan") ||
         !st.check(hipMemsetAsync(cnt.p, 0, (nseg + 1) * sizeof(unsigned int), s), "M2L plan") ||
-        !st.check(hipMallocAsync((void **)&targets, (size_t)std::max(ncl, 1) * sizeof(int), s), "M2L plan") ||
-        !st.check(hipMallocAsync((void **)&vslot, (size_t)std::max(ncl, 1) * 27 * sizeof(int), s), "M2L plan"))
+        !alloc_to(targets, ncl, s, st, "M2L plan") || !alloc_to(vslot, 27 * (int64_t)ncl, s, st, "M2L plan"))
         return failed();
     ak_m2l_keys<<<grid_for(ncl, 256), 256, 0, s>>>(t->d.cell, first, ncl, nseg, key.p, val.p, cnt.p);
     ak_vslot<<<grid_for(ncl, 256), 256, 0, s>>>(t->d.cell, first, ncl, t->d.v_off, t->d.v_idx, entries, vslot,
                                                 cnt.p + nseg);
     // stable by segment: Morton order inside a class as inside a level
-    if (!radix_sort(key.p, val.p, ncl, 6, s, st) ||
+    if (!radix_sort(key, val, ncl, 6, s, st) ||
         !st.check(hipMemcpyAsync(targets, val.p, (size_t)ncl * sizeof(int), hipMemcpyDeviceToDevice, s), "M2L plan"))
         return failed();
     std::vector<unsigned int> hc((size_t)nseg + 1);

@@ -130,11 +130,10 @@ struct fmm_atree {
     int *d_flag = nullptr;    // device result of that check
     std::vector<int> level_off;   // max_depth + 2 entries
     std::vector<int> inner_off;   // max_depth + 2 entries, into AtreeDev::inner
-    bool pooled = false;  // device arrays from the stream-ordered pool (the device build)
+    bool pooled = false;  // device arrays from the library's block cache (the device build)
     fmm::AtreeDev d;
     std::shared_ptr<fmm::AtreeWs> wsp = std::make_shared<fmm::AtreeWs>();  // shared by fmm_atree_share_workspace
-    hipStream_t own_side = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    fmm::SideStream aux;  // side stream and events, from the library's cache
     std::atomic<int> busy{0};
 };
 

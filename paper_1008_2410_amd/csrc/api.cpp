@@ -35,21 +35,21 @@ struct BusyGuard {
     }
 };
 
-// The workspace is allocated from the stream-ordered pool; callers have finished the
-// device work that used it (destroy) or synchronised (reallocation).
-void free_workspace(Workspace &ws, hipStream_t s)
+// The workspace's blocks go to the library's cache; callers have finished the device work
+// that used it (destroy) or synchronised (reallocation).
+void free_workspace(Workspace &ws)
 {
     for (void *p : {ws.gam, (void *)ws.stage, (void *)ws.near, (void *)ws.mp_d, (void *)ws.lo_d, (void *)ws.mp_f,
                     (void *)ws.lo_f, (void *)ws.adj, (void *)ws.mp2_d, (void *)ws.lo2_d, (void *)ws.mp2_f,
                     (void *)ws.lo2_f, (void *)ws.rec2, ws.sums})
-        if (p) hipFreeAsync(p, s);
+        block_free(p);
     ws = Workspace{};
 }
 
-// The tree's device arrays (not its workspace, streams or events), freed in the order of
+// The tree's device arrays (not its workspace, stream or events), freed in the order of
 // stream fs; the caller has finished the work that used them.  Arrays of the device build
-// come from the stream-ordered pool, those of the host build from hipMalloc; the
-// near-field plan and the leaf-unit coordinates are always pooled.
+// come from the stream-ordered pool (those of fixed size in one slab), those of the host
+// build from hipMalloc; the near-field plan and the leaf-unit coordinates are always pooled.
 void release_tree_arrays(fmm_tree *t, hipStream_t fs)
 {
     auto release = [fs](auto *&p, bool pooled) {
@@ -58,33 +58,75 @@ void release_tree_arrays(fmm_tree *t, hipStream_t fs)
         else hipFree((void *)p);
         p = nullptr;
     };
-    release(t->d_perm, t->pooled);
-    release(t->d_gpos1, t->pooled);
-    release(t->d_gpos2, t->pooled);
-    release(t->d_st1, t->pooled);
-    release(t->d_leaf_of, t->pooled);
-    release(t->d_xy, t->pooled);
-    release(t->d_leaf_start, t->pooled);
-    release(t->d_counts, t->pooled);
+    if (t->slab) {
+        release(t->slab, true);
+        t->d_perm = t->d_gpos1 = t->d_gpos2 = t->d_leaf_of = t->d_leaf_start = t->d_counts = t->d_tile_start = nullptr;
+        t->d_st1 = nullptr;
+        t->d_xy = nullptr;
+        t->d_leaf_mask = nullptr;
+    }
+    release(t->d_perm, false);
+    release(t->d_gpos1, false);
+    release(t->d_gpos2, false);
+    release(t->d_st1, false);
+    release(t->d_leaf_of, false);
+    release(t->d_xy, false);
+    release(t->d_leaf_start, false);
+    release(t->d_counts, false);
+    release(t->d_tile_start, false);
     release(t->d_lists, t->pooled);
     release(t->d_units, t->pooled);
-    release(t->d_tile_start, t->pooled);
     release(t->d_tile_box, t->pooled);
     release(t->d_near_work, true);
     release(t->d_leaf_mask, true);
-    release(t->d_pos[0], true);
-    release(t->d_pos[1], true);
+    t->cap_lists = t->cap_units = t->cap_tile_box = t->cap_near_work = 0;
+    for (int k = 0; k < 2; ++k) {
+        release(t->pos_buf[k], true);
+        t->d_pos[k] = nullptr;
+    }
+}
+
+// The arrays of a device-built tree pass to the tree rebuilt from it (same n and depth);
+// the caller has finished the work that used them.
+void take_over_arrays(fmm_tree *t, fmm_tree *from)
+{
+    auto take = [](auto &to, auto &of) {
+        to = of;
+        of = {};
+    };
+    take(t->slab, from->slab);
+    take(t->d_perm, from->d_perm);
+    take(t->d_gpos1, from->d_gpos1);
+    take(t->d_gpos2, from->d_gpos2);
+    take(t->d_st1, from->d_st1);
+    take(t->d_leaf_of, from->d_leaf_of);
+    take(t->d_xy, from->d_xy);
+    take(t->d_leaf_start, from->d_leaf_start);
+    take(t->d_counts, from->d_counts);
+    take(t->d_tile_start, from->d_tile_start);
+    take(t->d_leaf_mask, from->d_leaf_mask);
+    take(t->d_lists, from->d_lists);
+    take(t->d_units, from->d_units);
+    take(t->d_tile_box, from->d_tile_box);
+    take(t->d_near_work, from->d_near_work);
+    take(t->cap_lists, from->cap_lists);
+    take(t->cap_units, from->cap_units);
+    take(t->cap_tile_box, from->cap_tile_box);
+    take(t->cap_near_work, from->cap_near_work);
+    for (int k = 0; k < 2; ++k) {
+        take(t->pos_buf[k], from->pos_buf[k]);
+        from->d_pos[k] = nullptr;
+    }
 }
 
 void free_tree(fmm_tree *t)
 {
-    hipStream_t fs = t->own_side;  // the caller has finished the work on the tree
+    hipStream_t fs = t->aux.stream;  // the caller has finished the work on the tree
     release_tree_arrays(t, fs);
     hipFree(t->d_flag);
-    if (t->wsp.use_count() == 1) free_workspace(*t->wsp, fs);
-    if (t->own_side) hipStreamDestroy(t->own_side);
-    if (t->ev_fork) hipEventDestroy(t->ev_fork);
-    if (t->ev_join) hipEventDestroy(t->ev_join);
+    if (t->wsp.use_count() == 1) free_workspace(*t->wsp);
+    if (fs) hipStreamSynchronize(fs);  // the frees are in its order
+    side_stream_give(t->device, t->aux);
     for (auto &evs : t->pending_timing)
         for (auto e : evs) hipEventDestroy(e);
     delete t;
@@ -127,7 +169,7 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
     if (ws.p != p || ws.precision != precision || ws.split != split) {
         hipError_t e = hipDeviceSynchronize();
         if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
-        free_workspace(ws, s);
+        free_workspace(ws);
     }
     const int64_t n = t->n;
     const int64_t cells_d = level_base(std::min(split, L) + 1);
@@ -135,15 +177,15 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
     const size_t gam_bytes = precision == FMM_FP64 ? sizeof(double) : sizeof(float);
     int rc = FMM_OK;
     if (!ws.gam) {
-        if ((rc = dev_alloc_async((char **)&ws.gam, n * gam_bytes, "circulations in tree order", s))) return rc;
-        if ((rc = dev_alloc_async(&ws.stage, n, "velocities in tree order", s))) return rc;
-        if ((rc = dev_alloc_async(&ws.near, n, "near field", s))) return rc;
+        if ((rc = dev_alloc_block((char **)&ws.gam, n * gam_bytes, "circulations in tree order"))) return rc;
+        if ((rc = dev_alloc_block(&ws.stage, n, "velocities in tree order"))) return rc;
+        if ((rc = dev_alloc_block(&ws.near, n, "near field"))) return rc;
         if (L >= 2) {
-            if ((rc = dev_alloc_async(&ws.mp_d, cells_d * p + kCoefPad, "multipoles", s))) return rc;
-            if ((rc = dev_alloc_async(&ws.lo_d, cells_d * p + kCoefPad, "locals", s))) return rc;
+            if ((rc = dev_alloc_block(&ws.mp_d, cells_d * p + kCoefPad, "multipoles"))) return rc;
+            if ((rc = dev_alloc_block(&ws.lo_d, cells_d * p + kCoefPad, "locals"))) return rc;
             if (cells_f > 0) {
-                if ((rc = dev_alloc_async(&ws.mp_f, cells_f * p + kCoefPad, "multipoles", s))) return rc;
-                if ((rc = dev_alloc_async(&ws.lo_f, cells_f * p + kCoefPad, "locals", s))) return rc;
+                if ((rc = dev_alloc_block(&ws.mp_f, cells_f * p + kCoefPad, "multipoles"))) return rc;
+                if ((rc = dev_alloc_block(&ws.lo_f, cells_f * p + kCoefPad, "locals"))) return rc;
             }
             // Empty cells are never written; the MFMA M2L reads them as zero rows.
             HIP_TRY(hipMemsetAsync(ws.mp_d, 0, (cells_d * p + kCoefPad) * sizeof(double2), s));
@@ -164,7 +206,7 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
         const size_t nn = (size_t)n;
         const size_t o_b = a256(32 * nn), o_src = a256(o_b + 8 * nn);
         const size_t bytes = std::max(9 * nn * (precision == FMM_FP64 ? 16 : 8), o_src + 32 * nn);
-        if ((rc = dev_alloc_async((char **)&ws.sums, bytes, "near-field sums", s))) return rc;
+        if ((rc = dev_alloc_block((char **)&ws.sums, bytes, "near-field sums"))) return rc;
         ws.sums_bytes = bytes;
         ws.slots = ws.sums;
         ws.bwd_near = (double4 *)ws.sums;
@@ -172,16 +214,16 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
         ws.bwd_src = (double4 *)((char *)ws.sums + o_src);
     }
     if (backward && !ws.adj) {
-        if ((rc = dev_alloc_async(&ws.adj, n, "adjoint charges", s))) return rc;
-        if (precision != FMM_FP64 && (rc = dev_alloc_async((float2 **)&ws.rec2, n, "adjoint charges (FP32)", s))) return rc;
+        if ((rc = dev_alloc_block(&ws.adj, n, "adjoint charges"))) return rc;
+        if (precision != FMM_FP64 && (rc = dev_alloc_block((float2 **)&ws.rec2, n, "adjoint charges (FP32)"))) return rc;
         if (L >= 2) {
             // the far field of the charges q, computed beside that of the charges c
-            if ((rc = dev_alloc_async(&ws.mp2_d, cells_d * p + kCoefPad, "adjoint multipoles", s))) return rc;
-            if ((rc = dev_alloc_async(&ws.lo2_d, cells_d * p + kCoefPad, "adjoint locals", s))) return rc;
+            if ((rc = dev_alloc_block(&ws.mp2_d, cells_d * p + kCoefPad, "adjoint multipoles"))) return rc;
+            if ((rc = dev_alloc_block(&ws.lo2_d, cells_d * p + kCoefPad, "adjoint locals"))) return rc;
             HIP_TRY(hipMemsetAsync(ws.mp2_d, 0, (cells_d * p + kCoefPad) * sizeof(double2), s));
             if (cells_f > 0) {
-                if ((rc = dev_alloc_async(&ws.mp2_f, cells_f * p + kCoefPad, "adjoint multipoles", s))) return rc;
-                if ((rc = dev_alloc_async(&ws.lo2_f, cells_f * p + kCoefPad, "adjoint locals", s))) return rc;
+                if ((rc = dev_alloc_block(&ws.mp2_f, cells_f * p + kCoefPad, "adjoint multipoles"))) return rc;
+                if ((rc = dev_alloc_block(&ws.lo2_f, cells_f * p + kCoefPad, "adjoint locals"))) return rc;
                 HIP_TRY(hipMemsetAsync(ws.mp2_f, 0, (cells_f * p + kCoefPad) * sizeof(float2), s));
             }
         }
@@ -221,6 +263,8 @@ int validate_inputs(fmm_tree *t, const double *gamma, const double *dl_duv, hipS
 {
     if (!t->validate) return FMM_OK;
     int64_t bad = -1;
+    if (!t->d_flag)
+        if (int rc = dev_alloc(&t->d_flag, 1, "input check flag")) return rc;
     HIP_TRY(find_nonfinite(gamma, t->n, 1, t->d_flag, s, bad));
     if (bad >= 0) return fail(FMM_EINVAL, "non-finite circulation (particle " + std::to_string(bad) + ")");
     if (dl_duv) {
@@ -343,9 +387,12 @@ int ensure_positions(fmm_tree *t, int precision, hipStream_t s)
 {
     const int d = precision == FMM_FP64;
     if (t->d_pos[d]) return FMM_OK;
-    const int rc = dev_alloc_async((char **)&t->d_pos[d], (size_t)t->n * (d ? sizeof(double2) : sizeof(float2)),
-                                   "leaf-unit coordinates", s);
-    if (rc) return rc;
+    if (!t->pos_buf[d]) {
+        const int rc = dev_alloc_async((char **)&t->pos_buf[d], (size_t)t->n * (d ? sizeof(double2) : sizeof(float2)),
+                                       "leaf-unit coordinates", s);
+        if (rc) return rc;
+    }
+    t->d_pos[d] = t->pos_buf[d];
     launch_leaf_coords(t, d, t->d_pos[d], s);
     return FMM_OK;
 }
@@ -427,7 +474,7 @@ int run_forward(fmm_tree *t, const double *gamma, double sigma, int p, int preci
     Workspace &ws = noalloc ? local : *t->wsp;
     const void *pos = noalloc && local.sums ? local.sums : t->d_pos[precision == FMM_FP64];
 
-    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->own_side;
+    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
     const bool overlap = call_overlaps(t, precision);
     if (!overlap) ss = ms;
     const double alpha = record_alpha(sigma, precision);
@@ -443,20 +490,20 @@ int run_forward(fmm_tree *t, const double *gamma, double sigma, int p, int preci
     tm.mark(0, ms);
     launch_stage_in(t, gamma, ms);
     if (overlap) {  // the far chain needs only the staged circulations: it starts beside pack
-        HIP_TRY(hipEventRecord(t->ev_fork, ms));
-        HIP_TRY(hipStreamWaitEvent(ss, t->ev_fork, 0));
+        HIP_TRY(hipEventRecord(t->aux.fork, ms));
+        HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
     }
     launch_pack(t, is_double, ws.gam, ms);
     tm.mark(1, ms);
     tm.mark(2, ss);
     launch_far_chain(a, ss);
     tm.mark(3, ss);
-    if (overlap) HIP_TRY(hipEventRecord(t->ev_join, ss));
+    if (overlap) HIP_TRY(hipEventRecord(t->aux.join, ss));
     void *slots = use_mutual(t) ? ws.slots : nullptr;
     tm.mark(4, ms);
     launch_p2p_forward(t, pos, ws.gam, is_double, alpha, ws.near, slots, ms);
     tm.mark(5, ms);
-    if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->ev_join, 0));
+    if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
     tm.mark(6, ms);
     launch_finalize(t, a, ws.near, slots, is_double, alpha, uv, uv_near, uv_far, ws.stage, base, h, ms);
     tm.mark(7, ms);
@@ -498,18 +545,14 @@ int new_tree(const double *xy, int64_t n, int depth, const double *root_box, fmm
     return FMM_OK;
 }
 
-// Common end of both builds: the tree's side stream and events, the near-field plan
-// (device) and the near-field work counter.
-int finish_tree(fmm_tree *t, hipStream_t s)
+// Common end of both builds: the tree's side stream and events.
+int finish_tree(fmm_tree *t)
 {
-    hipError_t e = hipStreamCreateWithFlags(&t->own_side, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&t->ev_fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&t->ev_join, hipEventDisableTiming);
-    if (e != hipSuccess) return hip_fail(e, "creating stream/events");
-    std::string err;
-    const int rc = build_near_plan_device(t, s, err);
-    if (rc) return fail(rc, err);
-    return dev_alloc(&t->d_flag, 1, "input check flag");
+    if (!t->aux.stream) {
+        const hipError_t e = side_stream_take(t->device, t->aux);
+        if (e != hipSuccess) return hip_fail(e, "creating stream/events");
+    }
+    return FMM_OK;
 }
 
 }  // namespace
@@ -522,9 +565,11 @@ namespace {
 
 // The device build; the options of `opts` (a tree being replaced) are taken over before
 // the near-field plan is made, since that plan depends on them.  arena: device memory
-// idle during the build that its temporaries may use; after_checks: see build_tree_device.
+// idle during the build that its temporaries may use; after_checks(new tree): see
+// build_tree_device.
 int build_device(const double *xy, int64_t n, int depth, const double *root_box, void *stream, const fmm_tree *opts,
-                 fmm_tree **out, BuildArena *arena = nullptr, const std::function<void()> &after_checks = {})
+                 fmm_tree **out, BuildArena *arena = nullptr,
+                 const std::function<void(fmm_tree *)> &after_checks = {})
 {
     fmm_tree *t = nullptr;
     int rc = new_tree(xy, n, depth, root_box, out, t);
@@ -543,18 +588,23 @@ int build_device(const double *xy, int64_t n, int depth, const double *root_box,
     int64_t bad = -1;
     {
         BuildArenaScope scope(arena);
-        rc = build_tree_device(t, xy, root_box, s, err, bad, after_checks);
-        if (!rc) rc = finish_tree(t, s);
+        rc = build_tree_device(t, xy, root_box, s, err, bad, [&]() {
+            if (after_checks) after_checks(t);
+        });
+        if (!rc) rc = finish_tree(t);
         else {
             if (bad >= 0) err += " (particle " + std::to_string(bad) + ")";
             fail(rc, err);
         }
     }
+    if (!rc) {
+        const hipError_t e = hipDeviceSynchronize();
+        if (e != hipSuccess) rc = hip_fail(e, "hipDeviceSynchronize");
+    }
     if (rc) {
         free_tree(t);
         return rc;
     }
-    if (!arena) trim_pool(t->device);  // the temporaries came from the pool
     *out = t;
     return FMM_OK;
 }
@@ -583,26 +633,23 @@ extern "C" int fmm_rebuild_tree(fmm_tree *prev, const double *xy, int64_t n, con
     // workspace and prev's arrays.
     HIP_TRY(hipDeviceSynchronize());
     // One tree's arrays at a time: the build's temporaries go to the workspace's per-call
-    // region (idle between calls), and prev's arrays are released once the positions have
-    // passed their checks, before the new ones are allocated.
+    // region (idle between calls), and prev's arrays pass to the new tree once the positions
+    // have passed their checks (those of a host build are released there).
     BuildArena arena;
     arena.base = (char *)prev->wsp->sums;
     arena.cap = prev->wsp->sums ? prev->wsp->sums_bytes : 0;
     hipStream_t s = (hipStream_t)stream;
-    auto release_prev = [prev, s]() {
-        release_tree_arrays(prev, s);
+    auto hand_over = [prev, s](fmm_tree *t) {
+        if (prev->pooled) take_over_arrays(t, prev);
+        else release_tree_arrays(prev, s);
         prev->released = true;
     };
     fmm_tree *t = nullptr;
-    int rc = build_device(xy, n, prev->depth, root_box, stream, prev, &t, &arena, release_prev);
+    int rc = build_device(xy, n, prev->depth, root_box, stream, prev, &t, &arena, hand_over);
     if (rc) return rc;
-    hipError_t e = hipDeviceSynchronize();  // the build used the workspace
-    if (e != hipSuccess) {
-        free_tree(t);
-        return hip_fail(e, "hipDeviceSynchronize");
-    }
     std::swap(t->wsp, prev->wsp);
     t->wsp->owner = kForeignOwner;  // cleared by the next call
+    std::swap(t->d_flag, prev->d_flag);
     guard.release();
     free_tree(prev);
     *out = t;
@@ -656,7 +703,9 @@ extern "C" int fmm_build_tree_host(const double *xy, int64_t n, int depth, const
         if (!rc) rc = upload_as(&t->d_units, ht.units, "P2P work units");
         if (!rc) rc = upload(&t->d_tile_start, ht.tile_start, "tile offsets");
         if (!rc) rc = upload_as(&t->d_tile_box, ht.tile_box, "tile boxes");
-        if (!rc) rc = finish_tree(t, s);
+        if (!rc) rc = finish_tree(t);
+        std::string plan_err;
+        if (!rc && (rc = build_near_plan_device(t, s, plan_err))) fail(rc, plan_err);
         if (rc) {
             free_tree(t);
             return rc;
@@ -683,7 +732,7 @@ extern "C" int fmm_share_workspace(fmm_tree *t, fmm_tree *from)
     if (t->wsp == from->wsp) return FMM_OK;
     HIP_TRY(hipSetDevice(t->device));
     HIP_TRY(hipDeviceSynchronize());  // t's earlier calls may still use its workspace
-    if (t->wsp.use_count() == 1) free_workspace(*t->wsp, t->own_side);
+    if (t->wsp.use_count() == 1) free_workspace(*t->wsp);
     t->wsp = from->wsp;
     return FMM_OK;
 }
@@ -787,7 +836,7 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     const void *pos = t->d_pos[precision == FMM_FP64];
 
     hipStream_t ms = (hipStream_t)main_stream;
-    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->own_side;
+    hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
     const bool overlap = call_overlaps(t, precision);
     if (!overlap) ss = ms;
     t->occupancy_in_use = 0;  // the adjoint's near field is not capped
@@ -808,18 +857,18 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     tm.mark(0, ms);
     launch_stage_in(t, gamma, ms);
     if (overlap) {
-        HIP_TRY(hipEventRecord(t->ev_fork, ms));
-        HIP_TRY(hipStreamWaitEvent(ss, t->ev_fork, 0));
+        HIP_TRY(hipEventRecord(t->aux.fork, ms));
+        HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
     }
     tm.mark(2, ss);
     launch_far_chain(fc, ss);
     tm.mark(3, ss);
-    if (overlap) HIP_TRY(hipEventRecord(t->ev_join, ss));
+    if (overlap) HIP_TRY(hipEventRecord(t->aux.join, ss));
     launch_pack(t, is_double, ws.gam, ms);
     launch_pack_adjoint(t, cot, scale, ws.adj, ws.rec2, is_double, ws.stage, ms);  // stage: free until finalize
     tm.mark(1, ms);
     launch_far_chain(fq, ms);
-    if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->ev_join, 0));
+    if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
     tm.mark(4, ms);
     launch_p2p_backward(t, pos, ws.gam, is_double ? (const void *)ws.adj : ws.rec2, is_double, alpha, ws.bwd_near,
                         ws.bwd_b, need_src ? ws.bwd_src : nullptr, ms);
@@ -906,7 +955,7 @@ extern "C" int fmm_set_option(fmm_tree *t, int key, int64_t value)
         if (key == FMM_OPT_NEAR_MUTUAL) t->near_mutual = (int)value;
         else t->dense_leaf = (int)value;
         std::string err;
-        const int rc = build_near_plan_device(t, t->own_side, err);
+        const int rc = build_near_plan_device(t, t->aux.stream, err);
         return rc ? fail(rc, err) : FMM_OK;
     }
     case FMM_OPT_NEAR_OCCUPANCY:
@@ -994,9 +1043,7 @@ extern "C" void fmm_destroy_tree(fmm_tree *t)
     if (!t) return;
     hipSetDevice(t->device);
     hipDeviceSynchronize();
-    const int dev = t->device;
     free_tree(t);
-    trim_pool(dev);
 }
 
 int fmm::fail(int code, const std::string &msg)
@@ -1018,14 +1065,6 @@ void fmm::retain_pool(int device)
     }
     (void)hipGetLastError();
     done.fetch_or(uint64_t(1) << device);
-}
-
-void fmm::trim_pool(int device)
-{
-    hipMemPool_t pool;
-    if (hipDeviceSynchronize() == hipSuccess && hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess)
-        (void)hipMemPoolTrimTo(pool, 0);
-    (void)hipGetLastError();
 }
 
 double fmm::record_alpha(double sigma, int precision)

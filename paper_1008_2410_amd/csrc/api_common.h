@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/fmm2d.h"
+#include "device_cache.h"
 
 namespace fmm {
 
@@ -53,14 +54,19 @@ int dev_alloc_async(T **p, size_t count, const char *what, hipStream_t s)
     return FMM_OK;
 }
 
-// Keep freed blocks of the device's default memory pool for reuse instead of returning
-// them at every synchronisation, so that trees built and destroyed in a loop (time
-// stepping) allocate from the pool.  Once per device.
+// From the library's block cache.
+template <typename T>
+int dev_alloc_block(T **p, size_t count, const char *what)
+{
+    if (block_alloc((void **)p, count * sizeof(T)) == hipSuccess) return FMM_OK;
+    *p = nullptr;
+    return fail(FMM_ENOMEM, std::string("device allocation failed: ") + what);
+}
+
+// Keep freed blocks of the device's default memory pool (the uniform trees' arrays) for
+// reuse instead of returning them at every synchronisation.  Once per device.  (The runtime
+// still returns them once more is free than in use.)
 void retain_pool(int device);
-// Return the pool's unused memory to the device (after a fresh build, whose temporaries
-// are freed, and when a tree is destroyed), so that what the pool holds follows what the
-// library's trees and workspaces hold.  Synchronises the device first.
-void trim_pool(int device);
 
 template <typename T>
 int upload(T **p, const std::vector<T> &h, const char *what)

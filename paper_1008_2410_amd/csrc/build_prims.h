@@ -8,9 +8,11 @@
 #include <algorithm>
 #include <cstdint>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/fmm2d.h"
+#include "device_cache.h"
 
 namespace fmm {
 
@@ -21,7 +23,7 @@ inline unsigned grid_for(int64_t n, int per) { return (unsigned)std::max<int64_t
 // as a stack: a block is taken at the top and the top moves back down when the topmost
 // blocks have been given back.  All of a build's work runs on one stream, so a block
 // given back while kernels that use it are still queued is only reused by kernels queued
-// after them.  Requests that do not fit go to the stream-ordered pool.
+// after them.  Requests that do not fit go to the library's block cache.
 struct BuildArena {
     char *base = nullptr;
     size_t cap = 0;
@@ -45,7 +47,7 @@ struct BuildArena {
     }
 };
 
-// The arena of the build running on this host thread (null: temporaries from the pool).
+// The arena of the build running on this host thread (null: temporaries from the cache).
 inline thread_local BuildArena *t_build_arena = nullptr;
 
 struct BuildArenaScope {
@@ -54,26 +56,83 @@ struct BuildArenaScope {
     ~BuildArenaScope() { t_build_arena = prev; }
 };
 
+// The device memory of a build on stream s (one per build, the outermost counts): blocks
+// its steps give back are taken again by its later steps in stream order, and enter the
+// library's cache at its end, after the stream has been synchronised.
+struct BuildScope;
+inline thread_local BuildScope *t_build_scope = nullptr;
+struct BuildScope {
+    hipStream_t s;
+    BuildScope *prev;
+    std::vector<std::pair<void *, size_t>> freed;
+    explicit BuildScope(hipStream_t stream) : s(stream), prev(t_build_scope)
+    {
+        if (!prev || prev->s != s) t_build_scope = this;
+    }
+    ~BuildScope()
+    {
+        if (t_build_scope != this) return;
+        t_build_scope = prev;
+        (void)hipStreamSynchronize(s);
+        for (auto &f : freed) block_free(f.first);
+    }
+    BuildScope(const BuildScope &) = delete;
+    BuildScope &operator=(const BuildScope &) = delete;
+};
+
+inline hipError_t build_alloc(void **p, size_t bytes, hipStream_t s)
+{
+    if (t_build_scope && t_build_scope->s == s) {
+        auto &f = t_build_scope->freed;
+        size_t best = f.size();
+        for (size_t k = 0; k < f.size(); ++k)
+            if (f[k].second >= bytes && f[k].second / 4 <= bytes && (best == f.size() || f[k].second < f[best].second))
+                best = k;
+        if (best < f.size()) {
+            *p = f[best].first;
+            f.erase(f.begin() + (long)best);
+            return hipSuccess;
+        }
+    }
+    return block_alloc(p, bytes);
+}
+inline void build_free(void *p, size_t bytes, hipStream_t s)
+{
+    if (!p) return;
+    if (t_build_scope && t_build_scope->s == s) {
+        t_build_scope->freed.emplace_back(p, bytes);
+        return;
+    }
+    (void)hipStreamSynchronize(s);
+    block_free(p);
+}
+
 // Device buffer owned for the duration of a build step.
 template <typename T>
 struct Buf {
-    // stream-ordered: allocated and freed in the order of the build's stream, so a
-    // temporary can be released while kernels that use it are still queued
+    // given back in the order of the build's stream, so a temporary can be released while
+    // kernels that use it are still queued
     T *p = nullptr;
+    size_t bytes = 0;
     hipStream_t s = nullptr;
     BuildArena *arena = nullptr;  // the block came from this arena
+    bool kept = false;
+    Buf() = default;
+    Buf(const Buf &) = delete;
+    Buf &operator=(const Buf &) = delete;
     ~Buf()
     {
         if (!p) return;
         if (arena) arena->give(p);
-        else (void)hipFreeAsync(p, s);
+        else build_free(p, bytes, s);
     }
-    // kept: the buffer outlives the build (handed to the tree by release()), so it never
-    // comes from the arena
-    hipError_t alloc(int64_t count, hipStream_t stream, bool kept = false)
+    // keep: the buffer outlives the build (handed to the tree by release(), which gives it
+    // back with block_free), so it never comes from the arena
+    hipError_t alloc(int64_t count, hipStream_t stream, bool keep = false)
     {
         s = stream;
-        const size_t bytes = (size_t)std::max<int64_t>(count, 1) * sizeof(T);
+        kept = keep;
+        bytes = (size_t)std::max<int64_t>(count, 1) * sizeof(T);
         if (!kept && t_build_arena) {
             if (void *q = t_build_arena->take(bytes)) {
                 p = (T *)q;
@@ -81,14 +140,22 @@ struct Buf {
                 return hipSuccess;
             }
         }
-        return hipMallocAsync((void **)&p, bytes, stream);
+        return build_alloc((void **)&p, bytes, stream);
     }
-    // hands the buffer over (allocated with kept = true)
+    // hands the buffer over (allocated with keep = true)
     T *release()
     {
         T *q = p;
         p = nullptr;
         return q;
+    }
+    void swap(Buf &o)
+    {
+        std::swap(p, o.p);
+        std::swap(bytes, o.bytes);
+        std::swap(s, o.s);
+        std::swap(arena, o.arena);
+        std::swap(kept, o.kept);
     }
 };
 
@@ -110,16 +177,26 @@ struct Status {
 // *total_host receives the sum (after a synchronisation of s) if non-null.
 bool scan_exclusive(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total_host, hipStream_t s, Status &st);
 
-// Stable LSD sort of (keys, vals) in place by the low `bits` bits of the keys, 8-bit digits.
-bool radix_sort(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t s, Status &st);
+// Stable LSD sort of (keys, vals) by the low `bits` bits of the keys, 8-bit digits; the
+// result is in keys and vals (whose buffers may be swapped with the sort's own).
+bool radix_sort(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st);
+
+// Order key of a work entry of a near-field list by its estimated cost, heaviest first, in
+// 8 bits: the cost's binary exponent and its next two bits (within 25%, which is what an
+// order of dispatch needs).  One sort pass instead of four or five over the whole number.
+__host__ __device__ inline uint64_t cost_order(uint64_t cost)
+{
+    const int msb = 63 - __builtin_clzll(cost | 1);
+    const int e = msb > 2 ? msb - 2 : 0;  // cost >> e < 8
+    return 255 - (4 * (uint64_t)e + (cost >> e));
+}
 
 // Staging slots of the two-pass permutations for the sorted order perm (sorted slot ->
-// user index, device): bucket shift, gpos1 (user index -> staging slot), gpos2 (sorted
-// slot -> staging slot of its user index) and a staging array st1 of n doubles, the three
-// from the stream-ordered pool.  Buckets of 2^shift sorted slots, ordered by user index
+// user index, device): gpos1 (user index -> staging slot) and gpos2 (sorted slot -> staging
+// slot of its user index).  Buckets of 2^shift sorted slots, ordered by user index
 // inside a bucket.
-bool build_staging(const int *perm, int64_t n, hipStream_t s, Status &st, int &shift, int *&gpos1, int *&gpos2,
-                   double *&st1);
+int stage_shift_of(int64_t n);
+bool build_staging(const int *perm, int64_t n, hipStream_t s, Status &st, int shift, int *gpos1, int *gpos2);
 
 // Root cell when none is given: {x0, y0, side} = (min x, min y, max(range x, range y) (1 + 2^-20)),
 // side 1 for a single point; nonfinite when any coordinate is not finite.  Synchronises s.

@@ -12,6 +12,7 @@
 #include <string>
 #include <vector>
 
+#include "device_cache.h"
 #include "host_tree.h"
 #include "morton.h"
 
@@ -124,7 +125,10 @@ struct fmm_tree {
     std::vector<int64_t> list_len;
     std::vector<int64_t> class_off; // per level l: 4 entries, start of each parity class inside the level list
 
-    // device tree arrays
+    // device tree arrays; of the device build those of fixed size are parts of `slab`
+    char *slab = nullptr;
+    int64_t cap_lists = 0, cap_units = 0, cap_tile_box = 0, cap_near_work = 0;  // elements they have room for
+    void *pos_buf[2] = {nullptr, nullptr};  // memory of d_pos
     int *d_perm = nullptr;        // sorted slot -> user index
     // Two-pass permutation of the circulations into sorted order through a staging array
     // cut into buckets of 2^stage_shift consecutive sorted slots (at most kStageBuckets):
@@ -150,8 +154,7 @@ struct fmm_tree {
     // double2 [1], each made on the first evaluation in that precision
     void *d_pos[2] = {nullptr, nullptr};
 
-    hipStream_t own_side = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    fmm::SideStream aux;  // side stream and events, from the library's cache
 
     const fmm::Tables *tabs = nullptr;  // shared, never freed by the tree
     // evaluation workspace, shared by the trees of fmm_share_workspace (freed with the last)
@@ -193,7 +196,7 @@ struct FarArgs {
 // Stages 1-3 on the device (tree_build.hip); the near-field plan from the device leaf
 // offsets (used by both builds).  FMM_* status; err / bad_index describe a failure.
 // after_checks (if set) runs once the positions have passed their checks (inside the
-// root cell, finite), before the sorted arrays are allocated: a rebuild releases the old
+// root cell, finite), before the sorted arrays are made: a rebuild takes over the old
 // tree's arrays there.
 int build_tree_device(fmm_tree *t, const double *xy, const double *root_box, hipStream_t s, std::string &err,
                       int64_t &bad_index, const std::function<void()> &after_checks = {});

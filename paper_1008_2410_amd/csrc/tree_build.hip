@@ -22,8 +22,8 @@ namespace {
 
 // ---------------------------------------------------------------------------------
 // Device-wide exclusive scan of uint32 (totals below 2^32).  Tiles of 2048: each
-// thread scans 8 consecutive elements, the block scans the thread totals; tile sums
-// are scanned by a single workgroup and added back.  In place is allowed.
+// thread scans 8 consecutive elements, the block scans the thread totals; the tile sums
+// before a tile are added up by its workgroup.  In place is allowed.
 // ---------------------------------------------------------------------------------
 constexpr int kScanTile = 2048;
 
@@ -63,33 +63,37 @@ __global__ __launch_bounds__(256) void scan_tile_sums(const uint32_t *__restrict
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// One workgroup: exclusive scan of the tile sums in place, grand total to *total.
-__global__ __launch_bounds__(256) void scan_sums(uint32_t *__restrict__ sums, int64_t nb, uint32_t *__restrict__ total)
-{
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < nb; base += kScanTile) {
-        const int64_t b = base + (int64_t)threadIdx.x * 8;
-        uint32_t v[8], s = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            v[e] = b + e < nb ? sums[b + e] : 0u;
-            s += v[e];
-        }
-        uint32_t tot;
-        uint32_t run = carry + block_exclusive_sum(s, tot);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (b + e < nb) {
-                sums[b + e] = run;
-                run += v[e];
-            }
-        carry += tot;
-    }
-    if (threadIdx.x == 0) *total = carry;
-}
+// Each workgroup adds up the sums of the tiles before its own (at most kScanSelf of them,
+// so reading them costs less than a launch of its own for their scan).
+constexpr int kScanSelf = 8192;
 
 __global__ __launch_bounds__(256) void scan_tiles(const uint32_t *in, uint32_t *out, int64_t n,
-                                                   const uint32_t *__restrict__ sums)
+                                                   const uint32_t *__restrict__ sums, uint32_t *__restrict__ total)
+{
+    uint32_t before = 0, part = 0;
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += 256) part += sums[k];
+    block_exclusive_sum(part, before);
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * 8;
+    uint32_t v[8], s = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        v[e] = base + e < n ? in[base + e] : 0u;
+        s += v[e];
+    }
+    uint32_t tot;
+    uint32_t run = before + block_exclusive_sum(s, tot);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (base + e < n) {
+            out[base + e] = run;
+            run += v[e];
+        }
+    if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = before + tot;
+}
+
+// As scan_tiles with the exclusive sums before each tile already made.
+__global__ __launch_bounds__(256) void scan_add(const uint32_t *in, uint32_t *out, int64_t n,
+                                                 const uint32_t *__restrict__ sums, uint32_t *__restrict__ total)
 {
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * 8;
     uint32_t v[8], s = 0;
@@ -106,6 +110,33 @@ __global__ __launch_bounds__(256) void scan_tiles(const uint32_t *in, uint32_t *
             out[base + e] = run;
             run += v[e];
         }
+    if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = sums[blockIdx.x] + tot;
+}
+
+// Short arrays in one workgroup, tile after tile.
+__global__ __launch_bounds__(256) void scan_short(const uint32_t *in, uint32_t *out, int64_t n,
+                                                   uint32_t *__restrict__ total)
+{
+    uint32_t carry = 0;
+    for (int64_t t0 = 0; t0 < n; t0 += kScanTile) {
+        const int64_t base = t0 + (int64_t)threadIdx.x * 8;
+        uint32_t v[8], s = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[e] = base + e < n ? in[base + e] : 0u;
+            s += v[e];
+        }
+        uint32_t tot;
+        uint32_t run = carry + block_exclusive_sum(s, tot);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (base + e < n) {
+                out[base + e] = run;
+                run += v[e];
+            }
+        carry += tot;
+    }
+    if (total && threadIdx.x == 0) *total = carry;
 }
 
 // ---------------------------------------------------------------------------------
@@ -178,9 +209,30 @@ __global__ __launch_bounds__(256) void rs_scatter(const uint64_t *__restrict__ k
 // ---------------------------------------------------------------------------------
 // Tree kernels
 // ---------------------------------------------------------------------------------
-// Per-block min/max of the coordinates; flags bit 1: a non-finite coordinate.
+// What a uniform build reports to the host, read back twice: after the keys (the checks
+// and the root cell) and after the counts (the sizes of the lists).
+struct BuildFacts {
+    int flags;                    // k_minmax, k_keys
+    unsigned long long first_bad;
+    double x0, y0, side;
+    uint32_t ntiles, nlist, nwork;
+    uint32_t class_off[4 * (kMaxDepth + 1)];
+    unsigned long long plan[3];   // target-centric units, mutual items, mutual pairs
+    unsigned long long stats[4];  // near pairs (with the particle itself), non-empty leaves, largest, M2L pairs
+};
+
+__global__ void k_facts(BuildFacts *f, double x0, double y0, double side)
+{
+    *f = BuildFacts{};
+    f->first_bad = ~0ull;
+    f->x0 = x0;
+    f->y0 = y0;
+    f->side = side;
+}
+
+// Per-block min/max of the coordinates; flags bit 2: a non-finite coordinate.
 __global__ __launch_bounds__(256) void k_minmax(const double2 *__restrict__ xy, int64_t n, double4 *__restrict__ part,
-                                                 int *__restrict__ flags)
+                                                 int *__restrict__ flags, int nonfinite_bit)
 {
     double xmin = INFINITY, xmax = -INFINITY, ymin = INFINITY, ymax = -INFINITY;
     bool bad = false;
@@ -195,7 +247,7 @@ __global__ __launch_bounds__(256) void k_minmax(const double2 *__restrict__ xy, 
         ymin = fmin(ymin, z.y);
         ymax = fmax(ymax, z.y);
     }
-    if (bad) atomicOr(flags, 2);
+    if (bad) atomicOr(flags, nonfinite_bit);
     for (int o = 32; o > 0; o >>= 1) {
         xmin = fmin(xmin, __shfl_xor(xmin, o));
         xmax = fmax(xmax, __shfl_xor(xmax, o));
@@ -217,16 +269,46 @@ __global__ __launch_bounds__(256) void k_minmax(const double2 *__restrict__ xy, 
     }
 }
 
+// The bounding square from the block results: {x0, y0, side} = (min x, min y, largest range
+// (1 + 2^-20)), side 1 for a single point.
+__global__ __launch_bounds__(256) void k_root(const double4 *__restrict__ part, int nb, BuildFacts *__restrict__ f)
+{
+    __shared__ double4 w[256];
+    double4 r = part[min((int)threadIdx.x, nb - 1)];
+    for (int k = threadIdx.x + 256; k < nb; k += 256) {
+        r.x = fmin(r.x, part[k].x);
+        r.y = fmax(r.y, part[k].y);
+        r.z = fmin(r.z, part[k].z);
+        r.w = fmax(r.w, part[k].w);
+    }
+    w[threadIdx.x] = r;
+    __syncthreads();
+    if (threadIdx.x) return;
+    for (int k = 1; k < 256; ++k) {
+        r.x = fmin(r.x, w[k].x);
+        r.y = fmax(r.y, w[k].y);
+        r.z = fmin(r.z, w[k].z);
+        r.w = fmax(r.w, w[k].w);
+    }
+    double side = fmax(r.y - r.x, r.w - r.z);
+    if (!(side > 0.0)) side = 1.0;
+    f->x0 = r.x;
+    f->y0 = r.z;
+    f->side = side * (1.0 + 1.0 / 1048576.0);
+}
+
 // Leaf (floor binning, clamped at the top edge) and sub-leaf key (64 x 64 grid over the
 // leaf), as in the host build.  key = leaf Morton << 12 | sub-leaf Morton, value = index.
-// flags bit 0: outside the root cell, bit 1: non-finite; *first_bad: lowest such index.
-__global__ __launch_bounds__(256) void k_keys(const double2 *__restrict__ xy, int64_t n, double x0, double y0,
-                                               double w, int nside, uint64_t *__restrict__ key,
-                                               uint32_t *__restrict__ val, int *__restrict__ flags,
-                                               unsigned long long *__restrict__ first_bad)
+// flags bit 0: outside the root cell, bit 1: non-finite; first_bad: lowest such index.
+__global__ __launch_bounds__(256) void k_keys(const double2 *__restrict__ xy, int64_t n, int nside,
+                                               uint64_t *__restrict__ key, uint32_t *__restrict__ val,
+                                               BuildFacts *__restrict__ facts)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    const double x0 = facts->x0, y0 = facts->y0, w = facts->side / (double)nside;
+    int *flags = &facts->flags;
+    unsigned long long *first_bad = &facts->first_bad;
     const double2 z = xy[i];
     uint32_t c[2] = {0, 0}, f[2] = {0, 0};
     bool bad = false;
@@ -310,30 +392,38 @@ __global__ __launch_bounds__(256) void k_tile_leaf(const uint32_t *__restrict__ 
 }
 
 // Bounding box of each 64-particle tile in leaf units about the leaf centre, rounded
-// outwards to FP32 (as the host build).
+// outwards to FP32 (as the host build); 16 lanes per tile.
 __global__ __launch_bounds__(256) void k_tile_box(const int *__restrict__ tile_leaf,
                                                    const uint32_t *__restrict__ tile_start,
                                                    const int *__restrict__ ls, const double2 *__restrict__ xys,
                                                    int64_t ntiles, double x0, double y0, double w,
                                                    float4 *__restrict__ box)
 {
-    const int64_t tt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tt >= ntiles) return;
+    const int64_t tt = (int64_t)blockIdx.x * 16 + threadIdx.x / 16;
+    const int g = threadIdx.x % 16;
+    if (tt >= ntiles) return;  // whole groups
     const uint32_t c = (uint32_t)tile_leaf[tt];
     const double cx = x0 + (morton_x(c) + 0.5) * w;
     const double cy = y0 + (morton_y(c) + 0.5) * w;
     const int b = ls[c] + 64 * (int)(tt - tile_start[c]);
     const int e = min(b + 64, ls[c + 1]);
     double xmin = 1e300, ymin = 1e300, xmax = -1e300, ymax = -1e300;
-    for (int k = b; k < e; ++k) {
+    for (int k = b + g; k < e; k += 16) {
         const double xl = (xys[k].x - cx) / w, yl = (xys[k].y - cy) / w;
         xmin = fmin(xmin, xl);
         xmax = fmax(xmax, xl);
         ymin = fmin(ymin, yl);
         ymax = fmax(ymax, yl);
     }
-    box[tt] = make_float4(nextafterf((float)xmin, -INFINITY), nextafterf((float)ymin, -INFINITY),
-                          nextafterf((float)xmax, INFINITY), nextafterf((float)ymax, INFINITY));
+    for (int o = 8; o >= 1; o >>= 1) {
+        xmin = fmin(xmin, __shfl_xor(xmin, o));
+        xmax = fmax(xmax, __shfl_xor(xmax, o));
+        ymin = fmin(ymin, __shfl_xor(ymin, o));
+        ymax = fmax(ymax, __shfl_xor(ymax, o));
+    }
+    if (g == 0)
+        box[tt] = make_float4(nextafterf((float)xmin, -INFINITY), nextafterf((float)ymin, -INFINITY),
+                              nextafterf((float)xmax, INFINITY), nextafterf((float)ymax, INFINITY));
 }
 
 // Cell lists of levels 2..L grouped by parity class: index k runs over the levels in
@@ -355,7 +445,11 @@ __global__ __launch_bounds__(256) void k_list_flags(const int *__restrict__ coun
                                                      uint32_t *__restrict__ flag)
 {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nflags) return;
+    if (k > nflags) return;
+    if (k == nflags) {  // the scan leaves the total there
+        flag[k] = 0u;
+        return;
+    }
     int l;
     int64_t c;
     list_cell(k, l, c);
@@ -373,11 +467,29 @@ __global__ __launch_bounds__(256) void k_list_scatter(const int *__restrict__ co
     if (counts[level_base(l) + c] > 0) lists[pos[k]] = (int)c;
 }
 
-__global__ void k_gather_u32(const uint32_t *__restrict__ src, const int64_t *__restrict__ idx, int m,
-                              uint32_t *__restrict__ dst)
+// The sizes the host allocates by, from the scanned counts: tiles, cells in the lists (and
+// where each class of each level begins), near-field work entries.
+__global__ void k_sizes(const uint32_t *__restrict__ tile_start, const uint32_t *__restrict__ pos,
+                        const uint32_t *__restrict__ nent, int64_t nleaf, int L, BuildFacts *__restrict__ f)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < m) dst[k] = src[idx[k]];
+    const int k = threadIdx.x;
+    if (k == 0) {
+        f->ntiles = tile_start[nleaf];
+        f->nlist = L >= 2 ? pos[level_base(L + 1) - level_base(2)] : 0u;
+        f->nwork = nent ? nent[nleaf] : 0u;
+    }
+    if (k >= 8 && k < 4 * (L + 1)) {
+        const int l = k / 4, q = k % 4;
+        const int64_t quarter = int64_t(1) << (2 * l - 2);
+        f->class_off[k] = pos[level_base(l) - level_base(2) + q * quarter];
+    }
+}
+
+// The sum of v over the wavefront, added to *dst by one lane.
+__device__ __forceinline__ void wave_add(unsigned long long *dst, unsigned long long v)
+{
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, v);
 }
 
 __device__ inline int leaf_count(const int *__restrict__ ls, int nside, int x, int y)
@@ -396,16 +508,19 @@ __global__ __launch_bounds__(256) void k_leaf_stats(const int *__restrict__ ls, 
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int nside = 1 << L;
-    if (c >= (int64_t(1) << (2 * L))) return;
-    const int nt = ls[c + 1] - ls[c];
-    if (nt == 0) return;
-    const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
+    const int nt = c < (int64_t(1) << (2 * L)) ? ls[c + 1] - ls[c] : 0;
     int64_t nsrc = 0;
-    for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) nsrc += leaf_count(ls, nside, x + dx, y + dy);
-    atomicAdd(&stats[0], (unsigned long long)((int64_t)nt * nsrc));
-    atomicAdd(&stats[1], 1ull);
-    atomicMax(&stats[2], (unsigned long long)nt);
+    if (nt > 0) {
+        const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
+        for (int dy = -1; dy <= 1; ++dy)
+            for (int dx = -1; dx <= 1; ++dx) nsrc += leaf_count(ls, nside, x + dx, y + dy);
+    }
+    wave_add(&stats[0], (unsigned long long)((int64_t)nt * nsrc));
+    wave_add(&stats[1], nt > 0 ? 1ull : 0ull);
+    int most = nt;
+    for (int o = 32; o >= 1; o >>= 1) most = max(most, __shfl_xor(most, o));
+    if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(&stats[2], (unsigned long long)most);
+    if (nt == 0) return;
     uint32_t tt = tile_start[c];
     for (int c0 = 0; c0 < nt; c0 += 64, ++tt) {
         const int cnt = min(64, nt - c0);
@@ -413,31 +528,35 @@ __global__ __launch_bounds__(256) void k_leaf_stats(const int *__restrict__ ls, 
         while ((1 << logtp) < cnt) ++logtp;
         const int kstride = 64 >> logtp;
         units[tt] = make_int4((int)c, ls[c] + c0, cnt, logtp);
-        const uint64_t cost = (uint64_t)((nsrc + kstride - 1) / kstride);
-        ukey[tt] = 0xffffffffull - min(cost, 0xffffffffull);  // heaviest first
+        ukey[tt] = cost_order((uint64_t)((nsrc + kstride - 1) / kstride));  // heaviest first
         uval[tt] = tt;
     }
 }
 
-// Non-empty (target, source) cell pairs of the interaction lists at one level.
-__global__ __launch_bounds__(256) void k_m2l_count(const int *__restrict__ lst, int64_t len, int l,
+// Non-empty (target, source) cell pairs of the interaction lists, all levels: a thread per
+// list entry.
+__global__ __launch_bounds__(256) void k_m2l_count(const int *__restrict__ lists, int64_t nlist, int L,
+                                                    const BuildFacts *__restrict__ facts,
                                                     const int *__restrict__ counts,
                                                     unsigned long long *__restrict__ stats)
 {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= len) return;
-    const int n1 = 1 << l;
-    const int tx = (int)morton_x((uint32_t)lst[k]), ty = (int)morton_y((uint32_t)lst[k]);
-    const int qx = tx & 1, qy = ty & 1;
     unsigned long long m = 0;
-    for (int dy = -2 - qy; dy <= 3 - qy; ++dy)
-        for (int dx = -2 - qx; dx <= 3 - qx; ++dx) {
-            if (abs(dx) <= 1 && abs(dy) <= 1) continue;
-            const int sx = tx + dx, sy = ty + dy;
-            if (sx < 0 || sy < 0 || sx >= n1 || sy >= n1) continue;
-            if (counts[level_base(l) + morton_encode((uint32_t)sx, (uint32_t)sy)] > 0) ++m;
-        }
-    if (m) atomicAdd(&stats[3], m);
+    if (k < nlist) {
+        int l = 2;
+        while (l < L && k >= (int64_t)facts->class_off[4 * (l + 1)]) ++l;
+        const int n1 = 1 << l;
+        const int tx = (int)morton_x((uint32_t)lists[k]), ty = (int)morton_y((uint32_t)lists[k]);
+        const int qx = tx & 1, qy = ty & 1;
+        for (int dy = -2 - qy; dy <= 3 - qy; ++dy)
+            for (int dx = -2 - qx; dx <= 3 - qx; ++dx) {
+                if (abs(dx) <= 1 && abs(dy) <= 1) continue;
+                const int sx = tx + dx, sy = ty + dy;
+                if (sx < 0 || sy < 0 || sx >= n1 || sy >= n1) continue;
+                if (counts[level_base(l) + morton_encode((uint32_t)sx, (uint32_t)sy)] > 0) ++m;
+            }
+    }
+    wave_add(&stats[3], m);
 }
 
 template <typename T>
@@ -496,51 +615,42 @@ __global__ __launch_bounds__(256) void k_plan_count(const int *__restrict__ ls, 
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nleaf = int64_t(1) << (2 * L);
-    if (c > nleaf) return;
-    if (c == nleaf) {
-        nentries[c] = 0;
-        return;
-    }
     const int nside = 1 << L;
-    const int nt = ls[c + 1] - ls[c];
-    if (nt == 0) {
-        nentries[c] = 0;
-        mask[c] = 0;
-        return;
-    }
-    const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
-    const bool dense = nt >= D;
-    int64_t nsrc = 0;
-    uint32_t m = 0;
-    for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-            const int ns = leaf_count(ls, nside, x + dx, y + dy);
-            if (ns == 0) continue;
-            if (dense && ns >= D) m |= 1u << (3 * (dy + 1) + (dx + 1));
-            else nsrc += ns;
+    const int nt = c < nleaf ? ls[c + 1] - ls[c] : 0;
+    uint32_t units = 0, items = 0, m = 0;
+    int64_t pairs = 0;
+    if (nt > 0) {
+        const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
+        const bool dense = nt >= D;
+        int64_t nsrc = 0;
+        for (int dy = -1; dy <= 1; ++dy)
+            for (int dx = -1; dx <= 1; ++dx) {
+                const int ns = leaf_count(ls, nside, x + dx, y + dy);
+                if (ns == 0) continue;
+                if (dense && ns >= D) m |= 1u << (3 * (dy + 1) + (dx + 1));
+                else nsrc += ns;
+            }
+        if (nsrc > 0) {
+            m |= 1u << 9;
+            units = (uint32_t)((nt + 63) / 64);
         }
-    uint32_t cnt = 0;
-    if (nsrc > 0) {
-        m |= 1u << 9;
-        cnt += (uint32_t)((nt + 63) / 64);
-        atomicAdd(&stats[0], (unsigned long long)((nt + 63) / 64));
-    }
-    mask[c] = (uint16_t)m;
-    if (dense) {
-        int64_t pairs = (int64_t)nt * (nt - 1);
-        uint32_t items = 1;
-        for (int k = 0; k < 4; ++k) {
-            const int nr = leaf_count(ls, nside, x + kUp[k][0], y + kUp[k][1]);
-            if (nr >= D) {
-                ++items;
-                pairs += 2 * (int64_t)nt * nr;
+        if (dense) {
+            pairs = (int64_t)nt * (nt - 1);
+            items = 1;
+            for (int k = 0; k < 4; ++k) {
+                const int nr = leaf_count(ls, nside, x + kUp[k][0], y + kUp[k][1]);
+                if (nr >= D) {
+                    ++items;
+                    pairs += 2 * (int64_t)nt * nr;
+                }
             }
         }
-        cnt += items;
-        atomicAdd(&stats[1], (unsigned long long)items);
-        atomicAdd(&stats[2], (unsigned long long)pairs);
     }
-    nentries[c] = cnt;
+    wave_add(&stats[0], units);
+    wave_add(&stats[1], items);
+    wave_add(&stats[2], (unsigned long long)pairs);
+    if (c <= nleaf) nentries[c] = units + items;
+    if (c < nleaf) mask[c] = (uint16_t)m;
 }
 
 __global__ __launch_bounds__(256) void k_plan_fill(const int *__restrict__ ls, int L, int D,
@@ -562,10 +672,9 @@ __global__ __launch_bounds__(256) void k_plan_fill(const int *__restrict__ ls, i
             if (!(dense && ns >= D)) nsrc += ns;
         }
     uint32_t o = off[c];
-    const uint64_t kMax = (1ull << 40) - 1;
     auto put = [&](int4 e, int64_t cost) {
         work[o] = e;
-        key[o] = kMax - min((uint64_t)cost, kMax);  // heaviest first
+        key[o] = cost_order((uint64_t)cost);  // heaviest first
         val[o] = o;
         ++o;
     };
@@ -595,16 +704,90 @@ __global__ __launch_bounds__(256) void k_plan_fill(const int *__restrict__ ls, i
 
 }  // namespace
 
+namespace {
+
+// A tree array of at least `count` elements from the stream-ordered pool: the one it has
+// (taken over from the tree being rebuilt) when that is large enough, else a new one with
+// an eighth to spare for the next positions.
+template <typename T> hipError_t pool_array(T *&p, int64_t &cap, int64_t count, hipStream_t s)
+{
+    if (p && cap >= count) return hipSuccess;
+    if (p) (void)hipFreeAsync((void *)p, s);
+    p = nullptr;
+    cap = std::max<int64_t>(count + count / 8, 64);
+    const hipError_t e = hipMallocAsync((void **)&p, (size_t)cap * sizeof(T), s);
+    if (e != hipSuccess) {
+        p = nullptr;
+        cap = 0;
+        (void)hipGetLastError();
+    }
+    return e;
+}
+
+// The arrays whose sizes n and the depth fix, in one block of the pool (kept from the tree
+// being rebuilt, whose n and depth are the same).
+hipError_t alloc_slab(fmm_tree *t, hipStream_t s)
+{
+    if (t->slab) return hipSuccess;
+    const size_t n = (size_t)t->n, nleaf = size_t(1) << (2 * t->depth);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    const size_t xy = take(n * sizeof(double2)), st1 = take(n * sizeof(double)), perm = take(n * sizeof(int)),
+                 g1 = take(n * sizeof(int)), g2 = take(n * sizeof(int)), lo = take(n * sizeof(int)),
+                 ls = take((nleaf + 1) * sizeof(int)), ts = take((nleaf + 1) * sizeof(int)),
+                 co = take((size_t)level_base(t->depth + 1) * sizeof(int)), ma = take(nleaf * sizeof(uint16_t));
+    const hipError_t e = hipMallocAsync((void **)&t->slab, off, s);
+    if (e != hipSuccess) {
+        t->slab = nullptr;
+        (void)hipGetLastError();
+        return e;
+    }
+    char *b = t->slab;
+    t->d_xy = (double2 *)(b + xy);
+    t->d_st1 = (double *)(b + st1);
+    t->d_perm = (int *)(b + perm);
+    t->d_gpos1 = (int *)(b + g1);
+    t->d_gpos2 = (int *)(b + g2);
+    t->d_leaf_of = (int *)(b + lo);
+    t->d_leaf_start = (int *)(b + ls);
+    t->d_tile_start = (int *)(b + ts);
+    t->d_counts = (int *)(b + co);
+    t->d_leaf_mask = (uint16_t *)(b + ma);
+    return hipSuccess;
+}
+
+// Exclusive scan on stream s; *total (device, may be null) receives the sum.
+bool scan_on(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, hipStream_t s, Status &st)
+{
+    const int64_t nb = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
+    if (nb <= 8) {
+        scan_short<<<1, 256, 0, s>>>(in, out, n, total);
+        return st.check(hipGetLastError(), "scan launch");
+    }
+    Buf<uint32_t> sums;
+    if (!st.check(sums.alloc(nb, s), "scan workspace")) return false;
+    scan_tile_sums<<<(unsigned)nb, 256, 0, s>>>(in, n, sums.p);
+    if (nb > kScanSelf) {  // the sums' own scan first; every tile then reads only its own
+        if (!scan_on(sums.p, sums.p, nb, nullptr, s, st)) return false;
+        scan_add<<<(unsigned)nb, 256, 0, s>>>(in, out, n, sums.p, total);
+    } else {
+        scan_tiles<<<(unsigned)nb, 256, 0, s>>>(in, out, n, sums.p, total);
+    }
+    return st.check(hipGetLastError(), "scan launch");
+}
+
+}  // namespace
+
 // Exclusive scan of n uint32 (in place allowed); *total_host receives the sum if non-null.
 bool scan_exclusive(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total_host, hipStream_t s, Status &st)
 {
-    const int64_t nb = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
-    Buf<uint32_t> sums, total;
-    if (!st.check(sums.alloc(nb, s), "scan workspace") || !st.check(total.alloc(1, s), "scan workspace")) return false;
-    scan_tile_sums<<<(unsigned)nb, 256, 0, s>>>(in, n, sums.p);
-    scan_sums<<<1, 256, 0, s>>>(sums.p, nb, total.p);
-    scan_tiles<<<(unsigned)nb, 256, 0, s>>>(in, out, n, sums.p);
-    if (!st.check(hipGetLastError(), "scan launch")) return false;
+    Buf<uint32_t> total;
+    if (total_host && !st.check(total.alloc(1, s), "scan workspace")) return false;
+    if (!scan_on(in, out, n, total.p, s, st)) return false;
     if (total_host) {
         if (!st.check(hipMemcpyAsync(total_host, total.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "scan total") ||
             !st.check(hipStreamSynchronize(s), "scan total"))
@@ -613,34 +796,26 @@ bool scan_exclusive(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tota
     return true;
 }
 
-// Sort (keys, vals) in place by the low `bits` bits of the keys (stable).
-bool radix_sort(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t s, Status &st)
+// Stable sort of (keys, vals) by the low `bits` bits of the keys.
+bool radix_sort(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st)
 {
     if (n <= 1 || bits <= 0) return true;
     const int nb = (int)((n + kRsTile - 1) / kRsTile);
     Buf<uint64_t> k2;
     Buf<uint32_t> v2, counts;
-    if (!st.check(k2.alloc(n, s), "sort workspace") || !st.check(v2.alloc(n, s), "sort workspace") ||
+    if (!st.check(k2.alloc(n, s, keys.kept), "sort workspace") || !st.check(v2.alloc(n, s, vals.kept), "sort workspace") ||
         !st.check(counts.alloc((int64_t)256 * nb, s), "sort workspace"))
         return false;
-    uint64_t *ka = keys, *kb = k2.p;
-    uint32_t *va = vals, *vb = v2.p;
     for (int shift = 0; shift < bits; shift += 8) {
-        rs_hist<<<nb, 256, 0, s>>>(ka, n, shift, counts.p, nb);
-        if (!scan_exclusive(counts.p, counts.p, (int64_t)256 * nb, nullptr, s, st)) return false;
-        rs_scatter<<<nb, 256, 0, s>>>(ka, va, kb, vb, n, shift, counts.p, nb);
+        rs_hist<<<nb, 256, 0, s>>>(keys.p, n, shift, counts.p, nb);
+        if (!scan_on(counts.p, counts.p, (int64_t)256 * nb, nullptr, s, st)) return false;
+        rs_scatter<<<nb, 256, 0, s>>>(keys.p, vals.p, k2.p, v2.p, n, shift, counts.p, nb);
         if (!st.check(hipGetLastError(), "sort launch")) return false;
-        std::swap(ka, kb);
-        std::swap(va, vb);
-    }
-    if (ka != keys) {
-        if (!st.check(hipMemcpyAsync(keys, ka, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s), "sort copy") ||
-            !st.check(hipMemcpyAsync(vals, va, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s), "sort copy"))
-            return false;
+        keys.swap(k2);
+        vals.swap(v2);
     }
     return true;
 }
-
 
 bool bounding_square(const double2 *xy, int64_t n, hipStream_t s, Status &st, double box[3], bool &nonfinite)
 {
@@ -652,7 +827,7 @@ bool bounding_square(const double2 *xy, int64_t n, hipStream_t s, Status &st, do
     if (!st.check(part.alloc(nb, s), "bounding square") || !st.check(flags.alloc(1, s), "bounding square") ||
         !st.check(hipMemsetAsync(flags.p, 0, sizeof(int), s), "bounding square"))
         return false;
-    k_minmax<<<nb, 256, 0, s>>>(xy, n, part.p, flags.p);
+    k_minmax<<<nb, 256, 0, s>>>(xy, n, part.p, flags.p, 2);
     if (!st.check(hipMemcpyAsync(h.data(), part.p, nb * sizeof(double4), hipMemcpyDeviceToHost, s), "bounding square") ||
         !st.check(hipMemcpyAsync(&hf, flags.p, sizeof(int), hipMemcpyDeviceToHost, s), "bounding square") ||
         !st.check(hipStreamSynchronize(s), "bounding square"))
@@ -685,76 +860,84 @@ bool bounding_square(const double2 *xy, int64_t n, hipStream_t s, Status &st, do
 // near-field sum.  With the mutual form off the plan is empty and the target-centric
 // units cover every pair.
 // ---------------------------------------------------------------------------------
+namespace {
+
+// The plan's counts: entries per leaf (scanned into offsets, nleaf + 1), the leaf masks, and
+// plan[0..2] (device, zeroed): target-centric units, mutual items, mutual pairs.
+bool plan_count(fmm_tree *t, Buf<uint32_t> &nent, unsigned long long *plan, hipStream_t s, Status &st)
+{
+    const int64_t nleaf = int64_t(1) << (2 * t->depth);
+    if (!st.check(nent.alloc(nleaf + 1, s), "near-field plan")) return false;
+    k_plan_count<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, nent.p,
+                                                           t->d_leaf_mask, plan);
+    return scan_on(nent.p, nent.p, nleaf + 1, nullptr, s, st);
+}
+
+// The work list of `total` entries, heaviest first.
+bool plan_fill(fmm_tree *t, const Buf<uint32_t> &nent, uint32_t total, hipStream_t s, Status &st)
+{
+    const int64_t nleaf = int64_t(1) << (2 * t->depth);
+    Buf<int4> work;
+    Buf<uint64_t> key;
+    Buf<uint32_t> val;
+    if (!st.check(pool_array(t->d_near_work, t->cap_near_work, total, s), "near-field plan") ||
+        !st.check(work.alloc(total, s), "near-field plan") || !st.check(key.alloc(total, s), "near-field plan") ||
+        !st.check(val.alloc(total, s), "near-field plan"))
+        return false;
+    k_plan_fill<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, nent.p, work.p, key.p,
+                                                      val.p);
+    if (!st.check(hipGetLastError(), "near-field plan") || !radix_sort(key, val, total, 8, s, st)) return false;
+    k_gather<int4><<<grid_for(total, 256), 256, 0, s>>>(work.p, val.p, total, t->d_near_work);
+    t->nnear_work = total;
+    return st.check(hipGetLastError(), "near-field plan");
+}
+
+void plan_facts(fmm_tree *t, const unsigned long long *plan)
+{
+    t->nunits_tc = (int64_t)plan[0];
+    t->nmut = (int64_t)plan[1];
+    t->mutual_pairs = (int64_t)plan[2];
+}
+
+}  // namespace
+
 int build_near_plan_device(fmm_tree *t, hipStream_t s, std::string &err)
 {
-    if (t->d_near_work || t->d_leaf_mask) {  // a rebuild (option change): the old plan may be in use
-        const hipError_t e = hipDeviceSynchronize();
-        if (e != hipSuccess) {
-            err = std::string("near-field plan: ") + hipGetErrorString(e);
-            return FMM_EDEVICE;
-        }
-        if (t->d_near_work) hipFreeAsync(t->d_near_work, s);
-        if (t->d_leaf_mask) hipFreeAsync(t->d_leaf_mask, s);
-    }
-    t->d_near_work = nullptr;
-    t->d_leaf_mask = nullptr;
     t->nunits_tc = t->nmut = t->nnear_work = t->mutual_pairs = 0;
     if (!t->near_mutual) return FMM_OK;
     Status st;
-    const int L = t->depth;
-    const int64_t nleaf = int64_t(1) << (2 * L);
+    auto failed = [&]() {
+        err = st.msg;
+        return st.code;
+    };
+    // (an option change: the old plan may be in use)
+    if (!st.check(hipDeviceSynchronize(), "near-field plan")) return failed();
+    BuildScope scope(s);
+    const int64_t nleaf = int64_t(1) << (2 * t->depth);
     Buf<uint32_t> nent;
-    Buf<uint16_t> mask;
-    Buf<unsigned long long> stats;
-    if (!st.check(nent.alloc(nleaf + 1, s), "near-field plan") || !st.check(mask.alloc(nleaf, s, true), "near-field plan") ||
-        !st.check(stats.alloc(4, s), "near-field plan") ||
-        !st.check(hipMemsetAsync(stats.p, 0, 4 * sizeof(unsigned long long), s), "near-field plan")) {
-        err = st.msg;
-        return st.code;
-    }
-    k_plan_count<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_start, L, t->dense_leaf, nent.p, mask.p, stats.p);
+    Buf<unsigned long long> plan;
+    if ((!t->d_leaf_mask &&
+         !st.check(hipMallocAsync((void **)&t->d_leaf_mask, nleaf * sizeof(uint16_t), s), "near-field plan")) ||
+        !st.check(plan.alloc(3, s), "near-field plan") ||
+        !st.check(hipMemsetAsync(plan.p, 0, 3 * sizeof(unsigned long long), s), "near-field plan") ||
+        !plan_count(t, nent, plan.p, s, st))
+        return failed();
+    unsigned long long hs[3];
     uint32_t total = 0;
-    if (!scan_exclusive(nent.p, nent.p, nleaf + 1, &total, s, st)) {
-        err = st.msg;
-        return st.code;
-    }
-    unsigned long long hs[4];
-    if (!st.check(hipMemcpyAsync(hs, stats.p, sizeof hs, hipMemcpyDeviceToHost, s), "near-field plan") ||
-        !st.check(hipStreamSynchronize(s), "near-field plan")) {
-        err = st.msg;
-        return st.code;
-    }
-    Buf<int4> work, sorted;
-    Buf<uint64_t> key;
-    Buf<uint32_t> val;
-    if (!st.check(work.alloc(total, s), "near-field plan") || !st.check(sorted.alloc(total, s, true), "near-field plan") ||
-        !st.check(key.alloc(total, s), "near-field plan") || !st.check(val.alloc(total, s), "near-field plan")) {
-        err = st.msg;
-        return st.code;
-    }
-    k_plan_fill<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, L, t->dense_leaf, nent.p, work.p, key.p, val.p);
-    if (!st.check(hipGetLastError(), "near-field plan") || !radix_sort(key.p, val.p, total, 40, s, st)) {
-        err = st.msg;
-        return st.code;
-    }
-    k_gather<int4><<<grid_for(total, 256), 256, 0, s>>>(work.p, val.p, total, sorted.p);
-    if (!st.check(hipStreamSynchronize(s), "near-field plan")) {
-        err = st.msg;
-        return st.code;
-    }
-    t->d_near_work = total ? sorted.release() : nullptr;
-    t->d_leaf_mask = mask.release();
-    t->nunits_tc = (int64_t)hs[0];
-    t->nmut = (int64_t)hs[1];
-    t->mutual_pairs = (int64_t)hs[2];
-    t->nnear_work = total;
+    if (!st.check(hipMemcpyAsync(hs, plan.p, sizeof hs, hipMemcpyDeviceToHost, s), "near-field plan") ||
+        !st.check(hipMemcpyAsync(&total, nent.p + nleaf, sizeof total, hipMemcpyDeviceToHost, s), "near-field plan") ||
+        !st.check(hipStreamSynchronize(s), "near-field plan"))
+        return failed();
+    if (!plan_fill(t, nent, total, s, st) || !st.check(hipStreamSynchronize(s), "near-field plan")) return failed();
+    plan_facts(t, hs);
     return FMM_OK;
 }
 
 // ---------------------------------------------------------------------------------
 // Stages 1-3 on the device.  xy: device (n, 2) user order.  On success every device
 // array of the tree and its host-side counts are set; bad_index receives the first
-// offending particle for FMM_EINVAL / FMM_ERANGE.
+// offending particle for FMM_EINVAL / FMM_ERANGE.  The host waits three times: for the
+// checks, for the sizes of the lists, and at the end.
 // ---------------------------------------------------------------------------------
 int build_tree_device(fmm_tree *t, const double *xy, const double *root_box, hipStream_t s, std::string &err,
                       int64_t &bad_index, const std::function<void()> &after_checks)
@@ -771,170 +954,129 @@ int build_tree_device(fmm_tree *t, const double *xy, const double *root_box, hip
     const int64_t nleaf = int64_t(1) << (2 * L);
     const double2 *xy2 = (const double2 *)xy;
     bad_index = -1;
-    Buf<int> flags;
-    Buf<unsigned long long> first_bad;
-    if (!st.check(flags.alloc(1, s), "tree build") || !st.check(first_bad.alloc(1, s), "tree build") ||
-        !st.check(hipMemsetAsync(flags.p, 0, sizeof(int), s), "tree build") ||
-        !st.check(hipMemsetAsync(first_bad.p, 0xff, sizeof(unsigned long long), s), "tree build"))
-        return failed();
-    // Stage 1: root cell.
-    if (root_box) {
-        t->x0 = root_box[0];
-        t->y0 = root_box[1];
-        t->side = root_box[2];
-    } else {
-        double box[3];
-        bool nonfinite = false;
-        if (!bounding_square(xy2, n, s, st, box, nonfinite)) return failed();
-        if (nonfinite) {
-            err = "non-finite particle position";
-            return FMM_EINVAL;
-        }
-        t->x0 = box[0];
-        t->y0 = box[1];
-        t->side = box[2];
+    BuildScope scope(s);
+    Buf<BuildFacts> facts;
+    BuildFacts h;
+    if (!st.check(facts.alloc(1, s), "tree build")) return failed();
+    auto read_facts = [&]() {
+        return st.check(hipMemcpyAsync(&h, facts.p, sizeof h, hipMemcpyDeviceToHost, s), "tree build") &&
+               st.check(hipStreamSynchronize(s), "tree build");
+    };
+    // Stage 1: root cell (given, or the bounding square).
+    constexpr int kBoxNonfinite = 4;
+    k_facts<<<1, 1, 0, s>>>(facts.p, root_box ? root_box[0] : 0.0, root_box ? root_box[1] : 0.0,
+                            root_box ? root_box[2] : 1.0);
+    if (!root_box) {
+        const int nb = (int)std::min<int64_t>(1024, (n + 255) / 256);
+        Buf<double4> part;
+        if (!st.check(part.alloc(nb, s), "bounding square")) return failed();
+        k_minmax<<<nb, 256, 0, s>>>(xy2, n, part.p, &facts.p->flags, kBoxNonfinite);
+        k_root<<<1, 256, 0, s>>>(part.p, nb, facts.p);
     }
-    const double w = t->side / (double)nside;
     // Stage 2: keys, then the stable sort by (leaf, sub-leaf key), ties by user index.
     Buf<uint64_t> key;
     Buf<uint32_t> val;
     if (!st.check(key.alloc(n, s), "tree build") || !st.check(val.alloc(n, s), "tree build")) return failed();
-    k_keys<<<grid_for(n, 256), 256, 0, s>>>(xy2, n, t->x0, t->y0, w, nside, key.p, val.p, flags.p, first_bad.p);
-    {
-        int hf = 0;
-        unsigned long long hb = 0;
-        if (!st.check(hipMemcpyAsync(&hf, flags.p, sizeof(int), hipMemcpyDeviceToHost, s), "tree build") ||
-            !st.check(hipMemcpyAsync(&hb, first_bad.p, sizeof hb, hipMemcpyDeviceToHost, s), "tree build") ||
-            !st.check(hipStreamSynchronize(s), "tree build"))
-            return failed();
-        if (hf) {
-            bad_index = (int64_t)hb;
-            err = (hf & 2) ? "non-finite particle position" : "particle lies outside the root cell";
-            return (hf & 2) ? FMM_EINVAL : FMM_ERANGE;
-        }
+    k_keys<<<grid_for(n, 256), 256, 0, s>>>(xy2, n, nside, key.p, val.p, facts.p);
+    if (!st.check(hipGetLastError(), "tree build") || !read_facts()) return failed();
+    if (h.flags & kBoxNonfinite) {
+        err = "non-finite particle position";
+        return FMM_EINVAL;
     }
+    if (h.flags) {
+        bad_index = (int64_t)h.first_bad;
+        err = (h.flags & 2) ? "non-finite particle position" : "particle lies outside the root cell";
+        return (h.flags & 2) ? FMM_EINVAL : FMM_ERANGE;
+    }
+    t->x0 = h.x0;
+    t->y0 = h.y0;
+    t->side = h.side;
+    const double w = t->side / (double)nside;
     if (after_checks) after_checks();
-    if (!radix_sort(key.p, val.p, n, 2 * L + 12, s, st)) return failed();
-    if (!st.check(hipMallocAsync((void **)&t->d_perm, n * sizeof(int), s), "permutation") ||
-        !st.check(hipMallocAsync((void **)&t->d_leaf_of, n * sizeof(int), s), "leaf ids") ||
-        !st.check(hipMallocAsync((void **)&t->d_xy, n * sizeof(double2), s), "sorted positions") ||
-        !st.check(hipMallocAsync((void **)&t->d_leaf_start, (nleaf + 1) * sizeof(int), s), "leaf offsets"))
-        return failed();
+    if (!st.check(alloc_slab(t, s), "tree arrays")) return failed();
+    if (!radix_sort(key, val, n, 2 * L + 12, s, st)) return failed();
     k_sorted<<<grid_for(n, 256), 256, 0, s>>>(key.p, val.p, xy2, n, t->d_perm, t->d_leaf_of, t->d_xy);
     k_leaf_start<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_of, n, nleaf, t->d_leaf_start);
-    // Occupancy of all levels.
+    // Occupancy of all levels; how many tiles, list cells and near-field entries there are.
     const int64_t ncells = level_base(L + 1);
-    if (!st.check(hipMallocAsync((void **)&t->d_counts, ncells * sizeof(int), s), "cell counts")) return failed();
     k_counts<<<grid_for(ncells, 256), 256, 0, s>>>(t->d_leaf_start, L, ncells, t->d_counts);
-    // Tiles and their boxes.
-    uint32_t ntiles = 0;
-    Buf<uint32_t> tstart;
-    if (!st.check(tstart.alloc(nleaf + 1, s, true), "tile offsets")) return failed();
-    k_leaf_tiles<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_start, nleaf, tstart.p);
-    if (!scan_exclusive(tstart.p, tstart.p, nleaf + 1, &ntiles, s, st)) return failed();
-    Buf<int> tile_leaf;
-    if (!st.check(tile_leaf.alloc(ntiles, s), "tile leaves") ||
-        !st.check(hipMallocAsync((void **)&t->d_tile_box, std::max<size_t>(ntiles, 1) * sizeof(float4), s), "tile boxes"))
-        return failed();
-    k_tile_leaf<<<grid_for(nleaf, 256), 256, 0, s>>>(tstart.p, nleaf, tile_leaf.p);
-    k_tile_box<<<grid_for(ntiles, 256), 256, 0, s>>>(tile_leaf.p, tstart.p, t->d_leaf_start, t->d_xy, ntiles, t->x0,
-                                                      t->y0, w, t->d_tile_box);
-    t->d_tile_start = (int *)tstart.release();
-    // Cell lists of levels 2..L by parity class.
+    uint32_t *tstart = (uint32_t *)t->d_tile_start;
+    k_leaf_tiles<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_start, nleaf, tstart);
+    if (!scan_on(tstart, tstart, nleaf + 1, nullptr, s, st)) return failed();
+    const int64_t nflags = L >= 2 ? level_base(L + 1) - level_base(2) : 0;
+    Buf<uint32_t> pos, nent;
+    if (nflags > 0) {
+        if (!st.check(pos.alloc(nflags + 1, s), "cell lists")) return failed();
+        k_list_flags<<<grid_for(nflags + 1, 256), 256, 0, s>>>(t->d_counts, nflags, pos.p);
+        if (!scan_on(pos.p, pos.p, nflags + 1, nullptr, s, st)) return failed();
+    }
+    t->nunits_tc = t->nmut = t->nnear_work = t->mutual_pairs = 0;
+    if (t->near_mutual && !plan_count(t, nent, facts.p->plan, s, st)) return failed();
+    k_sizes<<<1, 64, 0, s>>>(tstart, pos.p, nent.p, nleaf, L, facts.p);
+    if (!st.check(hipGetLastError(), "tree build") || !read_facts()) return failed();
+    const uint32_t ntiles = h.ntiles;
     t->list_off.assign(L + 1, 0);
     t->list_len.assign(L + 1, 0);
     t->class_off.assign(4 * (L + 1), 0);
-    int64_t nflags = 0;
-    for (int l = 2; l <= L; ++l) nflags += int64_t(1) << (2 * l);
-    uint32_t nlist = 0;
-    if (nflags > 0) {
-        Buf<uint32_t> pos;
-        if (!st.check(pos.alloc(nflags + 1, s), "cell lists")) return failed();
-        k_list_flags<<<grid_for(nflags, 256), 256, 0, s>>>(t->d_counts, nflags, pos.p);
-        if (!scan_exclusive(pos.p, pos.p, nflags, &nlist, s, st)) return failed();
-        if (!st.check(hipMallocAsync((void **)&t->d_lists, std::max<size_t>(nlist, 1) * sizeof(int), s), "cell lists"))
-            return failed();
-        k_list_scatter<<<grid_for(nflags, 256), 256, 0, s>>>(t->d_counts, nflags, pos.p, t->d_lists);
-        // list offsets at the level and class boundaries
-        std::vector<int64_t> idx;
-        int64_t base = 0;
-        for (int l = 2; l <= L; ++l) {
-            const int64_t nc = int64_t(1) << (2 * l);
-            for (int q = 0; q < 4; ++q) idx.push_back(base + q * (nc / 4));
-            base += nc;
-        }
-        Buf<int64_t> didx;
-        Buf<uint32_t> dval;
-        std::vector<uint32_t> hv(idx.size());
-        const int m = (int)idx.size();
-        if (!st.check(didx.alloc(m, s), "cell lists") || !st.check(dval.alloc(m, s), "cell lists") ||
-            !st.check(hipMemcpyAsync(didx.p, idx.data(), m * sizeof(int64_t), hipMemcpyHostToDevice, s), "cell lists"))
-            return failed();
-        k_gather_u32<<<1, 256, 0, s>>>(pos.p, didx.p, m, dval.p);
-        if (!st.check(hipMemcpyAsync(hv.data(), dval.p, m * sizeof(uint32_t), hipMemcpyDeviceToHost, s), "cell lists") ||
-            !st.check(hipStreamSynchronize(s), "cell lists"))
-            return failed();
-        for (int l = 2; l <= L; ++l) {
-            const int64_t off = hv[4 * (l - 2)];
-            t->list_off[l] = off;
-            for (int q = 0; q < 4; ++q) t->class_off[4 * l + q] = (int64_t)hv[4 * (l - 2) + q] - off;
-            t->list_len[l] = (l < L ? (int64_t)hv[4 * (l - 1)] : (int64_t)nlist) - off;
-        }
-    } else if (!st.check(hipMallocAsync((void **)&t->d_lists, sizeof(int), s), "cell lists")) {
-        return failed();
+    for (int l = 2; l <= L; ++l) {
+        const int64_t off = h.class_off[4 * l];
+        t->list_off[l] = off;
+        for (int q = 0; q < 4; ++q) t->class_off[4 * l + q] = (int64_t)h.class_off[4 * l + q] - off;
+        t->list_len[l] = (l < L ? (int64_t)h.class_off[4 * (l + 1)] : (int64_t)h.nlist) - off;
     }
-    // Statistics and the target-centric units, heaviest first.
-    Buf<unsigned long long> stats;
+    // Tiles and their boxes, the cell lists, the target-centric units (heaviest first) and
+    // the statistics, the near-field plan, the staging slots.
+    Buf<int> tile_leaf;
     Buf<int4> units;
     Buf<uint64_t> ukey;
     Buf<uint32_t> uval;
-    if (!st.check(stats.alloc(4, s), "statistics") ||
-        !st.check(hipMemsetAsync(stats.p, 0, 4 * sizeof(unsigned long long), s), "statistics") ||
-        !st.check(units.alloc(ntiles, s), "work units") || !st.check(ukey.alloc(ntiles, s), "work units") ||
-        !st.check(uval.alloc(ntiles, s), "work units"))
+    if (!st.check(pool_array(t->d_tile_box, t->cap_tile_box, ntiles, s), "tile boxes") ||
+        !st.check(pool_array(t->d_lists, t->cap_lists, h.nlist, s), "cell lists") ||
+        !st.check(pool_array(t->d_units, t->cap_units, ntiles, s), "work units") ||
+        !st.check(tile_leaf.alloc(ntiles, s), "tile leaves") || !st.check(units.alloc(ntiles, s), "work units") ||
+        !st.check(ukey.alloc(ntiles, s), "work units") || !st.check(uval.alloc(ntiles, s), "work units"))
         return failed();
-    k_leaf_stats<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, L, (const uint32_t *)t->d_tile_start, stats.p,
-                                                       units.p, ukey.p, uval.p);
-    for (int l = 2; l <= L; ++l)
-        if (t->list_len[l] > 0)
-            k_m2l_count<<<grid_for(t->list_len[l], 256), 256, 0, s>>>(t->d_lists + t->list_off[l], t->list_len[l], l,
-                                                                       t->d_counts, stats.p);
-    if (!radix_sort(ukey.p, uval.p, ntiles, 32, s, st)) return failed();
-    if (!st.check(hipMallocAsync((void **)&t->d_units, std::max<size_t>(ntiles, 1) * sizeof(int4), s), "work units"))
-        return failed();
+    k_tile_leaf<<<grid_for(nleaf, 256), 256, 0, s>>>(tstart, nleaf, tile_leaf.p);
+    k_tile_box<<<grid_for(ntiles, 16), 256, 0, s>>>(tile_leaf.p, tstart, t->d_leaf_start, t->d_xy, ntiles, t->x0,
+                                                     t->y0, w, t->d_tile_box);
+    if (nflags > 0)
+        k_list_scatter<<<grid_for(nflags, 256), 256, 0, s>>>(t->d_counts, nflags, pos.p, t->d_lists);
+    k_leaf_stats<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, L, tstart, facts.p->stats, units.p, ukey.p,
+                                                       uval.p);
+    if (h.nlist > 0)
+        k_m2l_count<<<grid_for(h.nlist, 256), 256, 0, s>>>(t->d_lists, h.nlist, L, facts.p, t->d_counts,
+                                                            facts.p->stats);
+    if (!radix_sort(ukey, uval, ntiles, 8, s, st)) return failed();
     k_gather<int4><<<grid_for(ntiles, 256), 256, 0, s>>>(units.p, uval.p, ntiles, t->d_units);
-    {
-        unsigned long long hs[4];
-        if (!st.check(hipMemcpyAsync(hs, stats.p, sizeof hs, hipMemcpyDeviceToHost, s), "statistics") ||
-            !st.check(hipStreamSynchronize(s), "statistics"))
-            return failed();
-        t->p2p_pairs = (int64_t)hs[0] - n;
-        t->nonempty_leaves = (int64_t)hs[1];
-        t->max_leaf = (int64_t)hs[2];
-        t->m2l_pairs = (int64_t)hs[3];
-    }
     t->nunits = ntiles;
-    // Staging slots of the two-pass permutations between user and sorted order.
-    if (!build_staging(t->d_perm, n, s, st, t->stage_shift, t->d_gpos1, t->d_gpos2, t->d_st1)) return failed();
-    if (!st.check(hipGetLastError(), "tree build") || !st.check(hipStreamSynchronize(s), "tree build"))
-        return failed();
+    if (t->near_mutual && !plan_fill(t, nent, h.nwork, s, st)) return failed();
+    t->stage_shift = stage_shift_of(n);
+    if (!build_staging(t->d_perm, n, s, st, t->stage_shift, t->d_gpos1, t->d_gpos2)) return failed();
+    if (!st.check(hipGetLastError(), "tree build") || !read_facts()) return failed();
+    if (t->near_mutual) plan_facts(t, h.plan);
+    t->p2p_pairs = (int64_t)h.stats[0] - n;
+    t->nonempty_leaves = (int64_t)h.stats[1];
+    t->max_leaf = (int64_t)h.stats[2];
+    t->m2l_pairs = (int64_t)h.stats[3];
     return FMM_OK;
 }
 
-bool build_staging(const int *perm, int64_t n, hipStream_t s, Status &st, int &shift, int *&gpos1, int *&gpos2,
-                   double *&st1)
+int stage_shift_of(int64_t n)
 {
-    shift = kStageShiftMin;
+    int shift = kStageShiftMin;
     while ((((n - 1) >> shift) + 1) > kStageBuckets) ++shift;
+    return shift;
+}
+
+bool build_staging(const int *perm, int64_t n, hipStream_t s, Status &st, int shift, int *gpos1, int *gpos2)
+{
     Buf<uint64_t> key;
     Buf<uint32_t> val;
-    if (!st.check(key.alloc(n, s), "staging slots") || !st.check(val.alloc(n, s), "staging slots") ||
-        !st.check(hipMallocAsync((void **)&gpos1, n * sizeof(int), s), "staging slots") ||
-        !st.check(hipMallocAsync((void **)&gpos2, n * sizeof(int), s), "staging slots") ||
-        !st.check(hipMallocAsync((void **)&st1, n * sizeof(double), s), "staging array"))
-        return false;
+    if (!st.check(key.alloc(n, s), "staging slots") || !st.check(val.alloc(n, s), "staging slots")) return false;
     k_stage_keys<<<grid_for(n, 256), 256, 0, s>>>(perm, n, shift, key.p, val.p);
-    if (!radix_sort(key.p, val.p, n, kStageBucketsLog2, s, st)) return false;
+    int bits = 0;
+    while (((n - 1) >> shift) >> bits) ++bits;  // of the largest bucket number
+    if (!radix_sort(key, val, n, bits, s, st)) return false;
     k_gpos<<<grid_for(n, 256), 256, 0, s>>>(val.p, n, gpos1);
     k_gpos2<<<grid_for(n, 256), 256, 0, s>>>(gpos1, perm, n, gpos2);
     return st.check(hipGetLastError(), "staging slots");
