@@ -22,7 +22,8 @@ namespace {
 void free_ws(AtreeWs &w)
 {
     for (void *p : {w.gam, (void *)w.stage, (void *)w.gamma, (void *)w.near, w.slots, (void *)w.mp, (void *)w.lo,
-                    (void *)w.mp2, (void *)w.lo2, (void *)w.adj, w.qt, (void *)w.pa, (void *)w.pb, (void *)w.psrc})
+                    (void *)w.mp2, (void *)w.lo2, (void *)w.adj, w.qt, (void *)w.pa, (void *)w.pb, (void *)w.psrc, w.phi_slots,
+                    (void *)w.range})
         block_free(p);
     w = AtreeWs{};
 }
@@ -279,6 +280,14 @@ int ensure_ws_backward(fmm_atree *t, bool src)
         }
     }
     if (src && !w.psrc && (rc = dev_alloc_block(&w.psrc, n, "adjoint source-position sums"))) return rc;
+    if (src && !w.range) {  // the pair force; without it the separate sums serve
+        if (block_alloc((void **)&w.range, (kRangeBlocks + 1) * sizeof(double2)) != hipSuccess ||
+            block_alloc(&w.phi_slots, 9 * n * (w.precision == FMM_FP64 ? sizeof(double) : sizeof(float))) != hipSuccess) {
+            block_free(w.range);
+            w.range = nullptr;
+            w.phi_slots = nullptr;
+        }
+    }
     return FMM_OK;
 }
 
@@ -392,17 +401,20 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     hipStream_t ms = (hipStream_t)main_stream;
     hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
     if ((rc = validate_inputs(t, gamma, dl_duv, ms))) return rc;
-    if (t->nbwd_units < 0) {
-        std::string err;
-        if ((rc = build_atree_adjoint_units(t, ms, err))) return fail(rc, err);
-    }
     const Tables *tabs = nullptr;
     if ((rc = ensure_ws(t, p, precision)) || (rc = ensure_ws_backward(t, src)) ||
         (rc = ensure_coords(t, precision, ms)) || (rc = ensure_m2l_plan(t, p, ms, tabs)))
         return rc;
+    // the pair force for dl_dxy without its two parts, as for the uniform tree
+    const AtreeWs &w = *t->wsp;
+    const bool force = out.dxy && !out.dxe && !out.dxs && w.range;
+    if (!force && t->nbwd_units < 0) {
+        std::string err;
+        if ((rc = build_atree_adjoint_units(t, ms, err))) return fail(rc, err);
+    }
     const AtreeCall c{t, p, precision == FMM_FP64, record_alpha(sigma, precision), 0, tabs};
     launch_atree_pack(c, gamma, ms);
-    launch_atree_pack_adjoint(c, dl_duv, scale, ms);
+    launch_atree_pack_adjoint(c, gamma, dl_duv, scale, force, ms);
     // The two far chains run beside each other, then the near field (which holds every
     // wavefront slot, so that far kernels beside it would wait for it to drain).
     HIP_TRY(hipEventRecord(t->aux.fork, ms));
@@ -411,6 +423,21 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     launch_atree_far(c, ms, false);  // the charges c: derivative W' at the particles
     HIP_TRY(hipEventRecord(t->aux.join, ss));
     HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
+    if (force) {
+        ForceNear near;
+        near.near = w.near;
+        near.mask = t->d.mask;
+        near.slots = w.slots;
+        if (out.dg) {
+            near.phi = (double *)w.stage;
+            near.phi_slots = w.phi_slots;
+        }
+        near.qscale = c.is_double ? nullptr : (const double *)(w.range + kRangeBlocks);
+        launch_atree_force(c, near, ms);
+        launch_atree_finalize_force(c, near, out, ms);
+        HIP_TRY(hipGetLastError());
+        return FMM_OK;
+    }
     launch_atree_backward_near(c, src, ms);
     launch_atree_finalize_backward(c, out, ms);
     HIP_TRY(hipGetLastError());

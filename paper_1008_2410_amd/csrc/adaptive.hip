@@ -273,15 +273,16 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 8 : 4) void at_near_kernel(
     double y0, double side, double alpha, double cut, double scale, int dense, int64_t n,
     double2 *__restrict__ near, c2<T> *__restrict__ slots)
 {
-    __shared__ rec_t<T> tile_a[128], tile_b[128];
+    __shared__ NearLds<T, kVelocity> lds;
     const SoaRec<T> rec{pos, gam, (T)alpha};  // records alpha (z - c_leaf), Gamma
     const int4 u = work[blockIdx.x];
     if (u.w & kMutualItem) {
         const double step = alpha * ldexp(side, -(u.w >> 9));
-        mutual_item_src<T, SoaRec<T>>(u, tile_a, tile_b, rec, leaf_start, leaf_tile, tile_box_leaf, (T)step,
-                                      (float)(cut / (step * step)), n, slots);
+        mutual_item<kVelocity>(u, lds, rec,
+                               MutualTree{leaf_start, leaf_tile, tile_box_leaf, (float)(cut / (step * step)), 0.0f},
+                               (T)step, n, slots, (T *)nullptr);
     } else {
-        at_target_unit<T>(u, tile_a, cell, range, u_off, u_idx, tile_start, tile_box, rec, x0, y0, side, alpha, cut,
+        at_target_unit<T>(u, lds.a, cell, range, u_off, u_idx, tile_start, tile_box, rec, x0, y0, side, alpha, cut,
                           scale, dense, near);
     }
 }
@@ -364,14 +365,17 @@ __global__ __launch_bounds__(256) void at_finalize_kernel(int n, const int *__re
 template <typename T>
 __global__ __launch_bounds__(256) void at_pack_adjoint_kernel(int n, int nxcd, const int *__restrict__ gpos2,
                                                                const double2 *__restrict__ dl_st, double scale,
-                                                               double2 *__restrict__ adj, c2<T> *__restrict__ qt)
+                                                               double2 *__restrict__ adj, c2<T> *__restrict__ qt,
+                                                               const double2 *__restrict__ bounds,
+                                                               double *__restrict__ qscale)
 {
+    const double qs = charge_scale(bounds, qscale);
     const int i = xcd_block(nxcd) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double2 d = dl_st[gpos2[i]];  // the cotangent staged by bucket
     const double2 q = make_double2(scale * d.x, scale * d.y);
     adj[i] = q;
-    qt[i] = mk<T>((T)q.x, (T)q.y);
+    qt[i] = mk<T>((T)(qs * q.x), (T)(qs * q.y));
 }
 
 // Adjoint near field of one unit {leaf A, first, count <= 64, log2 TP}: every source leaf
@@ -533,6 +537,86 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void at_bac
                              x0, y0, side, alpha, cut, lambda, out_pa, out_b, out_src);
 }
 
+// The adjoint's near field over the pair force (dl_dxy without its two parts), over the
+// forward's work list: its units, and its mutual items with each pair evaluated once.
+template <typename T, int KIND>
+__global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 3) void at_force_kernel(
+    const int4 *__restrict__ work, const int4 *__restrict__ cell, const int2 *__restrict__ range,
+    const int *__restrict__ u_off, const int *__restrict__ u_idx, const int *__restrict__ tile_start,
+    const double4 *__restrict__ tile_box, const int *__restrict__ leaf_start, const int *__restrict__ leaf_tile,
+    const float4 *__restrict__ tile_box_leaf, const SoaRec<T> rec, double x0, double y0, double side, double alpha,
+    double cut, int dense, int64_t n, double2 *__restrict__ near, double *__restrict__ near_phi,
+    c2<T> *__restrict__ slots, T *__restrict__ phi_slots)
+{
+    constexpr int NS = kSums<KIND>;
+    __shared__ NearLds<T, KIND> lds;
+    const int4 u = work[blockIdx.x];
+    if (u.w & kMutualItem) {
+        const double step = alpha * ldexp(side, -(u.w >> 9));
+        mutual_item<KIND>(u, lds, rec,
+                          MutualTree{leaf_start, leaf_tile, tile_box_leaf, (float)(cut / (step * step)),
+                                     force_series_leaf2(step)},
+                          (T)step, n, slots, phi_slots);
+        return;
+    }
+    const int lane = threadIdx.x;
+    const bool skip_dense = (u.w >> 4) != 0;
+    const UnitLanes ul(lane, u.z, u.w & 15);
+    const int i = u.y + min(ul.t, u.z - 1);
+    T tiqy;
+    const rec_t<T> ti = load_rec<KIND>(rec, i, tiqy);
+    const int A = u.x;
+    const int4 cla = cell[A];
+    const double2 ca = cell_centre(x0, y0, side, cla);
+    const double4 tb = tile_box[tile_start[A] + ((u.y - range[A].x) >> 6)];
+    double sum[NS] = {};
+    const int eend = u_off[A + 1];
+    for (int e0 = u_off[A]; e0 < eend; e0 += 64) {
+        // lane k: the k-th source leaf of this group of U(A)
+        int s0 = 0, len = 0;
+        bool far = false;
+        T ox = 0, oy = 0;
+        if (e0 + lane < eend) {
+            const int S = u_idx[e0 + lane];
+            const int4 cls = cell[S];
+            const int2 r = range[S];
+            s0 = r.x;
+            len = skip_dense && cls.x == cla.x && r.y >= dense ? 0 : r.y;  // else in a mutual item
+            const double2 cs = cell_centre(x0, y0, side, cls);
+            ox = (T)(alpha * (cs.x - ca.x));  // moved into the frame of A
+            oy = (T)(alpha * (cs.y - ca.y));
+            if (len > 0 && len <= 64) {  // one tile (a larger leaf takes the general form)
+                const double4 sb = tile_box[tile_start[S]];
+                const double gx = fmax(0.0, fmax(sb.x - tb.z, tb.x - sb.z));
+                const double gy = fmax(0.0, fmax(sb.y - tb.w, tb.y - sb.w));
+                far = (gx * gx + gy * gy) * (alpha * alpha) >= cut;
+            }
+        }
+        auto stage = [&](int e, int j) {
+            const int from = __shfl(s0, e);
+            const T sx = __shfl(ox, e), sy = __shfl(oy, e);
+            stage_source<KIND>(lds.a, lds.qa, rec, j >= 0 ? from + j : -1, sx, sy);
+        };
+        source_batches<64>(far ? 0 : len, stage, [&](int count) {
+            T f[NS] = {};
+            force_batch<T, KIND, 0>(lds.a, lds.qa, count, ul.k, ul.K, ti, tiqy, f);
+            for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
+        });
+        if (__any(far))
+            source_batches<64>(far ? len : 0, stage, [&](int count) {
+                T f[NS] = {};
+                force_batch<T, KIND, 2>(lds.a, lds.qa, count, ul.k, ul.K, ti, tiqy, f);
+                for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
+            });
+    }
+    for (int m = 0; m < NS; ++m) sum[m] = ul.reduce(sum[m]);
+    if (lane < u.z) {
+        const double ka = alpha * alpha * kInv2Pi;
+        near[i] = make_double2(-ka * sum[0], ka * sum[1]);
+        if constexpr (KIND == kForcePhi) near_phi[i] = sum[2];
+    }
+}
+
 // Far field of scaled expansions at z in leaf A and its derivative (FP64):
 //   L2P  (1/w) sum_l b_l xi^l,             derivative (1/w^2) sum_{l>=1} l b_l xi^(l-1);
 //   M2P  (1/w_D) sum_m a_m zeta^-(m+1),     derivative -(1/w_D^2) sum_m (m+1) a_m zeta^-(m+2),
@@ -627,6 +711,35 @@ __global__ __launch_bounds__(256) void at_finalize_backward_kernel(
         sy = -G * (atr - btr);
     }
     store_adjoint(out, o, g, ex, ey, sx, sy);
+}
+
+// Adjoint finalize of the pair force: the near sums combined, the far parts as above.
+template <typename TS>
+__global__ __launch_bounds__(256) void at_finalize_force_kernel(
+    int n, const int *__restrict__ perm, const int *__restrict__ leaf_of, const int4 *__restrict__ cell,
+    const double2 *__restrict__ xy, const int *__restrict__ w_off, const int *__restrict__ w_idx,
+    const double2 *__restrict__ mp, const double2 *__restrict__ lo, const double2 *__restrict__ mp2,
+    const double2 *__restrict__ lo2, int p, double x0, double y0, double side, const ForceNear near,
+    const double2 *__restrict__ adj, const double *__restrict__ gamma, double alpha, AdjointOut out)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    // the per-particle loads first, in flight during the far-field work
+    const int64_t o = perm[i];
+    const int A = leaf_of[i];
+    const int4 c = cell[A];
+    const double2 z = xy[i], q = adj[i];
+    const double G = gamma[i] * kInv2Pi;
+    const int m = near.mask[A];
+    const double uq = near.qscale ? 1.0 / *near.qscale : 1.0;
+    const double2 nr = near_from_slots<TS>(i, n, m, near.near, (const c2<TS> *)near.slots, alpha * alpha * kInv2Pi);
+    double nphi = 0.0;
+    if (out.dg) nphi = alpha * uq * phi_from_slots<TS>(i, n, m, near.phi, (const TS *)near.phi_slots);
+    double2 wv, dw, phi, dphi;
+    far_value_deriv<false, true>(A, c, z, w_off, w_idx, cell, mp, lo, p, x0, y0, side, wv, dw);
+    far_value_deriv<true, true>(A, c, z, w_off, w_idx, cell, mp2, lo2, p, x0, y0, side, phi, dphi);
+    store_adjoint(out, o, -(nphi + phi.y) * kInv2Pi, uq * nr.x + (q.x * dw.x - q.y * dw.y),
+                  uq * nr.y - (q.x * dw.y + q.y * dw.x), -G * dphi.y, -G * dphi.x);
 }
 
 inline unsigned blocks(int64_t work, int per) { return (unsigned)((work + per - 1) / per); }
@@ -788,7 +901,8 @@ void launch_atree_finalize(const AtreeCall &c, double *uv, double *uv_near, doub
     else if (staged) scatter_rows_kernel<<<blocks(n, 256), 256, 0, s>>>(n, t->d.perm, staged, uv, base, h);
 }
 
-void launch_atree_pack_adjoint(const AtreeCall &c, const double *dl_duv, double scale, hipStream_t s)
+void launch_atree_pack_adjoint(const AtreeCall &c, const double *gamma, const double *dl_duv, double scale,
+                               bool force, hipStream_t s)
 {
     const fmm_atree *t = c.t;
     const int n = (int)t->n;
@@ -796,12 +910,15 @@ void launch_atree_pack_adjoint(const AtreeCall &c, const double *dl_duv, double 
     double2 *st = t->wsp->near;
     launch_stage_rows2(n, t->stage_shift, t->d.gpos1, (const double2 *)dl_duv, st, s);
     const unsigned g = xcd_grid(n, 256, kXcds);
+    double2 *bounds = force && !c.is_double ? t->wsp->range : nullptr;
+    if (bounds)
+        adjoint_range_kernel<<<kRangeBlocks, 256, 0, s>>>(n, gamma, (const double2 *)dl_duv, scale, bounds);
     if (c.is_double)
         at_pack_adjoint_kernel<double><<<g, 256, 0, s>>>(n, kXcds, t->d.gpos2, st, scale, t->wsp->adj,
-                                                         (double2 *)t->wsp->qt);
+                                                         (double2 *)t->wsp->qt, nullptr, nullptr);
     else
         at_pack_adjoint_kernel<float><<<g, 256, 0, s>>>(n, kXcds, t->d.gpos2, st, scale, t->wsp->adj,
-                                                        (float2 *)t->wsp->qt);
+                                                        (float2 *)t->wsp->qt, bounds, (double *)(bounds + kRangeBlocks));
 }
 
 void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t s)
@@ -825,6 +942,42 @@ void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t s)
                            t->y0, t->side, c.alpha, cut,
                            0.69314718055994530942f, w.pa, w.pb, src ? w.psrc : nullptr);
     }
+}
+
+namespace {
+
+template <typename T, int KIND> void force_launch(const AtreeCall &c, const ForceNear &near, hipStream_t s)
+{
+    const fmm_atree *t = c.t;
+    const AtreeDev &d = t->d;
+    const double cut = c.is_double ? 39.0 : 27.0;  // as for the forward near field
+    at_force_kernel<T, KIND><<<(unsigned)t->nwork, 64, 0, s>>>(
+        d.work, d.cell, d.range, d.u_off, d.u_idx, d.tile_start, d.tile_box, d.leaf_start, d.leaf_tile,
+        d.tile_box_leaf,
+        SoaRec<T>{(const c2<T> *)t->d_pos[c.is_double], (const T *)t->wsp->gam, (T)c.alpha, (const c2<T> *)t->wsp->qt},
+        t->x0, t->y0, t->side, c.alpha, cut, t->dense_leaf, t->n, near.near, near.phi, (c2<T> *)near.slots,
+        (T *)near.phi_slots);
+}
+
+}  // namespace
+
+void launch_atree_force(const AtreeCall &c, const ForceNear &near, hipStream_t s)
+{
+    if (c.t->nwork == 0) return;
+    auto k = c.is_double ? (near.phi ? force_launch<double, kForcePhi> : force_launch<double, kForce>)
+                         : (near.phi ? force_launch<float, kForcePhi> : force_launch<float, kForce>);
+    k(c, near, s);
+}
+
+void launch_atree_finalize_force(const AtreeCall &c, const ForceNear &near, const AdjointOut &out, hipStream_t s)
+{
+    const fmm_atree *t = c.t;
+    const int n = (int)t->n;
+    const AtreeDev &d = t->d;
+    const AtreeWs &w = *t->wsp;
+    auto k = c.is_double ? at_finalize_force_kernel<double> : at_finalize_force_kernel<float>;
+    k<<<blocks(n, 256), 256, 0, s>>>(n, d.perm, d.leaf_of, d.cell, d.xy, d.w_off, d.w_idx, w.mp, w.lo, w.mp2, w.lo2,
+                                     c.p, t->x0, t->y0, t->side, near, w.adj, w.gamma, c.alpha, out);
 }
 
 void launch_atree_finalize_backward(const AtreeCall &c, const AdjointOut &out, hipStream_t s)

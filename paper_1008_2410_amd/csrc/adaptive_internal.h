@@ -107,6 +107,9 @@ struct AtreeWs {
     void *qt = nullptr;
     double4 *pa = nullptr, *psrc = nullptr;
     double *pb = nullptr;
+    // the pair force: slots of Phi (9 x n in the records' precision), the charges' range
+    void *phi_slots = nullptr;
+    double2 *range = nullptr;
 };
 
 }  // namespace fmm
@@ -169,7 +172,10 @@ void launch_atree_coords(const fmm_atree *t, int is_double, void *pos, hipStream
 // adjoint false: the far field of the charges c (mp, lo); true: of the adjoint charges
 // q (mp2, lo2)
 void launch_atree_far(const AtreeCall &c, hipStream_t s, bool adjoint = false);
-void launch_atree_pack_adjoint(const AtreeCall &c, const double *dl_duv, double scale, hipStream_t s);
+void launch_atree_pack_adjoint(const AtreeCall &c, const double *gamma, const double *dl_duv, double scale,
+                               bool force, hipStream_t s);
+void launch_atree_force(const AtreeCall &c, const ForceNear &near, hipStream_t s);
+void launch_atree_finalize_force(const AtreeCall &c, const ForceNear &near, const AdjointOut &out, hipStream_t s);
 void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t s);
 void launch_atree_finalize_backward(const AtreeCall &c, const AdjointOut &out, hipStream_t s);
 void launch_atree_near(const AtreeCall &c, hipStream_t s);

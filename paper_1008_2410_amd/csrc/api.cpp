@@ -41,7 +41,7 @@ void free_workspace(Workspace &ws)
 {
     for (void *p : {ws.gam, (void *)ws.stage, (void *)ws.near, (void *)ws.mp_d, (void *)ws.lo_d, (void *)ws.mp_f,
                     (void *)ws.lo_f, (void *)ws.adj, (void *)ws.mp2_d, (void *)ws.lo2_d, (void *)ws.mp2_f,
-                    (void *)ws.lo2_f, (void *)ws.rec2, ws.sums})
+                    (void *)ws.lo2_f, (void *)ws.rec2, ws.sums, ws.phi_slots, (void *)ws.range})
         block_free(p);
     ws = Workspace{};
 }
@@ -135,6 +135,9 @@ void free_tree(fmm_tree *t)
 // The mutual form is used when its plan has items; else the target-centric units alone.
 bool use_mutual(const fmm_tree *t) { return t->near_mutual && t->nmut > 0; }
 
+// Output bytes per particle by which the adjoint's route is chosen (dl_dgamma, and two parts of dl_dxy).
+constexpr int64_t kForceRow = 40;
+
 // Last FP64 level: every level in FP64 precision; in the mixed form the coarse levels, and
 // always levels 2..5, whose few cells cost nothing in FP64 (their passes run in one launch).
 constexpr int kMinSplit = 5;
@@ -226,6 +229,13 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
                 if ((rc = dev_alloc_block(&ws.lo2_f, cells_f * p + kCoefPad, "adjoint locals"))) return rc;
                 HIP_TRY(hipMemsetAsync(ws.mp2_f, 0, (cells_f * p + kCoefPad) * sizeof(float2), s));
             }
+        }
+        // with them what the pair force needs beside the forward's arrays; without it the
+        // separate sums serve
+        if (!outputs_windowed(n, kForceRow)) {
+            for (auto [q, bytes] : {std::pair{(void **)&ws.range, (kRangeBlocks + 1) * sizeof(double2)},
+                                    std::pair{&ws.phi_slots, 9 * n * gam_bytes}})
+                if (block_alloc(q, bytes) != hipSuccess) *q = nullptr;
         }
     }
     if (ws.owner != t->serial) {
@@ -812,6 +822,21 @@ extern "C" int fmm_velocity_parts(fmm_tree *t, const double *gamma, double sigma
 
 namespace {
 
+// The arrays of the pair force: the forward's near-field array and slots, with Phi the staging
+// array and slots of its own, in FP32 the block maxima.  False (the separate sums then serve)
+// if device memory did not hold them.
+bool force_arrays(const fmm_tree *t, const Workspace &ws, bool phi, ForceNear &near)
+{
+    const bool mutual = use_mutual(t);
+    if (!ws.range || (phi && mutual && !ws.phi_slots)) return false;
+    near.near = ws.near;
+    near.mask = mutual ? t->d_leaf_mask : nullptr;
+    near.slots = mutual ? ws.slots : nullptr;
+    near.phi = phi ? (double *)ws.stage : nullptr;  // free between pack and finalize
+    near.phi_slots = phi && mutual ? ws.phi_slots : nullptr;
+    return true;
+}
+
 // The adjoint of stages 4-10 for the cotangent scale * cot (user order), written as `out`
 // says (see AdjointOut).
 int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int precision, const double *cot,
@@ -865,12 +890,35 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     tm.mark(3, ss);
     if (overlap) HIP_TRY(hipEventRecord(t->aux.join, ss));
     launch_pack(t, is_double, ws.gam, ms);
-    launch_pack_adjoint(t, cot, scale, ws.adj, ws.rec2, is_double, ws.stage, ms);  // stage: free until finalize
+    // The pair force gives dl_dxy without its two parts, in half the near field's time.  Where
+    // the outputs outgrow the last-level cache the separate sums stay: there a step's adjoint
+    // has the bits of velocity_backward's parts added up, and callers compare the two.
+    ForceNear near;
+    const bool force = out.dxy && !out.dxe && !out.dxs && !outputs_windowed(t->n, kForceRow) &&
+                       force_arrays(t, ws, out.dg != nullptr, near);
+    double *qscale = nullptr;
+    if (force && !is_double) {
+        launch_adjoint_range(t->n, gamma, cot, scale, ws.range, ms);
+        near.qscale = qscale = (double *)(ws.range + kRangeBlocks);
+    }
+    launch_pack_adjoint(t, cot, scale, ws.adj, ws.rec2, is_double, ws.stage, qscale ? ws.range : nullptr, qscale,
+                        ms);  // stage: free until finalize
     tm.mark(1, ms);
     launch_far_chain(fq, ms);
     if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
     tm.mark(4, ms);
-    launch_p2p_backward(t, pos, ws.gam, is_double ? (const void *)ws.adj : ws.rec2, is_double, alpha, ws.bwd_near,
+    const void *qv = is_double ? (const void *)ws.adj : ws.rec2;
+    if (force) {
+        launch_p2p_force(t, pos, ws.gam, qv, is_double, alpha, near, ms);
+        tm.mark(5, ms);
+        tm.mark(6, ms);
+        launch_finalize_force(t, fc, fq, ws.adj, near, is_double, alpha, out, ms);
+        tm.mark(7, ms);
+        HIP_TRY(hipGetLastError());
+        if (tm.on) t->pending_timing.push_back(tm.ev);
+        return FMM_OK;
+    }
+    launch_p2p_backward(t, pos, ws.gam, qv, is_double, alpha, ws.bwd_near,
                         ws.bwd_b, need_src ? ws.bwd_src : nullptr, ms);
     tm.mark(5, ms);
     tm.mark(6, ms);

@@ -90,6 +90,7 @@ template <typename T> struct SoaRec {
     const c2<T> *__restrict__ pos;
     const T *__restrict__ gam;
     T scale;
+    const c2<T> *__restrict__ q = nullptr;  // adjoint charges (the pair force)
     __device__ __forceinline__ rec_t<T> operator()(int64_t i) const
     {
         const c2<T> p = pos[i];
@@ -101,6 +102,23 @@ template <typename T> struct SoaRec {
         return r;
     }
 };
+
+// What the near field sums for a particle: its velocity, or in the adjoint the force on it
+// (see pair_force), alone or with Phi.  The adjoint's records carry the adjoint charge: its
+// real part as the record's fourth value, its imaginary part qy beside the record.
+enum NearSums { kVelocity = 0, kForce = 1, kForcePhi = 2 };
+template <int KIND> constexpr int kSums = KIND == kForcePhi ? 3 : 2;
+
+template <int KIND, typename T> __device__ __forceinline__ rec_t<T> load_rec(const SoaRec<T> &rec, int64_t i, T &qy)
+{
+    rec_t<T> r = rec(i);
+    if constexpr (KIND != kVelocity) {
+        const c2<T> q = rec.q[i];
+        r.w = q.x;
+        qy = q.y;
+    }
+    return r;
+}
 
 // g(s) = 1 - exp(-|dz|^2/(2 sigma^2)) in the scaled variable s, and 1/s.
 __device__ __forceinline__ float one_minus_exp(float s) { return 1.0f - __builtin_amdgcn_exp2f(-s); }
@@ -197,6 +215,88 @@ __device__ __forceinline__ void p2p_tile_any(const rec_t<T> *tile, int len, int 
 }
 
 // ---------------------------------------------------------------------------------
+// The pair force.  For particles that move as evaluation point and as source at once, what a
+// pair adds to dL/d(x, y) of its two particles is equal and opposite, since the kernel depends
+// on their difference alone.  With dz' = (dx', dy') the scaled difference z_i - z_j, e and g as
+// for the velocity, lambda ln 2 (FP32, whose exponent is base 2) or 1 (FP64),
+//   h = (lambda e - g/s')/s',  wr + i wi = h conj(dz')^2,  v = Gamma_j q_i - Gamma_i q_j,
+//   dL/dx_i += ka sum_j [v_x wi + v_y (wr + lambda e)],
+//   dL/dy_i += ka sum_j [v_x (wr - lambda e) - v_y wi],          ka = alpha^2/(2 pi),
+// the sum of the evaluation part Gamma_j (q_i A, B) and the source part Gamma_i (q_j ..) of the
+// separate sums below.  Two sums per particle in place of seven, and both particles of a pair
+// are served by one evaluation of the weights.  The sums kept are -dL/dx/ka and dL/dy/ka, the
+// signs of the velocity's.  Phi_i = alpha sum_j q_j (g/s') conj(dz') enters by its imaginary
+// part alone.
+//
+// The difference lambda e - g/s' cancels for small s', but |conj(dz')^2/s'| <= 1 puts its
+// error, a rounding of lambda e, beside lambda e itself.  g/s' = r - e r loses 1/s' roundings
+// in FP32 and is taken from its series below series_cut (class 0; class 1: the boxes of the
+// two tiles keep every pair above it; class 2: e rounds to 0 against 1).
+// ---------------------------------------------------------------------------------
+template <typename T> __device__ __forceinline__ constexpr T exponent_base_log();  // lambda
+template <> __device__ __forceinline__ constexpr float exponent_base_log<float>() { return 0.69314718055994530942f; }
+template <> __device__ __forceinline__ constexpr double exponent_base_log<double>() { return 1.0; }
+
+// The natural exponent x = |dz|^2/(2 sigma^2) below which FP32 takes the series
+// g/s' = lambda (1 - x/2 + x^2/6 - x^3/24 + x^4/120): the next term is under a rounding there.
+constexpr float kSeriesX = 0.125f;
+
+template <typename T, int CLS>
+__device__ __forceinline__ void force_weights(T ddx, T ddy, T &gr, T &w, T &a, T &b)
+{
+    constexpr T lam = exponent_base_log<T>();
+    const T dy2 = fma(ddy, ddy, tiny<T>());
+    const T s = fma(ddx, ddx, dy2);
+    const T r = recip(s);
+    if constexpr (CLS == 2) {
+        const T cx = r * ddx, cy = r * ddy;
+        gr = r;
+        a = b = fma(cy, cy, -cx * cx);
+        w = (T)-2 * cx * cy;
+    } else {
+        T e;
+        if constexpr (sizeof(T) == 4) {
+            e = __builtin_amdgcn_exp2f(-s);
+            gr = fma(-e, r, r);
+            if constexpr (CLS == 0) {
+                constexpr float l2 = lam * lam, l3 = l2 * lam;
+                const float series = fma(s, fma(s, fma(s, fma(s, l3 * l2 / 120.0f, -l2 * l2 / 24.0f), l3 / 6.0f), -l2 / 2.0f), lam);
+                gr = s < kSeriesX / lam ? series : gr;
+            }
+        } else {
+            double g;
+            exp_pair(s, e, g);
+            gr = g * r;
+        }
+        const T h = fma(lam, e, -gr) * r;
+        const T wr = h * fma((T)-2, dy2, s);
+        w = (h + h) * (ddx * ddy);
+        a = fma(lam, e, wr);
+        b = fma(-lam, e, wr);
+    }
+}
+
+// Source rj with qjy onto a particle at (tx, ty) with Gamma g and charge (qx, qy).
+template <typename T, int KIND, int CLS>
+__device__ __forceinline__ void force_pair(const rec_t<T> &rj, T qjy, const rec_t<T> &ti, T tiqy, T tx, T ty,
+                                           T (&f)[kSums<KIND>])
+{
+    const T ddx = tx - rj.x;
+    const T ddy = ty - rj.y;
+    T gr, w, a, b;
+    force_weights<T, CLS>(ddx, ddy, gr, w, a, b);
+    const T vx = fma(rj.z, ti.w, -(ti.z * rj.w));
+    const T vy = fma(rj.z, tiqy, -(ti.z * qjy));
+    f[0] = fma(vx, w, f[0]);
+    f[0] = fma(-vy, a, f[0]);
+    f[1] = fma(vx, b, f[1]);
+    f[1] = fma(vy, w, f[1]);
+    if constexpr (KIND == kForcePhi) {
+        f[2] = fma(gr, fma(qjy, ddx, -(rj.w * ddy)), f[2]);
+    }
+}
+
+// ---------------------------------------------------------------------------------
 // Target-centric units over sparse source leaves.  Taken leaf by leaf, a 3x3 neighbourhood
 // of ~16-particle leaves is nine dependent loads and barriers for nine steps of work each
 // (1024^2 lattice, 16 per leaf, FP64: 0.40 ms; its pairs issue in 0.17 ms).  So the unit's
@@ -270,6 +370,45 @@ __device__ __forceinline__ void p2p_batch(const rec_t<T> *tile, int count, int k
     const rec_t<T> *src = tile + k;
 #pragma unroll 4
     for (int it = 0; it < steps; ++it, src += K) p2p_pair<T, FAR>(*src, tx, ty, fu, fv);
+}
+
+template <typename T, int KIND, int CLS>
+__device__ __forceinline__ void force_batch(const rec_t<T> *tile, const T *qtile, int count, int k, int K,
+                                            const rec_t<T> &ti, T tiqy, T (&f)[kSums<KIND>])
+{
+    const int steps = (count + K - 1) / K;
+    const rec_t<T> *src = tile + k;
+    const T *qsrc = qtile + k;
+#pragma unroll 4
+    for (int it = 0; it < steps; ++it, src += K, qsrc += K)
+        force_pair<T, KIND, CLS>(*src, *qsrc, ti, tiqy, ti.x, ti.y, f);
+}
+
+// This lane's source of a batch into LDS, moved by (sx, sy), with a zero record 64 places on;
+// at < 0: none.
+template <int KIND, typename T>
+__device__ __forceinline__ void stage_source(rec_t<T> *tile, T *qtile, const SoaRec<T> &rec, int64_t at, T sx, T sy)
+{
+    const int lane = threadIdx.x;
+    rec_t<T> r, none;
+    r.x = r.y = r.z = r.w = (T)0;
+    none = r;
+    T qy = (T)0;
+    if (at >= 0) {
+        r = load_rec<KIND>(rec, at, qy);
+        r.x += sx;
+        r.y += sy;
+    }
+    tile[lane] = r;
+    tile[64 + lane] = none;
+    qtile[lane] = qy;
+    qtile[64 + lane] = (T)0;
+}
+
+// The squared gap in leaves from which two tiles of FP32 records need no series.
+__host__ __device__ inline float force_series_leaf2(double step)
+{
+    return (float)(2.0 * (0.125 / 0.69314718055994530942) / (step * step));
 }
 
 // Smallest squared distance between two boxes {xmin, ymin, xmax, ymax}, the first
@@ -351,146 +490,249 @@ __device__ __forceinline__ void mutual_chunk(const rec_t<T> *src, T rx, T ry, T 
     cv = row_rot(cv);
 }
 
+// The same for the pair force: qsrc the sources' qy; the source's sums are the negative of the
+// resident's terms.
+template <typename T, int KIND, int CLS>
+__device__ __forceinline__ void force_chunk(const rec_t<T> *src, const T *qsrc, T rx, T ry, T rg, T rqx, T rqy,
+                                            T (&f)[kSums<KIND>], T (&c)[kSums<KIND>])
+{
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const rec_t<T> sj = src[j];
+        const T sqy = qsrc[j];
+        const T ddx = rx - sj.x;
+        const T ddy = ry - sj.y;
+        T gr, w, a, b;
+        force_weights<T, CLS>(ddx, ddy, gr, w, a, b);
+        const T vx = fma(sj.z, rqx, -(rg * sj.w));
+        const T vy = fma(sj.z, rqy, -(rg * sqy));
+        const T fx = fma(vx, w, -(vy * a));
+        const T fy = fma(vx, b, vy * w);
+        T tj = 0;
+        if constexpr (KIND == kForcePhi) {
+            const T cx = gr * ddx, cy = gr * ddy;
+            f[2] = fma(sqy, cx, f[2]);
+            f[2] = fma(-sj.w, cy, f[2]);
+            tj = fma(rqx, cy, -(rqy * cx));
+        }
+        f[0] += fx;
+        f[1] += fy;
+        if (j == 0) {
+            c[0] = -fx;
+            c[1] = -fy;
+            if constexpr (KIND == kForcePhi) c[2] = tj;
+        } else {
+            c[0] = row_rot(c[0]) - fx;
+            c[1] = row_rot(c[1]) - fy;
+            if constexpr (KIND == kForcePhi) c[2] = row_rot(c[2]) + tj;
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < kSums<KIND>; ++m) c[m] = row_rot(c[m]);
+}
+
 // Records of one tile into LDS, each chunk of 16 stored twice in a row (so that the
 // sources of step j are at a constant offset), zero records past the tile's end.
-template <typename T, typename Src>
-__device__ __forceinline__ rec_t<T> stage_doubled(rec_t<T> *dst, const Src &rec, int first, int len)
+template <int KIND, typename T>
+__device__ __forceinline__ rec_t<T> stage_doubled(rec_t<T> *dst, T *qdst, const SoaRec<T> &rec, int first, int len,
+                                                  T &qy)
 {
     const int lane = threadIdx.x;
     rec_t<T> r;
     r.x = r.y = r.z = r.w = (T)0;
-    if (lane < len) r = rec(first + lane);
-    dst[(lane >> 4) * 32 + (lane & 15)] = r;
-    dst[(lane >> 4) * 32 + (lane & 15) + 16] = r;
+    qy = (T)0;
+    if (lane < len) r = load_rec<KIND>(rec, first + lane, qy);
+    const int at = (lane >> 4) * 32 + (lane & 15);
+    dst[at] = r;
+    dst[at + 16] = r;
+    if constexpr (KIND != kVelocity) {
+        qdst[at] = qy;
+        qdst[at + 16] = qy;
+    }
     return r;
 }
+
+// One direction's slots: the first two sums of a particle together, the third by itself.
+template <typename T, int KIND> struct NearSlot {
+    c2<T> *uv;
+    T *phi;
+    __device__ __forceinline__ void load(int64_t i, T (&f)[kSums<KIND>]) const
+    {
+        const c2<T> o = uv[i];
+        f[0] = o.x;
+        f[1] = o.y;
+        if constexpr (KIND == kForcePhi) f[2] = phi[i];
+    }
+    __device__ __forceinline__ void store(int64_t i, const T (&f)[kSums<KIND>]) const
+    {
+        uv[i] = mk<T>(f[0], f[1]);
+        if constexpr (KIND == kForcePhi) phi[i] = f[2];
+    }
+};
+
+// The LDS of a near-field workgroup.
+template <typename T, int KIND> struct NearLds {
+    rec_t<T> a[128], b[128];
+    T qa[128], qb[128];
+};
+template <typename T> struct NearLds<T, kVelocity> {
+    rec_t<T> a[128], b[128];
+    static constexpr T *qa = nullptr, *qb = nullptr;
+};
+
+// What a mutual item reads of the tree, and the squared gaps (in leaves) from which a pair of
+// tiles skips the exponential and the series.
+struct MutualTree {
+    const int *__restrict__ leaf_start;
+    const int *__restrict__ tile_start;
+    const float4 *__restrict__ tile_box;
+    float cut_leaf2, series_leaf2;
+};
 
 // One tile b of S against every tile a of R (a >= b when S = R).  Per block (b, a) the
 // tile with more chunks of 16 sits in the lanes and the other is streamed from LDS, so
 // that fewer steps are spent; either way both sums come out lane-indexed by particle.
-template <typename T, typename Src>
-__device__ __forceinline__ void mutual_resident_tile(const int4 it, rec_t<T> *tile_a, rec_t<T> *tile_b, int b,
-                                                     int tb, const Src &rec,
-                                                     const int *__restrict__ leaf_start,
-                                                     const int *__restrict__ tile_start,
-                                                     const float4 *__restrict__ tile_box, T step, float cut_leaf2,
-                                                     c2<T> *__restrict__ slot_s, c2<T> *__restrict__ slot_r)
+template <int KIND, typename T>
+__device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, KIND> &lds, int b, int tb,
+                                                     const SoaRec<T> &rec, const MutualTree &mt, T step,
+                                                     const NearSlot<T, KIND> &slot_s,
+                                                     const NearSlot<T, KIND> &slot_r)
 {
+    constexpr int NS = kSums<KIND>;
     const int lane = threadIdx.x;
     const uint32_t S = (uint32_t)it.x, R = (uint32_t)it.y;
     const bool self = S == R;
     const int ds = it.z & 15;
     const int dx = ds % 3 - 1, dy = ds / 3 - 1;  // R - S in leaves
     const T ox = (T)dx * step, oy = (T)dy * step;
-    const int s0 = leaf_start[S], s1 = leaf_start[S + 1];
-    const int r1 = leaf_start[R + 1];
+    const int s0 = mt.leaf_start[S], s1 = mt.leaf_start[S + 1];
+    const int r1 = mt.leaf_start[R + 1];
     const int lenb = min(64, s1 - b);
     const int nchb = (lenb + 15) >> 4;
     __syncthreads();
-    const rec_t<T> rb = stage_doubled<T, Src>(tile_b, rec, b, lenb);
+    T qyb;
+    const rec_t<T> rb = stage_doubled<KIND>(lds.b, lds.qb, rec, b, lenb, qyb);
     // tile b in the frame of leaf R (resident form); in the streamed form it stays in
     // the frame of S and tile a is moved there
     const T bx = rb.x - ox, by = rb.y - oy;
     const T bgn = lane < lenb ? -rb.z : (T)0;
-    const float4 bbox = tile_box[tb];
-    T fu = 0, fv = 0;
-    if (self && b > s0 && lane < lenb) {  // what the earlier tiles of S wrote for this tile
-        const c2<T> o = slot_s[b + lane];
-        fu = o.x;
-        fv = o.y;
-    }
+    const float4 bbox = mt.tile_box[tb];
+    T f[NS];
+#pragma unroll
+    for (int m = 0; m < NS; ++m) f[m] = 0;
+    if (self && b > s0 && lane < lenb) slot_s.load(b + lane, f);  // what the earlier tiles of S wrote for this tile
     const bool first_touch = b == s0;  // the first resident tile creates the streamed slots
-    int ta = self ? tb : tile_start[R];
-    for (int a = self ? b : leaf_start[R]; a < r1; a += 64, ++ta) {
+    int ta = self ? tb : mt.tile_start[R];
+    for (int a = self ? b : mt.leaf_start[R]; a < r1; a += 64, ++ta) {
         const int lena = min(64, r1 - a);
         const int ncha = (lena + 15) >> 4;
         const bool diag = self && a == b;
-        const bool far = box_gap2(bbox, (float)-dx, (float)-dy, tile_box[ta]) >= cut_leaf2;
+        const float gap2 = box_gap2(bbox, (float)-dx, (float)-dy, mt.tile_box[ta]);
+        const bool far = gap2 >= mt.cut_leaf2;
         if (diag) {
             // the tile with itself: every ordered pair from the resident end
             __syncthreads();
             for (int c = 0; c < nchb; ++c)
-                if (far) {
+                if constexpr (KIND == kVelocity) {
+                    if (far) {
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) p2p_pair<T, true>(tile_b[c * 32 + j], bx, by, fu, fv);
+                        for (int j = 0; j < 16; ++j) p2p_pair<T, true>(lds.b[c * 32 + j], bx, by, f[0], f[1]);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) p2p_pair<T, false>(lds.b[c * 32 + j], bx, by, f[0], f[1]);
+                    }
                 } else {
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) p2p_pair<T, false>(tile_b[c * 32 + j], bx, by, fu, fv);
+                    if (far) {
+#pragma unroll 2
+                        for (int j = 0; j < 16; ++j)
+                            force_pair<T, KIND, 2>(lds.b[c * 32 + j], lds.qb[c * 32 + j], rb, qyb, bx, by, f);
+                    } else {
+#pragma unroll 4
+                        for (int j = 0; j < 16; ++j)
+                            force_pair<T, KIND, 0>(lds.b[c * 32 + j], lds.qb[c * 32 + j], rb, qyb, bx, by, f);
+                    }
                 }
             continue;
         }
-        c2<T> old;
-        old.x = old.y = (T)0;
-        if (!first_touch && lane < lena) old = slot_r[a + lane];
+        T old[NS];
+#pragma unroll
+        for (int m = 0; m < NS; ++m) old[m] = 0;
+        if (!first_touch && lane < lena) slot_r.load(a + lane, old);
         const bool swap = ncha > nchb;  // tile a in the lanes, tile b streamed
         __syncthreads();
-        const rec_t<T> ra = stage_doubled<T, Src>(tile_a, rec, a, lena);
+        T qya;
+        const rec_t<T> ra = stage_doubled<KIND>(lds.a, lds.qa, rec, a, lena, qya);
         __syncthreads();
-        T px, py, pgn;
+        T px, py, pgn, pqx = 0, pqy = 0;
         const rec_t<T> *src;
+        const T *qsrc = nullptr;
         int nch;
         if (swap) {
             px = ra.x + ox;
             py = ra.y + oy;
             pgn = lane < lena ? -ra.z : (T)0;
-            src = tile_b;
+            src = lds.b;
             nch = nchb;
         } else {
             px = bx;
             py = by;
             pgn = bgn;
-            src = tile_a;
+            src = lds.a;
             nch = ncha;
         }
-        T ru = 0, rv = 0, colu = 0, colv = 0;
+        if constexpr (KIND != kVelocity) {
+            pqx = swap ? ra.w : rb.w;
+            pqy = swap ? qya : qyb;
+            qsrc = swap ? lds.qb : lds.qa;
+        }
+        T r[NS], col[NS];
+#pragma unroll
+        for (int m = 0; m < NS; ++m) r[m] = col[m] = 0;
         for (int c = 0; c < nch; ++c) {
-            T cu, cv;
-            const rec_t<T> *sp = src + c * 32 + (lane & 15);
-            if (far) mutual_chunk<T, true>(sp, px, py, pgn, ru, rv, cu, cv);
-            else mutual_chunk<T, false>(sp, px, py, pgn, ru, rv, cu, cv);
-            cu += __shfl_xor(cu, 16);
-            cv += __shfl_xor(cv, 16);
-            cu += __shfl_xor(cu, 32);
-            cv += __shfl_xor(cv, 32);
+            T cs[NS];
+            const int at = c * 32 + (lane & 15);
+            if constexpr (KIND == kVelocity) {
+                if (far) mutual_chunk<T, true>(src + at, px, py, pgn, r[0], r[1], cs[0], cs[1]);
+                else mutual_chunk<T, false>(src + at, px, py, pgn, r[0], r[1], cs[0], cs[1]);
+            } else {
+                if (far) force_chunk<T, KIND, 2>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, r, cs);
+                else if (sizeof(T) == 8 || gap2 >= mt.series_leaf2)
+                    force_chunk<T, KIND, 1>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, r, cs);
+                else force_chunk<T, KIND, 0>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, r, cs);
+            }
+#pragma unroll
+            for (int m = 0; m < NS; ++m) cs[m] += __shfl_xor(cs[m], 16);
+#pragma unroll
+            for (int m = 0; m < NS; ++m) cs[m] += __shfl_xor(cs[m], 32);
             if ((lane >> 4) == c) {
-                colu = cu;
-                colv = cv;
+#pragma unroll
+                for (int m = 0; m < NS; ++m) col[m] = cs[m];
             }
         }
         // sums of tile b and of tile a, lane-indexed
-        const T bu = swap ? colu : ru, bv = swap ? colv : rv;
-        const T au = swap ? ru : colu, av = swap ? rv : colv;
-        fu += bu;
-        fv += bv;
-        if (lane < lena) {
-            c2<T> nw;
-            nw.x = old.x + au;
-            nw.y = old.y + av;
-            slot_r[a + lane] = nw;
+#pragma unroll
+        for (int m = 0; m < NS; ++m) {
+            f[m] += swap ? col[m] : r[m];
+            old[m] += swap ? r[m] : col[m];
         }
+        if (lane < lena) slot_r.store(a + lane, old);
     }
-    if (lane < lenb) {
-        c2<T> nw;
-        nw.x = fu;
-        nw.y = fv;
-        slot_s[b + lane] = nw;
-    }
+    if (lane < lenb) slot_s.store(b + lane, f);
 }
 
-template <typename T, typename Src>
-__device__ __forceinline__ void mutual_item_src(const int4 it, rec_t<T> *tile_a, rec_t<T> *tile_b, const Src &rec,
-                                                const int *__restrict__ leaf_start,
-                                                const int *__restrict__ tile_start,
-                                                const float4 *__restrict__ tile_box, T step, float cut_leaf2,
-                                                int64_t n, c2<T> *__restrict__ slots)
+// The item's slots: 9 x n pairs of sums in uv, 9 x n third sums in phi.
+template <int KIND, typename T>
+__device__ __forceinline__ void mutual_item(const int4 it, NearLds<T, KIND> &lds, const SoaRec<T> &rec,
+                                            const MutualTree &mt, T step, int64_t n, c2<T> *__restrict__ uv,
+                                            T *__restrict__ phi)
 {
     const uint32_t S = (uint32_t)it.x;
-    c2<T> *slot_s = slots + (int64_t)(it.z & 15) * n;
-    c2<T> *slot_r = slots + (int64_t)(it.z >> 4) * n;
-    const int s0 = leaf_start[S], s1 = leaf_start[S + 1];
-    for (int b = s0, tb = tile_start[S]; b < s1; b += 64, ++tb)
-        mutual_resident_tile<T, Src>(it, tile_a, tile_b, b, tb, rec, leaf_start, tile_start, tile_box, step,
-                                     cut_leaf2, slot_s, slot_r);
+    const int64_t at_s = (int64_t)(it.z & 15) * n, at_r = (int64_t)(it.z >> 4) * n;
+    const NearSlot<T, KIND> slot_s{uv + at_s, KIND == kForcePhi ? phi + at_s : nullptr};
+    const NearSlot<T, KIND> slot_r{uv + at_r, KIND == kForcePhi ? phi + at_r : nullptr};
+    const int s0 = mt.leaf_start[S], s1 = mt.leaf_start[S + 1];
+    for (int b = s0, tb = mt.tile_start[S]; b < s1; b += 64, ++tb)
+        mutual_resident_tile<KIND>(it, lds, b, tb, rec, mt, step, slot_s, slot_r);
 }
 
 
@@ -633,6 +875,66 @@ __device__ __forceinline__ void p2p_bwd_batch(const rec_t<T> *tile, const c2<T> 
         p2p_bwd_pair<T, FAR, SRC>(*src, *qsrc, tx, ty, lambda, acc);
 }
 
+// The pair force multiplies Gamma_j q_i in the records' precision.  So that FP32 neither
+// overflows nor underflows where the separate sums (linear in each) did not, the FP32 charges
+// carry the power of two that brings max|q| max|Gamma| near 1: the maxima of every block here,
+// reduced by every block of the pack kernel, which leaves the factor for the finalize kernel.
+static __global__ __launch_bounds__(256) void adjoint_range_kernel(int64_t n, const double *__restrict__ gamma,
+                                                            const double2 *__restrict__ dl, double scale,
+                                                            double2 *__restrict__ range)
+{
+    double g = 0.0, q = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const double2 d = dl[i];
+        g = fmax(g, fabs(gamma[i]));
+        q = fmax(q, fmax(fabs(scale * d.x), fabs(scale * d.y)));
+    }
+    __shared__ double2 part[4];
+    for (int o = 32; o >= 1; o >>= 1) {
+        g = fmax(g, __shfl_xor(g, o));
+        q = fmax(q, __shfl_xor(q, o));
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_double2(g, q);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 4; ++k) {
+            g = fmax(g, part[k].x);
+            q = fmax(q, part[k].y);
+        }
+        range[blockIdx.x] = make_double2(g, q);
+    }
+}
+
+// The factor, by a whole block of 256 threads; block 0 writes it to qscale.  range NULL: 1.
+__device__ __forceinline__ double charge_scale(const double2 *__restrict__ range, double *__restrict__ qscale)
+{
+    if (!range) return 1.0;
+    __shared__ double2 part[4];
+    double g = 0.0, q = 0.0;
+#pragma unroll
+    for (int k = 0; k < kRangeBlocks / 256; ++k) {
+        const double2 v = range[k * 256 + threadIdx.x];
+        g = fmax(g, v.x);
+        q = fmax(q, v.y);
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        g = fmax(g, __shfl_xor(g, o));
+        q = fmax(q, __shfl_xor(q, o));
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_double2(g, q);
+    __syncthreads();
+    for (int k = 0; k < 4; ++k) {
+        g = fmax(g, part[k].x);
+        q = fmax(q, part[k].y);
+    }
+    // (a zero, infinite or NaN maximum counts as 1; FP32's own range bounds Gamma's exponent)
+    const int eg = g > 0.0 && g < 1e300 ? max(-120, min(120, ilogb(g))) : 0;
+    const int eq = q > 0.0 && q < 1e300 ? ilogb(q) : 0;
+    const double s = ldexp(1.0, -max(-900, min(900, eg + eq)));
+    if (blockIdx.x == 0 && threadIdx.x == 0) *qscale = s;
+    return s;
+}
+
 // ---------------------------------------------------------------------------------
 // Per-particle gathers of the finalize kernels, written so that a wavefront waits for
 // memory a few times rather than once per load.  A load guarded by a lane-dependent
@@ -670,6 +972,25 @@ __device__ __forceinline__ double2 near_from_slots(int64_t i, int64_t n, int m, 
         }
         r.x -= scale * su;
         r.y += scale * sv;
+    }
+    return r;
+}
+
+// The third sum of the adjoint's near field, gathered the same way.
+template <typename TS>
+__device__ __forceinline__ double phi_from_slots(int64_t i, int64_t n, int m, const double *__restrict__ near,
+                                                 const TS *__restrict__ slots)
+{
+    double r = 0.0;
+    if ((m >> 9) & 1) r = near[i];
+    const int set = m & 0x1FF;
+    if (set) {
+        const int64_t lowest = (int64_t)__builtin_ctz(set) * n + i;
+        TS v[9];
+#pragma unroll
+        for (int d = 0; d < 9; ++d) v[d] = slots[(set >> d) & 1 ? (int64_t)d * n + i : lowest];
+#pragma unroll
+        for (int d = 0; d < 9; ++d) r += (set >> d) & 1 ? (double)v[d] : 0.0;
     }
     return r;
 }

@@ -59,6 +59,8 @@ inline bool outputs_windowed(int64_t n, int64_t bytes_per_row)
 {
     return n * bytes_per_row >= kLastLevelCacheBytes;
 }
+// Blocks of the reduction that finds the range of an adjoint's charges.
+constexpr int kRangeBlocks = 1024;
 // Flag (in w) of a mutual item in the near-field work list.
 constexpr int kMutualItem = 256;
 
@@ -93,6 +95,8 @@ struct Workspace {
     void *sums = nullptr;
     size_t sums_bytes = 0;
     void *slots = nullptr;        // = sums
+    void *phi_slots = nullptr;    // the pair force with Phi: 9 x n sums in the near field's precision
+    double2 *range = nullptr;     // kRangeBlocks block maxima of |Gamma| and |q|, then their power of two
 };
 
 }  // namespace fmm
@@ -177,6 +181,18 @@ struct AdjointOut {
     int acc_g = 0, acc_xy = 0;
 };
 
+// The near field of the pair force (dl_dxy without its two parts): the target-centric part and
+// the slots as the forward's (mask NULL: no slots), the same for the sums of Phi when dl_dgamma
+// is asked for (phi not NULL), and the power of two the FP32 charges carry (NULL: none).
+struct ForceNear {
+    double2 *near = nullptr;
+    const uint16_t *mask = nullptr;
+    void *slots = nullptr;
+    double *phi = nullptr;
+    void *phi_slots = nullptr;
+    const double *qscale = nullptr;
+};
+
 // Launch parameters shared by the forward and backward far-field chains.
 struct FarArgs {
     const fmm_tree *t;
@@ -227,8 +243,14 @@ void launch_stage_rows(int64_t n, int shift, const int *gpos1, const double *src
 void launch_stage_rows2(int64_t n, int shift, const int *gpos1, const double2 *src, double2 *st, hipStream_t s);
 void launch_gather_rows(int64_t n, const int *gpos1, const double2 *staged, double *uv, const double *base, double h,
                         hipStream_t s);
+void launch_adjoint_range(int64_t n, const double *gamma, const double *dl_duv, double scale, double2 *range,
+                          hipStream_t s);
 void launch_pack_adjoint(const fmm_tree *t, const double *dl_duv, double scale, double2 *adj, void *qt, int is_double,
-                         double2 *staging, hipStream_t s);
+                         double2 *staging, const double2 *range, double *qscale, hipStream_t s);
+void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double, double alpha,
+                      const ForceNear &near, hipStream_t s);
+void launch_finalize_force(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double2 *adj,
+                           const ForceNear &near, int is_double, double alpha, const AdjointOut &out, hipStream_t s);
 void launch_p2p_backward(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double,
                          double alpha, double4 *out_pa, double *out_b, double4 *out_src, hipStream_t s);
 void launch_finalize_backward(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double4 *near_pa,

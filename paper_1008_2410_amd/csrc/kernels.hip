@@ -278,31 +278,95 @@ __device__ __forceinline__ void p2p_forward_unit(const int4 u, rec_t<T> *tile, c
 // its own outputs, so the result does not depend on which wavefront takes which entry.
 
 template <typename T>
-__device__ __forceinline__ void near_entry(const int4 u, rec_t<T> *tile_a, rec_t<T> *tile_b,
-                                           const SoaRec<T> &rec, const int *__restrict__ leaf_start,
-                                           const int *__restrict__ tile_start, const float4 *__restrict__ tile_box,
-                                           int nside, T step, float cut_leaf2, double scale, int dense, int64_t n,
-                                           double2 *__restrict__ near, c2<T> *__restrict__ slots)
-{
-    if (u.w & kMutualItem)
-        mutual_item_src<T, SoaRec<T>>(u, tile_a, tile_b, rec, leaf_start, tile_start, tile_box, step, cut_leaf2, n,
-                                      slots);
-    else
-        p2p_forward_unit<T>(u, tile_a, rec, leaf_start, tile_start, tile_box, nside, step, cut_leaf2, scale, dense,
-                            near);
-}
-
-template <typename T>
 __global__ __launch_bounds__(64, sizeof(T) == 4 ? 8 : 5) void p2p_near_kernel(
     const int4 *__restrict__ work, const c2<T> *__restrict__ pos, const T *__restrict__ gam,
     const int *__restrict__ leaf_start, const int *__restrict__ tile_start, const float4 *__restrict__ tile_box,
     int nside, T step, float cut_leaf2, double scale, int dense, int64_t n, double2 *__restrict__ near,
     c2<T> *__restrict__ slots)
 {
-    __shared__ rec_t<T> tile_a[128], tile_b[128];
+    __shared__ NearLds<T, kVelocity> lds;
     const SoaRec<T> rec{pos, gam, step};
-    near_entry<T>(work[blockIdx.x], tile_a, tile_b, rec, leaf_start, tile_start, tile_box, nside, step, cut_leaf2,
-                  scale, dense, n, near, slots);
+    const int4 u = work[blockIdx.x];
+    if (u.w & kMutualItem)
+        mutual_item<kVelocity>(u, lds, rec, MutualTree{leaf_start, tile_start, tile_box, cut_leaf2, 0.0f}, step, n,
+                               slots, (T *)nullptr);
+    else
+        p2p_forward_unit<T>(u, lds.a, rec, leaf_start, tile_start, tile_box, nside, step, cut_leaf2, scale, dense,
+                            near);
+}
+
+// The adjoint's target-centric unit over the pair force: the forward's, with every source
+// leaf in the concatenation (a leaf of one tile beyond the cut skips the exponential).
+template <typename T, int KIND>
+__device__ __forceinline__ void p2p_force_unit(const int4 u, rec_t<T> *tile, T *qtile, const SoaRec<T> &rec,
+                                               const MutualTree &mt, int nside, T step, double scale, int dense,
+                                               double2 *__restrict__ near, double *__restrict__ near_phi)
+{
+    constexpr int NS = kSums<KIND>;
+    const int lane = threadIdx.x;
+    const bool skip_dense = (u.w >> 4) != 0;  // pairs with dense leaves go to the mutual form
+    const int ix = (int)morton_x((uint32_t)u.x), iy = (int)morton_y((uint32_t)u.x);
+    // lane d < 9: the range of neighbour leaf d
+    int s0 = 0, len = 0, ddx = 0, ddy = 0;
+    bool far = false;
+    if (lane < 9) {
+        ddx = lane % 3 - 1;
+        ddy = lane / 3 - 1;
+        const int nx = ix + ddx, ny = iy + ddy;
+        if (nx >= 0 && ny >= 0 && nx < nside && ny < nside) {
+            const uint32_t S = morton_encode((uint32_t)nx, (uint32_t)ny);
+            s0 = mt.leaf_start[S];
+            len = mt.leaf_start[S + 1] - s0;
+            if (skip_dense && len >= dense) len = 0;
+            if (mt.cut_leaf2 < 8.0f && len > 0 && len <= 64) {
+                const float4 tbox = mt.tile_box[mt.tile_start[u.x] + ((u.y - mt.leaf_start[u.x]) >> 6)];
+                far = box_gap2(tbox, (float)-ddx, (float)-ddy, mt.tile_box[mt.tile_start[S]]) >= mt.cut_leaf2;
+            }
+        }
+    }
+    const UnitLanes ul(lane, u.z, u.w & 15);
+    const int i = u.y + min(ul.t, u.z - 1);
+    T tiqy;
+    const rec_t<T> ti = load_rec<KIND>(rec, i, tiqy);
+    const T ox = (T)ddx * step, oy = (T)ddy * step;
+    double sum[NS] = {};
+    auto stage = [&](int e, int j) {
+        const int from = __shfl(s0, e);
+        const T sx = __shfl(ox, e), sy = __shfl(oy, e);
+        stage_source<KIND>(tile, qtile, rec, j >= 0 ? from + j : -1, sx, sy);
+    };
+    source_batches<16>(far ? 0 : len, stage, [&](int count) {
+        T f[NS] = {};
+        force_batch<T, KIND, 0>(tile, qtile, count, ul.k, ul.K, ti, tiqy, f);
+        for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
+    });
+    if (__any(far))
+        source_batches<16>(far ? len : 0, stage, [&](int count) {
+            T f[NS] = {};
+            force_batch<T, KIND, 2>(tile, qtile, count, ul.k, ul.K, ti, tiqy, f);
+            for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
+        });
+    for (int m = 0; m < NS; ++m) sum[m] = ul.reduce(sum[m]);
+    if (lane < u.z) {
+        near[i] = make_double2(-scale * sum[0], scale * sum[1]);
+        if constexpr (KIND == kForcePhi) near_phi[i] = sum[2];
+    }
+}
+
+// The near-field grid of the pair force, over the forward's work list.  FP32 issues about 34
+// vector operations per unordered pair (42 with the series, 41 with Phi) against 36 per ordered
+// pair of the separate sums: 2^22 patch particles at depth 9, FP32, 3.6 -> 2.1 ms; 700001 at
+// depth 8 in FP64 with Phi, whose exponential alone is some 25 operations, 1.2 -> 0.74 ms.
+template <typename T, int KIND>
+__global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 3) void p2p_force_kernel(
+    const int4 *__restrict__ work, const SoaRec<T> rec, const MutualTree mt, int nside, T step, double scale,
+    int dense, int64_t n, double2 *__restrict__ near, double *__restrict__ near_phi, c2<T> *__restrict__ slots,
+    T *__restrict__ phi_slots)
+{
+    __shared__ NearLds<T, KIND> lds;
+    const int4 u = work[blockIdx.x];
+    if (u.w & kMutualItem) mutual_item<KIND>(u, lds, rec, mt, step, n, slots, phi_slots);
+    else p2p_force_unit<T, KIND>(u, lds.a, lds.qa, rec, mt, nside, step, scale, dense, near, near_phi);
 }
 
 // Sum over the lanes of a group of each of NC values (NC = 32 or 64) by recursive halving:
@@ -541,14 +605,17 @@ void p2m_launch(const FarArgs &a, hipStream_t s)
 template <typename T>
 __global__ __launch_bounds__(256) void pack_adjoint_kernel(int n, int nxcd, const int *__restrict__ gpos2,
                                                             const double2 *__restrict__ dl_st, double scale,
-                                                            double2 *__restrict__ adj, c2<T> *__restrict__ qt)
+                                                            double2 *__restrict__ adj, c2<T> *__restrict__ qt,
+                                                            const double2 *__restrict__ range,
+                                                            double *__restrict__ qscale)
 {
+    const double qs = charge_scale(range, qscale);
     const int i = xcd_block(nxcd) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double2 d = dl_st[gpos2[i]];
     const double2 q = make_double2(scale * d.x, scale * d.y);
     adj[i] = q;
-    if (qt) qt[i] = mk<T>((T)q.x, (T)q.y);
+    if (qt) qt[i] = mk<T>((T)(qs * q.x), (T)(qs * q.y));
 }
 
 // Adjoint near field of one work unit, organised as the forward P2P (LDS tiles,
@@ -710,6 +777,42 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void p2p_ba
 // Phi'_far = (1/w^2) sum_l l b_l(q) xi^(l-1) the derivative of the q-field's local
 // expansion (the far operator is antisymmetric).  gamma_st[gpos2[i]] is Gamma of
 // sorted particle i (the staged circulations).
+// The far part of a particle's adjoint: Im Phi_far, W'_far and (with need_s) Phi'_far.
+struct AdjointFar {
+    double phi = 0.0, dwr = 0.0, dwi = 0.0, dpr = 0.0, dpi = 0.0;
+};
+template <typename TL>
+__device__ __forceinline__ AdjointFar adjoint_far(uint32_t leaf, int i, const double2 *__restrict__ xy,
+                                                  const c2<TL> *__restrict__ loc_c, const c2<TL> *__restrict__ loc_q,
+                                                  const c2<TL> *__restrict__ pos, int p, double x0, double y0,
+                                                  double w, bool need_phi, bool need_s)
+{
+    AdjointFar f;
+    c2<TL> xi;
+    if (pos) {
+        xi = pos[i];
+    } else {
+        const double cx = x0 + (morton_x(leaf) + 0.5) * w;
+        const double cy = y0 + (morton_y(leaf) + 0.5) * w;
+        const double2 z = xy[i];
+        xi = mk<TL>((TL)((z.x - cx) / w), (TL)((z.y - cy) / w));
+    }
+    const c2<TL> *bq = loc_q + (int64_t)leaf * p;
+    const c2<TL> *bc = loc_c + (int64_t)leaf * p;
+    if (need_phi) f.phi = (double)horner_prefetch<TL>(bq, p, xi).y / w;
+    if (p >= 2) {
+        const c2<TL> accd = horner_weighted_prefetch<TL>(bc, p, xi, 1, 0);
+        f.dwr = (double)accd.x / (w * w);
+        f.dwi = (double)accd.y / (w * w);
+        if (need_s) {
+            const c2<TL> accp = horner_weighted_prefetch<TL>(bq, p, xi, 1, 0);
+            f.dpr = (double)accp.x / (w * w);
+            f.dpi = (double)accp.y / (w * w);
+        }
+    }
+    return f;
+}
+
 template <typename TL>
 __global__ __launch_bounds__(256) void finalize_backward_kernel(
     int n, const int *__restrict__ perm, const int *__restrict__ leaf_of, const double2 *__restrict__ xy,
@@ -736,30 +839,13 @@ __global__ __launch_bounds__(256) void finalize_backward_kernel(
     const double Bi = -ka * lambda * sb;
     double dwr = 0.0, dwi = 0.0, dpr = 0.0, dpi = 0.0;
     if (has_far) {
-        const uint32_t leaf = (uint32_t)leaf_of[i];
-        const double cx = x0 + (morton_x(leaf) + 0.5) * w;
-        const double cy = y0 + (morton_y(leaf) + 0.5) * w;
-        c2<TL> xi;
-        if (pos) {
-            xi = pos[i];
-        } else {
-            const double2 z = xy[i];
-            xi = mk<TL>((TL)((z.x - cx) / w), (TL)((z.y - cy) / w));
-        }
-        const c2<TL> *bq = loc_q + (int64_t)leaf * p;
-        const c2<TL> *bc = loc_c + (int64_t)leaf * p;
-        const c2<TL> accq = horner_prefetch<TL>(bq, p, xi);
-        phi += (double)accq.y / w;
-        if (p >= 2) {
-            const c2<TL> accd = horner_weighted_prefetch<TL>(bc, p, xi, 1, 0);
-            dwr = (double)accd.x / (w * w);
-            dwi = (double)accd.y / (w * w);
-            if (need_s) {
-                const c2<TL> accp = horner_weighted_prefetch<TL>(bq, p, xi, 1, 0);
-                dpr = (double)accp.x / (w * w);
-                dpi = (double)accp.y / (w * w);
-            }
-        }
+        const AdjointFar f =
+            adjoint_far<TL>((uint32_t)leaf_of[i], i, xy, loc_c, loc_q, pos, p, x0, y0, w, true, need_s);
+        phi += f.phi;
+        dwr = f.dwr;
+        dwi = f.dwi;
+        dpr = f.dpr;
+        dpi = f.dpi;
     }
     const double g = -phi * kInv2Pi;
     double ex = 0.0, ey = 0.0, sx = 0.0, sy = 0.0;
@@ -793,6 +879,33 @@ __global__ __launch_bounds__(256) void finalize_backward_kernel(
         return;
     }
     store_adjoint(out, o, g, ex, ey, sx, sy);
+}
+
+// Adjoint finalize of the pair force: the near sums come combined, from the target-centric
+// part and the slots as the velocity's; the far parts as above.  (Outputs dl_dxy and dl_dgamma.)
+template <typename TL, typename TS>
+__global__ __launch_bounds__(256) void finalize_force_kernel(
+    int n, const int *__restrict__ perm, const int *__restrict__ leaf_of, const double2 *__restrict__ xy,
+    const ForceNear near, const double2 *__restrict__ adj, const c2<TL> *__restrict__ loc_c,
+    const c2<TL> *__restrict__ loc_q, const c2<TL> *__restrict__ pos, int p, int has_far, double x0, double y0,
+    double w, double alpha, AdjointOut out, const int *__restrict__ gpos2, const double *__restrict__ gamma_st,
+    int nxcd)
+{
+    const int i = xcd_block(nxcd) * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int64_t o = perm[i];  // issued with the first loads
+    const uint32_t leaf = (uint32_t)leaf_of[i];
+    const double2 q = adj[i];
+    const double G = gamma_st[gpos2[i]] * kInv2Pi;
+    const int m = near.mask ? near.mask[leaf] : 1 << 9;
+    const double uq = near.qscale ? 1.0 / *near.qscale : 1.0;
+    const double2 nr = near_from_slots<TS>(i, n, m, near.near, (const c2<TS> *)near.slots, alpha * alpha * kInv2Pi);
+    double phi = 0.0;
+    if (out.dg) phi = alpha * uq * phi_from_slots<TS>(i, n, m, near.phi, (const TS *)near.phi_slots);
+    AdjointFar f;
+    if (has_far) f = adjoint_far<TL>(leaf, i, xy, loc_c, loc_q, pos, p, x0, y0, w, out.dg != nullptr, true);
+    store_adjoint(out, o, -(phi + f.phi) * kInv2Pi, uq * nr.x + (q.x * f.dwr - q.y * f.dwi),
+                  uq * nr.y - (q.x * f.dwi + q.y * f.dwr), -G * f.dpi, -G * f.dpr);
 }
 
 // The adjoint outputs from their staging slots (written by finalize_backward_kernel for n
@@ -981,6 +1094,35 @@ void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int
         p2p_near_kernel<float><<<grid, 64, near_lds_reserve(t, 256 * sizeof(float4)), s>>>(
             work, (const float2 *)pos, (const float *)gam, t->d_leaf_start, t->d_tile_start,
             t->d_tile_box, nside, (float)step, cut_leaf2, scale, t->dense_leaf, t->n, near, (float2 *)slots);
+}
+
+namespace {
+
+template <typename T, int KIND>
+void force_launch(const fmm_tree *t, const void *pos, const void *gam, const void *qv, double alpha,
+                  const ForceNear &near, hipStream_t s)
+{
+    const bool mutual = near.slots != nullptr;
+    const int64_t nwork = mutual ? t->nnear_work : t->nunits;
+    if (nwork == 0) return;
+    const int nside = 1 << t->depth;
+    const double step = alpha * (t->side / (double)nside);
+    const MutualTree mt{t->d_leaf_start, t->d_tile_start, t->d_tile_box, near_cut_leaf2(t, sizeof(T) == 8, alpha),
+                        force_series_leaf2(step)};
+    p2p_force_kernel<T, KIND><<<(unsigned)nwork, 64, 0, s>>>(
+        mutual ? t->d_near_work : t->d_units, SoaRec<T>{(const c2<T> *)pos, (const T *)gam, (T)step, (const c2<T> *)qv},
+        mt, nside, (T)step, alpha * alpha * kInv2Pi, t->dense_leaf, t->n, near.near, near.phi, (c2<T> *)near.slots,
+        (T *)near.phi_slots);
+}
+
+}  // namespace
+
+void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double, double alpha,
+                      const ForceNear &near, hipStream_t s)
+{
+    auto k = is_double ? (near.phi ? force_launch<double, kForcePhi> : force_launch<double, kForce>)
+                       : (near.phi ? force_launch<float, kForcePhi> : force_launch<float, kForce>);
+    k(t, pos, gam, qv, alpha, near, s);
 }
 
 void launch_p2m(const FarArgs &a, hipStream_t s)
@@ -1182,17 +1324,23 @@ void launch_finalize(const fmm_tree *t, const FarArgs &a, const double2 *near, c
     if (staged && windowed) gather_rows_kernel<<<g, 256, 0, s>>>(n, kXcds, t->d_gpos1, staged, uv, base, h);
     else if (staged) scatter_rows_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, t->d_perm, staged, uv, base, h);
 }
+void launch_adjoint_range(int64_t n, const double *gamma, const double *dl_duv, double scale, double2 *range,
+                          hipStream_t s)
+{
+    adjoint_range_kernel<<<kRangeBlocks, 256, 0, s>>>(n, gamma, (const double2 *)dl_duv, scale, range);
+}
+
 void launch_pack_adjoint(const fmm_tree *t, const double *dl_duv, double scale, double2 *adj, void *qt, int is_double,
-                         double2 *staging, hipStream_t s)
+                         double2 *staging, const double2 *range, double *qscale, hipStream_t s)
 {
     const int n = (int)t->n;
     launch_stage_rows2(n, t->stage_shift, t->d_gpos1, (const double2 *)dl_duv, staging, s);
     if (is_double)
         pack_adjoint_kernel<double><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, t->d_gpos2, staging, scale, adj,
-                                                                      nullptr);
+                                                                      nullptr, nullptr, nullptr);
     else
         pack_adjoint_kernel<float><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, t->d_gpos2, staging, scale, adj,
-                                                                     (float2 *)qt);
+                                                                     (float2 *)qt, range, qscale);
 }
 
 void launch_p2p_backward(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double,
@@ -1232,6 +1380,32 @@ void launch_p2p_backward(const fmm_tree *t, const void *pos, const void *gam, co
                 t->d_tile_start, t->d_tile_box, nside, (float)step, cut_leaf2, series_leaf2, (float)ln2, out_pa,
                 out_b, nullptr);
     }
+}
+
+namespace {
+
+template <typename TL, typename TS>
+void finalize_force_launch(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double2 *adj,
+                           const ForceNear &near, double alpha, const AdjointOut &out, hipStream_t s)
+{
+    const int L = t->depth;
+    const bool has_far = L >= 2;
+    finalize_force_kernel<TL, TS><<<xcd_grid(t->n, 256), 256, 0, s>>>(
+        (int)t->n, t->d_perm, t->d_leaf_of, t->d_xy, near, adj, has_far ? level_ptr<TL>(fc, L, true) : nullptr,
+        has_far ? level_ptr<TL>(fq, L, true) : nullptr,
+        (fc.rec_is_double != 0) == (sizeof(TL) == 8) ? (const c2<TL> *)fc.pos : nullptr, fc.p, has_far, t->x0, t->y0,
+        t->side / (double)(1 << L), alpha, out, t->d_gpos2, t->d_st1, kXcds);
+}
+
+}  // namespace
+
+void launch_finalize_force(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double2 *adj,
+                           const ForceNear &near, int is_double, double alpha, const AdjointOut &out, hipStream_t s)
+{
+    auto k = t->depth < 2 || t->depth <= fc.split
+                 ? (is_double ? finalize_force_launch<double, double> : finalize_force_launch<double, float>)
+                 : (is_double ? finalize_force_launch<float, double> : finalize_force_launch<float, float>);
+    k(t, fc, fq, adj, near, alpha, out, s);
 }
 
 void launch_finalize_backward(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double4 *near_pa,
