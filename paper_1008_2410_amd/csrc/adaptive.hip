@@ -280,7 +280,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 8 : 4) void at_near_kernel(
         const double step = alpha * ldexp(side, -(u.w >> 9));
         mutual_item<kVelocity>(u, lds, rec,
                                MutualTree{leaf_start, leaf_tile, tile_box_leaf, (float)(cut / (step * step)), 0.0f},
-                               (T)step, n, slots, (T *)nullptr);
+                               MutualParts{}, (T)step, n, slots, (T *)nullptr);
     } else {
         at_target_unit<T>(u, lds.a, cell, range, u_off, u_idx, tile_start, tile_box, rec, x0, y0, side, alpha, cut,
                           scale, dense, near);
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 
         mutual_item<KIND>(u, lds, rec,
                           MutualTree{leaf_start, leaf_tile, tile_box_leaf, (float)(cut / (step * step)),
                                      force_series_leaf2(step)},
-                          (T)step, n, slots, phi_slots);
+                          MutualParts{}, (T)step, n, slots, phi_slots);
         return;
     }
     const int lane = threadIdx.x;

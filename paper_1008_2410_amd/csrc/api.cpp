@@ -78,6 +78,10 @@ void release_tree_arrays(fmm_tree *t, hipStream_t fs)
     release(t->d_units, t->pooled);
     release(t->d_tile_box, t->pooled);
     release(t->d_near_work, true);
+    release(t->d_split, true);
+    release(t->d_parts, true);
+    release(t->d_part_sums, true);
+    t->cap_split = t->cap_parts = t->cap_part_sums = 0;
     release(t->d_leaf_mask, true);
     t->cap_lists = t->cap_units = t->cap_tile_box = t->cap_near_work = 0;
     for (int k = 0; k < 2; ++k) {
@@ -113,6 +117,12 @@ void take_over_arrays(fmm_tree *t, fmm_tree *from)
     take(t->cap_units, from->cap_units);
     take(t->cap_tile_box, from->cap_tile_box);
     take(t->cap_near_work, from->cap_near_work);
+    take(t->d_split, from->d_split);
+    take(t->d_parts, from->d_parts);
+    take(t->d_part_sums, from->d_part_sums);
+    take(t->cap_split, from->cap_split);
+    take(t->cap_parts, from->cap_parts);
+    take(t->cap_part_sums, from->cap_part_sums);
     for (int k = 0; k < 2; ++k) {
         take(t->pos_buf[k], from->pos_buf[k]);
         from->d_pos[k] = nullptr;

@@ -589,14 +589,22 @@ struct MutualTree {
     float cut_leaf2, series_leaf2;
 };
 
-// One tile b of S against every tile a of R (a >= b when S = R).  Per block (b, a) the
+// The tiles of R that an item takes (the particles from a0 to a1), and where its sums for the
+// particles of S go: their slot, or for a part of an item (see MutualPart) an array of the part's
+// own.
+template <typename T, int KIND> struct MutualRange {
+    int a0, a1;
+    bool part;
+    NearSlot<T, KIND> s, r;
+};
+
+// One tile b of S against every tile a of the range (a >= b when S = R).  Per block (b, a) the
 // tile with more chunks of 16 sits in the lanes and the other is streamed from LDS, so
 // that fewer steps are spent; either way both sums come out lane-indexed by particle.
 template <int KIND, typename T>
 __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, KIND> &lds, int b, int tb,
                                                      const SoaRec<T> &rec, const MutualTree &mt, T step,
-                                                     const NearSlot<T, KIND> &slot_s,
-                                                     const NearSlot<T, KIND> &slot_r)
+                                                     const MutualRange<T, KIND> &range)
 {
     constexpr int NS = kSums<KIND>;
     const int lane = threadIdx.x;
@@ -606,7 +614,7 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
     const int dx = ds % 3 - 1, dy = ds / 3 - 1;  // R - S in leaves
     const T ox = (T)dx * step, oy = (T)dy * step;
     const int s0 = mt.leaf_start[S], s1 = mt.leaf_start[S + 1];
-    const int r1 = mt.leaf_start[R + 1];
+    const int r0 = mt.leaf_start[R], r1 = range.a1;
     const int lenb = min(64, s1 - b);
     const int nchb = (lenb + 15) >> 4;
     __syncthreads();
@@ -620,10 +628,11 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
     T f[NS];
 #pragma unroll
     for (int m = 0; m < NS; ++m) f[m] = 0;
-    if (self && b > s0 && lane < lenb) slot_s.load(b + lane, f);  // what the earlier tiles of S wrote for this tile
+    if (self && !range.part && b > s0 && lane < lenb) range.s.load(b + lane, f);  // what the earlier tiles of S wrote for this tile
     const bool first_touch = b == s0;  // the first resident tile creates the streamed slots
-    int ta = self ? tb : mt.tile_start[R];
-    for (int a = self ? b : mt.leaf_start[R]; a < r1; a += 64, ++ta) {
+    const int from = self ? max(b, range.a0) : range.a0;
+    int ta = mt.tile_start[R] + ((from - r0) >> 6);
+    for (int a = from; a < r1; a += 64, ++ta) {
         const int lena = min(64, r1 - a);
         const int ncha = (lena + 15) >> 4;
         const bool diag = self && a == b;
@@ -657,7 +666,7 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
         T old[NS];
 #pragma unroll
         for (int m = 0; m < NS; ++m) old[m] = 0;
-        if (!first_touch && lane < lena) slot_r.load(a + lane, old);
+        if (!first_touch && lane < lena) range.r.load(a + lane, old);
         const bool swap = ncha > nchb;  // tile a in the lanes, tile b streamed
         __syncthreads();
         T qya;
@@ -715,24 +724,69 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
             f[m] += swap ? col[m] : r[m];
             old[m] += swap ? r[m] : col[m];
         }
-        if (lane < lena) slot_r.store(a + lane, old);
+        if (lane < lena) range.r.store(a + lane, old);
     }
-    if (lane < lenb) slot_s.store(b + lane, f);
+    if (lane < lenb) range.s.store(b + lane, f);
 }
 
 // The item's slots: 9 x n pairs of sums in uv, 9 x n third sums in phi.
 template <int KIND, typename T>
 __device__ __forceinline__ void mutual_item(const int4 it, NearLds<T, KIND> &lds, const SoaRec<T> &rec,
-                                            const MutualTree &mt, T step, int64_t n, c2<T> *__restrict__ uv,
-                                            T *__restrict__ phi)
+                                            const MutualTree &mt, const MutualParts &parts, T step, int64_t n,
+                                            c2<T> *__restrict__ uv, T *__restrict__ phi)
 {
     const uint32_t S = (uint32_t)it.x;
     const int64_t at_s = (int64_t)(it.z & 15) * n, at_r = (int64_t)(it.z >> 4) * n;
-    const NearSlot<T, KIND> slot_s{uv + at_s, KIND == kForcePhi ? phi + at_s : nullptr};
-    const NearSlot<T, KIND> slot_r{uv + at_r, KIND == kForcePhi ? phi + at_r : nullptr};
-    const int s0 = mt.leaf_start[S], s1 = mt.leaf_start[S + 1];
+    const int s0 = mt.leaf_start[S];
+    int s1 = mt.leaf_start[S + 1];
+    MutualRange<T, KIND> range{mt.leaf_start[it.y],
+                               mt.leaf_start[it.y + 1],
+                               false,
+                               {uv + at_s, KIND == kForcePhi ? phi + at_s : nullptr},
+                               {uv + at_r, KIND == kForcePhi ? phi + at_r : nullptr}};
+    if (parts.list && it.w > 2 * kMutualItem) {
+        const int4 q = parts.list[(it.w >> 9) - 1];
+        range.a0 = q.x;
+        range.a1 = q.y;
+        range.part = true;
+        const int64_t at = (int64_t)(unsigned)q.z - s0;
+        range.s.uv = (c2<T> *)parts.sums + at;
+        if (KIND == kForcePhi) range.s.phi = (T *)((c2<T> *)parts.sums + parts.count) + at;
+        if (it.y == it.x) s1 = min(s1, q.y);  // (later tiles of S meet none of the range)
+    }
     for (int b = s0, tb = mt.tile_start[S]; b < s1; b += 64, ++tb)
-        mutual_resident_tile<KIND>(it, lds, b, tb, rec, mt, step, slot_s, slot_r);
+        mutual_resident_tile<KIND>(it, lds, b, tb, rec, mt, step, range);
+}
+
+// The sums of a split item's particles of S, in the order of its parts, to their slot: one
+// workgroup per split item {S, direction of R, first part, parts}.
+template <typename T, int KIND>
+__global__ __launch_bounds__(256) void mutual_fold_kernel(const int4 *__restrict__ items, const MutualParts parts,
+                                                          const int *__restrict__ leaf_start, int64_t n,
+                                                          c2<T> *__restrict__ uv, T *__restrict__ phi)
+{
+    constexpr int NS = kSums<KIND>;
+    const int4 it = items[blockIdx.x];
+    const int s0 = leaf_start[it.x], s1 = leaf_start[it.x + 1];
+    const bool self = it.y == 4;
+    const NearSlot<T, KIND> slot{uv + it.y * n, KIND == kForcePhi ? phi + it.y * n : nullptr};
+    c2<T> *const puv = (c2<T> *)parts.sums;
+    const NearSlot<T, KIND> part{puv, KIND == kForcePhi ? (T *)(puv + parts.count) : nullptr};
+    for (int i = s0 + threadIdx.x; i < s1; i += 256) {
+        const int b = s0 + ((i - s0) & ~63);
+        T f[NS], g[NS];
+#pragma unroll
+        for (int m = 0; m < NS; ++m) f[m] = 0;
+        if (self && b > s0) slot.load(i, f);  // from the parts that hold the particle's own tile
+        for (int p = 0; p < it.w; ++p) {
+            const int4 q = parts.list[it.z + p];
+            if (self && b >= q.y) continue;
+            part.load((int64_t)(unsigned)q.z + (i - s0), g);
+#pragma unroll
+            for (int m = 0; m < NS; ++m) f[m] += g[m];
+        }
+        slot.store(i, f);
+    }
 }
 
 

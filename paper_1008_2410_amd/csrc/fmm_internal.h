@@ -64,6 +64,22 @@ constexpr int kRangeBlocks = 1024;
 // Flag (in w) of a mutual item in the near-field work list.
 constexpr int kMutualItem = 256;
 
+// A mutual item of leaves of many tiles is one wavefront's serial chain: 700001 patch particles
+// in FP64, one tight patch: the heaviest item is 10816 steps and all items together 8000 per
+// SIMD.  So items of more than twice kSplitShare-th of a SIMD's share of the near field's cost
+// (and of more than kSplitLeast, four blocks of tiles) are cut into parts of about that
+// cost, each a range of the tiles of the leaf with more of them (R) against all of S, an entry
+// of its own.  A part's sums for R are whole and go to R's slot; those for S go to an array of
+// the part's own and are added up by a kernel after the near field, in the order of the parts.
+// Entry: kMutualItem | (1 + its place in the list) << 9.
+constexpr int kSplitShare = 8, kSplitSimds = 1024;
+constexpr int64_t kSplitLeast = 768;
+struct MutualParts {
+    const int4 *list = nullptr;  // {first and end particle of R, first place in sums, -}; NULL: none
+    void *sums = nullptr;        // count pairs of sums, then count third sums
+    int64_t count = 0;
+};
+
 // Owner value of a workspace handed to a tree over other particles (clear before use).
 constexpr uint64_t kForeignOwner = ~uint64_t(0);
 
@@ -148,6 +164,11 @@ struct fmm_tree {
     int4 *d_units = nullptr;      // P2P work units {leaf, first, count, log2 lanes per target}
     // near-field plan of the mutual form (see build_near_plan)
     int64_t nunits_tc = 0, nmut = 0, nnear_work = 0;
+    // split mutual items (MutualParts), the places in the parts' sums
+    int64_t nsplit = 0, npart_sums = 0;
+    int4 *d_split = nullptr, *d_parts = nullptr;
+    double *d_part_sums = nullptr;  // 3 per place
+    int64_t cap_split = 0, cap_parts = 0, cap_part_sums = 0;
     int64_t mutual_pairs = 0;     // ordered pairs (i != j) evaluated by the mutual items
     int4 *d_near_work = nullptr;  // mutual items and target-centric units, heaviest first
     uint16_t *d_leaf_mask = nullptr; // per leaf: bit d slot d written, bit 9 target-centric part

@@ -282,14 +282,14 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 8 : 5) void p2p_near_kernel(
     const int4 *__restrict__ work, const c2<T> *__restrict__ pos, const T *__restrict__ gam,
     const int *__restrict__ leaf_start, const int *__restrict__ tile_start, const float4 *__restrict__ tile_box,
     int nside, T step, float cut_leaf2, double scale, int dense, int64_t n, double2 *__restrict__ near,
-    c2<T> *__restrict__ slots)
+    c2<T> *__restrict__ slots, const MutualParts parts)
 {
     __shared__ NearLds<T, kVelocity> lds;
     const SoaRec<T> rec{pos, gam, step};
     const int4 u = work[blockIdx.x];
     if (u.w & kMutualItem)
-        mutual_item<kVelocity>(u, lds, rec, MutualTree{leaf_start, tile_start, tile_box, cut_leaf2, 0.0f}, step, n,
-                               slots, (T *)nullptr);
+        mutual_item<kVelocity>(u, lds, rec, MutualTree{leaf_start, tile_start, tile_box, cut_leaf2, 0.0f}, parts,
+                               step, n, slots, (T *)nullptr);
     else
         p2p_forward_unit<T>(u, lds.a, rec, leaf_start, tile_start, tile_box, nside, step, cut_leaf2, scale, dense,
                             near);
@@ -361,11 +361,11 @@ template <typename T, int KIND>
 __global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 3) void p2p_force_kernel(
     const int4 *__restrict__ work, const SoaRec<T> rec, const MutualTree mt, int nside, T step, double scale,
     int dense, int64_t n, double2 *__restrict__ near, double *__restrict__ near_phi, c2<T> *__restrict__ slots,
-    T *__restrict__ phi_slots)
+    T *__restrict__ phi_slots, const MutualParts parts)
 {
     __shared__ NearLds<T, KIND> lds;
     const int4 u = work[blockIdx.x];
-    if (u.w & kMutualItem) mutual_item<KIND>(u, lds, rec, mt, step, n, slots, phi_slots);
+    if (u.w & kMutualItem) mutual_item<KIND>(u, lds, rec, mt, parts, step, n, slots, phi_slots);
     else p2p_force_unit<T, KIND>(u, lds.a, lds.qa, rec, mt, nside, step, scale, dense, near, near_phi);
 }
 
@@ -1073,6 +1073,23 @@ inline size_t near_lds_reserve(const fmm_tree *t, size_t static_bytes)
     return per_wave > static_bytes ? per_wave - static_bytes : 0;
 }
 
+namespace {
+
+MutualParts mutual_parts(const fmm_tree *t, bool mutual)
+{
+    if (!mutual || t->nsplit == 0) return MutualParts{};
+    return MutualParts{t->d_parts, t->d_part_sums, t->npart_sums};
+}
+
+template <typename T, int KIND>
+void fold_launch(const fmm_tree *t, const MutualParts &parts, void *slots, void *phi, hipStream_t s)
+{
+    mutual_fold_kernel<T, KIND><<<(unsigned)t->nsplit, 256, 0, s>>>(t->d_split, parts, t->d_leaf_start, t->n,
+                                                                    (c2<T> *)slots, (T *)phi);
+}
+
+}  // namespace
+
 void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int is_double, double alpha,
                         double2 *near, void *slots, hipStream_t s)
 {
@@ -1086,14 +1103,19 @@ void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int
     const double step = alpha * w;
     const float cut_leaf2 = near_cut_leaf2(t, is_double, alpha);
     const unsigned grid = (unsigned)nwork;
+    const MutualParts parts = mutual_parts(t, mutual);
     if (is_double)
         p2p_near_kernel<double><<<grid, 64, near_lds_reserve(t, 256 * sizeof(double4)), s>>>(
             work, (const double2 *)pos, (const double *)gam, t->d_leaf_start, t->d_tile_start,
-            t->d_tile_box, nside, step, cut_leaf2, scale, t->dense_leaf, t->n, near, (double2 *)slots);
+            t->d_tile_box, nside, step, cut_leaf2, scale, t->dense_leaf, t->n, near, (double2 *)slots, parts);
     else
         p2p_near_kernel<float><<<grid, 64, near_lds_reserve(t, 256 * sizeof(float4)), s>>>(
             work, (const float2 *)pos, (const float *)gam, t->d_leaf_start, t->d_tile_start,
-            t->d_tile_box, nside, (float)step, cut_leaf2, scale, t->dense_leaf, t->n, near, (float2 *)slots);
+            t->d_tile_box, nside, (float)step, cut_leaf2, scale, t->dense_leaf, t->n, near, (float2 *)slots, parts);
+    if (parts.list) {
+        if (is_double) fold_launch<double, kVelocity>(t, parts, slots, nullptr, s);
+        else fold_launch<float, kVelocity>(t, parts, slots, nullptr, s);
+    }
 }
 
 namespace {
@@ -1109,10 +1131,12 @@ void force_launch(const fmm_tree *t, const void *pos, const void *gam, const voi
     const double step = alpha * (t->side / (double)nside);
     const MutualTree mt{t->d_leaf_start, t->d_tile_start, t->d_tile_box, near_cut_leaf2(t, sizeof(T) == 8, alpha),
                         force_series_leaf2(step)};
+    const MutualParts parts = mutual_parts(t, mutual);
     p2p_force_kernel<T, KIND><<<(unsigned)nwork, 64, 0, s>>>(
         mutual ? t->d_near_work : t->d_units, SoaRec<T>{(const c2<T> *)pos, (const T *)gam, (T)step, (const c2<T> *)qv},
         mt, nside, (T)step, alpha * alpha * kInv2Pi, t->dense_leaf, t->n, near.near, near.phi, (c2<T> *)near.slots,
-        (T *)near.phi_slots);
+        (T *)near.phi_slots, parts);
+    if (parts.list) fold_launch<T, KIND>(t, parts, near.slots, near.phi_slots, s);
 }
 
 }  // namespace

@@ -211,13 +211,16 @@ __global__ __launch_bounds__(256) void rs_scatter(const uint64_t *__restrict__ k
 // ---------------------------------------------------------------------------------
 // What a uniform build reports to the host, read back twice: after the keys (the checks
 // and the root cell) and after the counts (the sizes of the lists).
+// target-centric units, mutual items, mutual pairs, estimated cost; split items, their parts and
+// the places in the parts' sums; then how many of these three are given out
+enum PlanFact { kPlanUnits, kPlanItems, kPlanPairs, kPlanCost, kPlanSplit, kPlanParts, kPlanSums, kPlanNext, kPlanFacts = 10 };
 struct BuildFacts {
     int flags;                    // k_minmax, k_keys
     unsigned long long first_bad;
     double x0, y0, side;
     uint32_t ntiles, nlist, nwork;
     uint32_t class_off[4 * (kMaxDepth + 1)];
-    unsigned long long plan[3];   // target-centric units, mutual items, mutual pairs
+    unsigned long long plan[kPlanFacts];  // see PlanFact
     unsigned long long stats[4];  // near pairs (with the particle itself), non-empty leaves, largest, M2L pairs
 };
 
@@ -607,99 +610,193 @@ __device__ inline int64_t block_steps(int cs, int cr)
     return 16 * (fs * fr * 4 + fs * nch16(rr) + fr * nch16(rs) + min(nch16(rs), nch16(rr)));
 }
 
+// Estimated costs of the entries (a multiple of the steps of 64 pairs that they take).
+__device__ inline int log2_lanes(int cnt)
+{
+    int logtp = 0;
+    while ((1 << logtp) < cnt) ++logtp;
+    return logtp;
+}
+__device__ inline int64_t unit_cost(int64_t nsrc, int cnt)
+{
+    const int kstride = 64 >> log2_lanes(cnt);
+    return 2 * ((nsrc + kstride - 1) / kstride);
+}
+__device__ inline int64_t self_cost(int nt)
+{
+    const int64_t f = nt / 64;
+    const int r = nt % 64;
+    return 3 * 16 * (f * (f - 1) / 2 * 4 + f * nch16(r)) + 2 * 16 * (f * 4 + nch16(r));
+}
+
 __constant__ int kUp[4][2] = {{1, 0}, {-1, 1}, {0, 1}, {1, 1}};
 
-__global__ __launch_bounds__(256) void k_plan_count(const int *__restrict__ ls, int L, int D,
-                                                     uint32_t *__restrict__ nentries, uint16_t *__restrict__ mask,
-                                                     unsigned long long *__restrict__ stats)
+// A dense leaf's mutual items: item(R, count of R, direction, cost) for itself and for its dense
+// upper neighbours.
+template <typename Item>
+__device__ __forceinline__ void leaf_items(const int *__restrict__ ls, int nside, int64_t c, int nt, int D, Item item)
+{
+    const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
+    item((int)c, nt, 4, self_cost(nt));
+    for (int k = 0; k < 4; ++k) {
+        const int nr = leaf_count(ls, nside, x + kUp[k][0], y + kUp[k][1]);
+        if (nr >= D)
+            item((int)morton_encode((uint32_t)(x + kUp[k][0]), (uint32_t)(y + kUp[k][1])), nr,
+                 3 * (kUp[k][1] + 1) + (kUp[k][0] + 1), 3 * block_steps(nt, nr));
+    }
+}
+
+// How an item of this cost between leaves of ns and nr particles is cut (kSplitShare): the tiles
+// of the larger leaf in `parts` <= most ranges of `tiles`; one part: not at all.
+struct Split {
+    int parts, tiles;
+};
+__device__ inline Split split_of(int64_t cost, int ns, int nr, unsigned long long total, int most)
+{
+    const int64_t target = max(kSplitLeast, (int64_t)(total / ((unsigned long long)kSplitSimds * kSplitShare)));
+    const int na = (max(ns, nr) + 63) / 64;
+    if (cost <= 2 * target || na < 2 || most < 2) return Split{1, na};
+    const int tiles = (int)max(target * na / cost, (int64_t)max(1, (na + most - 1) / most));
+    return Split{(na + tiles - 1) / tiles, tiles};
+}
+
+// Sources that the target-centric units of a leaf of nt take, and (mask) the slots its mutual
+// items write.
+__device__ __forceinline__ int64_t unit_sources(const int *__restrict__ ls, int nside, int64_t c, int nt, int D,
+                                                uint32_t &mask)
+{
+    const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
+    int64_t nsrc = 0;
+    for (int dy = -1; dy <= 1; ++dy)
+        for (int dx = -1; dx <= 1; ++dx) {
+            const int ns = leaf_count(ls, nside, x + dx, y + dy);
+            if (ns == 0) continue;
+            if (nt >= D && ns >= D) mask |= 1u << (3 * (dy + 1) + (dx + 1));
+            else nsrc += ns;
+        }
+    return nsrc;
+}
+
+// Per leaf: its mask and units, and the estimated cost of the whole near field.
+__global__ __launch_bounds__(256) void k_plan_cost(const int *__restrict__ ls, int L, int D, uint16_t *__restrict__ mask,
+                                                   unsigned long long *__restrict__ stats)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nleaf = int64_t(1) << (2 * L);
     const int nside = 1 << L;
     const int nt = c < nleaf ? ls[c + 1] - ls[c] : 0;
-    uint32_t units = 0, items = 0, m = 0;
-    int64_t pairs = 0;
+    uint32_t m = 0;
+    int64_t units = 0, items = 0, pairs = 0, cost = 0;
     if (nt > 0) {
-        const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
-        const bool dense = nt >= D;
-        int64_t nsrc = 0;
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int ns = leaf_count(ls, nside, x + dx, y + dy);
-                if (ns == 0) continue;
-                if (dense && ns >= D) m |= 1u << (3 * (dy + 1) + (dx + 1));
-                else nsrc += ns;
-            }
+        const int64_t nsrc = unit_sources(ls, nside, c, nt, D, m);
         if (nsrc > 0) {
             m |= 1u << 9;
-            units = (uint32_t)((nt + 63) / 64);
+            units = (nt + 63) / 64;
+            cost = (nt / 64) * unit_cost(nsrc, 64) + (nt % 64 ? unit_cost(nsrc, nt % 64) : 0);
         }
-        if (dense) {
-            pairs = (int64_t)nt * (nt - 1);
-            items = 1;
-            for (int k = 0; k < 4; ++k) {
-                const int nr = leaf_count(ls, nside, x + kUp[k][0], y + kUp[k][1]);
-                if (nr >= D) {
-                    ++items;
-                    pairs += 2 * (int64_t)nt * nr;
-                }
-            }
-        }
+        if (nt >= D)
+            leaf_items(ls, nside, c, nt, D, [&](int R, int nr, int, int64_t cst) {
+                ++items;
+                pairs += R == (int)c ? (int64_t)nt * (nt - 1) : 2 * (int64_t)nt * nr;
+                cost += cst;
+            });
     }
-    wave_add(&stats[0], units);
-    wave_add(&stats[1], items);
-    wave_add(&stats[2], (unsigned long long)pairs);
-    if (c <= nleaf) nentries[c] = units + items;
+    wave_add(&stats[kPlanUnits], (unsigned long long)units);
+    wave_add(&stats[kPlanItems], (unsigned long long)items);
+    wave_add(&stats[kPlanPairs], (unsigned long long)pairs);
+    wave_add(&stats[kPlanCost], (unsigned long long)cost);
     if (c < nleaf) mask[c] = (uint16_t)m;
 }
 
+// Per leaf: how many entries (nleaf + 1 counts, the last 0); split items, parts and places in the
+// parts' sums in all.
+__global__ __launch_bounds__(256) void k_plan_count(const int *__restrict__ ls, int L, int D,
+                                                     const uint16_t *__restrict__ mask, int most,
+                                                     unsigned long long *__restrict__ stats,
+                                                     uint32_t *__restrict__ nentries)
+{
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t nleaf = int64_t(1) << (2 * L);
+    const int nt = c < nleaf ? ls[c + 1] - ls[c] : 0;
+    const unsigned long long total = stats[kPlanCost];
+    uint32_t entries = 0;
+    unsigned long long split = 0, parts = 0, sums = 0;
+    if (nt > 0) {
+        if (mask[c] >> 9) entries = (uint32_t)((nt + 63) / 64);
+        if (nt >= D)
+            leaf_items(ls, 1 << L, c, nt, D, [&](int, int nr, int, int64_t cost) {
+                const Split sp = split_of(cost, nt, nr, total, most);
+                entries += sp.parts;
+                if (sp.parts == 1) return;
+                ++split;
+                parts += sp.parts;
+                sums += (unsigned long long)sp.parts * min(nt, nr);
+            });
+    }
+    if (__any(split > 0)) {
+        wave_add(&stats[kPlanSplit], split);
+        wave_add(&stats[kPlanParts], parts);
+        wave_add(&stats[kPlanSums], sums);
+    }
+    if (c <= nleaf) nentries[c] = entries;
+}
+
+struct PlanOut {
+    int4 *work;
+    uint64_t *key;
+    uint32_t *val;
+    int4 *split, *parts;
+};
+
 __global__ __launch_bounds__(256) void k_plan_fill(const int *__restrict__ ls, int L, int D,
-                                                    const uint32_t *__restrict__ off, int4 *__restrict__ work,
-                                                    uint64_t *__restrict__ key, uint32_t *__restrict__ val)
+                                                    int most, unsigned long long *__restrict__ stats,
+                                                    const uint32_t *__restrict__ off, const PlanOut out)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= (int64_t(1) << (2 * L))) return;
     const int nside = 1 << L;
     const int nt = ls[c + 1] - ls[c];
     if (nt == 0) return;
-    const int x = (int)morton_x((uint32_t)c), y = (int)morton_y((uint32_t)c);
-    const bool dense = nt >= D;
-    int64_t nsrc = 0;
-    for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-            const int ns = leaf_count(ls, nside, x + dx, y + dy);
-            if (ns == 0) continue;
-            if (!(dense && ns >= D)) nsrc += ns;
-        }
+    uint32_t m = 0;
+    const int64_t nsrc = unit_sources(ls, nside, c, nt, D, m);
     uint32_t o = off[c];
     auto put = [&](int4 e, int64_t cost) {
-        work[o] = e;
-        key[o] = cost_order((uint64_t)cost);  // heaviest first
-        val[o] = o;
+        out.work[o] = e;
+        out.key[o] = cost_order((uint64_t)cost);  // heaviest first
+        out.val[o] = o;
         ++o;
     };
     if (nsrc > 0)
         for (int c0 = 0; c0 < nt; c0 += 64) {
             const int cnt = min(64, nt - c0);
-            int logtp = 0;
-            while ((1 << logtp) < cnt) ++logtp;
-            const int kstride = 64 >> logtp;
-            put(make_int4((int)c, ls[c] + c0, cnt, logtp | (dense ? 16 : 0)), 2 * ((nsrc + kstride - 1) / kstride));
+            put(make_int4((int)c, ls[c] + c0, cnt, log2_lanes(cnt) | (nt >= D ? 16 : 0)), unit_cost(nsrc, cnt));
         }
-    if (!dense) return;
-    const int64_t f = nt / 64;
-    const int r = nt % 64;
-    const int64_t diag = 16 * (f * 4 + nch16(r));
-    const int64_t st = 16 * (f * (f - 1) / 2 * 4 + f * nch16(r));
-    put(make_int4((int)c, (int)c, 4 | (4 << 4), kMutualItem), 3 * st + 2 * diag);
-    for (int k = 0; k < 4; ++k) {
-        const int nr = leaf_count(ls, nside, x + kUp[k][0], y + kUp[k][1]);
-        if (nr < D) continue;
-        const int ds = 3 * (kUp[k][1] + 1) + (kUp[k][0] + 1);
-        put(make_int4((int)c, (int)morton_encode((uint32_t)(x + kUp[k][0]), (uint32_t)(y + kUp[k][1])),
-                      ds | ((8 - ds) << 4), kMutualItem),
-            3 * block_steps(nt, nr));
-    }
+    if (nt < D) return;
+    const unsigned long long total = stats[kPlanCost];
+    leaf_items(ls, nside, c, nt, D, [&](int R, int nr, int ds, int64_t cost) {
+        const Split sp = split_of(cost, nt, nr, total, most);
+        if (sp.parts == 1) {
+            put(make_int4((int)c, R, ds | ((8 - ds) << 4), kMutualItem), cost);
+            return;
+        }
+        // the larger leaf is the one cut
+        const bool self = R == (int)c, turn = nt > nr;
+        const int S = turn ? R : (int)c, A = turn ? (int)c : R, d = turn ? 8 - ds : ds;
+        const int a0 = ls[A], a1 = ls[A + 1], ns = min(nt, nr);
+        // (the places are given out in any order: they are addresses, not an order of sums)
+        uint32_t at_part = (uint32_t)atomicAdd(&stats[kPlanNext + 1], (unsigned long long)sp.parts);
+        uint32_t at_sum = (uint32_t)atomicAdd(&stats[kPlanNext + 2], (unsigned long long)sp.parts * ns);
+        out.split[atomicAdd(&stats[kPlanNext], 1ull)] = make_int4(S, d, (int)at_part, sp.parts);
+        for (int p = 0; p < sp.parts; ++p) {
+            const int first = a0 + 64 * sp.tiles * p, end = min(a1, first + 64 * sp.tiles);
+            out.parts[at_part] = make_int4(first, end, (int)at_sum, 0);
+            ++at_part;
+            at_sum += (uint32_t)ns;
+            // (of a leaf with itself a part meets the tiles up to its own)
+            const int64_t part_cost = self ? 3 * block_steps(end - a0, end - first) : 3 * block_steps(ns, end - first);
+            put(make_int4(S, A, d | ((8 - d) << 4), kMutualItem | ((int)at_part << 9)), part_cost);
+        }
+    });
 }
 
 }  // namespace
@@ -862,48 +959,65 @@ bool bounding_square(const double2 *xy, int64_t n, hipStream_t s, Status &st, do
 // ---------------------------------------------------------------------------------
 namespace {
 
-// The plan's counts: entries per leaf (scanned into offsets, nleaf + 1), the leaf masks, and
-// plan[0..2] (device, zeroed): target-centric units, mutual items, mutual pairs.
+// Most parts of a split item: 32, but few enough that their sums (which at worst every leaf has
+// with five neighbours) stay below some GB.
+int most_parts(int64_t n)
+{
+    if (n > int64_t(1) << 26) return 1;
+    return (int)std::min<int64_t>(32, std::max<int64_t>(4, (int64_t(1) << 25) / n));
+}
+
+// The plan's counts: entries per leaf (scanned into offsets, nleaf + 1), the leaf masks, and the
+// first of plan[] (device, zeroed), see PlanFact.
 bool plan_count(fmm_tree *t, Buf<uint32_t> &nent, unsigned long long *plan, hipStream_t s, Status &st)
 {
     const int64_t nleaf = int64_t(1) << (2 * t->depth);
     if (!st.check(nent.alloc(nleaf + 1, s), "near-field plan")) return false;
-    k_plan_count<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, nent.p,
-                                                           t->d_leaf_mask, plan);
+    k_plan_cost<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, t->d_leaf_mask, plan);
+    k_plan_count<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, t->d_leaf_mask,
+                                                           most_parts(t->n), plan, nent.p);
     return scan_on(nent.p, nent.p, nleaf + 1, nullptr, s, st);
 }
 
-// The work list of `total` entries, heaviest first.
-bool plan_fill(fmm_tree *t, const Buf<uint32_t> &nent, uint32_t total, hipStream_t s, Status &st)
+// The work list of `total` entries, heaviest first, and the parts of the split items; plan as the
+// host read it and on the device.
+bool plan_fill(fmm_tree *t, const Buf<uint32_t> &nent, uint32_t total, const unsigned long long *h,
+               unsigned long long *plan, hipStream_t s, Status &st)
 {
     const int64_t nleaf = int64_t(1) << (2 * t->depth);
     Buf<int4> work;
     Buf<uint64_t> key;
     Buf<uint32_t> val;
     if (!st.check(pool_array(t->d_near_work, t->cap_near_work, total, s), "near-field plan") ||
+        (h[kPlanSplit] > 0 &&
+         (!st.check(pool_array(t->d_split, t->cap_split, (int64_t)h[kPlanSplit], s), "near-field plan") ||
+          !st.check(pool_array(t->d_parts, t->cap_parts, (int64_t)h[kPlanParts], s), "near-field plan") ||
+          !st.check(pool_array(t->d_part_sums, t->cap_part_sums, 3 * (int64_t)h[kPlanSums], s), "near-field plan"))) ||
         !st.check(work.alloc(total, s), "near-field plan") || !st.check(key.alloc(total, s), "near-field plan") ||
         !st.check(val.alloc(total, s), "near-field plan"))
         return false;
-    k_plan_fill<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, nent.p, work.p, key.p,
-                                                      val.p);
+    k_plan_fill<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, most_parts(t->n), plan,
+                                                      nent.p, PlanOut{work.p, key.p, val.p, t->d_split, t->d_parts});
     if (!st.check(hipGetLastError(), "near-field plan") || !radix_sort(key, val, total, 8, s, st)) return false;
     k_gather<int4><<<grid_for(total, 256), 256, 0, s>>>(work.p, val.p, total, t->d_near_work);
     t->nnear_work = total;
+    t->nsplit = (int64_t)h[kPlanSplit];
+    t->npart_sums = (int64_t)h[kPlanSums];
     return st.check(hipGetLastError(), "near-field plan");
 }
 
 void plan_facts(fmm_tree *t, const unsigned long long *plan)
 {
-    t->nunits_tc = (int64_t)plan[0];
-    t->nmut = (int64_t)plan[1];
-    t->mutual_pairs = (int64_t)plan[2];
+    t->nunits_tc = (int64_t)plan[kPlanUnits];
+    t->nmut = (int64_t)plan[kPlanItems];
+    t->mutual_pairs = (int64_t)plan[kPlanPairs];
 }
 
 }  // namespace
 
 int build_near_plan_device(fmm_tree *t, hipStream_t s, std::string &err)
 {
-    t->nunits_tc = t->nmut = t->nnear_work = t->mutual_pairs = 0;
+    t->nunits_tc = t->nmut = t->nnear_work = t->nsplit = t->npart_sums = t->mutual_pairs = 0;
     if (!t->near_mutual) return FMM_OK;
     Status st;
     auto failed = [&]() {
@@ -918,17 +1032,17 @@ int build_near_plan_device(fmm_tree *t, hipStream_t s, std::string &err)
     Buf<unsigned long long> plan;
     if ((!t->d_leaf_mask &&
          !st.check(hipMallocAsync((void **)&t->d_leaf_mask, nleaf * sizeof(uint16_t), s), "near-field plan")) ||
-        !st.check(plan.alloc(3, s), "near-field plan") ||
-        !st.check(hipMemsetAsync(plan.p, 0, 3 * sizeof(unsigned long long), s), "near-field plan") ||
+        !st.check(plan.alloc(kPlanFacts, s), "near-field plan") ||
+        !st.check(hipMemsetAsync(plan.p, 0, kPlanFacts * sizeof(unsigned long long), s), "near-field plan") ||
         !plan_count(t, nent, plan.p, s, st))
         return failed();
-    unsigned long long hs[3];
+    unsigned long long hs[kPlanFacts];
     uint32_t total = 0;
     if (!st.check(hipMemcpyAsync(hs, plan.p, sizeof hs, hipMemcpyDeviceToHost, s), "near-field plan") ||
         !st.check(hipMemcpyAsync(&total, nent.p + nleaf, sizeof total, hipMemcpyDeviceToHost, s), "near-field plan") ||
         !st.check(hipStreamSynchronize(s), "near-field plan"))
         return failed();
-    if (!plan_fill(t, nent, total, s, st) || !st.check(hipStreamSynchronize(s), "near-field plan")) return failed();
+    if (!plan_fill(t, nent, total, hs, plan.p, s, st) || !st.check(hipStreamSynchronize(s), "near-field plan")) return failed();
     plan_facts(t, hs);
     return FMM_OK;
 }
@@ -1010,7 +1124,7 @@ int build_tree_device(fmm_tree *t, const double *xy, const double *root_box, hip
         k_list_flags<<<grid_for(nflags + 1, 256), 256, 0, s>>>(t->d_counts, nflags, pos.p);
         if (!scan_on(pos.p, pos.p, nflags + 1, nullptr, s, st)) return failed();
     }
-    t->nunits_tc = t->nmut = t->nnear_work = t->mutual_pairs = 0;
+    t->nunits_tc = t->nmut = t->nnear_work = t->nsplit = t->npart_sums = t->mutual_pairs = 0;
     if (t->near_mutual && !plan_count(t, nent, facts.p->plan, s, st)) return failed();
     k_sizes<<<1, 64, 0, s>>>(tstart, pos.p, nent.p, nleaf, L, facts.p);
     if (!st.check(hipGetLastError(), "tree build") || !read_facts()) return failed();
@@ -1049,7 +1163,7 @@ int build_tree_device(fmm_tree *t, const double *xy, const double *root_box, hip
     if (!radix_sort(ukey, uval, ntiles, 8, s, st)) return failed();
     k_gather<int4><<<grid_for(ntiles, 256), 256, 0, s>>>(units.p, uval.p, ntiles, t->d_units);
     t->nunits = ntiles;
-    if (t->near_mutual && !plan_fill(t, nent, h.nwork, s, st)) return failed();
+    if (t->near_mutual && !plan_fill(t, nent, h.nwork, h.plan, facts.p->plan, s, st)) return failed();
     t->stage_shift = stage_shift_of(n);
     if (!build_staging(t->d_perm, n, s, st, t->stage_shift, t->d_gpos1, t->d_gpos2)) return failed();
     if (!st.check(hipGetLastError(), "tree build") || !read_facts()) return failed();
