@@ -41,12 +41,18 @@ struct TransArgs {
     TransSeg seg[kMaxTransSegs];
 };
 
-// Uniform tree, levels [2, hi] below: the whole upward or downward pass of a block's subtree.
+// Three levels of the upward or downward pass, a workgroup per cell of level `base` and its
+// descendants.
 struct SubtreeArgs {
-    int p, base, deepest;             // blocks: cells of level `base`; deepest: last level read (up) or written (down)
-    const int *counts;                // occupancy by global cell index
-    double *rows;                     // FP64 rows from global cell 0: multipoles (up) or locals (down)
+    int p, base, deepest;             // deepest: last level read (up) or written (down)
+    const int *counts;                // uniform tree: occupancy by global cell index
+    double *rows;                     // FP64 rows from cell 0: multipoles (up) or locals (down)
     const double *tab;
+    // adaptive tree
+    const int *cells = nullptr;       // the split cells of level `base`
+    int ncells = 0;
+    const int4 *child = nullptr;
+    const double *zero = nullptr;     // the row of absent cells
 };
 
 // Tables of p terms: KS(p) steps of four rows and columns in blocks of 16 (FP64), KF(p)
@@ -73,7 +79,7 @@ void launch_trans64(TransArgs a, Trans mode, bool adaptive, hipStream_t s);
 // L2L along.
 void launch_trans32(TransArgs a, Trans mode, bool src_double, bool out_double, hipStream_t s);
 // Levels base + 2 .. base of the upward pass, or base + 1 .. base + 3 of the downward pass
-// (at most to `deepest`), a workgroup per cell of level `base`.
+// (at most to `deepest`), a workgroup per cell of level `base` (adaptive tree: per split cell).
 void launch_subtree(const SubtreeArgs &a, bool up, hipStream_t s);
 
 }  // namespace fmm

@@ -366,6 +366,118 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(Sub
 }
 
 // ---------------------------------------------------------------------------------
+// The same for the adaptive tree: one workgroup per split cell of level `base`, its descendants
+// found through the child indices.  A row of the tile of level base + 1 (+ 2) is a place in the
+// subtree, quadrant by quadrant; places without a cell read the zero row and are not written.
+// A level of its own cost a launch of 5 us whatever it held (150001 clustered particles: 60
+// launches of a gradient's 700 us), and one launch of three levels costs 8.
+// ---------------------------------------------------------------------------------
+__device__ __forceinline__ int pick(int4 c, int q) { return q == 0 ? c.x : q == 1 ? c.y : q == 2 ? c.z : c.w; }
+
+// Lane row r of a wavefront: its cell at level base + d (d = 0, 1, 2; -1: none) and that cell's
+// children.
+struct SubtreePlaces {
+    int id[3];
+    int4 ch[3];
+    __device__ __forceinline__ SubtreePlaces(const SubtreeArgs &a, int cell0, int row)
+    {
+        const int4 none = make_int4(-1, -1, -1, -1);
+        const int4 c0 = a.child[cell0];
+        id[0] = row == 0 ? cell0 : -1;
+        ch[0] = row == 0 ? c0 : none;
+        id[1] = row < 4 ? pick(c0, row & 3) : -1;
+        const int i1 = pick(c0, row >> 2);
+        const int4 g = a.child[max(i1, 0)];
+        ch[1] = a.child[max(id[1], 0)];
+        if (id[1] < 0) ch[1] = none;
+        id[2] = i1 >= 0 ? pick(g, row & 3) : -1;
+        ch[2] = a.child[max(id[2], 0)];
+        if (id[2] < 0) ch[2] = none;
+    }
+};
+
+template <int KS>
+__global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_adaptive_kernel(SubtreeArgs a)
+{
+    constexpr int NB = col_blocks<KS>();
+    const int lane = threadIdx.x & 63, cb = threadIdx.x >> 6;
+    const int row = lane & 15, kq = lane >> 4;
+    const int two_p = 2 * a.p, k0 = KS * kq, col = 16 * cb + row;
+    double bv[4][KS];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) load_op<KS, NB>(bv[e], a.tab, 53 + e, cb, lane);
+    const SubtreePlaces pl(a, a.cells[blockIdx.x], row);
+#pragma unroll
+    for (int d = 2; d >= 0; --d) {
+        if (a.base + d > a.deepest - 1) continue;  // (no level below)
+        const int4 ch = pl.ch[d];
+        // a cell without children is a leaf, whose row the particles gave
+        const int target = max(max(ch.x, ch.y), max(ch.z, ch.w)) >= 0 ? pl.id[d] : -1;
+        if (__any(target >= 0)) {
+            double av[4][KS];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int S = pick(ch, e);
+                load_row<KS>(av[e], S >= 0 ? a.rows + (int64_t)S * two_p : a.zero, k0);
+            }
+            doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row(av[e][s], k0 + s, two_p), bv[e][s], acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int t = __shfl(target, kq + 4 * r);
+                if (t >= 0 && col < two_p) a.rows[(int64_t)t * two_p + col] = acc[r];
+            }
+        }
+        __syncthreads();  // the next level reads these rows
+    }
+}
+
+template <int KS> __global__ __launch_bounds__(256) void subtree_down_adaptive_kernel(SubtreeArgs a)
+{
+    constexpr int NB = col_blocks<KS>();
+    const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, kq = lane >> 4;
+    const int two_p = 2 * a.p, k0 = KS * kq;
+    double bv[NB][KS];  // the class's operator, the same at every level
+#pragma unroll
+    for (int c = 0; c < NB; ++c) load_op<KS, NB>(bv[c], a.tab, 49 + q, c, lane);
+    const SubtreePlaces pl(a, a.cells[blockIdx.x], row);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        if (a.base + d > a.deepest - 1) continue;  // (no level below)
+        const int target = pick(pl.ch[d], q);
+        if (__any(target >= 0)) {
+            double av[KS];
+            load_row<KS>(av, target >= 0 ? a.rows + (int64_t)pl.id[d] * two_p : a.zero, k0);
+            int to[4];
+            doublex4 acc[NB];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                to[r] = __shfl(target, kq + 4 * r);
+#pragma unroll
+                for (int c = 0; c < NB; ++c)
+                    acc[c][r] = to[r] >= 0 && 16 * c + row < two_p ? a.rows[(int64_t)to[r] * two_p + 16 * c + row] : 0.0;
+            }
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int c = 0; c < NB; ++c)
+                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row(av[s], k0 + s, two_p), bv[c][s], acc[c], 0, 0, 0);
+#pragma unroll
+            for (int c = 0; c < NB; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (to[r] >= 0 && 16 * c + row < two_p) a.rows[(int64_t)to[r] * two_p + 16 * c + row] = acc[c][r];
+        }
+        __syncthreads();  // the next level reads these rows
+    }
+}
+
+// ---------------------------------------------------------------------------------
 // FP32 (the fine levels of the mixed form): one wavefront per tile of 32 targets and block
 // of 32 columns, the next operator's operands loaded ahead of the current one's products.
 // ---------------------------------------------------------------------------------
@@ -544,6 +656,12 @@ template <int KF> void trans32(TransArgs &a, Trans mode, bool src_double, bool o
 
 template <int KS> void subtree(const SubtreeArgs &a, bool up, hipStream_t s)
 {
+    if (a.cells) {
+        const unsigned g = (unsigned)a.ncells;
+        if (up) subtree_up_adaptive_kernel<KS><<<g, 64 * col_blocks<KS>(), 0, s>>>(a);
+        else subtree_down_adaptive_kernel<KS><<<g, 256, 0, s>>>(a);
+        return;
+    }
     const unsigned g = 1u << (2 * a.base);
     if (up) subtree_up_kernel<KS><<<g, 64 * col_blocks<KS>(), 0, s>>>(a);
     else subtree_down_kernel<KS><<<g, 256, 0, s>>>(a);
