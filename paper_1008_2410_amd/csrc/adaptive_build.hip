@@ -95,121 +95,158 @@ __global__ __launch_bounds__(256) void ak_sorted(const uint64_t *__restrict__ ke
     xs[j] = xy[u];
 }
 
-__global__ void ak_root(int4 *cell, int2 *range, int *parent, int *coll, int n)
+// ---------------------------------------------------------------------------------
+// The cells of all levels at once.  In the sorted order a cell is a run of equal key prefixes,
+// and it exists when its parent's run is longer than smax; so every particle says by itself
+// which cells begin with it, from its key and those smax places away.  (Level by level, each
+// level waited for the host to learn how many cells the next one has: 16 levels of 3000001
+// clustered particles, 0.9 ms.)
+// ---------------------------------------------------------------------------------
+
+// The last level at which two keys lie in one cell.
+__device__ inline int common_level(uint32_t a, uint32_t b, int L)
 {
-    cell[0] = make_int4(0, 0, 0, 0);
-    range[0] = make_int2(0, n);
-    parent[0] = -1;
-    for (int j = 0; j < 8; ++j) coll[j] = -1;
+    const uint32_t x = a ^ b;
+    return x == 0 ? L : L - (33 - __builtin_clz(x)) / 2;
 }
 
-// Cells [c0, c0 + m) of level l: the leaf flag; for a cell that splits, the ends of its
-// four quadrants' particle ranges (stored in child until the children are numbered)
-// and the number of non-empty quadrants.
-__global__ __launch_bounds__(256) void ak_split(int4 *__restrict__ cell, const int2 *__restrict__ range,
-                                                 int4 *__restrict__ child, const uint32_t *__restrict__ skey, int c0,
-                                                 int m, int l, int L, int smax, uint32_t *__restrict__ nchild,
-                                                 unsigned int *__restrict__ nsplit)
+// The cells that begin with sorted particle j: levels `first` to `last` (none: last < first),
+// those of them below `split` split.
+struct CellsAt {
+    int first, last, split;
+};
+__device__ inline CellsAt cells_at(const uint32_t *__restrict__ skey, int64_t n, int64_t j, int smax, int L)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const int c = c0 + i;
-    const int2 r = range[c];
-    int4 cc = cell[c];
-    const bool split = r.y > smax && l < L;
-    cc.w = split ? 0 : 1;
-    cell[c] = cc;
-    if (!split) {
-        child[c] = make_int4(-1, -1, -1, -1);
-        nchild[i] = 0;
-        return;
-    }
-    atomicAdd(nsplit, 1u);
-    const int shift = 2 * (L - l - 1);
-    const uint64_t code = morton_encode((uint32_t)cc.y, (uint32_t)cc.z);
-    const int end = r.x + r.y;
-    int b[4];
-    int lo = r.x;
-    for (int q = 0; q < 3; ++q) {
-        const uint64_t next = code * 4 + q + 1;  // first code of the next quadrant
-        int a = lo, e = end;
-        while (a < e) {
-            const int mid = a + (e - a) / 2;
-            if (((uint64_t)skey[mid] >> shift) < next)
-                a = mid + 1;
-            else
-                e = mid;
-        }
-        b[q] = a;
-        lo = a;
-    }
-    b[3] = end;
-    uint32_t k = 0;
-    int prev = r.x;
-    for (int q = 0; q < 4; ++q) {
-        k += b[q] > prev;
-        prev = b[q];
-    }
-    child[c] = make_int4(b[0], b[1], b[2], b[3]);
-    nchild[i] = k;
-}
-
-// Children of the split cells of level l, numbered from `base` in the order of their
-// parents with quadrants ascending (Morton order on level l + 1).
-__global__ __launch_bounds__(256) void ak_children(int4 *__restrict__ cell, int2 *__restrict__ range,
-                                                    int *__restrict__ parent, int4 *__restrict__ child, int c0, int m,
-                                                    int l, const uint32_t *__restrict__ offs, int base)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const int c = c0 + i;
-    const int4 cc = cell[c];
-    if (cc.w) return;  // a leaf: child is already -1
-    const int4 b = child[c];
-    const int2 r = range[c];
-    int idx = base + (int)offs[i];
-    int prev = r.x;
-    int ch[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int hi = quadrant(b, q);
-        if (hi > prev) {
-            cell[idx] = make_int4(l + 1, 2 * cc.y + (q & 1), 2 * cc.z + (q >> 1), 0);
-            range[idx] = make_int2(prev, hi - prev);
-            parent[idx] = c;
-            ch[q] = idx++;
-        } else {
-            ch[q] = -1;
-        }
-        prev = hi;
-    }
-    child[c] = make_int4(ch[0], ch[1], ch[2], ch[3]);
-}
-
-// Same-level neighbours of the cells [c0, c0 + m) of level l >= 1 (slot order of nb_slot,
-// -1 where there is no cell).
-__global__ __launch_bounds__(256) void ak_neighbours(const int4 *__restrict__ cell, const int *__restrict__ parent,
-                                                      const int4 *__restrict__ child, int *__restrict__ coll, int c0,
-                                                      int m, int l)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const int c = c0 + i;
-    const int4 cc = cell[c];
-    const int P = parent[c];
-    const int nside = 1 << l, pix = cc.y >> 1, piy = cc.z >> 1;
-    for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-            if (!dx && !dy) continue;
-            const int nx = cc.y + dx, ny = cc.z + dy;
-            int r = -1;
-            if (nx >= 0 && ny >= 0 && nx < nside && ny < nside) {
-                const int qx = (nx >> 1) - pix, qy = (ny >> 1) - piy;
-                const int PP = (!qx && !qy) ? P : coll[(int64_t)P * 8 + nb_slot(qx, qy)];
-                if (PP >= 0) r = quadrant(child[PP], (nx & 1) | ((ny & 1) << 1));
+    const uint32_t me = skey[j];
+    // the run that begins with j is longer than smax down to this level
+    const int big = j + smax < n ? common_level(me, skey[j + smax], L) : -1;
+    const int split = min(big + 1, L);
+    if (j == 0) return CellsAt{0, min(big + 1, L), split};
+    const int c = common_level(skey[j - 1], me, L);  // the deepest cell j shares with its predecessor
+    if (c == L) return CellsAt{1, 0, 0};
+    bool exists = big >= c;  // that cell's run is longer than smax
+    if (!exists) {
+        if (j >= smax && common_level(skey[j - smax], me, L) >= c) {
+            exists = true;
+        } else {  // it begins within the smax places before j
+            const int shift = 2 * (L - c);
+            int64_t lo = j >= smax ? j - smax + 1 : 0, hi = j - 1;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) / 2;
+                if ((skey[mid] >> shift) == (me >> shift)) hi = mid;
+                else lo = mid + 1;
             }
-            coll[(int64_t)c * 8 + nb_slot(dx, dy)] = r;
+            exists = lo + smax < n && common_level(skey[lo], skey[lo + smax], L) >= c;
         }
+    }
+    if (!exists) return CellsAt{1, 0, 0};
+    return CellsAt{c + 1, max(c + 1, min(big + 1, L)), split};
+}
+
+constexpr int kLevels = 32;  // counters per kind: cells, split cells
+
+// How many cells begin with each particle, and the cells and split cells of every level.
+__global__ __launch_bounds__(256) void ak_cell_count(const uint32_t *__restrict__ skey, int64_t n, int smax, int L,
+                                                     uint32_t *__restrict__ ncells,
+                                                     unsigned long long *__restrict__ levels)
+{
+    __shared__ unsigned int h[2 * kLevels];
+    if (threadIdx.x < 2 * kLevels) h[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (int64_t)gridDim.x * 256) {
+        const CellsAt c = cells_at(skey, n, j, smax, L);
+        ncells[j] = (uint32_t)(c.last - c.first + 1);
+        for (int l = c.first; l <= c.last; ++l) {
+            atomicAdd(&h[l], 1u);
+            if (l < c.split) atomicAdd(&h[kLevels + l], 1u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * kLevels && h[threadIdx.x]) atomicAdd(&levels[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+}
+
+// The cells in the order of their first particles: sort key = level, value = first particle.
+__global__ __launch_bounds__(256) void ak_cell_fill(const uint32_t *__restrict__ skey, int64_t n, int smax, int L,
+                                                    const uint32_t *__restrict__ off, uint64_t *__restrict__ key,
+                                                    uint32_t *__restrict__ val)
+{
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (j >= n) return;
+    const CellsAt c = cells_at(skey, n, j, smax, L);
+    uint32_t o = off[j];
+    for (int l = c.first; l <= c.last; ++l, ++o) {
+        key[o] = (uint64_t)l;
+        val[o] = (uint32_t)j;
+    }
+}
+
+struct LevelOffsets {
+    int at[kLevels + 1];
+};
+
+// The cells in level order (and Morton order inside a level) from their first particles: square,
+// leaf flag, range, parent, the parent's child entry (child filled with -1 before), and code,
+// the cell's place in the Morton order of its level.
+__global__ __launch_bounds__(256) void ak_cells(const uint32_t *__restrict__ skey, int64_t n, int smax, int L, int K,
+                                                const LevelOffsets off, const uint32_t *__restrict__ start,
+                                                int4 *__restrict__ cell, int2 *__restrict__ range,
+                                                int *__restrict__ parent, int4 *__restrict__ child,
+                                                uint32_t *__restrict__ code)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= K) return;
+    int l = 0;
+    while (k >= off.at[l + 1]) ++l;
+    const int64_t j = start[k];
+    const int shift = 2 * (L - l);
+    const uint32_t me = skey[j], pre = shift < 32 ? me >> shift : 0u;
+    const bool split = l < L && j + smax < n && common_level(me, skey[j + smax], L) >= l;
+    // one past the run: within smax places of j unless the cell is split or of the last level
+    int64_t lo = j + 1, hi = split || l == L ? n : min(n, j + smax);
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if ((shift < 32 ? skey[mid] >> shift : 0u) == pre) lo = mid + 1;
+        else hi = mid;
+    }
+    cell[k] = make_int4(l, (int)morton_x(pre), (int)morton_y(pre), split ? 0 : 1);
+    range[k] = make_int2((int)j, (int)(lo - j));
+    code[k] = pre;
+    int P = -1;
+    if (l > 0) {  // the last cell of the level above that begins at or before j
+        int a = off.at[l - 1], b = off.at[l] - 1;
+        while (a < b) {
+            const int mid = (a + b + 1) / 2;
+            if (start[mid] <= (uint32_t)j) a = mid;
+            else b = mid - 1;
+        }
+        P = a;
+        ((int *)(child + P))[pre & 3u] = k;
+    }
+    parent[k] = P;
+}
+
+// Same-level neighbours of every cell (slot order of nb_slot, -1 where there is no cell).
+__global__ __launch_bounds__(256) void ak_neighbours(const int4 *__restrict__ cell, const uint32_t *__restrict__ code,
+                                                     int K, const LevelOffsets off, int *__restrict__ coll)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t k = t >> 3;
+    if (k >= K) return;
+    const int slot = (int)(t & 7), d = slot < 4 ? slot : slot + 1;
+    const int4 c = cell[k];
+    const int nx = c.y + d % 3 - 1, ny = c.z + d / 3 - 1, nside = 1 << c.x;
+    int r = -1;
+    if (nx >= 0 && ny >= 0 && nx < nside && ny < nside) {
+        const uint32_t want = (uint32_t)morton_encode((uint32_t)nx, (uint32_t)ny);
+        int a = off.at[c.x], b = off.at[c.x + 1];
+        while (a < b) {
+            const int mid = (a + b) / 2;
+            if (code[mid] < want) a = mid + 1;
+            else b = mid;
+        }
+        if (a < off.at[c.x + 1] && code[a] == want) r = a;
+    }
+    coll[t] = r;
 }
 
 // V list of every cell: children of the parent's neighbours that do not touch it.
@@ -346,11 +383,11 @@ __global__ __launch_bounds__(256) void ak_leaf_marks(const int4 *__restrict__ ce
     if (k < K && cell[k].w) flag[range[k].x] = 1;
 }
 
-// Leaf index (position in sorted order) of every leaf; deepest leaf level.
+// Leaf index (position in sorted order) of every leaf.
 __global__ __launch_bounds__(256) void ak_leaf_index(const int4 *__restrict__ cell, const int2 *__restrict__ range,
                                                       int K, const uint32_t *__restrict__ e,
                                                       int *__restrict__ leaf_index, int *__restrict__ leaves,
-                                                      int *__restrict__ leaf_start, unsigned int *__restrict__ deepest)
+                                                      int *__restrict__ leaf_start)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= K) return;
@@ -364,7 +401,6 @@ __global__ __launch_bounds__(256) void ak_leaf_index(const int4 *__restrict__ ce
     leaf_index[k] = li;
     leaves[li] = k;
     leaf_start[li] = first;
-    atomicMax(deepest, (unsigned int)c.x);
 }
 
 // Leaf of every sorted particle: the leaf whose first slot is the last flagged slot <= j.
@@ -514,11 +550,7 @@ __global__ __launch_bounds__(256) void ak_plan(const int *__restrict__ leaves, c
         v[kStMutualPairs] = (unsigned long long)mp;
         v[kStMutualItems] = (unsigned long long)items;
         v[kStUnits] = (unsigned long long)units;
-#pragma unroll
-        for (int q = 0; q < kStCount; ++q) {
-            for (int o2 = 32; o2 >= 1; o2 >>= 1) v[q] += __shfl_xor(v[q], o2);
-            if ((threadIdx.x & 63) == 0 && v[q]) atomicAdd(&stats[q], v[q]);
-        }
+        block_add<kStCount>(stats, v);
     }
 }
 
@@ -575,53 +607,6 @@ __global__ __launch_bounds__(256) void ak_adj_units(const int *__restrict__ leaf
         order[t] = (uint32_t)t;
     }
 }
-
-// The per-cell arrays while the levels are made: grown by doubling, first `used`
-// entries kept.  Released to the tree (cell, range, parent, child) or freed.
-struct CellStore {
-    int4 *cell = nullptr;
-    int2 *range = nullptr;
-    int *parent = nullptr;
-    int4 *child = nullptr;
-    int *coll = nullptr;  // 8 neighbour slots per cell
-    int64_t cap = 0;
-    hipStream_t s = nullptr;
-
-    template <typename T> void drop(T *&p, int per) { build_free(p, (size_t)cap * per * sizeof(T), s); }
-    ~CellStore()
-    {
-        drop(cell, 1);
-        drop(range, 1);
-        drop(parent, 1);
-        drop(child, 1);
-        drop(coll, 8);
-    }
-    template <typename T>
-    bool regrow(T *&p, int64_t ncap, int64_t used, int per, Status &st)
-    {
-        T *q = nullptr;
-        const size_t bytes = (size_t)ncap * per * sizeof(T);
-        if (!st.check(build_alloc((void **)&q, bytes, s), "adaptive tree cells")) return false;
-        if (used > 0 && !st.check(hipMemcpyAsync(q, p, (size_t)used * per * sizeof(T), hipMemcpyDeviceToDevice, s),
-                                  "adaptive tree cells")) {
-            build_free(q, bytes, s);
-            return false;
-        }
-        drop(p, per);
-        p = q;
-        return true;
-    }
-    bool reserve(int64_t need, int64_t used, Status &st)
-    {
-        if (need <= cap) return true;
-        const int64_t ncap = std::max<int64_t>(need, 2 * cap);
-        if (!regrow(cell, ncap, used, 1, st) || !regrow(range, ncap, used, 1, st) || !regrow(parent, ncap, used, 1, st) ||
-            !regrow(child, ncap, used, 1, st) || !regrow(coll, ncap, used, 8, st))
-            return false;
-        cap = ncap;
-        return true;
-    }
-};
 
 template <typename T>
 bool alloc_to(T *&p, int64_t count, hipStream_t s, Status &st, const char *what)
@@ -710,48 +695,49 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         return failed();
     ak_sorted<<<grid_for(n, 256), 256, 0, s>>>(key.p, val.p, xy2, n, d.perm, skey.p, d.xy);
 
-    // Stage 3a: cells, level by level.
-    CellStore cs;
-    cs.s = s;
-    Buf<unsigned int> nsplit;
-    if (!cs.reserve(std::max<int64_t>(1024, 4 * (n / (smax + 1)) + 64), 0, st) ||
-        !st.check(nsplit.alloc(L + 1, s), "adaptive tree build") ||
-        !st.check(hipMemsetAsync(nsplit.p, 0, (L + 1) * sizeof(unsigned int), s), "adaptive tree build"))
+    // Stage 3a: cells.
+    Buf<unsigned long long> levels;
+    Buf<uint32_t> cfirst, code;
+    Buf<uint64_t> clevel;
+    Buf<int> coll;
+    if (!st.check(levels.alloc(2 * kLevels, s), "adaptive tree build") ||
+        !st.check(hipMemsetAsync(levels.p, 0, 2 * kLevels * sizeof(unsigned long long), s), "adaptive tree build"))
         return failed();
-    ak_root<<<1, 1, 0, s>>>(cs.cell, cs.range, cs.parent, cs.coll, (int)n);
-    std::vector<int> level_off(L + 2, 0);
-    level_off[1] = 1;
-    int begin = 0, end = 1, l = 0;
-    for (;; ++l) {
-        const int m = end - begin;
-        Buf<uint32_t> nchild;
-        if (!st.check(nchild.alloc(m, s), "adaptive tree build")) return failed();
-        ak_split<<<grid_for(m, 256), 256, 0, s>>>(cs.cell, cs.range, cs.child, skey.p, begin, m, l, L, smax, nchild.p,
-                                                  nsplit.p + l);
-        if (l == L) break;
-        uint32_t total = 0;
-        if (!scan_exclusive(nchild.p, nchild.p, m, &total, s, st)) return failed();
-        if (total == 0) break;
-        if ((int64_t)end + total >= (int64_t(1) << 31)) {
+    ak_cell_count<<<std::min<unsigned>(grid_for(n, 256), 1024), 256, 0, s>>>(skey.p, n, smax, L, val.p, levels.p);
+    unsigned long long hl[2 * kLevels];
+    if (!scan_exclusive(val.p, val.p, n, nullptr, s, st) || !read_back(hl, levels.p, sizeof hl, s, st)) return failed();
+    LevelOffsets off{};
+    int64_t total = 0, splits = 0;
+    int deepest = 0;
+    t->inner_off.assign(L + 2, 0);
+    t->level_off.assign(L + 2, 0);
+    for (int l = 0; l <= L; ++l) {
+        total += (int64_t)hl[l];
+        splits += (int64_t)hl[kLevels + l];
+        if (total >= (int64_t(1) << 31)) {
             err = "adaptive tree: too many cells";
             return FMM_ENOMEM;
         }
-        if (!cs.reserve((int64_t)end + total, end, st)) return failed();
-        ak_children<<<grid_for(m, 256), 256, 0, s>>>(cs.cell, cs.range, cs.parent, cs.child, begin, m, l, nchild.p, end);
-        ak_neighbours<<<grid_for(total, 256), 256, 0, s>>>(cs.cell, cs.parent, cs.child, cs.coll, end, (int)total, l + 1);
-        if (!st.check(hipGetLastError(), "adaptive tree build")) return failed();
-        begin = end;
-        end += (int)total;
-        level_off[l + 2] = end;
+        if (hl[l] > 0) deepest = l;
+        t->level_off[l + 1] = (int)total;
+        t->inner_off[l + 1] = t->inner_off[l] + (l >= 2 ? (int)hl[kLevels + l] : 0);
     }
-    for (int k = l + 2; k <= L + 1; ++k) level_off[k] = end;
-    const int K = end;
+    for (int l = 0; l <= kLevels; ++l) off.at[l] = l <= L + 1 ? t->level_off[l] : (int)total;
+    const int K = (int)total;
+    const uint32_t NL = (uint32_t)(total - splits);
     t->ncells = K;
-    t->level_off = level_off;
-    std::vector<unsigned int> splits(L + 1);
-    if (!read_back(splits.data(), nsplit.p, (L + 1) * sizeof(unsigned int), s, st)) return failed();
-    t->inner_off.assign(L + 2, 0);
-    for (int k = 0; k <= L; ++k) t->inner_off[k + 1] = t->inner_off[k] + (k >= 2 ? (int)splits[k] : 0);
+    if (!st.check(cfirst.alloc(K, s), "adaptive tree cells") || !st.check(clevel.alloc(K, s), "adaptive tree cells") ||
+        !st.check(code.alloc(K, s), "adaptive tree cells") || !st.check(coll.alloc(8 * (int64_t)K, s), "adaptive tree cells") ||
+        !alloc_to(d.cell, K, s, st, "adaptive tree cells") || !alloc_to(d.range, K, s, st, "adaptive tree cells") ||
+        !alloc_to(d.parent, K, s, st, "adaptive tree cells") || !alloc_to(d.child, K, s, st, "adaptive tree cells") ||
+        !st.check(hipMemsetAsync(d.child, 0xff, (size_t)K * sizeof(int4), s), "adaptive tree cells"))
+        return failed();
+    ak_cell_fill<<<grid_for(n, 256), 256, 0, s>>>(skey.p, n, smax, L, val.p, clevel.p, cfirst.p);
+    if (!radix_sort(clevel, cfirst, K, 8, s, st)) return failed();
+    ak_cells<<<grid_for(K, 256), 256, 0, s>>>(skey.p, n, smax, L, K, off, cfirst.p, d.cell, d.range, d.parent, d.child,
+                                              code.p);
+    ak_neighbours<<<grid_for(8 * (int64_t)K, 256), 256, 0, s>>>(d.cell, code.p, K, off, coll.p);
+    if (!st.check(hipGetLastError(), "adaptive tree build")) return failed();
 
     // Stage 3b: lists.
     Buf<int> werr;
@@ -761,9 +747,9 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         !st.check(ucnt.alloc(K + 1, s, true), "adaptive tree lists") || !st.check(wcnt.alloc(K + 1, s, true), "adaptive tree lists") ||
         !st.check(vcnt.alloc(K + 1, s, true), "adaptive tree lists"))
         return failed();
-    ak_vlist<false><<<grid_for(K + 1, 256), 256, 0, s>>>(cs.cell, cs.parent, cs.child, cs.coll, K, vcnt.p, nullptr,
+    ak_vlist<false><<<grid_for(K + 1, 256), 256, 0, s>>>(d.cell, d.parent, d.child, coll.p, K, vcnt.p, nullptr,
                                                          nullptr);
-    ak_uwlist<false><<<grid_for(K + 1, 256), 256, 0, s>>>(cs.cell, cs.parent, cs.child, cs.coll, K, L, ucnt.p, wcnt.p,
+    ak_uwlist<false><<<grid_for(K + 1, 256), 256, 0, s>>>(d.cell, d.parent, d.child, coll.p, K, L, ucnt.p, wcnt.p,
                                                           nullptr, nullptr, nullptr, nullptr, nullptr, werr.p);
     uint32_t nv = 0, nu = 0, nw = 0;
     if (!scan_exclusive(vcnt.p, vcnt.p, K + 1, nullptr, s, st) || !scan_exclusive(ucnt.p, ucnt.p, K + 1, nullptr, s, st) ||
@@ -780,9 +766,9 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
     if (!alloc_to(d.v_idx, nv, s, st, "V list") || !alloc_to(d.u_idx, nu, s, st, "U list") ||
         !alloc_to(d.w_idx, nw, s, st, "W list") || !st.check(wown.alloc(nw, s, true), "W list"))
         return failed();
-    ak_vlist<true><<<grid_for(K + 1, 256), 256, 0, s>>>(cs.cell, cs.parent, cs.child, cs.coll, K, nullptr, d.v_off,
+    ak_vlist<true><<<grid_for(K + 1, 256), 256, 0, s>>>(d.cell, d.parent, d.child, coll.p, K, nullptr, d.v_off,
                                                         d.v_idx);
-    ak_uwlist<true><<<grid_for(K + 1, 256), 256, 0, s>>>(cs.cell, cs.parent, cs.child, cs.coll, K, L, nullptr, nullptr,
+    ak_uwlist<true><<<grid_for(K + 1, 256), 256, 0, s>>>(d.cell, d.parent, d.child, coll.p, K, L, nullptr, nullptr,
                                                          d.u_off, d.w_off, d.u_idx, d.w_idx, wown.p, werr.p);
     // X: the W entries (in owner order) stably sorted by the cell they name.
     {
@@ -800,52 +786,26 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         d.x_off = (int *)xcnt.release();
         d.x_idx = (int *)wown.release();
     }
-    {
-        int he = 0;
-        if (!read_back(&he, werr.p, sizeof he, s, st)) return failed();
-        if (he) {
-            err = "adaptive tree: list walk deeper than the stack";
-            return FMM_EDEVICE;
-        }
-    }
-
     // Stage 3c: leaves in sorted order, the leaf of every particle, tiles and their boxes.
     Buf<uint32_t> lflag, lscan;
     Buf<int> leaf_index, leaves;
-    Buf<unsigned int> deepest;
-    uint32_t NL = 0;
     if (!st.check(lflag.alloc(n, s), "adaptive tree leaves") || !st.check(lscan.alloc(n, s), "adaptive tree leaves") ||
         !st.check(hipMemsetAsync(lflag.p, 0, n * sizeof(uint32_t), s), "adaptive tree leaves") ||
-        !st.check(leaf_index.alloc(K, s), "adaptive tree leaves") ||
-        !st.check(deepest.alloc(1, s), "adaptive tree leaves") ||
-        !st.check(hipMemsetAsync(deepest.p, 0, sizeof(unsigned int), s), "adaptive tree leaves"))
+        !st.check(leaf_index.alloc(K, s), "adaptive tree leaves"))
         return failed();
-    ak_leaf_marks<<<grid_for(K, 256), 256, 0, s>>>(cs.cell, cs.range, K, lflag.p);
-    if (!scan_exclusive(lflag.p, lscan.p, n, &NL, s, st)) return failed();
+    ak_leaf_marks<<<grid_for(K, 256), 256, 0, s>>>(d.cell, d.range, K, lflag.p);
+    if (!scan_exclusive(lflag.p, lscan.p, n, nullptr, s, st)) return failed();
     if (!st.check(leaves.alloc(NL, s), "adaptive tree leaves") ||
         !alloc_to(d.leaf_start, (int64_t)NL + 1, s, st, "leaf offsets"))
         return failed();
-    ak_leaf_index<<<grid_for(K, 256), 256, 0, s>>>(cs.cell, cs.range, K, lscan.p, leaf_index.p, leaves.p, d.leaf_start,
-                                                   deepest.p);
+    ak_leaf_index<<<grid_for(K, 256), 256, 0, s>>>(d.cell, d.range, K, lscan.p, leaf_index.p, leaves.p, d.leaf_start);
     ak_set<<<1, 1, 0, s>>>(d.leaf_start + NL, (int)n);
     ak_leaf_of<<<grid_for(n, 256), 256, 0, s>>>(lflag.p, lscan.p, leaves.p, n, d.leaf_of);
-    uint32_t ntiles = 0;
-    {
-        Buf<uint32_t> nt;
-        if (!st.check(nt.alloc((int64_t)NL + 1, s, true), "tiles")) return failed();
-        ak_leaf_ntiles<<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, cs.range, (int)NL, nt.p);
-        if (!scan_exclusive(nt.p, nt.p, (int64_t)NL + 1, &ntiles, s, st)) return failed();
-        d.leaf_tile = (int *)nt.release();  // NL + 1 entries, the last = ntiles
-    }
-    Buf<int> tile_leaf;
-    if (!alloc_to(d.tile_start, K, s, st, "tiles") ||
-        !st.check(hipMemsetAsync(d.tile_start, 0, (size_t)K * sizeof(int), s), "tiles") ||
-        !st.check(tile_leaf.alloc(ntiles, s), "tiles") || !alloc_to(d.tile_box, ntiles, s, st, "tile boxes") ||
-        !alloc_to(d.tile_box_leaf, ntiles, s, st, "tile boxes"))
-        return failed();
-    ak_tiles<<<grid_for(NL, 256), 256, 0, s>>>(leaves.p, d.leaf_tile, (int)NL, d.tile_start, tile_leaf.p);
-    ak_tile_box<<<grid_for(ntiles, 256), 256, 0, s>>>(tile_leaf.p, leaves.p, d.leaf_tile, cs.cell, cs.range, d.xy,
-                                                      ntiles, t->x0, t->y0, t->side, d.tile_box, d.tile_box_leaf);
+    Buf<uint32_t> ntile;
+    if (!st.check(ntile.alloc((int64_t)NL + 1, s, true), "tiles")) return failed();
+    ak_leaf_ntiles<<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, d.range, (int)NL, ntile.p);
+    if (!scan_exclusive(ntile.p, ntile.p, (int64_t)NL + 1, nullptr, s, st)) return failed();
+    d.leaf_tile = (int *)ntile.release();  // NL + 1 entries, the last = the number of tiles
 
     // Stage 3d: the near-field plan, heaviest first.
     Buf<uint32_t> pcnt;
@@ -857,50 +817,55 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         !st.check(stats.alloc(kStCount, s), "near-field plan") ||
         !st.check(hipMemsetAsync(stats.p, 0, kStCount * sizeof(unsigned long long), s), "near-field plan"))
         return failed();
-    ak_plan<false><<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, leaf_index.p, (int)NL, cs.cell, cs.range,
-                                                                   cs.coll, d.u_off, d.u_idx, t->dense_leaf, pcnt.p,
+    ak_plan<false><<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, leaf_index.p, (int)NL, d.cell, d.range,
+                                                                   coll.p, d.u_off, d.u_idx, t->dense_leaf, pcnt.p,
                                                                    nullptr, nullptr, nullptr, nullptr, d.mask,
                                                                    stats.p);
-    if (!scan_exclusive(pcnt.p, pcnt.p, (int64_t)NL + 1, &nwork, s, st)) return failed();
+    unsigned long long hs[kStCount];
+    uint32_t ntiles = 0;
+    if (!scan_exclusive(pcnt.p, pcnt.p, (int64_t)NL + 1, nullptr, s, st) ||
+        !st.check(hipMemcpyAsync(&nwork, pcnt.p + NL, sizeof nwork, hipMemcpyDeviceToHost, s), "near-field plan") ||
+        !st.check(hipMemcpyAsync(&ntiles, d.leaf_tile + NL, sizeof ntiles, hipMemcpyDeviceToHost, s), "tiles") ||
+        !read_back(hs, stats.p, sizeof hs, s, st))
+        return failed();
+    Buf<int> tile_leaf;
+    if (!alloc_to(d.tile_start, K, s, st, "tiles") ||
+        !st.check(hipMemsetAsync(d.tile_start, 0, (size_t)K * sizeof(int), s), "tiles") ||
+        !st.check(tile_leaf.alloc(ntiles, s), "tiles") || !alloc_to(d.tile_box, ntiles, s, st, "tile boxes") ||
+        !alloc_to(d.tile_box_leaf, ntiles, s, st, "tile boxes"))
+        return failed();
+    ak_tiles<<<grid_for(NL, 256), 256, 0, s>>>(leaves.p, d.leaf_tile, (int)NL, d.tile_start, tile_leaf.p);
+    ak_tile_box<<<grid_for(ntiles, 256), 256, 0, s>>>(tile_leaf.p, leaves.p, d.leaf_tile, d.cell, d.range, d.xy,
+                                                      ntiles, t->x0, t->y0, t->side, d.tile_box, d.tile_box_leaf);
     Buf<int4> work;
     Buf<uint64_t> cost;
     Buf<uint32_t> order;
     if (!st.check(work.alloc(nwork, s), "near-field plan") || !st.check(cost.alloc(nwork, s), "near-field plan") ||
         !st.check(order.alloc(nwork, s), "near-field plan"))
         return failed();
-    ak_plan<true><<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, leaf_index.p, (int)NL, cs.cell, cs.range,
-                                                                  cs.coll, d.u_off, d.u_idx, t->dense_leaf, nullptr,
+    ak_plan<true><<<grid_for((int64_t)NL + 1, 256), 256, 0, s>>>(leaves.p, leaf_index.p, (int)NL, d.cell, d.range,
+                                                                  coll.p, d.u_off, d.u_idx, t->dense_leaf, nullptr,
                                                                   (const int *)pcnt.p, work.p, cost.p, order.p, nullptr,
                                                                   nullptr);
-    unsigned long long hs[kStCount];
-    if (!read_back(hs, stats.p, sizeof hs, s, st)) return failed();
     if (!alloc_to(d.work, nwork, s, st, "near-field work")) return failed();
     if (!radix_sort(cost, order, nwork, 8, s, st)) return failed();
     ak_gather_work<<<grid_for(nwork, 256), 256, 0, s>>>(work.p, order.p, nwork, d.work);
 
     // Leaves and split cells of level >= 2, in cell order.
-    uint32_t np2m = 0, ninner = 0;
+    const uint32_t ninner = (uint32_t)t->inner_off[L + 1];
+    const uint32_t np2m = L >= 2 ? (uint32_t)(K - t->level_off[2]) - ninner : 0u;
     {
         Buf<uint32_t> fl, fi, pl, pi;
         if (!st.check(fl.alloc(K + 1, s), "adaptive tree build") || !st.check(fi.alloc(K + 1, s), "adaptive tree build") ||
             !st.check(pl.alloc(K + 1, s), "adaptive tree build") || !st.check(pi.alloc(K + 1, s), "adaptive tree build"))
             return failed();
-        ak_cell_flags<<<grid_for(K + 1, 256), 256, 0, s>>>(cs.cell, K, fl.p, fi.p);
-        if (!scan_exclusive(fl.p, pl.p, K + 1, nullptr, s, st) || !scan_exclusive(fi.p, pi.p, K + 1, nullptr, s, st) ||
-            !st.check(hipMemcpyAsync(&np2m, pl.p + K, sizeof np2m, hipMemcpyDeviceToHost, s), "adaptive tree build") ||
-            !read_back(&ninner, pi.p + K, sizeof ninner, s, st))
+        ak_cell_flags<<<grid_for(K + 1, 256), 256, 0, s>>>(d.cell, K, fl.p, fi.p);
+        if (!scan_exclusive(fl.p, pl.p, K + 1, nullptr, s, st) || !scan_exclusive(fi.p, pi.p, K + 1, nullptr, s, st))
             return failed();
         if (!alloc_to(d.p2m_cells, np2m, s, st, "leaves with expansions") || !alloc_to(d.inner, ninner, s, st, "split cells"))
             return failed();
         ak_compact<<<grid_for(K, 256), 256, 0, s>>>(fl.p, pl.p, K, d.p2m_cells);
         ak_compact<<<grid_for(K, 256), 256, 0, s>>>(fi.p, pi.p, K, d.inner);
-    }
-    unsigned int hdeep = 0;
-    if (!read_back(&hdeep, deepest.p, sizeof hdeep, s, st) || !st.check(hipGetLastError(), "adaptive tree build"))
-        return failed();
-    if ((int64_t)ninner != (int64_t)t->inner_off[L + 1]) {
-        err = "adaptive tree: inconsistent split-cell count";
-        return FMM_EDEVICE;
     }
 
     // Staging slots of the two-pass permutations between user and sorted order.
@@ -909,17 +874,14 @@ int build_atree_device(fmm_atree *t, const double *xy, const double *root_box, h
         !alloc_to(d.st1, n, s, st, "staging array") || !build_staging(d.perm, n, s, st, t->stage_shift, d.gpos1, d.gpos2))
         return failed();
 
-    // The cell arrays pass to the tree; the neighbour slots were the build's alone.
-    d.cell = cs.cell;
-    d.range = cs.range;
-    d.parent = cs.parent;
-    d.child = cs.child;
-    cs.cell = nullptr;
-    cs.range = nullptr;
-    cs.parent = nullptr;
-    cs.child = nullptr;
+    int he = 0;
+    if (!read_back(&he, werr.p, sizeof he, s, st) || !st.check(hipGetLastError(), "adaptive tree build")) return failed();
+    if (he) {
+        err = "adaptive tree: list walk deeper than the stack";
+        return FMM_EDEVICE;
+    }
 
-    const int64_t sz[FMM_AT_COUNT] = {K, (int64_t)NL, (int64_t)nu, (int64_t)nv, (int64_t)nw, (int64_t)nw, (int64_t)hdeep,
+    const int64_t sz[FMM_AT_COUNT] = {K, (int64_t)NL, (int64_t)nu, (int64_t)nv, (int64_t)nw, (int64_t)nw, deepest,
                                       (int64_t)hs[kStPairs]};
     std::copy(sz, sz + FMM_AT_COUNT, t->sizes);
     t->np2m = np2m;
@@ -985,28 +947,33 @@ __global__ __launch_bounds__(256) void ak_m2l_keys(const int4 *__restrict__ cell
 // Source cell of each interaction offset {dx, dy} of the cell's class (entries 28 q ..
 // 28 q + 26 of the operator tables) from its V list; a V member of another level or at an
 // offset outside the class's 27 counts into *bad.
+// (vslot holds -1 before; eight lanes per cell.)
 __global__ __launch_bounds__(256) void ak_vslot(const int4 *__restrict__ cell, int first, int ncl,
                                                 const int *__restrict__ v_off, const int *__restrict__ v_idx,
                                                 const int4 *__restrict__ entries, int *__restrict__ vslot,
                                                 unsigned int *__restrict__ bad)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ int place[4][49];  // of offset 7 (dx + 3) + dy + 3 among the class's 27, or -1
+    for (int t = threadIdx.x; t < 4 * 49; t += 256) (&place[0][0])[t] = -1;
+    __syncthreads();
+    if (threadIdx.x < 4 * 27) {
+        const int q = threadIdx.x / 27, j = threadIdx.x % 27;
+        const int4 en = entries[28 * q + j];
+        place[q][7 * (en.x + 3) + en.y + 3] = j;
+    }
+    __syncthreads();
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;
     if (i >= ncl) return;
-    const int k = first + i;
+    const int k = first + (int)i;
     const int4 c = cell[k];
     const int q = (c.y & 1) | ((c.z & 1) << 1);
-    int *vs = vslot + (int64_t)i * 27;
-    for (int j = 0; j < 27; ++j) vs[j] = -1;
-    for (int e = v_off[k]; e < v_off[k + 1]; ++e) {
+    int *vs = vslot + i * 27;
+    for (int e = v_off[k] + (threadIdx.x & 7); e < v_off[k + 1]; e += 8) {
         const int S = v_idx[e];
         const int4 cs = cell[S];
         const int dx = cs.y - c.y, dy = cs.z - c.z;
-        int slot = -1;
-        for (int j = 0; j < 27; ++j) {
-            const int4 en = entries[28 * q + j];
-            if (en.x == dx && en.y == dy) slot = j;
-        }
-        if (slot < 0 || cs.x != c.x) atomicAdd(bad, 1u);
+        const int slot = cs.x == c.x && abs(dx) <= 3 && abs(dy) <= 3 ? place[q][7 * (dx + 3) + dy + 3] : -1;
+        if (slot < 0) atomicAdd(bad, 1u);
         else vs[slot] = S;
     }
 }
@@ -1039,7 +1006,8 @@ int build_atree_m2l_plan(fmm_atree *t, const int4 *entries, hipStream_t s, std::
         !alloc_to(targets, ncl, s, st, "M2L plan") || !alloc_to(vslot, 27 * (int64_t)ncl, s, st, "M2L plan"))
         return failed();
     ak_m2l_keys<<<grid_for(ncl, 256), 256, 0, s>>>(t->d.cell, first, ncl, nseg, key.p, val.p, cnt.p);
-    ak_vslot<<<grid_for(ncl, 256), 256, 0, s>>>(t->d.cell, first, ncl, t->d.v_off, t->d.v_idx, entries, vslot,
+    if (!st.check(hipMemsetAsync(vslot, 0xff, 27 * (size_t)ncl * sizeof(int), s), "M2L plan")) return failed();
+    ak_vslot<<<grid_for(8 * (int64_t)ncl, 256), 256, 0, s>>>(t->d.cell, first, ncl, t->d.v_off, t->d.v_idx, entries, vslot,
                                                 cnt.p + nseg);
     // stable by segment: Morton order inside a class as inside a level
     if (!radix_sort(key, val, ncl, 6, s, st) ||

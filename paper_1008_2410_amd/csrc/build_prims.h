@@ -191,6 +191,27 @@ __host__ __device__ inline uint64_t cost_order(uint64_t cost)
     return 255 - (4 * (uint64_t)e + (cost >> e));
 }
 
+// The sums of v[0..NV) over a workgroup of 256 threads (all of them), added to dst by one thread
+// each: an atomic per wavefront and value had every wavefront of the launch wait in line for the
+// same few addresses (2^20 particles at depth 8: 28 us for three sums over 65536 leaves).
+template <int NV>
+__device__ __forceinline__ void block_add(unsigned long long *dst, const unsigned long long (&v)[NV])
+{
+    __shared__ unsigned long long part[4][NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        unsigned long long x = v[q];
+        for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][q] = x;
+    }
+    __syncthreads();
+    if (threadIdx.x < NV) {
+        const unsigned long long x =
+            part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
+        if (x) atomicAdd(&dst[threadIdx.x], x);
+    }
+}
+
 // Staging slots of the two-pass permutations for the sorted order perm (sorted slot ->
 // user index, device): gpos1 (user index -> staging slot) and gpos2 (sorted slot -> staging
 // slot of its user index).  Buckets of 2^shift sorted slots, ordered by user index

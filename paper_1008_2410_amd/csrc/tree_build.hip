@@ -488,13 +488,6 @@ __global__ void k_sizes(const uint32_t *__restrict__ tile_start, const uint32_t 
     }
 }
 
-// The sum of v over the wavefront, added to *dst by one lane.
-__device__ __forceinline__ void wave_add(unsigned long long *dst, unsigned long long v)
-{
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, v);
-}
-
 __device__ inline int leaf_count(const int *__restrict__ ls, int nside, int x, int y)
 {
     if (x < 0 || y < 0 || x >= nside || y >= nside) return 0;
@@ -518,11 +511,15 @@ __global__ __launch_bounds__(256) void k_leaf_stats(const int *__restrict__ ls, 
         for (int dy = -1; dy <= 1; ++dy)
             for (int dx = -1; dx <= 1; ++dx) nsrc += leaf_count(ls, nside, x + dx, y + dy);
     }
-    wave_add(&stats[0], (unsigned long long)((int64_t)nt * nsrc));
-    wave_add(&stats[1], nt > 0 ? 1ull : 0ull);
+    __shared__ int top[4];
     int most = nt;
     for (int o = 32; o >= 1; o >>= 1) most = max(most, __shfl_xor(most, o));
-    if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(&stats[2], (unsigned long long)most);
+    if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = most;
+    block_add<2>(stats, {(unsigned long long)((int64_t)nt * nsrc), nt > 0 ? 1ull : 0ull});  // (a barrier inside)
+    if (threadIdx.x == 0) {
+        most = max(max(top[0], top[1]), max(top[2], top[3]));
+        if (most > 0) atomicMax(&stats[2], (unsigned long long)most);
+    }
     if (nt == 0) return;
     uint32_t tt = tile_start[c];
     for (int c0 = 0; c0 < nt; c0 += 64, ++tt) {
@@ -559,7 +556,7 @@ __global__ __launch_bounds__(256) void k_m2l_count(const int *__restrict__ lists
                 if (counts[level_base(l) + morton_encode((uint32_t)sx, (uint32_t)sy)] > 0) ++m;
             }
     }
-    wave_add(&stats[3], m);
+    block_add<1>(&stats[3], {m});
 }
 
 template <typename T>
@@ -701,10 +698,9 @@ __global__ __launch_bounds__(256) void k_plan_cost(const int *__restrict__ ls, i
                 cost += cst;
             });
     }
-    wave_add(&stats[kPlanUnits], (unsigned long long)units);
-    wave_add(&stats[kPlanItems], (unsigned long long)items);
-    wave_add(&stats[kPlanPairs], (unsigned long long)pairs);
-    wave_add(&stats[kPlanCost], (unsigned long long)cost);
+    static_assert(kPlanUnits == 0 && kPlanItems == 1 && kPlanPairs == 2 && kPlanCost == 3, "added together");
+    block_add<4>(stats, {(unsigned long long)units, (unsigned long long)items, (unsigned long long)pairs,
+                         (unsigned long long)cost});
     if (c < nleaf) mask[c] = (uint16_t)m;
 }
 
@@ -733,11 +729,8 @@ __global__ __launch_bounds__(256) void k_plan_count(const int *__restrict__ ls, 
                 sums += (unsigned long long)sp.parts * min(nt, nr);
             });
     }
-    if (__any(split > 0)) {
-        wave_add(&stats[kPlanSplit], split);
-        wave_add(&stats[kPlanParts], parts);
-        wave_add(&stats[kPlanSums], sums);
-    }
+    static_assert(kPlanParts == kPlanSplit + 1 && kPlanSums == kPlanSplit + 2, "added together");
+    block_add<3>(stats + kPlanSplit, {split, parts, sums});
     if (c <= nleaf) nentries[c] = entries;
 }
 
