@@ -59,23 +59,6 @@ __global__ __launch_bounds__(256) void at_coords_kernel(int n, const int *__rest
     pos[i] = mk<T>((T)(z.x - c.x), (T)(z.y - c.y));
 }
 
-// One step of a wavefront butterfly over all N coefficients (independent shuffles).
-template <int N>
-__device__ __forceinline__ void butterfly_step(double2 (&acc)[N], int o)
-{
-    double sx[N], sy[N];
-#pragma unroll
-    for (int m = 0; m < N; ++m) {
-        sx[m] = __shfl_xor(acc[m].x, o);
-        sy[m] = __shfl_xor(acc[m].y, o);
-    }
-#pragma unroll
-    for (int m = 0; m < N; ++m) {
-        acc[m].x += sx[m];
-        acc[m].y += sy[m];
-    }
-}
-
 // Charge of sorted particle j: c_j = -i Gamma_j / (2 pi), or (CPLX) the complex charge
 // q_j of the adjoint pass.
 template <bool CPLX>
@@ -88,8 +71,7 @@ __device__ __forceinline__ double2 charge(const double *__restrict__ gamma, cons
 // P2M (stage 4) at the leaves of level >= 2, G lanes per leaf (64/G leaves per
 // wavefront):
 //   a_m / w^m = sum_j c_j xi_j^m,  xi_j = (z_j - c)/w,
-// the G lanes over the leaf's particles, then a butterfly over the G lanes per
-// coefficient (log2 G steps of independent shuffles).
+// the G lanes over the leaf's particles, then the sums over the G lanes by halving.
 template <int PMAX, bool CPLX, int G>
 __global__ __launch_bounds__(64) void at_p2m_kernel(const int *__restrict__ cells, int ncells,
                                                      const int4 *__restrict__ cell, const int2 *__restrict__ range,
@@ -106,38 +88,30 @@ __global__ __launch_bounds__(64) void at_p2m_kernel(const int *__restrict__ cell
     const double w = ldexp(side, -c.x);
     const double rw = 1.0 / w;
     const double2 ctr = cell_centre(x0, y0, side, c);
-    // PMAX coefficients throughout (those at m >= p are never stored): no branches on
-    // p, so the butterfly below runs step by step over all coefficients at once
-    double2 acc[PMAX];
+    // PMAX coefficients throughout (those at m >= p are never stored): no branches on p
+    constexpr int NC = 2 * PMAX;
+    double acc[NC];
 #pragma unroll
-    for (int m = 0; m < PMAX; ++m) acc[m] = make_double2(0.0, 0.0);
+    for (int m = 0; m < NC; ++m) acc[m] = 0.0;
     for (int j = r.x + g; j < r.x + r.y; j += G) {
         const double2 z = xy[j];
         const double2 xi = make_double2((z.x - ctr.x) * rw, (z.y - ctr.y) * rw);
         double2 pw = charge<CPLX>(gamma, q, j);
 #pragma unroll
         for (int m = 0; m < PMAX; ++m) {
-            acc[m].x += pw.x;
-            acc[m].y += pw.y;
+            acc[2 * m] += pw.x;
+            acc[2 * m + 1] += pw.y;
             pw = cmul<double>(pw, xi);
         }
     }
-#pragma unroll
-    for (int o = G / 2; o >= 1; o >>= 1) butterfly_step<PMAX>(acc, o);
-    // every lane of the group holds the sums; its first lane stores them (constant
-    // indices: a lane-dependent pick would make the compiler address the array in
-    // scratch memory)
-    if (valid && g == 0)
-#pragma unroll
-        for (int m = 0; m < PMAX; ++m)
-            if (m < p) mp[(int64_t)k * p + m] = acc[m];
+    lane_halve<double, NC, NC, G / 2>(acc, lane);
+    if (valid) store_halved<double, NC, G>(acc, g, 2 * p, (double *)(mp + (int64_t)k * p));
 }
 
 // P2L from X, written to the locals of the cells with a non-empty X list before the M2L
 // adds to them, G lanes per cell (64/G cells per wavefront):
 //   b_l = -sum_{j in A} c_j u_j^(l+1),  u_j = w/(z_j - c),
-// the G lanes over the particles of a source leaf, then a butterfly over the G lanes per
-// coefficient.  (One thread per cell was a serial chain over the list's particles.)
+// the G lanes over the particles of a source leaf, then the sums over the G lanes by halving.  (One thread per cell was a serial chain over the list's particles.)
 template <int PMAX, bool CPLX, int G>
 __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const int4 *__restrict__ cell,
                                                      const int *__restrict__ x_off, const int *__restrict__ x_idx,
@@ -152,9 +126,10 @@ __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const
     const int e0 = x_off[k], e1 = t < ncells ? x_off[k + 1] : e0;
     if (!__any(e0 < e1)) return;  // a group without a list idles (its shuffles stay inside it)
     const int4 c = cell[k];
-    double2 b[PMAX];
+    constexpr int NC = 2 * PMAX;
+    double b[NC];
 #pragma unroll
-    for (int l = 0; l < PMAX; ++l) b[l] = make_double2(0.0, 0.0);
+    for (int l = 0; l < NC; ++l) b[l] = 0.0;
     const double rw = 1.0 / ldexp(side, -c.x);
     const double2 ctr = cell_centre(x0, y0, side, c);
     for (int e = e0; e < e1; ++e) {
@@ -166,18 +141,14 @@ __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const
             double2 ul = cmul<double>(cj, u);  // c_j u^(l+1)
 #pragma unroll
             for (int l = 0; l < PMAX; ++l) {
-                b[l].x -= ul.x;
-                b[l].y -= ul.y;
+                b[2 * l] -= ul.x;
+                b[2 * l + 1] -= ul.y;
                 ul = cmul<double>(ul, u);
             }
         }
     }
-#pragma unroll
-    for (int o = G / 2; o >= 1; o >>= 1) butterfly_step<PMAX>(b, o);
-    if (e0 < e1 && g == 0)
-#pragma unroll
-        for (int l = 0; l < PMAX; ++l)
-            if (l < p) lo[(int64_t)k * p + l] = b[l];
+    lane_halve<double, NC, NC, G / 2>(b, lane);
+    if (e0 < e1) store_halved<double, NC, G>(b, g, 2 * p, (double *)(lo + (int64_t)k * p));
 }
 
 // Near field (stage 9) over U.  One wavefront per work entry:

@@ -369,36 +369,12 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 
     else p2p_force_unit<T, KIND>(u, lds.a, lds.qa, rec, mt, nside, step, scale, dense, near, near_phi);
 }
 
-// Sum over the lanes of a group of each of NC values (NC = 32 or 64) by recursive halving:
-// at offset o a lane keeps the half of its values that its lane bit o selects and adds its
-// partner's copy of that half.  Starting from O = G/2, lane g of a group of G ends with the
-// totals of values g NC/G on in v[0 .. NC/G) (G <= NC; with G = 2 NC both lanes of a pair
-// hold value g/2).  Shuffles only: no LDS, so the kernel fits beside near-field workgroups
-// that hold the LDS.
-template <typename TC, int NC, int W, int O>
-__device__ __forceinline__ void lane_halve(TC (&v)[NC], int lane)
-{
-    if constexpr (O >= 1) {
-        if constexpr (W > 1) {
-            const bool hi = (lane & O) != 0;
-#pragma unroll
-            for (int k = 0; k < W / 2; ++k) {
-                const TC send = hi ? v[k] : v[k + W / 2];
-                const TC keep = hi ? v[k + W / 2] : v[k];
-                v[k] = keep + __shfl_xor(send, O);
-            }
-            lane_halve<TC, NC, W / 2, O / 2>(v, lane);
-        } else {
-            v[0] += __shfl_xor(v[0], O);
-            lane_halve<TC, NC, 1, O / 2>(v, lane);
-        }
-    }
-}
-
 // Stage 4, P2M: a_m / w^m = sum_j c_j xi_j^m, G lanes per leaf (64/G leaves per wavefront),
-// each over every G-th particle.  G follows the mean occupancy (p2m_launch): a wavefront
-// per sparse leaf idles most lanes and pays the whole reduction for a few particles (2^22
-// uniform particles in 2^20 leaves: 577 us).
+// each over every G-th particle.  Bound by the chain of loads before a leaf's first term (list,
+// offsets, staging slot, circulation), so several leaves share a wavefront; G follows the mean
+// occupancy (p2m_launch).  2^24 patch particles at depth 10, FP32: 285 us with a wavefront per
+// leaf, 252 with 16 lanes, 220 with 32; 2^22 at depth 9: 77, 60 and 54.  (A wavefront per
+// sparse leaf idles most lanes: 2^22 uniform particles in 2^20 leaves, 577 us.)
 template <typename TR, typename TC, int PMAX, int G>
 __global__ __launch_bounds__(64) void p2m_kernel(const int *__restrict__ leaves, int nleaves,
                                                   const int *__restrict__ leaf_start,
@@ -449,14 +425,7 @@ __global__ __launch_bounds__(64) void p2m_kernel(const int *__restrict__ leaves,
         }
     }
     lane_halve<TC, NC, NC, G / 2>(v, lane);
-    TC *o = (TC *)out + (int64_t)leaf * 2 * p;
-    if constexpr (G > NC) {
-        if (valid && (g & 1) == 0 && g / 2 < 2 * p) o[g / 2] = v[0];
-    } else {
-#pragma unroll
-        for (int k = 0; k < NC / G; ++k)
-            if (valid && g * (NC / G) + k < 2 * p) o[g * (NC / G) + k] = v[k];
-    }
+    if (valid) store_halved<TC, NC, G>(v, g, 2 * p, (TC *)out + (int64_t)leaf * 2 * p);
 }
 
 // ---------------------------------------------------------------------------------
@@ -579,10 +548,10 @@ void p2m_launch(const FarArgs &a, hipStream_t s)
     if (a.p <= 16) {
         if (mean <= 6) go(p2m_kernel<TR, TC, 16, 8>, 8);
         else if (mean <= 32) go(p2m_kernel<TR, TC, 16, 16>, 4);
-        else go(p2m_kernel<TR, TC, 16, 64>, 1);
+        else go(p2m_kernel<TR, TC, 16, 32>, 2);
     } else {
         if (mean <= 32) go(p2m_kernel<TR, TC, 32, 16>, 4);
-        else go(p2m_kernel<TR, TC, 32, 64>, 1);
+        else go(p2m_kernel<TR, TC, 32, 32>, 2);
     }
 }
 
