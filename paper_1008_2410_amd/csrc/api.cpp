@@ -356,21 +356,22 @@ bool call_overlaps(const fmm_tree *t, int precision)
     return precision == FMM_FP64 || far_near_ratio(t) <= kSerialRatio;
 }
 
-// Near-field occupancy cap of a call (FMM_OPT_NEAR_OCCUPANCY), automatic from the tree:
-//  - mixed, leaves of more than ~2500 near-field pairs per particle and a work list of at
-//    least 64K entries (2^22-2^24 patch particles at depths 8-9): 3 wavefronts per SIMD, at
-//    which the near field itself runs faster (2^24 patches at depth 9: 28.5 ms against 32.4
-//    uncapped; 2^23: 8.1 against 9.1).  With fewer entries the cap idles the chip (uniform
-//    2^22 particles at depth 6, 20K entries: 9.5 ms at cap 3 against 7.6 uncapped);
-//  - mixed, by the predicted far/near ratio r (the far chain takes the slots the cap
-//    leaves): r < 0.05 none, r < 0.3 six (2^24 patches at depth 10: 6.65 ms against 6.84 at
-//    five and 7.00 uncapped; 2^22 at depth 9: 1.50 against 1.56 and 1.70), r < 1 five (10^6
-//    patch particles at depth 8: four to six within 0.004 of 0.42 ms, 0.454 uncapped), above
-//    three (uniform 2^20 at depth 8: 0.274 ms against 0.294 at four and 0.308 uncapped; 2^22
-//    at depth 10: 2.44 against 2.55 and 2.53);
-//  - FP64 (at most 5 wavefronts per SIMD): r < 0.05 none, r < 0.3 four, r < 1 three (7 10^5
-//    patch particles at depth 8: 0.561 ms against 0.620 at four and 0.632 uncapped), above two
-//    (1024^2 lattice, depth 8, p = 12: 0.416 against 0.435 at three and 0.457 uncapped);
+// Near-field occupancy cap of a call (FMM_OPT_NEAR_OCCUPANCY), automatic from the tree: the far
+// chain takes the slots the cap leaves.  By the predicted far/near ratio r and near-field time T
+// (best cap in brackets, from all caps on 40 trees):
+//  - r < 0.05: none (2^24 patch particles at depth 9, mixed: 21.1 ms uncapped, 21.6 at six,
+//    26.7 at three);
+//  - mixed, r < 0.3 or T >= 0.25 ms: six (2^24 patches at depth 10: 7.47 ms [7.45], 2^23 at
+//    depth 9: 5.94, 5.98 uncapped, 7.34 at three; uniform 2^22 at depth 10: 1.57 against 1.68 at
+//    four and 2.02 at three, at depth 9: 0.777 against 0.831 and 0.958);
+//  - mixed, T >= 0.1 ms: five for r < 1 (2^20 uniform at depth 7: 0.261 [0.255 at six]), else
+//    four (2^21 uniform at depth 9: 0.482, 0.505 at five, 0.581 at three);
+//  - mixed, smaller: three for r < 2.2 (2^20 uniform at depth 8: 0.230, 0.240 at five), else two
+//    (2^19 at depth 8: 0.195, 0.204 at three and at six);
+//  - FP64 (at most 5 wavefronts per SIMD), r < 1.2: four (2^21 patches at depth 9: 1.62 ms, 1.69
+//    at three and uncapped; 4 10^5 at depth 7: 0.565, 0.600 and 0.571), else three (1024^2
+//    lattice, depth 8, p = 12: 0.364, 0.380 at four, 0.413 at two, 0.397 uncapped), two below
+//    T = 0.05 ms (200003 uniform at depth 6, p = 24: 0.168, 0.176 at three, 0.206 uncapped);
 //  - a work list of less than 4096 entries leaves slots free by itself: no cap.
 int choose_occupancy(const fmm_tree *t, int precision, bool overlap)
 {
@@ -378,12 +379,12 @@ int choose_occupancy(const fmm_tree *t, int precision, bool overlap)
     if (t->near_occupancy >= 0) return t->near_occupancy;
     const int64_t entries = use_mutual(t) ? t->nnear_work : t->nunits;
     if (entries < 4096) return 0;
-    const double r = far_near_ratio(t);
-    if (precision == FMM_FP64) return r < 0.05 ? 0 : r < 0.3 ? 4 : r < 1.0 ? 3 : 2;
-    if ((double)t->p2p_pairs >= 2500.0 * (double)t->n && entries >= 65536) return 3;
+    const double r = far_near_ratio(t), near = kNear0 + near_work_ms(t);
     if (r < 0.05) return 0;
-    if (r < 0.3) return 6;
-    return r < 1.0 ? 5 : 3;
+    if (precision == FMM_FP64) return r < 1.2 ? 4 : near < 0.05 ? 2 : 3;
+    if (r < 0.3 || near >= 0.25) return 6;
+    if (near >= 0.1) return r < 1.0 ? 5 : 4;
+    return r < 2.2 ? 3 : 2;
 }
 
 struct Timing {
