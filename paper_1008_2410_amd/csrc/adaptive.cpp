@@ -320,12 +320,20 @@ int check_eval(const fmm_atree *t, const double *gamma, double sigma, int p, int
 // Near-field occupancy cap of a forward call (FMM_OPT_NEAR_OCCUPANCY), for the far chain
 // on the other stream.  Without a cap the near-field workgroups take every wavefront slot
 // and the far kernels wait for them to retire, so the two hardly overlap (2^24 particles:
-// 9.78 ms beside each other against 9.83 ms one after the other).  Automatic (mixed
-// precision): the stage times predicted from the tree's sizes (ms, fitted to the kernels
-// run alone on Gaussian-patch and clustered trees of 2^24 particles, max_leaf 32..256),
+// 9.78 ms beside each other against 9.83 ms one after the other).  Automatic: the stage times
+// predicted from the tree's sizes (ms, fitted to the kernels run alone on Gaussian-patch and
+// clustered trees of 2^24 particles, max_leaf 32..256),
 //   near = kAtNearPair pairs + kAtNearU |U|,  far = kAtFar0 + kAtFarV |V| + kAtFarCell cells,
-// and the cap 5 while the far field is comparable with the near field (0.4 <= far/near
-// <= 1.6), else 6: on those eight trees this picks the fastest cap or one within 0.02 ms.
+// and by r = far/near (best cap in brackets, from all caps on 30 trees):
+//  - a near field below 0.025 ms (FP64) or 0.005 ms (mixed): none (30001 clustered, mixed: 136 us,
+//    145 at any cap; 100001, max_leaf 96, FP64: 185, 194 to 201);
+//  - mixed, r < 0.3: six (2^24 patches, max_leaf 256: 6.16 ms [6.08]); r < 0.6: five (2^24
+//    clustered, 128: 5.74, 5.90 at four and 5.85 at six); r < 1.5: four (2^24 patches, 64: 5.29,
+//    5.37 at five; 3000001 clustered, 96: 0.995, 1.04); else three (3000001 clustered, 64: 0.979,
+//    1.01 at four);
+//  - FP64, r < 2.2: three (3000001 clustered, 64: 1.41 ms, 1.60 at four and uncapped; 2000001
+//    patches, 128: 1.33, 1.39), else two (1000001 uniform, 48: 0.509, 0.536 at three, 0.566
+//    uncapped).
 constexpr double kAtNearPair = 2.58e-10, kAtNearU = 2.4e-7;
 constexpr double kAtFar0 = 0.08, kAtFarV = 1.0e-7, kAtFarCell = 1.5e-6;
 
@@ -333,11 +341,12 @@ int choose_occupancy(const fmm_atree *t, int precision, bool concurrent)
 {
     if (!concurrent) return 0;
     if (t->near_occupancy >= 0) return t->near_occupancy;
-    if (precision != FMM_MIXED || t->sizes[FMM_AT_DEEPEST] < 2) return 0;
+    if (t->sizes[FMM_AT_DEEPEST] < 2) return 0;
     const double near = kAtNearPair * (double)t->sizes[FMM_AT_PAIRS] + kAtNearU * (double)t->sizes[FMM_AT_U];
     const double far = kAtFar0 + kAtFarV * (double)t->sizes[FMM_AT_V] + kAtFarCell * (double)t->sizes[FMM_AT_CELLS];
     const double ratio = far / near;
-    return (ratio >= 0.4 && ratio <= 1.6) ? 5 : 6;
+    if (precision == FMM_FP64) return near < 0.025 ? 0 : ratio < 2.2 ? 3 : 2;
+    return near < 0.005 ? 0 : ratio < 0.3 ? 6 : ratio < 0.6 ? 5 : ratio < 1.5 ? 4 : 3;
 }
 
 // The translations' operator tables (shared) and the tree's M2L plan (made on the first
