@@ -78,13 +78,12 @@ enum {
                                  for both particles (the kernel is odd), the rest from the target
                                  end; 0: every pair from the target end.  Results agree to rounding. */
     FMM_OPT_DENSE_LEAF = 7,   /* particles that make a leaf dense for FMM_OPT_NEAR_MUTUAL (default 32) */
-    FMM_OPT_NEAR_OCCUPANCY = 8, /* 1..8: in a concurrent call the forward near-field kernel keeps at
-                                  most this many wavefronts per SIMD resident (by reserving LDS),
-                                  leaving room for the far field beside it; 0 = no cap; -1 (default)
-                                  = per call from the tree (mixed: 3 for leaves of more than 2500
-                                  near-field pairs per particle with at least 64K near-field work
-                                  entries, else by the predicted far/near time ratio 6, 5, 4 or
-                                  none; FP64: 2 or none) */
+    FMM_OPT_NEAR_OCCUPANCY = 8, /* 1..8: in a concurrent call the near-field kernel (forward, and the
+                                  adjoint for dl_dxy without its two parts) keeps at most this many
+                                  wavefronts per SIMD resident (by reserving LDS), leaving room for
+                                  the far field beside it; 0 = no cap; -1 (default) = per call from
+                                  the tree, by the predicted far/near time ratio and the near field's
+                                  time */
     FMM_OPT_VALIDATE = 9      /* 1: every evaluation first checks the circulations (and an adjoint
                                  call its dL/du) for NaN and infinities on the device and returns
                                  FMM_EINVAL, naming the lowest particle index, before any other

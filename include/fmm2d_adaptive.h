@@ -91,10 +91,10 @@ int fmm_atree_rebuild(fmm_atree *prev, const double *xy, int64_t n, const double
                       fmm_atree **out);
 
 /* Set an option of the tree.  Two keys of fmm2d.h apply here:
- *  FMM_OPT_NEAR_OCCUPANCY: 1..8 keeps at most that many forward near-field wavefronts per
- *    SIMD resident (by reserving LDS) while the far field runs beside them on side_stream,
- *    0 = no cap, -1 (default) = chosen per call from the tree's predicted far/near time
- *    ratio (mixed precision; no cap in FP64).  A call whose side_stream is main_stream runs
+ *  FMM_OPT_NEAR_OCCUPANCY: 1..8 keeps at most that many near-field wavefronts per SIMD
+ *    resident (forward, and the adjoint for dl_dxy without its two parts; by reserving LDS)
+ *    while the far field runs beside them on side_stream, 0 = no cap, -1 (default) = chosen
+ *    per call from the tree's predicted near-field time and far/near time ratio.  A call whose side_stream is main_stream runs
  *    serialised and uncapped.  Results do not depend on it.
  *  FMM_OPT_VALIDATE: 1 checks the circulations (and dL/du of an adjoint call) for NaN and
  *    infinities first, FMM_EINVAL naming the lowest particle index (synchronises

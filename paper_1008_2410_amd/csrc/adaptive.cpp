@@ -349,6 +349,16 @@ int choose_occupancy(const fmm_atree *t, int precision, bool concurrent)
     return near < 0.005 ? 0 : ratio < 0.3 ? 6 : ratio < 0.6 ? 5 : ratio < 1.5 ? 4 : 3;
 }
 
+// The same for the adjoint's pair force, whose kernels hold fewer wavefronts, beside its two far
+// chains, as for the uniform tree (1000001 clustered particles, FP64: 0.897 ms at two, 0.930 at
+// three).
+int choose_force_occupancy(const fmm_atree *t, int precision, bool concurrent, bool phi)
+{
+    const int cap = choose_occupancy(t, precision, concurrent);
+    if (t->near_occupancy >= 0) return cap;
+    return precision == FMM_FP64 ? (cap > 2 ? cap - 1 : cap) : std::min(cap, phi ? 4 : 5);
+}
+
 // The translations' operator tables (shared) and the tree's M2L plan (made on the first
 // call, synchronising s); a tree without expansions needs neither (tabs NULL).
 int ensure_m2l_plan(fmm_atree *t, int p, hipStream_t s, const Tables *&tabs)
@@ -421,17 +431,20 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
         std::string err;
         if ((rc = build_atree_adjoint_units(t, ms, err))) return fail(rc, err);
     }
-    const AtreeCall c{t, p, precision == FMM_FP64, record_alpha(sigma, precision), 0, tabs};
+    if (!force) ss = ms;
+    const AtreeCall c{t, p, precision == FMM_FP64, record_alpha(sigma, precision),
+                      choose_force_occupancy(t, precision, ss != ms, out.dg != nullptr), tabs};
     launch_atree_pack(c, gamma, ms);
     launch_atree_pack_adjoint(c, gamma, dl_duv, scale, force, ms);
-    // The two far chains run beside each other, then the near field (which holds every
-    // wavefront slot, so that far kernels beside it would wait for it to drain).
-    HIP_TRY(hipEventRecord(t->aux.fork, ms));
-    HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
-    launch_atree_far(c, ss, true);   // the charges q: the transpose pass
-    launch_atree_far(c, ms, false);  // the charges c: derivative W' at the particles
-    HIP_TRY(hipEventRecord(t->aux.join, ss));
-    HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
+    // The two far chains (charges c: the derivative W' at the particles; charges q: the transpose
+    // pass) go through the same launches, beside the pair force; the separate sums, which hold
+    // every wavefront slot, follow them.
+    if (ss != ms) {
+        HIP_TRY(hipEventRecord(t->aux.fork, ms));
+        HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
+    }
+    launch_atree_far(c, ss, true);
+    if (ss != ms) HIP_TRY(hipEventRecord(t->aux.join, ss));
     if (force) {
         ForceNear near;
         near.near = w.near;
@@ -443,6 +456,7 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
         }
         near.qscale = c.is_double ? nullptr : (const double *)(w.range + kRangeBlocks);
         launch_atree_force(c, near, ms);
+        if (ss != ms) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
         launch_atree_finalize_force(c, near, out, ms);
         HIP_TRY(hipGetLastError());
         return FMM_OK;

@@ -59,26 +59,28 @@ __global__ __launch_bounds__(256) void at_coords_kernel(int n, const int *__rest
     pos[i] = mk<T>((T)(z.x - c.x), (T)(z.y - c.y));
 }
 
-// Charge of sorted particle j: c_j = -i Gamma_j / (2 pi), or (CPLX) the complex charge
-// q_j of the adjoint pass.
-template <bool CPLX>
+// Charge of sorted particle j: c_j = -i Gamma_j / (2 pi), or with q the complex charge q_j of
+// the adjoint pass.
 __device__ __forceinline__ double2 charge(const double *__restrict__ gamma, const double2 *__restrict__ q, int j)
 {
-    if constexpr (CPLX) return q[j];
-    else return make_double2(0.0, -gamma[j] * kInv2Pi);
+    return q ? q[j] : make_double2(0.0, -gamma[j] * kInv2Pi);
 }
 
 // P2M (stage 4) at the leaves of level >= 2, G lanes per leaf (64/G leaves per
 // wavefront):
 //   a_m / w^m = sum_j c_j xi_j^m,  xi_j = (z_j - c)/w,
 // the G lanes over the leaf's particles, then the sums over the G lanes by halving.
-template <int PMAX, bool CPLX, int G>
+template <int PMAX, int G>
 __global__ __launch_bounds__(64) void at_p2m_kernel(const int *__restrict__ cells, int ncells,
                                                      const int4 *__restrict__ cell, const int2 *__restrict__ range,
                                                      const double2 *__restrict__ xy, const double *__restrict__ gamma,
-                                                     const double2 *__restrict__ q, double x0, double y0, double side,
-                                                     int p, double2 *__restrict__ mp)
+                                                     const double2 *q, double x0, double y0, double side, int p,
+                                                     double2 *mp, const double2 *q2, double2 *mp2)
 {
+    if (blockIdx.y) {  // the second set of charges
+        q = q2;
+        mp = mp2;
+    }
     const int lane = threadIdx.x, g = lane % G;
     const int idx = blockIdx.x * (64 / G) + lane / G;
     const bool valid = idx < ncells;  // a group past the end idles (its shuffles stay inside it)
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(64) void at_p2m_kernel(const int *__restrict__ cell
     for (int j = r.x + g; j < r.x + r.y; j += G) {
         const double2 z = xy[j];
         const double2 xi = make_double2((z.x - ctr.x) * rw, (z.y - ctr.y) * rw);
-        double2 pw = charge<CPLX>(gamma, q, j);
+        double2 pw = charge(gamma, q, j);
 #pragma unroll
         for (int m = 0; m < PMAX; ++m) {
             acc[2 * m] += pw.x;
@@ -112,14 +114,18 @@ __global__ __launch_bounds__(64) void at_p2m_kernel(const int *__restrict__ cell
 // adds to them, G lanes per cell (64/G cells per wavefront):
 //   b_l = -sum_{j in A} c_j u_j^(l+1),  u_j = w/(z_j - c),
 // the G lanes over the particles of a source leaf, then the sums over the G lanes by halving.  (One thread per cell was a serial chain over the list's particles.)
-template <int PMAX, bool CPLX, int G>
+template <int PMAX, int G>
 __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const int4 *__restrict__ cell,
                                                      const int *__restrict__ x_off, const int *__restrict__ x_idx,
                                                      const int2 *__restrict__ range, const double2 *__restrict__ xy,
-                                                     const double *__restrict__ gamma,
-                                                     const double2 *__restrict__ q, double x0, double y0,
-                                                     double side, int p, double2 *__restrict__ lo)
+                                                     const double *__restrict__ gamma, const double2 *q, double x0,
+                                                     double y0, double side, int p, double2 *lo, const double2 *q2,
+                                                     double2 *lo2)
 {
+    if (blockIdx.y) {  // the second set of charges
+        q = q2;
+        lo = lo2;
+    }
     const int lane = threadIdx.x, g = lane % G;
     const int t = blockIdx.x * (64 / G) + lane / G;
     const int k = first + min(t, ncells - 1);
@@ -137,7 +143,7 @@ __global__ __launch_bounds__(64) void at_p2l_kernel(int first, int ncells, const
         for (int j = r.x + g; j < r.x + r.y; j += G) {
             const double2 z = xy[j];
             const double2 u = cinv(make_double2((z.x - ctr.x) * rw, (z.y - ctr.y) * rw));
-            const double2 cj = charge<CPLX>(gamma, q, j);
+            const double2 cj = charge(gamma, q, j);
             double2 ul = cmul<double>(cj, u);  // c_j u^(l+1)
 #pragma unroll
             for (int l = 0; l < PMAX; ++l) {
@@ -747,24 +753,20 @@ void launch_atree_coords(const fmm_atree *t, int is_double, void *pos, hipStream
 // 3000001 with their rebuild 3.68 ms, 3.70, 3.68 and 3.72.
 constexpr int kSubtreeCells = 2048;
 
-template <bool CPLX>
-void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
+void launch_atree_far(const AtreeCall &c, hipStream_t s, bool both)
 {
     const fmm_atree *t = c.t;
     const int deepest = (int)t->sizes[6];
     if (deepest < 2) return;
     const int p = c.p;
-    const double2 *q = t->wsp->adj;
+    const AtreeWs &w = *t->wsp;
+    const unsigned sets = both ? 2 : 1;
     if (t->np2m > 0) {
         // 16 lanes per leaf, four leaves per wavefront
         const int np = (int)t->np2m;
-        const unsigned g = (unsigned)((np + 3) / 4);
-        if (p <= 16)
-            at_p2m_kernel<16, CPLX, 16><<<g, 64, 0, s>>>(t->d.p2m_cells, np, t->d.cell, t->d.range, t->d.xy,
-                                                         t->wsp->gamma, q, t->x0, t->y0, t->side, p, mp);
-        else
-            at_p2m_kernel<32, CPLX, 16><<<g, 64, 0, s>>>(t->d.p2m_cells, np, t->d.cell, t->d.range, t->d.xy,
-                                                         t->wsp->gamma, q, t->x0, t->y0, t->side, p, mp);
+        auto k = p <= 16 ? at_p2m_kernel<16, 16> : at_p2m_kernel<32, 16>;
+        k<<<dim3(blocks(np, 4), sets), 64, 0, s>>>(t->d.p2m_cells, np, t->d.cell, t->d.range, t->d.xy, w.gamma, nullptr,
+                                                   t->x0, t->y0, t->side, p, w.mp, w.adj, w.mp2);
     }
     TransArgs a{};
     a.p = p;
@@ -785,11 +787,12 @@ void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
     st.zero = c.tabs->zero_row;
     // three levels from `base` on in one launch where a workgroup per split cell of `base` is
     // not many more than fit at once
-    auto subtree = [&](int base, double2 *rows, bool up) {
+    auto subtree = [&](int base, bool up) {
         const int n = t->inner_off[base + 1] - t->inner_off[base];
         if (n > kSubtreeCells) return false;
         st.base = base;
-        st.rows = (double *)rows;
+        st.rows = (double *)(up ? w.mp : w.lo);
+        st.rows2 = both ? (double *)(up ? w.mp2 : w.lo2) : nullptr;
         st.cells = t->d.inner + t->inner_off[base];
         st.ncells = n;
         if (n > 0) launch_subtree(st, up, s);
@@ -797,13 +800,14 @@ void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
     };
     // stage 5 upward
     a.targets = t->d.inner;
-    a.src = a.out = mp;
+    a.src = a.out = w.mp;
+    if (both) a.src2 = a.out2 = w.mp2;
     a.nseg = 1;
     for (int l = deepest - 1; l >= 2; --l) {
         if (l >= 3) {
             st.deepest = l + 1;
             const int base = l >= 4 ? l - 2 : 2;
-            if (subtree(base, mp, true)) {
+            if (subtree(base, true)) {
                 l = base;
                 continue;
             }
@@ -816,12 +820,13 @@ void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
     // P2L into the locals of the cells with an X list, then the M2L from V of every level
     // added to them, then the L2L level by level downward
     if (t->sizes[5] > 0) {  // |X|
-        auto k = p <= 16 ? at_p2l_kernel<16, CPLX, 16> : at_p2l_kernel<32, CPLX, 16>;
-        k<<<blocks(cnt, 4), 64, 0, s>>>(a.first, cnt, t->d.cell, t->d.x_off, t->d.x_idx, t->d.range, t->d.xy,
-                                         t->wsp->gamma, q, t->x0, t->y0, t->side, p, lo);
+        auto k = p <= 16 ? at_p2l_kernel<16, 16> : at_p2l_kernel<32, 16>;
+        k<<<dim3(blocks(cnt, 4), sets), 64, 0, s>>>(a.first, cnt, t->d.cell, t->d.x_off, t->d.x_idx, t->d.range, t->d.xy,
+                                                    w.gamma, nullptr, t->x0, t->y0, t->side, p, w.lo, w.adj, w.lo2);
     }
     a.targets = t->d.m2l_targets;
-    a.out = lo;
+    a.out = w.lo;
+    if (both) a.out2 = w.lo2;
     auto level_segs = [&](int l0, int l1) {
         a.nseg = 0;
         for (int l = l0; l <= l1; ++l)
@@ -832,10 +837,11 @@ void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
     };
     level_segs(2, deepest);
     launch_trans64(a, Trans::M2L, true, s);
-    a.src = lo;
+    a.src = w.lo;
+    if (both) a.src2 = w.lo2;
     for (int l = 3; l <= deepest; ++l) {
         st.deepest = std::min(deepest, l + 2);
-        if (l < deepest && subtree(l - 1, lo, false)) {
+        if (l < deepest && subtree(l - 1, false)) {
             l += 2;
             continue;
         }
@@ -844,13 +850,18 @@ void far_chain(const AtreeCall &c, double2 *mp, double2 *lo, hipStream_t s)
     }
 }
 
-void launch_atree_far(const AtreeCall &c, hipStream_t s, bool adjoint)
+namespace {
+
+// Occupancy cap: each near-field workgroup (one wavefront) reserves LDS so that at most near_occ
+// of them fit on a SIMD (160 KiB per CU, 4 SIMDs); the far chain on the other stream takes the
+// wavefront slots left over.
+size_t near_lds_reserve(const AtreeCall &c, size_t static_bytes)
 {
-    if (adjoint)
-        far_chain<true>(c, c.t->wsp->mp2, c.t->wsp->lo2, s);
-    else
-        far_chain<false>(c, c.t->wsp->mp, c.t->wsp->lo, s);
+    const size_t per_wave = c.near_occ > 0 ? (size_t)160 * 1024 / (4 * (size_t)c.near_occ) : 0;
+    return per_wave > static_bytes ? per_wave - static_bytes : 0;
 }
+
+}  // namespace
 
 void launch_atree_near(const AtreeCall &c, hipStream_t s)
 {
@@ -860,12 +871,7 @@ void launch_atree_near(const AtreeCall &c, hipStream_t s)
     // exponent at which 1 - e rounds to 1: FP32 base 2 at 26, FP64 base e at 37.5, one
     // unit of margin for the rounding of the records and the boxes
     const double cut = c.is_double ? 39.0 : 27.0;
-    // Occupancy cap: each workgroup (one wavefront) reserves LDS so that at most near_occ
-    // of them fit on a SIMD (160 KiB per CU, 4 SIMDs); the far chain on the other stream
-    // takes the wavefront slots left over.
-    const size_t static_lds = 256 * (c.is_double ? sizeof(double4) : sizeof(float4));
-    const size_t per_wave = c.near_occ > 0 ? (size_t)160 * 1024 / (4 * (size_t)c.near_occ) : 0;
-    const size_t dyn = per_wave > static_lds ? per_wave - static_lds : 0;
+    const size_t dyn = near_lds_reserve(c, 256 * (c.is_double ? sizeof(double4) : sizeof(float4)));
     if (c.is_double)
         at_near_kernel<double><<<(unsigned)t->nwork, 64, dyn, s>>>(
             t->d.work, t->d.cell, t->d.range, t->d.u_off, t->d.u_idx, t->d.tile_start, t->d.tile_box,
@@ -958,7 +964,7 @@ template <typename T, int KIND> void force_launch(const AtreeCall &c, const Forc
     const fmm_atree *t = c.t;
     const AtreeDev &d = t->d;
     const double cut = c.is_double ? 39.0 : 27.0;  // as for the forward near field
-    at_force_kernel<T, KIND><<<(unsigned)t->nwork, 64, 0, s>>>(
+    at_force_kernel<T, KIND><<<(unsigned)t->nwork, 64, near_lds_reserve(c, sizeof(NearLds<T, KIND>)), s>>>(
         d.work, d.cell, d.range, d.u_off, d.u_idx, d.tile_start, d.tile_box, d.leaf_start, d.leaf_tile,
         d.tile_box_leaf,
         SoaRec<T>{(const c2<T> *)t->d_pos[c.is_double], (const T *)t->wsp->gam, (T)c.alpha, (const c2<T> *)t->wsp->qt},

@@ -171,7 +171,8 @@ void launch_atree_pack(const AtreeCall &c, const double *gamma, hipStream_t s);
 void launch_atree_coords(const fmm_atree *t, int is_double, void *pos, hipStream_t s);
 // adjoint false: the far field of the charges c (mp, lo); true: of the adjoint charges
 // q (mp2, lo2)
-void launch_atree_far(const AtreeCall &c, hipStream_t s, bool adjoint = false);
+// both: the adjoint's two sets of expansions (charges c and q) in the same launches
+void launch_atree_far(const AtreeCall &c, hipStream_t s, bool both = false);
 void launch_atree_pack_adjoint(const AtreeCall &c, const double *gamma, const double *dl_duv, double scale,
                                bool force, hipStream_t s);
 void launch_atree_force(const AtreeCall &c, const ForceNear &near, hipStream_t s);

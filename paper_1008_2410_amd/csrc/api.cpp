@@ -387,6 +387,19 @@ int choose_occupancy(const fmm_tree *t, int precision, bool overlap)
     return r < 2.2 ? 3 : 2;
 }
 
+// The same for the adjoint's pair force, whose kernels hold fewer wavefronts (FP32 six per SIMD,
+// five with Phi; FP64 four and three), beside its two far chains: mixed at most five, four with
+// Phi (adjoint of 2^22 patch particles at depth 9: 3.04 ms at five, 3.09 at six; with dl_dgamma
+// 3.73 at four, 3.82; uniform 2^22 at depth 9: 1.48 at five, 1.53), FP64 one less than the forward
+// (700001 patches at depth 8: 1.02 ms at three, 1.05 at four; 1024^2 lattice: 0.619 at two, 0.658
+// at three).
+int choose_force_occupancy(const fmm_tree *t, int precision, bool overlap, bool phi)
+{
+    const int cap = choose_occupancy(t, precision, overlap);
+    if (t->near_occupancy >= 0) return cap;
+    return precision == FMM_FP64 ? (cap > 2 ? cap - 1 : cap) : std::min(cap, phi ? 4 : 5);
+}
+
 struct Timing {
     std::array<hipEvent_t, kNumEvents> ev{};
     bool on = false;
@@ -873,40 +886,29 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
 
     hipStream_t ms = (hipStream_t)main_stream;
     hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
-    const bool overlap = call_overlaps(t, precision);
-    if (!overlap) ss = ms;
-    t->occupancy_in_use = 0;  // the adjoint's near field is not capped
     const double alpha = record_alpha(sigma, precision);
     const int is_double = precision == FMM_FP64;
-    FarArgs fc = far_args(t, ws, p, precision, false);
-    fc.gam = nullptr;  // P2M of the charges c reads the staging array: it starts before pack
-    const FarArgs fq = far_args(t, ws, p, precision, true);
-    Timing tm;
-    if ((rc = tm.init(t))) return rc;
-
-    // The two far chains (the charges c: the derivative of their local expansion; the
-    // charges q: the transpose pass A^T q = -A q) are independent: with the two streams the
-    // chain of c runs on the side stream from the staged circulations on, beside the packing
-    // and then the chain of q on the main stream, and the near field follows both.  (Beside
-    // the adjoint's near field, which holds every wavefront slot, they would wait for it to
-    // drain.)
-    tm.mark(0, ms);
-    launch_stage_in(t, gamma, ms);
-    if (overlap) {
-        HIP_TRY(hipEventRecord(t->aux.fork, ms));
-        HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
-    }
-    tm.mark(2, ss);
-    launch_far_chain(fc, ss);
-    tm.mark(3, ss);
-    if (overlap) HIP_TRY(hipEventRecord(t->aux.join, ss));
-    launch_pack(t, is_double, ws.gam, ms);
     // The pair force gives dl_dxy without its two parts, in half the near field's time.  Where
     // the outputs outgrow the last-level cache the separate sums stay: there a step's adjoint
     // has the bits of velocity_backward's parts added up, and callers compare the two.
     ForceNear near;
     const bool force = out.dxy && !out.dxe && !out.dxs && !outputs_windowed(t->n, kForceRow) &&
                        force_arrays(t, ws, out.dg != nullptr, near);
+    // The two far chains (the charges c: the derivative of their local expansion; the charges q:
+    // the transpose pass A^T q = -A q) go through the same launches.  The pair force runs beside
+    // them; the separate sums, which hold every wavefront slot, follow them.
+    const bool overlap = force && call_overlaps(t, precision);
+    if (!overlap) ss = ms;
+    t->occupancy_in_use = choose_force_occupancy(t, precision, overlap, out.dg != nullptr);
+    FarArgs fc = far_args(t, ws, p, precision, false);
+    fc.no_lds = t->occupancy_in_use > 0;
+    const FarArgs fq = far_args(t, ws, p, precision, true);
+    Timing tm;
+    if ((rc = tm.init(t))) return rc;
+
+    tm.mark(0, ms);
+    launch_stage_in(t, gamma, ms);
+    launch_pack(t, is_double, ws.gam, ms);
     double *qscale = nullptr;
     if (force && !is_double) {
         launch_adjoint_range(t->n, gamma, cot, scale, ws.range, ms);
@@ -915,13 +917,20 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     launch_pack_adjoint(t, cot, scale, ws.adj, ws.rec2, is_double, ws.stage, qscale ? ws.range : nullptr, qscale,
                         ms);  // stage: free until finalize
     tm.mark(1, ms);
-    launch_far_chain(fq, ms);
-    if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
+    if (overlap) {
+        HIP_TRY(hipEventRecord(t->aux.fork, ms));
+        HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
+    }
+    tm.mark(2, ss);
+    launch_far_chain(fc, ss, &fq);
+    tm.mark(3, ss);
+    if (overlap) HIP_TRY(hipEventRecord(t->aux.join, ss));
     tm.mark(4, ms);
     const void *qv = is_double ? (const void *)ws.adj : ws.rec2;
     if (force) {
         launch_p2p_force(t, pos, ws.gam, qv, is_double, alpha, near, ms);
         tm.mark(5, ms);
+        if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
         tm.mark(6, ms);
         launch_finalize_force(t, fc, fq, ws.adj, near, is_double, alpha, out, ms);
         tm.mark(7, ms);

@@ -248,8 +248,8 @@ void launch_leaf_coords(const fmm_tree *t, int is_double, void *pos, hipStream_t
 void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int is_double, double alpha,
                         double2 *near, void *slots, hipStream_t s);
 // Stages 4-7 (P2M, M2M, M2L, L2L), or 5-7 without P2M when it was launched on its own.
-void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m = true);
-void launch_p2m(const FarArgs &a, hipStream_t s);
+// b: a second set of expansions (its own storage and charges, the rest as a's), in the same launches.
+void launch_far_chain(const FarArgs &a, hipStream_t s, const FarArgs *b = nullptr);
 // uv alone is written through `stage` (a buffer of n double2); with base, uv = base + h u.
 void launch_finalize(const fmm_tree *t, const FarArgs &a, const double2 *near, const void *slots, int slots_double,
                      double alpha, double *uv, double *uv_near, double *uv_far, void *stage, const double *base,

@@ -381,9 +381,13 @@ __global__ __launch_bounds__(64) void p2m_kernel(const int *__restrict__ leaves,
                                                   const double2 *__restrict__ xy, const c2<TC> *__restrict__ pos,
                                                   const int *__restrict__ gpos2, const double *__restrict__ gamma_st,
                                                   const typename RecScalar<TR>::type *__restrict__ gam,
-                                                  const double2 *__restrict__ adj, double x0, double y0, double w,
-                                                  int p, c2<TC> *__restrict__ out, int nxcd)
+                                                  const double2 *adj, double x0, double y0, double w, int p,
+                                                  c2<TC> *out, int nxcd, const double2 *adj2, c2<TC> *out2)
 {
+    if (blockIdx.y) {  // the second set of charges
+        adj = adj2;
+        out = out2;
+    }
     constexpr int NC = 2 * PMAX;             // partial sums per lane (re, im interleaved)
     const int lane = threadIdx.x, g = lane % G;
     // each XCD takes a contiguous run of leaves, so the staging windows its circulation
@@ -527,7 +531,7 @@ template <> float2 *level_ptr<float>(const FarArgs &a, int l, bool local)
 const int *level_list(const fmm_tree *t, int l) { return t->d_lists + t->list_off[l]; }
 
 template <typename TR, typename TC>
-void p2m_launch(const FarArgs &a, hipStream_t s)
+void p2m_launch(const FarArgs &a, const FarArgs *b, hipStream_t s)
 {
     const fmm_tree *t = a.t;
     const int L = t->depth;
@@ -540,8 +544,9 @@ void p2m_launch(const FarArgs &a, hipStream_t s)
     const c2<TC> *pos = std::is_same<TRs, TC>::value ? (const c2<TC> *)a.pos : nullptr;
     const TRs *gam = (const TRs *)a.gam;
     auto go = [&](auto kernel, int per) {
-        kernel<<<xcd_grid(nl, per), 64, 0, s>>>(level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos, t->d_gpos2,
-                                                t->d_st1, gam, a.adj, t->x0, t->y0, w, a.p, out, kXcds);
+        kernel<<<dim3(xcd_grid(nl, per), b ? 2 : 1), 64, 0, s>>>(
+            level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos, t->d_gpos2, t->d_st1, gam, a.adj, t->x0, t->y0, w,
+            a.p, out, kXcds, b ? b->adj : nullptr, b ? level_ptr<TC>(*b, L, false) : nullptr);
     };
     // lanes per leaf by the mean occupancy
     const double mean = (double)t->n / (double)nl;
@@ -1101,7 +1106,7 @@ void force_launch(const fmm_tree *t, const void *pos, const void *gam, const voi
     const MutualTree mt{t->d_leaf_start, t->d_tile_start, t->d_tile_box, near_cut_leaf2(t, sizeof(T) == 8, alpha),
                         force_series_leaf2(step)};
     const MutualParts parts = mutual_parts(t, mutual);
-    p2p_force_kernel<T, KIND><<<(unsigned)nwork, 64, 0, s>>>(
+    p2p_force_kernel<T, KIND><<<(unsigned)nwork, 64, near_lds_reserve(t, sizeof(NearLds<T, KIND>)), s>>>(
         mutual ? t->d_near_work : t->d_units, SoaRec<T>{(const c2<T> *)pos, (const T *)gam, (T)step, (const c2<T> *)qv},
         mt, nside, (T)step, alpha * alpha * kInv2Pi, t->dense_leaf, t->n, near.near, near.phi, (c2<T> *)near.slots,
         (T *)near.phi_slots, parts);
@@ -1118,19 +1123,14 @@ void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const
     k(t, pos, gam, qv, alpha, near, s);
 }
 
-void launch_p2m(const FarArgs &a, hipStream_t s)
-{
-    if (a.t->depth < 2) return;
-    if (a.t->depth <= a.split) {
-        if (a.rec_is_double) p2m_launch<double4, double>(a, s);
-        else p2m_launch<float4, double>(a, s);
-    } else {
-        if (a.rec_is_double) p2m_launch<double4, float>(a, s);
-        else p2m_launch<float4, float>(a, s);
-    }
-}
-
 namespace {
+
+void launch_p2m(const FarArgs &a, const FarArgs *b, hipStream_t s)
+{
+    auto k = a.t->depth <= a.split ? (a.rec_is_double ? p2m_launch<double4, double> : p2m_launch<float4, double>)
+                                   : (a.rec_is_double ? p2m_launch<double4, float> : p2m_launch<float4, float>);
+    k(a, b, s);
+}
 
 // The target segments of levels l0..l1 for one launch: the four parity classes of each.
 void class_segs(TransArgs &a, const fmm_tree *t, int l0, int l1)
@@ -1151,13 +1151,13 @@ void class_segs(TransArgs &a, const fmm_tree *t, int l0, int l1)
 // Stage 5 up to level 2, stage 6 (M2L) for every level but the widest at once (one launch
 // per precision), stage 7 down, with the M2L of the widest levels.  FP64 levels that a 1024-workgroup grid covers run three to a launch
 // (launch_subtree); the rest one level to a launch.
-void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
+void launch_far_chain(const FarArgs &a, hipStream_t s, const FarArgs *b)
 {
     const fmm_tree *t = a.t;
     const int L = t->depth;
     if (L < 2) return;
     const Tables &tb = *t->tabs;
-    if (with_p2m) launch_p2m(a, s);  // stage 4
+    launch_p2m(a, b, s);  // stage 4
     const int S = std::min(L, a.split);  // last FP64 level
     const int64_t fbase = level_base(a.split + 1);
 
@@ -1173,6 +1173,11 @@ void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
     st.counts = t->d_counts;
     st.tab = tb.mfma_d;
 
+    // the source and target rows of both sets
+    auto set = [&](TransArgs &to, auto rows) {
+        rows(a, to.src, to.out);
+        if (b) rows(*b, to.src2, to.out2);
+    };
     // the group of three levels a subtree launch covers: bases 2 and 5 (16 and 1024 workgroups)
     auto group = [](int rank) { return 2 + 3 * (rank / 3); };
 
@@ -1181,25 +1186,28 @@ void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
         g.seg[0] = TransSeg{0, (int)t->list_off[l], (int)t->list_len[l], l};
         if (l >= a.split) {  // FP32 children
             g.tab = tb.mfma_f;
-            g.src = a.mp_f;
+            set(g, [&](const FarArgs &f, const void *&src, void *&out) {
+                src = f.mp_f;
+                out = l == f.split ? (void *)f.mp_d : (void *)f.mp_f;
+            });
             g.src_off = fbase;
-            g.out = l == a.split ? (void *)a.mp_d : (void *)a.mp_f;
             g.out_off = l == a.split ? 0 : fbase;
             launch_trans32(g, Trans::M2M, false, l == a.split, s);
             --l;
             continue;
         }
-        const int b = group(l - 2);
-        if (b == 2 || (b == 5 && l > 5)) {
-            st.base = b;
+        const int base = group(l - 2);
+        if (base == 2 || (base == 5 && l > 5)) {
+            st.base = base;
             st.rows = (double *)a.mp_d;
+            st.rows2 = b ? (double *)b->mp_d : nullptr;
             st.deepest = l + 1;
             launch_subtree(st, true, s);
-            l = b - 1;
+            l = base - 1;
             continue;
         }
         g.tab = tb.mfma_d;
-        g.src = g.out = a.mp_d;
+        set(g, [](const FarArgs &f, const void *&src, void *&out) { src = out = f.mp_d; });
         g.src_off = g.out_off = 0;
         launch_trans64(g, Trans::M2M, false, s);
         --l;
@@ -1212,15 +1220,19 @@ void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
         --wide;
     class_segs(g, t, 2, std::min(S, wide - 1));
     g.tab = tb.mfma_d;
-    g.src = a.mp_d;
-    g.out = a.lo_d;
+    set(g, [](const FarArgs &f, const void *&src, void *&out) {
+        src = f.mp_d;
+        out = f.lo_d;
+    });
     g.src_off = g.out_off = 0;
     launch_trans64(g, Trans::M2L, false, s);
     if (wide - 1 > S) {
         class_segs(g, t, S + 1, wide - 1);
         g.tab = tb.mfma_f;
-        g.src = a.mp_f;
-        g.out = a.lo_f;
+        set(g, [](const FarArgs &f, const void *&src, void *&out) {
+            src = f.mp_f;
+            out = f.lo_f;
+        });
         g.src_off = g.out_off = fbase;
         launch_trans32(g, Trans::M2L, false, false, s);
     }
@@ -1228,33 +1240,39 @@ void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
     for (int l = 3; l <= L;) {
         if (l >= wide) {
             class_segs(g, t, l, l);
-            g.par = l <= S ? (const void *)a.lo_d : (const void *)a.lo_f;
+            set(g, [&](const FarArgs &f, const void *&src, void *&out) {
+                src = l <= S ? (const void *)f.mp_d : (const void *)f.mp_f;
+                out = l <= S ? (void *)f.lo_d : (void *)f.lo_f;
+            });
+            g.par = g.out;
+            g.par2 = g.out2;
             g.par_off = l <= S ? 0 : fbase;
             g.tab = l <= S ? (const void *)tb.mfma_d : (const void *)tb.mfma_f;
-            g.src = l <= S ? (const void *)a.mp_d : (const void *)a.mp_f;
-            g.out = l <= S ? (void *)a.lo_d : (void *)a.lo_f;
             g.src_off = g.out_off = l <= S ? 0 : fbase;
             if (l <= S) launch_trans64(g, Trans::M2L, false, s);
             else launch_trans32(g, Trans::M2L, false, false, s);
-            g.par = nullptr;
+            g.par = g.par2 = nullptr;
             ++l;
             continue;
         }
         if (l > S) {  // FP32 targets
             class_segs(g, t, l, l);
             g.tab = tb.mfma_f;
-            g.src = l - 1 <= S ? (const void *)a.lo_d : (const void *)a.lo_f;
+            set(g, [&](const FarArgs &f, const void *&src, void *&out) {
+                src = l - 1 <= S ? (const void *)f.lo_d : (const void *)f.lo_f;
+                out = f.lo_f;
+            });
             g.src_off = l - 1 <= S ? 0 : fbase;
-            g.out = a.lo_f;
             g.out_off = fbase;
             launch_trans32(g, Trans::L2L, l - 1 <= S, false, s);
             ++l;
             continue;
         }
-        const int b = group(l - 3), last = std::min({S, b + 3, wide - 1});
-        if (b == 2 || (b == 5 && last > 6)) {
-            st.base = b;
+        const int base = group(l - 3), last = std::min({S, base + 3, wide - 1});
+        if (base == 2 || (base == 5 && last > 6)) {
+            st.base = base;
             st.rows = (double *)a.lo_d;
+            st.rows2 = b ? (double *)b->lo_d : nullptr;
             st.deepest = last;
             launch_subtree(st, false, s);
             l = last + 1;
@@ -1262,7 +1280,7 @@ void launch_far_chain(const FarArgs &a, hipStream_t s, bool with_p2m)
         }
         class_segs(g, t, l, l);
         g.tab = tb.mfma_d;
-        g.src = g.out = a.lo_d;
+        set(g, [](const FarArgs &f, const void *&src, void *&out) { src = out = f.lo_d; });
         g.src_off = g.out_off = 0;
         launch_trans64(g, Trans::L2L, false, s);
         ++l;

@@ -32,6 +32,9 @@ struct TransArgs {
     int64_t src_off = 0, out_off = 0; // uniform tree: global cell index of row 0 of src / out
     const void *par = nullptr;        // uniform tree, M2L of one level: the parents' locals, for its L2L as well
     int64_t par_off = 0;
+    // the same for a second set of expansions, in the same launch (the adjoint's two chains)
+    const void *src2 = nullptr, *par2 = nullptr;
+    void *out2 = nullptr;
     // adaptive tree
     const int *vslot = nullptr;       // 27 source cells per cell of level >= 2 (cell - first)
     const int *x_off = nullptr;       // cells with an X list start from their P2L sums
@@ -47,6 +50,7 @@ struct SubtreeArgs {
     int p, base, deepest;             // deepest: last level read (up) or written (down)
     const int *counts;                // uniform tree: occupancy by global cell index
     double *rows;                     // FP64 rows from cell 0: multipoles (up) or locals (down)
+    double *rows2 = nullptr;          // a second set of them, in the same launch
     const double *tab;
     // adaptive tree
     const int *cells = nullptr;       // the split cells of level `base`

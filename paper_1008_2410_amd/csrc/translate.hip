@@ -115,8 +115,10 @@ __global__ __launch_bounds__(64 * col_blocks<KS>() * (SEQ ? 1 : KG)) void trans6
     const int64_t here = ADAPT ? 0 : level_base(seg.level) - a.out_off;
     const int64_t from =
         ADAPT ? 0 : level_base(seg.level + (MODE == Trans::M2M ? 1 : MODE == Trans::L2L ? -1 : 0)) - a.src_off;
-    const double *src = (const double *)a.src;
-    double *out = (double *)a.out;
+    const bool second = blockIdx.y != 0;
+    const double *src = (const double *)(second ? a.src2 : a.src);
+    double *out = (double *)(second ? a.out2 : a.out);
+    const double *par = (const double *)(second ? a.par2 : a.par);
 
     // the source row of target block b for operator e, or the zero row: selected, not
     // branched over, so that the loads of the next operator stay in flight
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>() * (SEQ ? 1 : KG)) void trans6
             const bool l2l = e == 27;  // wavefront-uniform
             ok = ok && (l2l || (sx < nside && sy < nside));
             S = l2l ? level_base(seg.level - 1) - a.par_off + (c >> 2) : from + morton_encode(sx, sy);
-            rows = l2l ? (const double *)a.par : src;
+            rows = l2l ? par : src;
         } else if constexpr (MODE == Trans::M2M && !ADAPT) {
             S = from + 4 * c + e;
         } else if constexpr (MODE == Trans::L2L && !ADAPT) {
@@ -295,6 +297,7 @@ template <int KS>
 __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(SubtreeArgs a)
 {
     constexpr int NB = col_blocks<KS>();
+    double *const rows = blockIdx.y ? a.rows2 : a.rows;
     const int cell0 = blockIdx.x;
     if (a.counts[level_base(a.base) + cell0] == 0) return;
     const int lane = threadIdx.x & 63, cb = threadIdx.x >> 6;
@@ -302,7 +305,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(Subtr
     const int two_p = 2 * a.p, k0 = KS * kq, col = 16 * cb + row;
     for (int l = min(a.deepest - 1, a.base + 2); l >= a.base; --l) {
         const int n = 1 << (2 * (l - a.base));
-        const double *child = a.rows + (level_base(l + 1) + 4 * ((int64_t)cell0 * n + min(row, n - 1))) * two_p;
+        const double *child = rows + (level_base(l + 1) + 4 * ((int64_t)cell0 * n + min(row, n - 1))) * two_p;
         double av[4][KS], bv[4][KS];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -315,7 +318,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(Subtr
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in_row(av[e][s], k0 + s, two_p), bv[e][s], acc, 0, 0, 0);
-        double *out = a.rows + (level_base(l) + (int64_t)cell0 * n) * two_p;
+        double *out = rows + (level_base(l) + (int64_t)cell0 * n) * two_p;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (kq + 4 * r < n && col < two_p) out[(kq + 4 * r) * two_p + col] = acc[r];
@@ -326,6 +329,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_kernel(Subtr
 template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(SubtreeArgs a)
 {
     constexpr int NB = col_blocks<KS>();
+    double *const rows = blockIdx.y ? a.rows2 : a.rows;
     const int cell0 = blockIdx.x;
     if (a.counts[level_base(a.base) + cell0] == 0) return;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;  // wavefront: parity class of the targets
@@ -337,8 +341,8 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_kernel(Sub
         load_op<KS, NB>(bv[c], a.tab, 49 + q, c, lane);
     for (int l = a.base + 1; l <= min(a.deepest, a.base + 3); ++l) {
         const int n = 1 << (2 * (l - a.base - 1));  // parents in the subtree, one target each per class
-        const double *par = a.rows + (level_base(l - 1) + (int64_t)cell0 * n) * two_p;
-        double *out = a.rows + (level_base(l) + 4 * (int64_t)cell0 * n + q) * two_p;  // target of parent k: row 4 k
+        const double *par = rows + (level_base(l - 1) + (int64_t)cell0 * n) * two_p;
+        double *out = rows + (level_base(l) + 4 * (int64_t)cell0 * n + q) * two_p;  // target of parent k: row 4 k
         double av[KS];
         load_row<KS>(av, par + (int64_t)min(row, n - 1) * two_p, k0);
         doublex4 acc[NB];
@@ -400,6 +404,7 @@ template <int KS>
 __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_adaptive_kernel(SubtreeArgs a)
 {
     constexpr int NB = col_blocks<KS>();
+    double *const rows = blockIdx.y ? a.rows2 : a.rows;
     const int lane = threadIdx.x & 63, cb = threadIdx.x >> 6;
     const int row = lane & 15, kq = lane >> 4;
     const int two_p = 2 * a.p, k0 = KS * kq, col = 16 * cb + row;
@@ -418,7 +423,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_adaptive_ker
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int S = pick(ch, e);
-                load_row<KS>(av[e], S >= 0 ? a.rows + (int64_t)S * two_p : a.zero, k0);
+                load_row<KS>(av[e], S >= 0 ? rows + (int64_t)S * two_p : a.zero, k0);
             }
             doublex4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -429,7 +434,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_adaptive_ker
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int t = __shfl(target, kq + 4 * r);
-                if (t >= 0 && col < two_p) a.rows[(int64_t)t * two_p + col] = acc[r];
+                if (t >= 0 && col < two_p) rows[(int64_t)t * two_p + col] = acc[r];
             }
         }
         __syncthreads();  // the next level reads these rows
@@ -439,6 +444,7 @@ __global__ __launch_bounds__(64 * col_blocks<KS>()) void subtree_up_adaptive_ker
 template <int KS> __global__ __launch_bounds__(256) void subtree_down_adaptive_kernel(SubtreeArgs a)
 {
     constexpr int NB = col_blocks<KS>();
+    double *const rows = blockIdx.y ? a.rows2 : a.rows;
     const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 15, kq = lane >> 4;
     const int two_p = 2 * a.p, k0 = KS * kq;
@@ -452,7 +458,7 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_adaptive_k
         const int target = pick(pl.ch[d], q);
         if (__any(target >= 0)) {
             double av[KS];
-            load_row<KS>(av, target >= 0 ? a.rows + (int64_t)pl.id[d] * two_p : a.zero, k0);
+            load_row<KS>(av, target >= 0 ? rows + (int64_t)pl.id[d] * two_p : a.zero, k0);
             int to[4];
             doublex4 acc[NB];
 #pragma unroll
@@ -460,7 +466,7 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_adaptive_k
                 to[r] = __shfl(target, kq + 4 * r);
 #pragma unroll
                 for (int c = 0; c < NB; ++c)
-                    acc[c][r] = to[r] >= 0 && 16 * c + row < two_p ? a.rows[(int64_t)to[r] * two_p + 16 * c + row] : 0.0;
+                    acc[c][r] = to[r] >= 0 && 16 * c + row < two_p ? rows[(int64_t)to[r] * two_p + 16 * c + row] : 0.0;
             }
 #pragma unroll
             for (int s = 0; s < KS; ++s)
@@ -471,7 +477,7 @@ template <int KS> __global__ __launch_bounds__(256) void subtree_down_adaptive_k
             for (int c = 0; c < NB; ++c)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (to[r] >= 0 && 16 * c + row < two_p) a.rows[(int64_t)to[r] * two_p + 16 * c + row] = acc[c][r];
+                    if (to[r] >= 0 && 16 * c + row < two_p) rows[(int64_t)to[r] * two_p + 16 * c + row] = acc[c][r];
         }
         __syncthreads();  // the next level reads these rows
     }
@@ -518,8 +524,10 @@ __global__ __launch_bounds__(256, KF <= 16 ? 4 : 2) void trans32_kernel(TransArg
     const int tx = (int)morton_x((uint32_t)tcell), ty = (int)morton_y((uint32_t)tcell);
     const int64_t here = level_base(seg.level) - a.out_off;
     const int64_t from = level_base(seg.level + (MODE == Trans::M2M ? 1 : MODE == Trans::L2L ? -1 : 0)) - a.src_off;
-    const TSrc *src = (const TSrc *)a.src;
-    TOut *out = (TOut *)a.out;
+    const bool second = blockIdx.y != 0;
+    const TSrc *src = (const TSrc *)(second ? a.src2 : a.src);
+    TOut *out = (TOut *)(second ? a.out2 : a.out);
+    const float *par = (const float *)(second ? a.par2 : a.par);
     const float *tab = (const float *)a.tab;
     const int e0 = MODE == Trans::M2L ? 28 * q : MODE == Trans::M2M ? 112 : 28 * q + 27;
     const int col = 32 * cb + row;
@@ -554,7 +562,7 @@ __global__ __launch_bounds__(256, KF <= 16 ? 4 : 2) void trans32_kernel(TransArg
             const int64_t S = from + morton_encode(sx, sy);
             const bool l2l = e == 27 && a.par;  // wavefront-uniform
             const int64_t P = level_base(seg.level - 1) - a.par_off + (c >> 2);
-            const float *r = (l2l ? (const float *)a.par : (const float *)src) + (l2l ? P : S) * two_p;
+            const float *r = (l2l ? par : (const float *)src) + (l2l ? P : S) * two_p;
             const bool ok = tcell >= 0 && (l2l || (e < 27 && sx < nside && sy < nside));
             r = ok ? r : (const float *)a.zero;
             load_row32<KF>(av[slot], r + k0);
@@ -603,7 +611,7 @@ template <int KS, int RB, int KG, Trans MODE, bool ADAPT, bool SEQ = false> void
     number_tiles(a, 16 * RB);
     if (a.ntiles == 0) return;
     trans64_kernel<KS, RB, KG, SEQ, MODE, ADAPT>
-        <<<xcd_grid(a.ntiles, 1, kXcds), 64 * col_blocks<KS>() * (SEQ ? 1 : KG), 0, s>>>(a);
+        <<<dim3(xcd_grid(a.ntiles, 1, kXcds), a.out2 ? 2 : 1), 64 * col_blocks<KS>() * (SEQ ? 1 : KG), 0, s>>>(a);
 }
 
 // KG partial sums side by side, or one after the other where the LDS is held.
@@ -643,7 +651,7 @@ template <int KS> void trans64(TransArgs &a, Trans mode, bool adaptive, hipStrea
 
 template <int KF, Trans MODE, typename TSrc, typename TOut> void go32(TransArgs &a, hipStream_t s)
 {
-    trans32_kernel<KF, MODE, TSrc, TOut><<<xcd_grid((int64_t)a.ntiles * col_blocks32<KF>(), 4, kXcds), 256, 0, s>>>(a);
+    trans32_kernel<KF, MODE, TSrc, TOut><<<dim3(xcd_grid((int64_t)a.ntiles * col_blocks32<KF>(), 4, kXcds), a.out2 ? 2 : 1), 256, 0, s>>>(a);
 }
 
 template <int KF> void trans32(TransArgs &a, Trans mode, bool src_double, bool out_double, hipStream_t s)
@@ -657,12 +665,12 @@ template <int KF> void trans32(TransArgs &a, Trans mode, bool src_double, bool o
 template <int KS> void subtree(const SubtreeArgs &a, bool up, hipStream_t s)
 {
     if (a.cells) {
-        const unsigned g = (unsigned)a.ncells;
+        const dim3 g((unsigned)a.ncells, a.rows2 ? 2 : 1);
         if (up) subtree_up_adaptive_kernel<KS><<<g, 64 * col_blocks<KS>(), 0, s>>>(a);
         else subtree_down_adaptive_kernel<KS><<<g, 256, 0, s>>>(a);
         return;
     }
-    const unsigned g = 1u << (2 * a.base);
+    const dim3 g(1u << (2 * a.base), a.rows2 ? 2 : 1);
     if (up) subtree_up_kernel<KS><<<g, 64 * col_blocks<KS>(), 0, s>>>(a);
     else subtree_down_kernel<KS><<<g, 256, 0, s>>>(a);
 }

@@ -12,7 +12,6 @@ from conftest import rel_l2
 from test_gpu_sparse_units import BOX, BWD, OPT_DENSE_LEAF, SIZES, _leaves, _t
 
 pytestmark = pytest.mark.gpu
-OPT_NEAR_MUTUAL = 3
 
 
 def _vjp(tree, g, sigma, p, precision, dl, with_gamma):
@@ -96,3 +95,20 @@ def test_replays(fmm_mod, kind):
         got = dg.cpu().numpy(), dx.cpu().numpy()
         ref = _vjp(tree, g, 0.03, 6, "mixed", d, True)
         assert all(np.array_equal(a, b) for a, b in zip(got, ref)), k
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind", ["uniform", "adaptive"])
+def test_bits_of_every_schedule(fmm_mod, kind, precision):
+    """The pair force beside the far chains, at every cap, and after them: one set of bits."""
+    r = np.random.Generator(np.random.PCG64(12))
+    xy, g, dl = r.random((6000, 2)), r.standard_normal(6000), r.standard_normal((6000, 2))
+    tree = fmm_mod.ATree(_t(xy), 20, 6, BOX) if kind == "adaptive" else fmm_mod.Tree(_t(xy), 4, BOX)
+    ref = _vjp(tree, g, 0.01, 9, precision, dl, True)
+    for schedule in (0, 1) if kind == "uniform" else (None,):
+        if schedule is not None:
+            tree.set_option(1, schedule)
+        for cap in (0, 1, 2, 3, 4, 5, 6):
+            tree.set_option(8, cap)
+            got = _vjp(tree, g, 0.01, 9, precision, dl, True)
+            assert all(np.array_equal(a, b) for a, b in zip(got, ref)), (schedule, cap)
