@@ -293,6 +293,13 @@ __global__ __launch_bounds__(256) void at_finalize_kernel(int n, const int *__re
     const int4 c = cell[A];
     const double2 z = xy[i];
     double2 W = make_double2(0.0, 0.0);
+    const int e1 = w_off[A + 1];
+    int e = w_off[A], D = 0;
+    int4 cd = make_int4(0, 0, 0, 0);
+    if (e < e1) {
+        D = w_idx[e];
+        cd = cell[D];
+    }
     if (c.x >= 2) {
         const double w = ldexp(side, -c.x);
         const double2 ctr = cell_centre(x0, y0, side, c);
@@ -300,15 +307,16 @@ __global__ __launch_bounds__(256) void at_finalize_kernel(int n, const int *__re
         const double2 acc = horner_prefetch<double>(lo + (int64_t)A * p, p, xi);
         W = make_double2(acc.x / w, acc.y / w);
     }
-    for (int e = w_off[A]; e < w_off[A + 1]; ++e) {
-        const int D = w_idx[e];
-        const int4 cd = cell[D];
-        const double w = ldexp(side, -cd.x);
+    for (; e < e1; ++e) {
+        const double rw = 1.0 / ldexp(side, -cd.x);
         const double2 ctr = cell_centre(x0, y0, side, cd);
-        const double2 inv = cinv(make_double2((z.x - ctr.x) / w, (z.y - ctr.y) / w));
-        const double2 acc = cmul<double>(horner_prefetch<double>(mp + (int64_t)D * p, p, inv), inv);
-        W.x += acc.x / w;
-        W.y += acc.y / w;
+        const double2 *const m = mp + (int64_t)D * p;
+        if (e + 1 < e1) {  // the next entry ahead of this one's products
+            D = w_idx[e + 1];
+            cd = cell[D];
+        }
+        const double2 inv = cinv(make_double2((z.x - ctr.x) * rw, (z.y - ctr.y) * rw));
+        W = cmac<double>(W, horner_prefetch<double>(m, p, inv), make_double2(inv.x * rw, inv.y * rw));
     }
     if (staged) {  // at its staging slot (windows) or in sorted order
         staged[o] = make_double2(nr.x + W.x, nr.y - W.y);
@@ -594,49 +602,81 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 
     }
 }
 
-// Far field of scaled expansions at z in leaf A and its derivative (FP64):
-//   L2P  (1/w) sum_l b_l xi^l,             derivative (1/w^2) sum_{l>=1} l b_l xi^(l-1);
-//   M2P  (1/w_D) sum_m a_m zeta^-(m+1),     derivative -(1/w_D^2) sum_m (m+1) a_m zeta^-(m+2),
-// over D in W(A), xi = (z - c_A)/w, zeta = (z - c_D)/w_D.  DERIV false: the value only.
-template <bool VALUE, bool DERIV>
-__device__ __forceinline__ void far_value_deriv(int A, int4 c, double2 z, const int *__restrict__ w_off,
-                                                const int *__restrict__ w_idx, const int4 *__restrict__ cell,
-                                                const double2 *__restrict__ mp, const double2 *__restrict__ lo, int p,
-                                                double x0, double y0, double side, double2 &val, double2 &der)
+// Values and derivatives of two polynomials of p terms at x, by Horner's rule for both at once
+// (P' x + P, then P x + a_l), the coefficients eight at a time ahead of their use.
+__device__ __forceinline__ void horner_pair(const double2 *__restrict__ a, const double2 *__restrict__ b, int p,
+                                            double2 x, double2 &va, double2 &da, double2 &vb, double2 &db)
 {
-    val = make_double2(0.0, 0.0);
-    der = make_double2(0.0, 0.0);
+    va = a[p - 1];
+    vb = b[p - 1];
+    da = db = make_double2(0.0, 0.0);
+    for (int l0 = p - 2; l0 >= 0; l0 -= 8) {
+        double2 ca[8], cb[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int l = max(l0 - k, 0);
+            ca[k] = a[l];
+            cb[k] = b[l];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (l0 - k >= 0) {
+                da = cmac<double>(va, da, x);
+                va = cmac<double>(ca[k], va, x);
+                db = cmac<double>(vb, db, x);
+                vb = cmac<double>(cb[k], vb, x);
+            }
+    }
+}
+
+// Far field of the adjoint at z in leaf A (FP64): the derivative dw of the charges c's field, the
+// value phi and the derivative dphi of the charges q's, from the scaled expansions
+//   L2P  (1/w) P(xi),  derivative (1/w^2) P'(xi),   P(x) = sum_l b_l x^l,  xi = (z - c_A)/w;
+//   M2P  (1/w_D) x P(x),  derivative -(x/w_D)^2 (P + x P')(x),   x = w_D/(z - c_D),
+// over D in W(A).  Both fields in one walk of the list, the next cell of it loaded ahead: bound
+// by the chain list, cell, coefficients, Horner, which three walks had three times (150001
+// clustered particles: 100 us, 60 in one walk).
+__device__ __forceinline__ void far_adjoint(int A, int4 c, double2 z, const int *__restrict__ w_off,
+                                            const int *__restrict__ w_idx, const int4 *__restrict__ cell,
+                                            const double2 *__restrict__ mp, const double2 *__restrict__ lo,
+                                            const double2 *__restrict__ mp2, const double2 *__restrict__ lo2, int p,
+                                            double x0, double y0, double side, double2 &dw, double2 &phi, double2 &dphi)
+{
+    dw = phi = dphi = make_double2(0.0, 0.0);
+    double2 va, da, vb, db;
+    const int e1 = w_off[A + 1];
+    int e = w_off[A], D = 0;
+    int4 cd = make_int4(0, 0, 0, 0);
+    if (e < e1) {
+        D = w_idx[e];
+        cd = cell[D];
+    }
     if (c.x >= 2) {
         const double w = ldexp(side, -c.x);
         const double2 ctr = cell_centre(x0, y0, side, c);
         const double2 xi = make_double2((z.x - ctr.x) / w, (z.y - ctr.y) / w);
-        const double2 *b = lo + (int64_t)A * p;
-        if (VALUE) {
-            const double2 acc = horner_prefetch<double>(b, p, xi);
-            val = make_double2(acc.x / w, acc.y / w);
-        }
-        if (DERIV && p >= 2) {
-            const double2 acc = horner_weighted_prefetch<double>(b, p, xi, 1, 0);
-            der = make_double2(acc.x / (w * w), acc.y / (w * w));
-        }
+        horner_pair(lo + (int64_t)A * p, lo2 + (int64_t)A * p, p, xi, va, da, vb, db);
+        phi = make_double2(vb.x / w, vb.y / w);
+        dphi = make_double2(db.x / (w * w), db.y / (w * w));
+        dw = make_double2(da.x / (w * w), da.y / (w * w));
     }
-    for (int e = w_off[A]; e < w_off[A + 1]; ++e) {
-        const int D = w_idx[e];
-        const int4 cd = cell[D];
+    for (; e < e1; ++e) {
         const double w = ldexp(side, -cd.x);
         const double2 ctr = cell_centre(x0, y0, side, cd);
-        const double2 inv = cinv(make_double2((z.x - ctr.x) / w, (z.y - ctr.y) / w));
-        const double2 *a = mp + (int64_t)D * p;
-        if (VALUE) {
-            const double2 acc = cmul<double>(horner_prefetch<double>(a, p, inv), inv);
-            val.x += acc.x / w;
-            val.y += acc.y / w;
+        const double2 *const a = mp + (int64_t)D * p, *const b = mp2 + (int64_t)D * p;
+        if (e + 1 < e1) {
+            D = w_idx[e + 1];
+            cd = cell[D];
         }
-        if (DERIV) {
-            const double2 acc = cmul<double>(horner_weighted_prefetch<double>(a, p, inv, 0, 1), cmul<double>(inv, inv));
-            der.x -= acc.x / (w * w);
-            der.y -= acc.y / (w * w);
-        }
+        const double rw = 1.0 / w;
+        const double2 x = cinv(make_double2((z.x - ctr.x) * rw, (z.y - ctr.y) * rw));
+        horner_pair(a, b, p, x, va, da, vb, db);
+        const double2 xw = make_double2(x.x * rw, x.y * rw);
+        const double2 x2 = cmul<double>(xw, xw);
+        phi = cmac<double>(phi, xw, vb);
+        const double2 sq = cmul<double>(x2, cmac<double>(vb, x, db)), sc = cmul<double>(x2, cmac<double>(va, x, da));
+        dphi = make_double2(dphi.x - sq.x, dphi.y - sq.y);
+        dw = make_double2(dw.x - sc.x, dw.y - sc.y);
     }
 }
 
@@ -663,9 +703,8 @@ __global__ __launch_bounds__(256) void at_finalize_backward_kernel(
     const int A = leaf_of[i];
     const int4 c = cell[A];
     const double2 z = xy[i];
-    double2 wv, dw, phi, dphi;
-    far_value_deriv<false, true>(A, c, z, w_off, w_idx, cell, mp, lo, p, x0, y0, side, wv, dw);
-    far_value_deriv<true, SRC>(A, c, z, w_off, w_idx, cell, mp2, lo2, p, x0, y0, side, phi, dphi);
+    double2 dw, phi, dphi;
+    far_adjoint(A, c, z, w_off, w_idx, cell, mp, lo, mp2, lo2, p, x0, y0, side, dw, phi, dphi);
     const double ka = alpha * alpha * kInv2Pi;
     const double Ar = ka * (-2.0 * a.w), Ai = -ka * a.z;
     const double Bi = -ka * lambda * sb;
@@ -712,9 +751,8 @@ __global__ __launch_bounds__(256) void at_finalize_force_kernel(
     const double2 nr = near_from_slots<TS>(i, n, m, near.near, (const c2<TS> *)near.slots, alpha * alpha * kInv2Pi);
     double nphi = 0.0;
     if (out.dg) nphi = alpha * uq * phi_from_slots<TS>(i, n, m, near.phi, (const TS *)near.phi_slots);
-    double2 wv, dw, phi, dphi;
-    far_value_deriv<false, true>(A, c, z, w_off, w_idx, cell, mp, lo, p, x0, y0, side, wv, dw);
-    far_value_deriv<true, true>(A, c, z, w_off, w_idx, cell, mp2, lo2, p, x0, y0, side, phi, dphi);
+    double2 dw, phi, dphi;
+    far_adjoint(A, c, z, w_off, w_idx, cell, mp, lo, mp2, lo2, p, x0, y0, side, dw, phi, dphi);
     store_adjoint(out, o, -(nphi + phi.y) * kInv2Pi, uq * nr.x + (q.x * dw.x - q.y * dw.y),
                   uq * nr.y - (q.x * dw.y + q.y * dw.x), -G * dphi.y, -G * dphi.x);
 }
