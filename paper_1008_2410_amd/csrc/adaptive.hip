@@ -281,7 +281,8 @@ __global__ __launch_bounds__(256) void at_finalize_kernel(int n, const int *__re
                                                            const c2<TS> *__restrict__ slots, double scale,
                                                            double *__restrict__ uv, double *__restrict__ uv_near,
                                                            double *__restrict__ uv_far, double2 *__restrict__ staged,
-                                                           const int *__restrict__ gpos2, int nxcd)
+                                                           const int *__restrict__ gpos2, int nxcd,
+                                                           const double *base, double h)
 {
     const int i = xcd_block(nxcd) * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -322,10 +323,7 @@ __global__ __launch_bounds__(256) void at_finalize_kernel(int n, const int *__re
         staged[o] = make_double2(nr.x + W.x, nr.y - W.y);
         return;
     }
-    if (uv) {
-        uv[2 * o] = nr.x + W.x;
-        uv[2 * o + 1] = nr.y - W.y;
-    }
+    if (uv) store_velocity(uv, o, make_double2(nr.x + W.x, nr.y - W.y), base, h);
     if (uv_near) {
         uv_near[2 * o] = nr.x;
         uv_near[2 * o + 1] = nr.y;
@@ -765,14 +763,15 @@ void launch_atree_pack(const AtreeCall &c, const double *gamma, hipStream_t s)
 {
     const fmm_atree *t = c.t;
     const int n = (int)t->n;
-    launch_stage_rows(n, t->stage_shift, t->d.gpos1, gamma, t->d.st1, s);
+    const bool direct = direct_rows(n, kForwardRow);
+    if (!direct) launch_stage_rows(n, t->stage_shift, t->d.gpos1, gamma, t->d.st1, s);
+    const int *idx = direct ? t->d.perm : t->d.gpos2;
+    const double *rows = direct ? gamma : t->d.st1;
     const unsigned g = xcd_grid(n, 256, kXcds);
     if (c.is_double)
-        at_pack_kernel<double><<<g, 256, 0, s>>>(n, kXcds, t->d.gpos2, t->d.st1, (double *)t->wsp->gam,
-                                                 t->wsp->gamma);
+        at_pack_kernel<double><<<g, 256, 0, s>>>(n, kXcds, idx, rows, (double *)t->wsp->gam, t->wsp->gamma);
     else
-        at_pack_kernel<float><<<g, 256, 0, s>>>(n, kXcds, t->d.gpos2, t->d.st1, (float *)t->wsp->gam,
-                                                t->wsp->gamma);
+        at_pack_kernel<float><<<g, 256, 0, s>>>(n, kXcds, idx, rows, (float *)t->wsp->gam, t->wsp->gamma);
 }
 
 void launch_atree_coords(const fmm_atree *t, int is_double, void *pos, hipStream_t s)
@@ -932,8 +931,8 @@ void launch_atree_finalize(const AtreeCall &c, double *uv, double *uv_near, doub
     const double scale = c.alpha * kInv2Pi;
     // uv alone: the totals go to the staging array (n double2), then to user order:
     // through the staging windows once the output fills the last-level cache, else in
-    // sorted order and scattered
-    double2 *staged = uv && !uv_near && !uv_far ? t->wsp->stage : nullptr;
+    // sorted order and scattered; small outputs directly
+    double2 *staged = uv && !uv_near && !uv_far && !direct_rows(n, kForwardRow) ? t->wsp->stage : nullptr;
     const bool windowed = staged && outputs_windowed(n, sizeof(double2));
     const int *gp = windowed ? t->d.gpos2 : nullptr;
     double *uv_direct = staged ? nullptr : uv;
@@ -942,12 +941,12 @@ void launch_atree_finalize(const AtreeCall &c, double *uv, double *uv_near, doub
         at_finalize_kernel<double><<<g, 256, 0, s>>>(
             n, t->d.perm, t->d.leaf_of, t->d.cell, t->d.xy, t->d.w_off, t->d.w_idx, t->wsp->mp, t->wsp->lo, c.p, t->x0,
             t->y0, t->side, t->wsp->near, t->d.mask, (const double2 *)t->wsp->slots, scale, uv_direct, uv_near, uv_far,
-            staged, gp, kXcds);
+            staged, gp, kXcds, base, h);
     else
         at_finalize_kernel<float><<<g, 256, 0, s>>>(
             n, t->d.perm, t->d.leaf_of, t->d.cell, t->d.xy, t->d.w_off, t->d.w_idx, t->wsp->mp, t->wsp->lo, c.p, t->x0,
             t->y0, t->side, t->wsp->near, t->d.mask, (const float2 *)t->wsp->slots, scale, uv_direct, uv_near, uv_far,
-            staged, gp, kXcds);
+            staged, gp, kXcds, base, h);
     if (windowed) launch_gather_rows(n, t->d.gpos1, staged, uv, base, h, s);
     else if (staged) scatter_rows_kernel<<<blocks(n, 256), 256, 0, s>>>(n, t->d.perm, staged, uv, base, h);
 }
@@ -959,16 +958,19 @@ void launch_atree_pack_adjoint(const AtreeCall &c, const double *gamma, const do
     const int n = (int)t->n;
     // the forward's near-field array (n double2) is free during the adjoint: the staging
     double2 *st = t->wsp->near;
-    launch_stage_rows2(n, t->stage_shift, t->d.gpos1, (const double2 *)dl_duv, st, s);
+    const bool direct = direct_rows(n, kAdjointRow);
+    if (!direct) launch_stage_rows2(n, t->stage_shift, t->d.gpos1, (const double2 *)dl_duv, st, s);
+    const int *idx = direct ? t->d.perm : t->d.gpos2;
+    const double2 *rows = direct ? (const double2 *)dl_duv : st;
     const unsigned g = xcd_grid(n, 256, kXcds);
     double2 *bounds = force && !c.is_double ? t->wsp->range : nullptr;
     if (bounds)
         adjoint_range_kernel<<<kRangeBlocks, 256, 0, s>>>(n, gamma, (const double2 *)dl_duv, scale, bounds);
     if (c.is_double)
-        at_pack_adjoint_kernel<double><<<g, 256, 0, s>>>(n, kXcds, t->d.gpos2, st, scale, t->wsp->adj,
+        at_pack_adjoint_kernel<double><<<g, 256, 0, s>>>(n, kXcds, idx, rows, scale, t->wsp->adj,
                                                          (double2 *)t->wsp->qt, nullptr, nullptr);
     else
-        at_pack_adjoint_kernel<float><<<g, 256, 0, s>>>(n, kXcds, t->d.gpos2, st, scale, t->wsp->adj,
+        at_pack_adjoint_kernel<float><<<g, 256, 0, s>>>(n, kXcds, idx, rows, scale, t->wsp->adj,
                                                         (float2 *)t->wsp->qt, bounds, (double *)(bounds + kRangeBlocks));
 }
 

@@ -522,12 +522,12 @@ int run_forward(fmm_tree *t, const double *gamma, double sigma, int p, int preci
     if (!noalloc && (rc = tm.init(t))) return rc;
 
     tm.mark(0, ms);
-    launch_stage_in(t, gamma, ms);
+    a.gamma = launch_stage_in(t, gamma, kForwardRow, ms);
     if (overlap) {  // the far chain needs only the staged circulations: it starts beside pack
         HIP_TRY(hipEventRecord(t->aux.fork, ms));
         HIP_TRY(hipStreamWaitEvent(ss, t->aux.fork, 0));
     }
-    launch_pack(t, is_double, ws.gam, ms);
+    launch_pack(t, a.gamma, is_double, ws.gam, ms);
     tm.mark(1, ms);
     tm.mark(2, ss);
     launch_far_chain(a, ss);
@@ -907,8 +907,8 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     if ((rc = tm.init(t))) return rc;
 
     tm.mark(0, ms);
-    launch_stage_in(t, gamma, ms);
-    launch_pack(t, is_double, ws.gam, ms);
+    fc.gamma = launch_stage_in(t, gamma, kAdjointRow, ms);
+    launch_pack(t, fc.gamma, is_double, ws.gam, ms);
     double *qscale = nullptr;
     if (force && !is_double) {
         launch_adjoint_range(t->n, gamma, cot, scale, ws.range, ms);

@@ -1168,8 +1168,7 @@ __device__ __forceinline__ c2<T> horner_weighted_prefetch(const c2<T> *__restric
 
 // A velocity row of user row o: the velocity itself, or with a base (the transport
 // update of section "Test problem", dx/dt = u, one explicit stage) base + h u.
-__device__ __forceinline__ void store_velocity(double *__restrict__ uv, int64_t o, double2 v,
-                                               const double *__restrict__ base, double h)
+__device__ __forceinline__ void store_velocity(double *uv, int64_t o, double2 v, const double *base, double h)
 {
     if (base) {
         v.x = fma(h, v.x, base[2 * o]);

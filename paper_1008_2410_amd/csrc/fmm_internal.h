@@ -59,6 +59,21 @@ inline bool outputs_windowed(int64_t n, int64_t bytes_per_row)
 {
     return n * bytes_per_row >= kLastLevelCacheBytes;
 }
+// Whether per-particle rows go between user and sorted order directly (random rows of an array that
+// the caches hold) rather than through a staging pass of its own, whose launch costs 3 to 5 us: up
+// to 8 MiB of rows, twice the L2 of an XCD.  Forward (circulations of 8 bytes): 4096 particles 48 ->
+// 42 us, 500001 170 -> 155, 1000001 244 -> 232, 2000001 463 -> 459; adjoint (cotangents of 16):
+// 500001 269 -> 265 us, 2^20 394 -> 408.
+constexpr int64_t kDirectBytes = int64_t(8) << 20;
+constexpr int64_t kForwardRow = 8, kAdjointRow = 16;
+inline bool direct_rows(int64_t n, int64_t row) { return n * row <= kDirectBytes; }
+
+// Where the circulation of sorted particle i is: rows[idx[i]], in the caller's array (idx = perm) or
+// in the staging array (idx = gpos2).
+struct GammaRows {
+    const int *idx = nullptr;
+    const double *rows = nullptr;
+};
 // Blocks of the reduction that finds the range of an adjoint's charges.
 constexpr int kRangeBlocks = 1024;
 // Flag (in w) of a mutual item in the near-field work list.
@@ -222,10 +237,11 @@ struct FarArgs {
     double2 *mp_d, *lo_d;      // FP64 storage (levels 0..split)
     float2 *mp_f, *lo_f;       // FP32 storage (levels split+1..L)
     const void *pos;           // the tree's leaf-unit coordinates in the records' precision (or null)
-    const void *gam;           // circulations in tree order in that precision (null: P2M reads the staging array)
+    const void *gam;           // circulations in tree order in that precision (null: P2M reads `gamma`)
     int rec_is_double;
     int charge_kind;           // 0: real Gamma in rec.z -> c = -i Gamma/(2 pi); 1: complex q from adj array
     const double2 *adj;        // complex charges in sorted order (charge_kind 1)
+    GammaRows gamma{};         // the circulations
     bool no_lds = false;       // beside a capped near field, which holds the LDS: kernels without any
 };
 
@@ -241,8 +257,9 @@ int build_near_plan_device(fmm_tree *t, hipStream_t s, std::string &err);
 
 // Pass 1 of the circulations into tree order (the staging array, all P2M needs), then
 // pass 2 with the near-field records.
-void launch_stage_in(const fmm_tree *t, const double *gamma, hipStream_t s);
-void launch_pack(const fmm_tree *t, int is_double, void *gam, hipStream_t s);
+// The circulations: staged unless direct_rows; then gathered into tree order.
+GammaRows launch_stage_in(const fmm_tree *t, const double *gamma, int64_t row, hipStream_t s);
+void launch_pack(const fmm_tree *t, const GammaRows &gamma, int is_double, void *gam, hipStream_t s);
 // The tree's leaf-unit coordinates (float2 or double2, n) into pos.
 void launch_leaf_coords(const fmm_tree *t, int is_double, void *pos, hipStream_t s);
 void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int is_double, double alpha,

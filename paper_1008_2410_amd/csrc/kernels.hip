@@ -452,7 +452,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(int n, const int *__restr
                                                         double y0, double w, double *__restrict__ uv,
                                                         double *__restrict__ uv_near, double *__restrict__ uv_far,
                                                         double2 *__restrict__ staged, const int *__restrict__ gpos2,
-                                                        int nxcd)
+                                                        int nxcd, const double *base, double h)
 {
     const int i = xcd_block(nxcd) * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -478,10 +478,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(int n, const int *__restr
         staged[gpos2 ? gpos2[i] : i] = make_double2(nr.x + fu, nr.y + fv);
         return;
     }
-    if (uv) {
-        uv[2 * o] = nr.x + fu;
-        uv[2 * o + 1] = nr.y + fv;
-    }
+    if (uv) store_velocity(uv, o, make_double2(nr.x + fu, nr.y + fv), base, h);
     if (uv_near) {
         uv_near[2 * o] = nr.x;
         uv_near[2 * o + 1] = nr.y;
@@ -545,7 +542,7 @@ void p2m_launch(const FarArgs &a, const FarArgs *b, hipStream_t s)
     const TRs *gam = (const TRs *)a.gam;
     auto go = [&](auto kernel, int per) {
         kernel<<<dim3(xcd_grid(nl, per), b ? 2 : 1), 64, 0, s>>>(
-            level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos, t->d_gpos2, t->d_st1, gam, a.adj, t->x0, t->y0, w,
+            level_list(t, L), (int)nl, t->d_leaf_start, t->d_xy, pos, a.gamma.idx, a.gamma.rows, gam, a.adj, t->x0, t->y0, w,
             a.p, out, kXcds, b ? b->adj : nullptr, b ? level_ptr<TC>(*b, L, false) : nullptr);
     };
     // lanes per leaf by the mean occupancy
@@ -749,8 +746,8 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void p2p_ba
 //   At = alpha^2 (near sum) + Phi'_far,  Bt = alpha^2 lambda (near sum),
 //   dL/dx_src = -Re(c (At + Bt)),  dL/dy_src = Im(c (At - Bt)),
 // Phi'_far = (1/w^2) sum_l l b_l(q) xi^(l-1) the derivative of the q-field's local
-// expansion (the far operator is antisymmetric).  gamma_st[gpos2[i]] is Gamma of
-// sorted particle i (the staged circulations).
+// expansion (the far operator is antisymmetric).  gamma gives Gamma of sorted
+// particle i.
 // The far part of a particle's adjoint: Im Phi_far, W'_far and (with need_s) Phi'_far.
 struct AdjointFar {
     double phi = 0.0, dwr = 0.0, dwi = 0.0, dpr = 0.0, dpi = 0.0;
@@ -794,7 +791,7 @@ __global__ __launch_bounds__(256) void finalize_backward_kernel(
     const c2<TL> *__restrict__ loc_c, const c2<TL> *__restrict__ loc_q, const c2<TL> *__restrict__ pos, int p,
     int has_far, double x0, double y0,
     double w, double alpha, double lambda, AdjointOut out, const double4 *__restrict__ near_src,
-    const int *__restrict__ gpos2, const double *__restrict__ gamma_st, double *__restrict__ stage_g,
+    const int *__restrict__ gpos2, const GammaRows gamma, double *__restrict__ stage_g,
     double *__restrict__ stage_x, double *__restrict__ stage_s, int nxcd)
 {
     const bool stage = stage_x != nullptr;
@@ -836,7 +833,7 @@ __global__ __launch_bounds__(256) void finalize_backward_kernel(
         const double a2 = alpha * alpha;
         const double atr = a2 * ns.x + dpr, ati = a2 * ns.y + dpi;
         const double btr = a2 * lambda * ns.z, bti = a2 * lambda * ns.w;
-        const double G = gamma_st[gpos2[i]] * kInv2Pi;  // c = -i G: Re(c w) = G Im w, Im(c w) = -G Re w
+        const double G = gamma.rows[gamma.idx[i]] * kInv2Pi;  // c = -i G: Re(c w) = G Im w, Im(c w) = -G Re w
         sx = -G * (ati + bti);
         sy = -G * (atr - btr);
     }
@@ -862,7 +859,7 @@ __global__ __launch_bounds__(256) void finalize_force_kernel(
     int n, const int *__restrict__ perm, const int *__restrict__ leaf_of, const double2 *__restrict__ xy,
     const ForceNear near, const double2 *__restrict__ adj, const c2<TL> *__restrict__ loc_c,
     const c2<TL> *__restrict__ loc_q, const c2<TL> *__restrict__ pos, int p, int has_far, double x0, double y0,
-    double w, double alpha, AdjointOut out, const int *__restrict__ gpos2, const double *__restrict__ gamma_st,
+    double w, double alpha, AdjointOut out, const int *__restrict__ gamma_idx, const double *__restrict__ gamma,
     int nxcd)
 {
     const int i = xcd_block(nxcd) * blockDim.x + threadIdx.x;
@@ -870,7 +867,7 @@ __global__ __launch_bounds__(256) void finalize_force_kernel(
     const int64_t o = perm[i];  // issued with the first loads
     const uint32_t leaf = (uint32_t)leaf_of[i];
     const double2 q = adj[i];
-    const double G = gamma_st[gpos2[i]] * kInv2Pi;
+    const double G = gamma[gamma_idx[i]] * kInv2Pi;
     const int m = near.mask ? near.mask[leaf] : 1 << 9;
     const double uq = near.qscale ? 1.0 / *near.qscale : 1.0;
     const double2 nr = near_from_slots<TS>(i, n, m, near.near, (const c2<TS> *)near.slots, alpha * alpha * kInv2Pi);
@@ -1001,18 +998,18 @@ void launch_gather_rows(int64_t n, const int *gpos1, const double2 *staged, doub
     gather_rows_kernel<<<xcd_grid(n, 256), 256, 0, s>>>((int)n, kXcds, gpos1, staged, uv, base, h);
 }
 
-void launch_stage_in(const fmm_tree *t, const double *gamma, hipStream_t s)
+GammaRows launch_stage_in(const fmm_tree *t, const double *gamma, int64_t row, hipStream_t s)
 {
+    if (direct_rows(t->n, row)) return GammaRows{t->d_perm, gamma};
     launch_stage_rows(t->n, t->stage_shift, t->d_gpos1, gamma, t->d_st1, s);
+    return GammaRows{t->d_gpos2, t->d_st1};
 }
 
-void launch_pack(const fmm_tree *t, int is_double, void *gam, hipStream_t s)
+void launch_pack(const fmm_tree *t, const GammaRows &gamma, int is_double, void *gam, hipStream_t s)
 {
     const int n = (int)t->n;
-    if (is_double)
-        pack_kernel<double><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, t->d_gpos2, t->d_st1, (double *)gam);
-    else
-        pack_kernel<float><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, t->d_gpos2, t->d_st1, (float *)gam);
+    if (is_double) pack_kernel<double><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, gamma.idx, gamma.rows, (double *)gam);
+    else pack_kernel<float><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, gamma.idx, gamma.rows, (float *)gam);
 }
 
 void launch_leaf_coords(const fmm_tree *t, int is_double, void *pos, hipStream_t s)
@@ -1292,8 +1289,8 @@ void launch_finalize(const fmm_tree *t, const FarArgs &a, const double2 *near, c
                      double h, hipStream_t s)
 {
     // uv alone: the totals go to stage (n double2), then out in user order; through the
-    // staging windows once the output outgrows the last-level cache
-    double2 *staged = uv && !uv_near && !uv_far ? (double2 *)stage : nullptr;
+    // staging windows once the output outgrows the last-level cache; small outputs directly
+    double2 *staged = uv && !uv_near && !uv_far && !direct_rows(t->n, kForwardRow) ? (double2 *)stage : nullptr;
     const bool windowed = outputs_windowed(t->n, sizeof(double2));
     double *uv_direct = staged ? nullptr : uv;
     const int L = t->depth;
@@ -1312,12 +1309,12 @@ void launch_finalize(const fmm_tree *t, const FarArgs &a, const double2 *near, c
             finalize_kernel<double, double><<<g, 256, 0, s>>>(n, t->d_perm, t->d_leaf_of, t->d_xy, near, mask,
                                                               (const double2 *)slots, scale, loc, pos, a.p, has_far,
                                                               t->x0, t->y0, w, uv_direct, uv_near, uv_far, staged, gp,
-                                                              kXcds);
+                                                              kXcds, base, h);
         else
             finalize_kernel<double, float><<<g, 256, 0, s>>>(n, t->d_perm, t->d_leaf_of, t->d_xy, near, mask,
                                                              (const float2 *)slots, scale, loc, pos, a.p, has_far,
                                                              t->x0, t->y0, w, uv_direct, uv_near, uv_far, staged, gp,
-                                                             kXcds);
+                                                             kXcds, base, h);
     } else {
         const float2 *loc = level_ptr<float>(a, L, true);
         const float2 *pos = a.rec_is_double ? nullptr : (const float2 *)a.pos;
@@ -1325,12 +1322,12 @@ void launch_finalize(const fmm_tree *t, const FarArgs &a, const double2 *near, c
             finalize_kernel<float, double><<<g, 256, 0, s>>>(n, t->d_perm, t->d_leaf_of, t->d_xy, near, mask,
                                                              (const double2 *)slots, scale, loc, pos, a.p, has_far,
                                                              t->x0, t->y0, w, uv_direct, uv_near, uv_far, staged, gp,
-                                                             kXcds);
+                                                             kXcds, base, h);
         else
             finalize_kernel<float, float><<<g, 256, 0, s>>>(n, t->d_perm, t->d_leaf_of, t->d_xy, near, mask,
                                                             (const float2 *)slots, scale, loc, pos, a.p, has_far,
                                                             t->x0, t->y0, w, uv_direct, uv_near, uv_far, staged, gp,
-                                                            kXcds);
+                                                            kXcds, base, h);
     }
     if (staged && windowed) gather_rows_kernel<<<g, 256, 0, s>>>(n, kXcds, t->d_gpos1, staged, uv, base, h);
     else if (staged) scatter_rows_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, t->d_perm, staged, uv, base, h);
@@ -1345,12 +1342,15 @@ void launch_pack_adjoint(const fmm_tree *t, const double *dl_duv, double scale, 
                          double2 *staging, const double2 *range, double *qscale, hipStream_t s)
 {
     const int n = (int)t->n;
-    launch_stage_rows2(n, t->stage_shift, t->d_gpos1, (const double2 *)dl_duv, staging, s);
+    const bool direct = direct_rows(n, kAdjointRow);
+    const int *idx = direct ? t->d_perm : t->d_gpos2;
+    const double2 *rows = direct ? (const double2 *)dl_duv : staging;
+    if (!direct) launch_stage_rows2(n, t->stage_shift, t->d_gpos1, (const double2 *)dl_duv, staging, s);
     if (is_double)
-        pack_adjoint_kernel<double><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, t->d_gpos2, staging, scale, adj,
+        pack_adjoint_kernel<double><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, idx, rows, scale, adj,
                                                                       nullptr, nullptr, nullptr);
     else
-        pack_adjoint_kernel<float><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, t->d_gpos2, staging, scale, adj,
+        pack_adjoint_kernel<float><<<xcd_grid(n, 256), 256, 0, s>>>(n, kXcds, idx, rows, scale, adj,
                                                                      (float2 *)qt, range, qscale);
 }
 
@@ -1405,7 +1405,7 @@ void finalize_force_launch(const fmm_tree *t, const FarArgs &fc, const FarArgs &
         (int)t->n, t->d_perm, t->d_leaf_of, t->d_xy, near, adj, has_far ? level_ptr<TL>(fc, L, true) : nullptr,
         has_far ? level_ptr<TL>(fq, L, true) : nullptr,
         (fc.rec_is_double != 0) == (sizeof(TL) == 8) ? (const c2<TL> *)fc.pos : nullptr, fc.p, has_far, t->x0, t->y0,
-        t->side / (double)(1 << L), alpha, out, t->d_gpos2, t->d_st1, kXcds);
+        t->side / (double)(1 << L), alpha, out, fc.gamma.idx, fc.gamma.rows, kXcds);
 }
 
 }  // namespace
@@ -1434,13 +1434,13 @@ void launch_finalize_backward(const fmm_tree *t, const FarArgs &fc, const FarArg
         finalize_backward_kernel<double><<<g, 256, 0, s>>>(
             n, t->d_perm, t->d_leaf_of, t->d_xy, near_pa, near_b, adj,
             has_far ? level_ptr<double>(fc, L, true) : nullptr, has_far ? level_ptr<double>(fq, L, true) : nullptr,
-            fc.rec_is_double ? (const double2 *)fc.pos : nullptr, fc.p, has_far, t->x0, t->y0, w, alpha, lambda, out, near_src, t->d_gpos2, t->d_st1, stage_g, stage_x,
+            fc.rec_is_double ? (const double2 *)fc.pos : nullptr, fc.p, has_far, t->x0, t->y0, w, alpha, lambda, out, near_src, t->d_gpos2, fc.gamma, stage_g, stage_x,
             stage_s, kXcds);
     else
         finalize_backward_kernel<float><<<g, 256, 0, s>>>(
             n, t->d_perm, t->d_leaf_of, t->d_xy, near_pa, near_b, adj, level_ptr<float>(fc, L, true),
             level_ptr<float>(fq, L, true), fc.rec_is_double ? nullptr : (const float2 *)fc.pos, fc.p, has_far, t->x0, t->y0, w, alpha, lambda, out, near_src, t->d_gpos2,
-            t->d_st1, stage_g, stage_x, stage_s, kXcds);
+            fc.gamma, stage_g, stage_x, stage_s, kXcds);
     if (stage_x) gather_adjoint_kernel<<<g, 256, 0, s>>>(n, kXcds, t->d_gpos1, stage_g, stage_x, stage_s, out);
 }
 
