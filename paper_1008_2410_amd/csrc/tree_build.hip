@@ -141,50 +141,97 @@ __global__ __launch_bounds__(256) void scan_short(const uint32_t *in, uint32_t *
 
 // ---------------------------------------------------------------------------------
 // Stable LSD radix sort of (key, value) pairs by the low `bits` bits of the key,
-// 8-bit digits.  Per pass: per-tile digit histograms (digit-major), their exclusive
-// scan, then a scatter in which each tile of 2048 pairs is taken in 8 rounds of 256;
+// 8-bit digits.  Per pass: per-tile digit histograms (digit-major), their exclusive scan within
+// each digit, then a scatter in which each tile of 256 R pairs is taken in R rounds of 256;
 // inside a wavefront the lanes with the same digit find each other with 8 ballots
 // (rank = lanes below with the same digit), across wavefronts and rounds the digit
-// counts accumulate in LDS, so equal digits keep their input order.
+// counts accumulate in LDS, so equal digits keep their input order.  Small sorts are a chain of
+// launches and round trips to memory: the scatter adds up the digits' totals itself instead of a
+// scan over all counts (of 1000003 pairs: 8 us and two launches a pass, now 3.3 and one), a tile's
+// pairs are all loaded before its first round, and up to kSmallSort pairs a tile is two rounds
+// (scatter of 12289 pairs 8.2 -> 3.8 us; of 1000003 pairs 14.8 us with eight rounds, 16.2 with
+// four, 13.6 with two, whose counts then cost more: 2.10, 2.13 and 2.22 ms of an RK2 step).
 // ---------------------------------------------------------------------------------
-constexpr int kRsTile = 2048;
+constexpr int64_t kSmallSort = int64_t(1) << 18;  // pairs up to which a tile is two rounds
 
+template <int R>
 __global__ __launch_bounds__(256) void rs_hist(const uint64_t *__restrict__ keys, int64_t n, int shift,
                                                 uint32_t *__restrict__ counts, int nb)
 {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    for (int r = 0; r < kRsTile / 256; ++r) {
-        const int64_t i = base + r * 256 + threadIdx.x;
-        if (i < n) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & 255u], 1u);
-    }
+    const int64_t base = (int64_t)blockIdx.x * (256 * R) + threadIdx.x;
+    uint32_t d[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) d[r] = base + r * 256 < n ? (uint32_t)(keys[base + r * 256] >> shift) & 255u : 256u;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (d[r] < 256u) atomicAdd(&h[d[r]], 1u);
     __syncthreads();
     counts[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
+// Exclusive sum over a workgroup of 256 threads, and the total.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t &total)
+{
+    __shared__ uint32_t wsum[4];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint32_t incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(incl, o);
+        if (lane >= o) incl += u;
+    }
+    __syncthreads();  // (a caller's earlier sum)
+    if (lane == 63) wsum[wid] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int w = 0; w < 4; ++w) before += w < wid ? wsum[w] : 0u;
+    total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    return before + incl - v;
+}
+
+// Per digit (workgroup): its tiles' counts to exclusive offsets within the digit, and its total.
+__global__ __launch_bounds__(256) void rs_scan(uint32_t *__restrict__ counts, int nb, uint32_t *__restrict__ totals)
+{
+    uint32_t *c = counts + (int64_t)blockIdx.x * nb;
+    uint32_t carry = 0;
+    for (int b = 0; b < nb; b += 256) {
+        const int k = b + threadIdx.x;
+        uint32_t total;
+        const uint32_t e = block_scan(k < nb ? c[k] : 0u, total);
+        if (k < nb) c[k] = carry + e;
+        carry += total;
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+template <int R>
 __global__ __launch_bounds__(256) void rs_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                                                    uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t n,
-                                                   int shift, const uint32_t *__restrict__ offs, int nb)
+                                                   int shift, const uint32_t *__restrict__ offs, int nb,
+                                                   const uint32_t *__restrict__ totals)
 {
     __shared__ uint32_t start[256];
     __shared__ uint32_t wcnt[4][256];
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-    start[t] = offs[(int64_t)t * nb + blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    for (int r = 0; r < kRsTile / 256; ++r) {
+    const int64_t base = (int64_t)blockIdx.x * (256 * R) + t;
+    uint64_t key[R];
+    uint32_t val[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = min(base + r * 256, n - 1);
+        key[r] = kin[i];
+        val[r] = vin[i];
+    }
+    uint32_t all;
+    start[t] = offs[(int64_t)t * nb + blockIdx.x] + block_scan(totals[t], all);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
         wcnt[0][t] = wcnt[1][t] = wcnt[2][t] = wcnt[3][t] = 0;
         __syncthreads();
-        const int64_t i = base + r * 256 + t;
-        const bool valid = i < n;
-        uint64_t key = 0;
-        uint32_t val = 0, d = 0;
-        if (valid) {
-            key = kin[i];
-            val = vin[i];
-            d = (uint32_t)(key >> shift) & 255u;
-        }
+        const bool valid = base + r * 256 < n;
+        const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
         uint64_t m = __ballot(valid);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -198,8 +245,8 @@ __global__ __launch_bounds__(256) void rs_scatter(const uint64_t *__restrict__ k
         if (valid) {
             uint32_t pos = start[d] + (uint32_t)__popcll(below);
             for (int w = 0; w < wid; ++w) pos += wcnt[w][d];
-            kout[pos] = key;
-            vout[pos] = val;
+            kout[pos] = key[r];
+            vout[pos] = val[r];
         }
         __syncthreads();
         start[t] += wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t];
@@ -887,24 +934,35 @@ bool scan_exclusive(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tota
 }
 
 // Stable sort of (keys, vals) by the low `bits` bits of the keys.
-bool radix_sort(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st)
+namespace {
+
+template <int R>
+bool radix_passes(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st)
 {
-    if (n <= 1 || bits <= 0) return true;
-    const int nb = (int)((n + kRsTile - 1) / kRsTile);
+    const int nb = (int)((n + 256 * R - 1) / (256 * R));
     Buf<uint64_t> k2;
     Buf<uint32_t> v2, counts;
     if (!st.check(k2.alloc(n, s, keys.kept), "sort workspace") || !st.check(v2.alloc(n, s, vals.kept), "sort workspace") ||
-        !st.check(counts.alloc((int64_t)256 * nb, s), "sort workspace"))
+        !st.check(counts.alloc((int64_t)256 * nb + 256, s), "sort workspace"))
         return false;
+    uint32_t *totals = counts.p + (int64_t)256 * nb;
     for (int shift = 0; shift < bits; shift += 8) {
-        rs_hist<<<nb, 256, 0, s>>>(keys.p, n, shift, counts.p, nb);
-        if (!scan_on(counts.p, counts.p, (int64_t)256 * nb, nullptr, s, st)) return false;
-        rs_scatter<<<nb, 256, 0, s>>>(keys.p, vals.p, k2.p, v2.p, n, shift, counts.p, nb);
+        rs_hist<R><<<nb, 256, 0, s>>>(keys.p, n, shift, counts.p, nb);
+        rs_scan<<<256, 256, 0, s>>>(counts.p, nb, totals);
+        rs_scatter<R><<<nb, 256, 0, s>>>(keys.p, vals.p, k2.p, v2.p, n, shift, counts.p, nb, totals);
         if (!st.check(hipGetLastError(), "sort launch")) return false;
         keys.swap(k2);
         vals.swap(v2);
     }
     return true;
+}
+
+}  // namespace
+
+bool radix_sort(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st)
+{
+    if (n <= 1 || bits <= 0) return true;
+    return n <= kSmallSort ? radix_passes<2>(keys, vals, n, bits, s, st) : radix_passes<8>(keys, vals, n, bits, s, st);
 }
 
 bool bounding_square(const double2 *xy, int64_t n, hipStream_t s, Status &st, double box[3], bool &nonfinite)
