@@ -128,13 +128,13 @@ __device__ __forceinline__ float one_minus_exp(float s) { return 1.0f - __builti
 // of expm1(x)/x economized by Chebyshev polynomials on |x| <= 0.3467, in exact rational
 // arithmetic, coefficients rounded to double: within 2.3e-17 of p), then e = 2^-k (1 + em1)
 // and g = (1 - 2^-k) - 2^-k em1, where 1 - 2^-k is exact.  Within about 2 ulp of both; 2^-k
-// underflows to 0 for large s (e = 0, g = 1).  Branch-free, 20 instructions.
+// underflows to 0 for large s (e = 0, g = 1).  Branch-free, 19 instructions.
 __device__ __forceinline__ void exp_pair(double s, double &e, double &g)
 {
     constexpr double kInvLn2 = 1.4426950408889634, kLn2Hi = 6.93147180369123816490e-01,
                      kLn2Lo = 1.90821492927058770002e-10;
-    const double k = rint(s * kInvLn2);
-    const double x = -fma(-k, kLn2Lo, fma(-k, kLn2Hi, s));  // -(s - k ln2)
+    const double k = rint(s * -kInvLn2);  // minus the k above: the exponent as ldexp takes it
+    const double x = -fma(k, kLn2Lo, fma(k, kLn2Hi, s));  // -(s - k ln2)
     double p = 2.5110080609180445e-08;
     p = fma(p, x, 2.7626408708679167e-07);
     p = fma(p, x, 2.7557240802111588e-06);
@@ -147,7 +147,7 @@ __device__ __forceinline__ void exp_pair(double s, double &e, double &g)
     p = fma(p, x, 0.5000000000000006);
     p = fma(p, x, 1.0);
     const double em1 = p * x;  // expm1(-r)
-    const double t = ldexp(1.0, -(int)k);
+    const double t = ldexp(1.0, (int)k);
     e = fma(t, em1, t);
     g = fma(-t, em1, 1.0 - t);
 }
@@ -449,8 +449,8 @@ __device__ __forceinline__ float row_rot(float v)
 __device__ __forceinline__ double row_rot(double v)
 {
     const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffff), 0x12F, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x12F, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffff), 0x12F, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x12F, 0xF, 0xF, true);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
 
@@ -997,7 +997,7 @@ __device__ __forceinline__ double charge_scale(const double2 *__restrict__ range
 template <int O> __device__ __forceinline__ int lane_partner(int v)
 {
     constexpr int ctrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : O == 4 ? 0x141 : 0x128;
-    return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xF, 0xF, false);
+    return __builtin_amdgcn_mov_dpp(v, ctrl, 0xF, 0xF, true);
 }
 template <int O> __device__ __forceinline__ float lane_partner(float v)
 {
