@@ -428,9 +428,9 @@ __device__ __forceinline__ float box_gap2(float4 a, float ox, float oy, float4 b
 // one item.  For each pair of 64-particle tiles (b of S, a of R), one tile is held one
 // particle per lane ("resident") and the other is staged in LDS and streamed in chunks
 // of 16 sources.  Within a chunk, lane l of a 16-lane row meets source (l + j) mod 16
-// at step j; the resident sums stay in the lane and each source's sum travels with its
-// source: a one-lane rotation within the row per step, fused into the add (a DPP
-// operand).  After 16 steps every row holds its partial sums of the chunk's sources;
+// at step j; the resident sums stay in the lane, and each source's terms meet its sum by a
+// rotation within the row: of the sum, one lane per step, or in FP32 velocities of the term (a
+// DPP operand).  After 16 steps every row holds its partial sums of the chunk's sources;
 // two butterfly steps across rows complete them.  Sums for tile b stay in registers
 // over the tiles of R; sums for tile a accumulate in its particles' slot in memory.
 // Slots: nine per particle, one per neighbour direction d = 3(dy+1) + (dx+1), written
@@ -454,40 +454,124 @@ __device__ __forceinline__ double row_rot(double v)
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
 
+// Lane l receives the value of lane 16 (l / 16) + ((l - J) mod 16): DPP row_ror:J.
+template <int J> __device__ __forceinline__ float row_back(float v)
+{
+    if constexpr (J == 0) return v;
+    else
+        return __builtin_bit_cast(float,
+                                  __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + J, 0xF, 0xF, true));
+}
+
+// -Gamma of the resident particles as the chunk's steps take it.  FP32: of the lane J before in
+// its row, for J < 8.
+template <typename T> struct RowGamma;
+template <> struct RowGamma<double> {
+    double g;
+    __device__ __forceinline__ explicit RowGamma(double v) : g(v) {}
+};
+template <> struct RowGamma<float> {
+    float g[8];
+    template <int J = 0> __device__ __forceinline__ void spread(float v)
+    {
+        g[J] = row_back<J>(v);
+        if constexpr (J < 7) spread<J + 1>(v);
+    }
+    __device__ __forceinline__ explicit RowGamma(float v) { spread(v); }
+};
+
 // 16 steps of one chunk: src points at this lane's start in the chunk's doubled copy
-// (src[j] = source (l + j) mod 16).  rgn = -Gamma of the resident particle (zero for an
-// idle lane).  On return (cu, cv)[l] = this row's sum for source l mod 16 of the chunk.
-template <typename T, bool FAR>
-__device__ __forceinline__ void mutual_chunk(const rec_t<T> *src, T rx, T ry, T rgn, T &fu, T &fv, T &cu, T &cv)
+// (src[j] = source (l + j) mod 16).  rg: -Gamma of the resident particles (zero for an idle
+// lane).  On return (cu, cv)[l] = this row's sum for source l mod 16 of the chunk.
+template <bool FAR>
+__device__ __forceinline__ void mutual_chunk(const rec_t<double> *src, double rx, double ry,
+                                             const RowGamma<double> &rg, double &fu, double &fv, double &cu,
+                                             double &cv)
 {
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        const rec_t<T> sj = src[j];
-        const T ddx = rx - sj.x;
-        const T ddy = ry - sj.y;
-        const T ss = fma(ddx, ddx, fma(ddy, ddy, tiny<T>()));
-        const T r = recip(ss);
-        T h;  // g(s)/s
-        if (FAR) h = r;
-        else if (sizeof(T) == 4) h = fma(-exp_neg_scaled(ss), r, r);
-        else h = one_minus_exp(ss) * r;
-        const T wt = h * sj.z;
+        const rec_t<double> sj = src[j];
+        const double ddx = rx - sj.x;
+        const double ddy = ry - sj.y;
+        const double ss = fma(ddx, ddx, fma(ddy, ddy, tiny<double>()));
+        const double r = recip(ss);
+        const double h = FAR ? r : one_minus_exp(ss) * r;  // g(s)/s
+        const double wt = h * sj.z;
         fu = fma(wt, ddy, fu);
         fv = fma(wt, ddx, fv);
-        const T ws = h * rgn;
+        const double ws = h * rg.g;
         if (j == 0) {
             cu = ws * ddy;
             cv = ws * ddx;
         } else {
-            // Not contracted: a multiply and an add that takes the rotation as its DPP
-            // operand are two instructions; an FMA needs the rotation as a separate move.
-#pragma clang fp contract(off)
             cu = row_rot(cu) + ws * ddy;
             cv = row_rot(cv) + ws * ddx;
         }
     }
     cu = row_rot(cu);
     cv = row_rot(cv);
+}
+
+// FP32: the sums stay in their lanes and the terms move.  The terms of source s at step q come
+// from the lane q before it, through the DPP operand of a fused multiply-add with that lane's
+// Gamma: 11 vector operations besides the reciprocal and the exponential, where sums that
+// travel with their source take a rounded product and a rotating add each, 13.  Sources l + 8 to
+// l + 15 come first and their sums move by half a row before sources l to l + 7, so that eight
+// of the row's Gamma do: with sixteen the kernel holds 70 registers, 7 wavefronts per SIMD
+// instead of 8, and 1000003 patch particles at depth 8 took 0.452 ms against 0.433 before.
+// Now 0.413; 2^22 at depth 9 1.76 -> 1.67, 2^24 at depth 10 7.06 -> 6.75.  (FP64 has no such
+// operand: two moves per term either way, and its Gamma would take 16 registers more.)
+//
+// The compiler does not form the instruction, and does not look into the block for hazards: a
+// DPP read needs two wait states after the write.  In front stand the resident's two sums;
+// behind the last step before the move, an s_nop.
+template <int Q>
+__device__ __forceinline__ void mutual_add(float ux, float uy, float z, float g, float &fu, float &fv, float &cu,
+                                           float &cv)
+{
+    if constexpr (Q == 0) {
+        fu = fma(z, uy, fu);
+        fv = fma(z, ux, fv);
+        cu = g * uy;
+        cv = g * ux;
+    } else if constexpr (Q == 8) {
+        fu = fma(z, uy, fu);
+        fv = fma(z, ux, fv);
+        cu = fma(g, uy, row_back<8>(cu));
+        cv = fma(g, ux, row_back<8>(cv));
+    } else {
+        asm("v_fmac_f32_e32 %0, %4, %5\n\t"
+            "v_fmac_f32_e32 %1, %4, %6\n\t"
+            "v_fmac_f32_dpp %2, %5, %7 row_ror:%8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %3, %6, %7 row_ror:%8 row_mask:0xf bank_mask:0xf"
+            : "+&v"(fu), "+&v"(fv), "+&v"(cu), "+&v"(cv)
+            : "v"(z), "v"(uy), "v"(ux), "v"(g), "n"(Q % 8));
+        if constexpr (Q == 7) asm("s_nop 1" : "+v"(cu), "+v"(cv));
+    }
+}
+
+// (Two steps at a time: both chains up to the terms are in flight together.)
+template <bool FAR, int Q = 0>
+__device__ __forceinline__ void mutual_chunk(const rec_t<float> *src, float rx, float ry, const RowGamma<float> &rg,
+                                             float &fu, float &fv, float &cu, float &cv)
+{
+    float ux[2], uy[2], z[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const rec_t<float> sj = src[(Q + k + 8) % 16];
+        const float ddx = rx - sj.x;
+        const float ddy = ry - sj.y;
+        const float ss = fma(ddx, ddx, fma(ddy, ddy, tiny<float>()));
+        const float r = recip(ss);
+        const float h = FAR ? r : fma(-exp_neg_scaled(ss), r, r);  // g(s)/s
+        ux[k] = h * ddx;
+        uy[k] = h * ddy;
+        z[k] = sj.z;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    mutual_add<Q>(ux[0], uy[0], z[0], rg.g[Q % 8], fu, fv, cu, cv);
+    mutual_add<Q + 1>(ux[1], uy[1], z[1], rg.g[Q % 8 + 1], fu, fv, cu, cv);
+    if constexpr (Q < 14) mutual_chunk<FAR, Q + 2>(src, rx, ry, rg, fu, fv, cu, cv);
 }
 
 // The same for the pair force: qsrc the sources' qy; the source's sums are the negative of the
@@ -694,6 +778,7 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
             pqy = swap ? qya : qyb;
             qsrc = swap ? lds.qb : lds.qa;
         }
+        const RowGamma<T> back(pgn);
         T r[NS], col[NS];
 #pragma unroll
         for (int m = 0; m < NS; ++m) r[m] = col[m] = 0;
@@ -701,8 +786,8 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
             T cs[NS];
             const int at = c * 32 + (lane & 15);
             if constexpr (KIND == kVelocity) {
-                if (far) mutual_chunk<T, true>(src + at, px, py, pgn, r[0], r[1], cs[0], cs[1]);
-                else mutual_chunk<T, false>(src + at, px, py, pgn, r[0], r[1], cs[0], cs[1]);
+                if (far) mutual_chunk<true>(src + at, px, py, back, r[0], r[1], cs[0], cs[1]);
+                else mutual_chunk<false>(src + at, px, py, back, r[0], r[1], cs[0], cs[1]);
             } else {
                 if (far) force_chunk<T, KIND, 2>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, r, cs);
                 else if (sizeof(T) == 8 || gap2 >= mt.series_leaf2)
