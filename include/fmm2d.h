@@ -61,14 +61,12 @@ enum {
 enum {
     FMM_OPT_SCHEDULE = 1,     /* 0: far field on a second stream, concurrent with P2P;
                                  1: everything serialised on the main stream;
-                                 2 (default): per call from the tree's predicted far/near time
-                                 ratio: serialised in the mixed form when the far field is
-                                 predicted more than 2.5 times the near field (where overlapping
-                                 measured slower on one GPU), concurrent otherwise and in FP64 */
-    FMM_OPT_COARSE_LEVEL = 2, /* L_c: levels <= L_c of the up/down sweeps run in FP64 on the far-
-                                 field stream (default 3, range 1..depth); those of them with at
-                                 most 256 cells (levels <= 4) in one single-workgroup kernel, the
-                                 others as wide launches */
+                                 2 (default): per call from the tree's predicted stage times:
+                                 serialised where the near field is too short to be worth the
+                                 second stream, and in the mixed form when the far field is
+                                 predicted more than 4 times the near field; concurrent otherwise */
+    FMM_OPT_COARSE_LEVEL = 2, /* L_c: in the mixed form levels <= max(L_c, 5) of the up/down
+                                 sweeps run in FP64 (default 3, range 1..depth) */
     FMM_OPT_TIMING = 3,       /* 1: record HIP events around each stage of every call for
                                  fmm_get_timings (default 0) */
                               /* keys 4 and 5 (a persistent near-field grid, a cap on the far-field

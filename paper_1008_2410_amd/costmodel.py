@@ -15,8 +15,8 @@ On one GPU the same terms are the measured stages of an evaluation, each timed a
 (serial schedule), with the counts a GPU launch actually pays for:
     per particle (pack, finalize):                    T_part = a_g N
     far field: per fine-level cell (M2M, M2L, L2L
-    above L_c), per cell of the single-workgroup
-    coarse sweep (levels <= L_c; the paper's b term),
+    above L_c), per cell of the coarse sweep
+    (levels <= L_c; the paper's b term),
     per fine level (launches):                        T_far = c_g C_fine + b_g C_coarse + h_g (L - L_c)
     near field: per pair, per leaf visit (a 64-lane
     wavefront visiting a neighbour leaf, staging it):  T_near = d_g pairs + g_g 9 N_leaves
@@ -94,7 +94,7 @@ class Sample:
 @dataclass
 class Fit:
     a: float   # ms per particle
-    b: float   # ms per coarse-level cell (single-workgroup sweep)
+    b: float   # ms per coarse-level cell
     c: float   # ms per non-empty fine-level cell
     d: float   # ms per near-field pair
     far0: float
@@ -120,7 +120,7 @@ class Fit:
         return math.sqrt(4.0 * self.c / (27.0 * self.d))
 
     def coarse_ms(self, s: Sample) -> float:
-        """The single-workgroup coarse sweep (the b term) of a sample."""
+        """The coarse sweep (the b term) of a sample."""
         return self.b * s.coarse_cells
 
     def covered(self, s: Sample) -> bool:
@@ -166,5 +166,5 @@ def fine_cells(counts_per_level: list[int], lc: int) -> int:
 
 
 def coarse_cells(counts_per_level: list[int], lc: int) -> int:
-    """Non-empty cells of the levels of the single-workgroup sweep (2 .. lc)."""
+    """Non-empty cells of the coarse sweep (levels 2 .. lc)."""
     return int(sum(counts_per_level[l] for l in range(2, min(lc, len(counts_per_level) - 1) + 1)))

@@ -51,7 +51,7 @@ struct AtreeDev {
     // Adjoint near field: target-centric units over all of U, one per 64-particle tile
     // {leaf cell, first, count, log2 TP}, heaviest first (made on the first adjoint call).
     int4 *bwd_units = nullptr;
-    // Translations on MFMA (made on the first evaluation with p <= 16): the cells of level
+    // Translations on MFMA (made on the first evaluation): the cells of level
     // >= 2 grouped by level and, inside a level, by parity class (x bit | y bit << 1), and
     // per such cell (index - level_off[2]) the source cell of each of its class's 27
     // interaction offsets, -1 where V holds none.
