@@ -253,6 +253,92 @@ __global__ __launch_bounds__(256) void rs_scatter(const uint64_t *__restrict__ k
     }
 }
 
+// All passes of a small sort in one workgroup of 16 wavefronts: a pass above costs three launches
+// of 3 us each.  A wavefront takes 64 consecutive pairs a round, in order, and counts its digits
+// apart, so that its rounds need no barrier: the places of its digits (after those of lower digits
+// and of earlier wavefronts) advance as it goes.  One compute unit does the work of all, so the
+// line lies where its rounds take as long as the launches: a stage with its rebuild of 4097
+// uniform particles 326 -> 292 us, 8001 328 -> 307; up to 16384 pairs 12289 particles take 321
+// instead of 307, 16001 take 336 instead of 312 (325 before).
+constexpr int64_t kOneSort = 8192;
+
+template <int R>
+__global__ __launch_bounds__(1024) void rs_one(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int n, int bits)
+{
+    __shared__ uint32_t place[16][256];
+    __shared__ uint32_t wsum[4];
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int rounds = (n + 1023) / 1024;  // at most R
+    const int first = wid * 64 * rounds + lane;
+    for (int shift = 0; shift < bits; shift += 8) {
+        uint64_t key[R];
+        uint32_t val[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = min(first + r * 64, n - 1);
+            key[r] = ka[i];
+            val[r] = va[i];
+        }
+        for (int k = 0; k < 4; ++k) (&place[0][0])[k * 1024 + t] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r < rounds && first + r * 64 < n) atomicAdd(&place[wid][(key[r] >> shift) & 255u], 1u);
+        __syncthreads();
+        uint32_t total = 0, incl = 0;
+        if (t < 256) {  // digit t
+            for (int w = 0; w < 16; ++w) {
+                const uint32_t c = place[w][t];
+                place[w][t] = total;
+                total += c;
+            }
+            incl = total;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t u = __shfl_up(incl, o);
+                if (lane >= o) incl += u;
+            }
+            if (lane == 63) wsum[wid] = incl;
+        }
+        __syncthreads();
+        if (t < 256) {
+            uint32_t before = incl - total;
+            for (int w = 0; w < wid; ++w) before += wsum[w];
+            for (int w = 0; w < 16; ++w) place[w][t] += before;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r >= rounds) break;
+            const bool valid = first + r * 64 < n;
+            const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
+            uint64_t m = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t bm = __ballot(valid && bit);
+                m &= bit ? bm : ~bm;
+            }
+            const uint64_t below = m & ((1ull << lane) - 1ull);
+            const uint32_t at = place[wid][d];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (valid && below == 0) place[wid][d] = at + (uint32_t)__popcll(m);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (valid) {
+                const uint32_t pos = at + (uint32_t)__popcll(below);
+                kb[pos] = key[r];
+                vb[pos] = val[r];
+            }
+        }
+        __syncthreads();
+        uint64_t *const k = ka;
+        ka = kb;
+        kb = k;
+        uint32_t *const v = va;
+        va = vb;
+        vb = v;
+    }
+}
+
 // ---------------------------------------------------------------------------------
 // Tree kernels
 // ---------------------------------------------------------------------------------
@@ -959,9 +1045,30 @@ bool radix_passes(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits,
 
 }  // namespace
 
+namespace {
+
+bool radix_one(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st)
+{
+    Buf<uint64_t> k2;
+    Buf<uint32_t> v2;
+    if (!st.check(k2.alloc(n, s, keys.kept), "sort workspace") || !st.check(v2.alloc(n, s, vals.kept), "sort workspace"))
+        return false;
+    auto k = n <= 4096 ? rs_one<4> : rs_one<8>;
+    k<<<1, 1024, 0, s>>>(keys.p, vals.p, k2.p, v2.p, (int)n, bits);
+    if (!st.check(hipGetLastError(), "sort launch")) return false;
+    if ((bits + 7) / 8 % 2 == 1) {
+        keys.swap(k2);
+        vals.swap(v2);
+    }
+    return true;
+}
+
+}  // namespace
+
 bool radix_sort(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st)
 {
     if (n <= 1 || bits <= 0) return true;
+    if (n <= kOneSort) return radix_one(keys, vals, n, bits, s, st);
     return n <= kSmallSort ? radix_passes<2>(keys, vals, n, bits, s, st) : radix_passes<8>(keys, vals, n, bits, s, st);
 }
 
