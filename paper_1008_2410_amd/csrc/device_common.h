@@ -219,17 +219,20 @@ __device__ __forceinline__ void p2p_tile_any(const rec_t<T> *tile, int len, int 
 // pair adds to dL/d(x, y) of its two particles is equal and opposite, since the kernel depends
 // on their difference alone.  With dz' = (dx', dy') the scaled difference z_i - z_j, e and g as
 // for the velocity, lambda ln 2 (FP32, whose exponent is base 2) or 1 (FP64),
-//   h = (lambda e - g/s')/s',  wr + i wi = h conj(dz')^2,  v = Gamma_j q_i - Gamma_i q_j,
-//   dL/dx_i += ka sum_j [v_x wi + v_y (wr + lambda e)],
-//   dL/dy_i += ka sum_j [v_x (wr - lambda e) - v_y wi],          ka = alpha^2/(2 pi),
-// the sum of the evaluation part Gamma_j (q_i A, B) and the source part Gamma_i (q_j ..) of the
-// separate sums below.  Two sums per particle in place of seven, and both particles of a pair
+//   h = (lambda e - g/s')/s' = d(g/s')/ds',  v = Gamma_j q_i - Gamma_i q_j,  c = v_y dx' - v_x dy',
+//   dL/dx_i += ka sum_j [ v_y g/s' + 2 h c dx'],
+//   dL/dy_i += ka sum_j [-v_x g/s' + 2 h c dy'],          ka = alpha^2/(2 pi),
+// the gradient of (v_y dx' - v_x dy') g/s', and the sum of the evaluation part Gamma_j (q_i A, B)
+// and the source part Gamma_i (q_j ..) of the separate sums below.  (As a turned product of v with
+// h conj(dz')^2 +- lambda e a step took three operations more, 28 in FP32 instead of 25, 62 in FP64
+// with Phi instead of 60: adjoint of 2^22 patch particles, mixed, 2.90 -> 2.77 ms, of 2^20 uniform
+// 0.395 -> 0.372.)  Two sums per particle in place of seven, and both particles of a pair
 // are served by one evaluation of the weights.  The sums kept are -dL/dx/ka and dL/dy/ka, the
 // signs of the velocity's.  Phi_i = alpha sum_j q_j (g/s') conj(dz') enters by its imaginary
 // part alone.
 //
-// The difference lambda e - g/s' cancels for small s', but |conj(dz')^2/s'| <= 1 puts its
-// error, a rounding of lambda e, beside lambda e itself.  g/s' = r - e r loses 1/s' roundings
+// The difference lambda e - g/s' cancels for small s', but |c dz'/s'| <= |v| puts its error, a
+// rounding of lambda e, beside v g/s' itself.  g/s' = r - e r loses 1/s' roundings
 // in FP32 and is taken from its series below series_cut (class 0; class 1: the boxes of the
 // two tiles keep every pair above it; class 2: e rounds to 0 against 1).
 // ---------------------------------------------------------------------------------
@@ -241,18 +244,15 @@ template <> __device__ __forceinline__ constexpr double exponent_base_log<double
 // g/s' = lambda (1 - x/2 + x^2/6 - x^3/24 + x^4/120): the next term is under a rounding there.
 constexpr float kSeriesX = 0.125f;
 
-template <typename T, int CLS>
-__device__ __forceinline__ void force_weights(T ddx, T ddy, T &gr, T &w, T &a, T &b)
+// gr = g/s' and (of no use to class 2) k = 2 h.
+template <typename T, int CLS> __device__ __forceinline__ void force_weights(T ddx, T ddy, T &gr, T &k)
 {
     constexpr T lam = exponent_base_log<T>();
-    const T dy2 = fma(ddy, ddy, tiny<T>());
-    const T s = fma(ddx, ddx, dy2);
+    const T s = fma(ddx, ddx, fma(ddy, ddy, tiny<T>()));
     const T r = recip(s);
     if constexpr (CLS == 2) {
-        const T cx = r * ddx, cy = r * ddy;
         gr = r;
-        a = b = fma(cy, cy, -cx * cx);
-        w = (T)-2 * cx * cy;
+        k = 0;
     } else {
         T e;
         if constexpr (sizeof(T) == 4) {
@@ -268,11 +268,23 @@ __device__ __forceinline__ void force_weights(T ddx, T ddy, T &gr, T &w, T &a, T
             exp_pair(s, e, g);
             gr = g * r;
         }
-        const T h = fma(lam, e, -gr) * r;
-        const T wr = h * fma((T)-2, dy2, s);
-        w = (h + h) * (ddx * ddy);
-        a = fma(lam, e, wr);
-        b = fma(-lam, e, wr);
+        const T t = fma(lam, e, -gr);
+        k = (t + t) * r;
+    }
+}
+
+// n (x, y) is the part of the pair's sums along dz', (x, y) being dz' or gr dz'.
+template <typename T, int CLS>
+__device__ __forceinline__ void force_along(T ddx, T ddy, T gr, T k, T vx, T vy, T &x, T &y, T &n)
+{
+    if constexpr (CLS == 2) {  // k = -2 gr^2
+        x = gr * ddx;
+        y = gr * ddy;
+        n = (T)-2 * fma(vx, y, -(vy * x));
+    } else {
+        x = ddx;
+        y = ddy;
+        n = k * fma(vx, y, -(vy * x));
     }
 }
 
@@ -283,14 +295,16 @@ __device__ __forceinline__ void force_pair(const rec_t<T> &rj, T qjy, const rec_
 {
     const T ddx = tx - rj.x;
     const T ddy = ty - rj.y;
-    T gr, w, a, b;
-    force_weights<T, CLS>(ddx, ddy, gr, w, a, b);
+    T gr, k;
+    force_weights<T, CLS>(ddx, ddy, gr, k);
     const T vx = fma(rj.z, ti.w, -(ti.z * rj.w));
     const T vy = fma(rj.z, tiqy, -(ti.z * qjy));
-    f[0] = fma(vx, w, f[0]);
-    f[0] = fma(-vy, a, f[0]);
-    f[1] = fma(vx, b, f[1]);
-    f[1] = fma(vy, w, f[1]);
+    T x, y, n;
+    force_along<T, CLS>(ddx, ddy, gr, k, vx, vy, x, y, n);
+    f[0] = fma(n, x, f[0]);
+    f[0] = fma(-gr, vy, f[0]);
+    f[1] = fma(-n, y, f[1]);
+    f[1] = fma(-gr, vx, f[1]);
     if constexpr (KIND == kForcePhi) {
         f[2] = fma(gr, fma(qjy, ddx, -(rj.w * ddy)), f[2]);
     }
@@ -586,12 +600,14 @@ __device__ __forceinline__ void force_chunk(const rec_t<T> *src, const T *qsrc, 
         const T sqy = qsrc[j];
         const T ddx = rx - sj.x;
         const T ddy = ry - sj.y;
-        T gr, w, a, b;
-        force_weights<T, CLS>(ddx, ddy, gr, w, a, b);
+        T gr, k;
+        force_weights<T, CLS>(ddx, ddy, gr, k);
         const T vx = fma(sj.z, rqx, -(rg * sj.w));
         const T vy = fma(sj.z, rqy, -(rg * sqy));
-        const T fx = fma(vx, w, -(vy * a));
-        const T fy = fma(vx, b, vy * w);
+        T x, y, n;
+        force_along<T, CLS>(ddx, ddy, gr, k, vx, vy, x, y, n);
+        const T fx = fma(n, x, -(gr * vy));
+        const T fy = fma(-n, y, -(gr * vx));
         T tj = 0;
         if constexpr (KIND == kForcePhi) {
             const T cx = gr * ddx, cy = gr * ddy;
