@@ -22,7 +22,7 @@ namespace {
 void free_ws(AtreeWs &w)
 {
     for (void *p : {w.gam, (void *)w.stage, (void *)w.gamma, (void *)w.near, w.slots, (void *)w.mp, (void *)w.lo,
-                    (void *)w.mp2, (void *)w.lo2, (void *)w.adj, w.qt, (void *)w.pa, (void *)w.pb, (void *)w.psrc, w.phi_slots,
+                    (void *)w.mp2, (void *)w.lo2, (void *)w.adj, w.qt, (void *)w.pa, (void *)w.psrc, w.phi_slots,
                     (void *)w.range})
         block_free(p);
     w = AtreeWs{};
@@ -270,12 +270,11 @@ int ensure_ws_backward(fmm_atree *t, bool src)
         if ((rc = dev_alloc_block(&w.adj, n, "adjoint charges")) ||
             (rc = dev_alloc_block((char **)&w.qt, n * (w.precision == FMM_FP64 ? sizeof(double2) : sizeof(float2)),
                             "adjoint charges")) ||
-            (rc = dev_alloc_block(&w.pa, n, "adjoint near sums")) || (rc = dev_alloc_block(&w.pb, n, "adjoint near sums"))) {
-            for (void *q : {(void *)w.adj, w.qt, (void *)w.pa, (void *)w.pb}) block_free(q);
+            (rc = dev_alloc_block(&w.pa, n, "adjoint near sums"))) {
+            for (void *q : {(void *)w.adj, w.qt, (void *)w.pa}) block_free(q);
             w.adj = nullptr;
             w.qt = nullptr;
             w.pa = nullptr;
-            w.pb = nullptr;
             return rc;
         }
     }

@@ -373,10 +373,10 @@ __device__ __forceinline__ void at_backward_unit(const int4 u, rec_t<T> *tile, c
                                                  const double4 *__restrict__ tile_box,
                                                  const SoaRec<T> &rec, const c2<T> *__restrict__ qt,
                                                  double x0, double y0, double side, double alpha, double cut,
-                                                 T lambda, double4 *__restrict__ out_pa, double *__restrict__ out_b,
+                                                 T lambda, double4 *__restrict__ out_pa,
                                                  double4 *__restrict__ out_src)
 {
-    constexpr int NA = SRC ? 9 : 5;
+    constexpr int NA = SRC ? 8 : 4;
     const int lane = threadIdx.x;
     const int logtp = u.w & 15;
     const int A = u.x;
@@ -447,8 +447,7 @@ __device__ __forceinline__ void at_backward_unit(const int4 u, rec_t<T> *tile, c
         for (int c = 0; c < NA; ++c) sum[c] = ul.reduce(sum[c]);
         if (lane < u.z) {
             out_pa[i] = make_double4(sum[0], sum[1], sum[2], sum[3]);
-            out_b[i] = sum[4];
-            if constexpr (SRC) out_src[i] = make_double4(sum[5], sum[6], sum[7], sum[8]);
+            if constexpr (SRC) out_src[i] = make_double4(sum[4], sum[5], sum[6], sum[7]);
         }
         return;
     }
@@ -499,8 +498,7 @@ __device__ __forceinline__ void at_backward_unit(const int4 u, rec_t<T> *tile, c
         for (int c = 0; c < NA; ++c) sum[c] += __shfl_xor(sum[c], o);
     if (k == 0 && t < u.z) {
         out_pa[i] = make_double4(sum[0], sum[1], sum[2], sum[3]);
-        out_b[i] = sum[4];
-        if constexpr (SRC) out_src[i] = make_double4(sum[5], sum[6], sum[7], sum[8]);
+        if constexpr (SRC) out_src[i] = make_double4(sum[4], sum[5], sum[6], sum[7]);
     }
 }
 
@@ -511,13 +509,13 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void at_bac
     const int *__restrict__ u_off, const int *__restrict__ u_idx, const int *__restrict__ tile_start,
     const double4 *__restrict__ tile_box, const c2<T> *__restrict__ pos, const T *__restrict__ gam,
     const c2<T> *__restrict__ qt, double x0, double y0, double side, double alpha, double cut, T lambda,
-    double4 *__restrict__ out_pa, double *__restrict__ out_b, double4 *__restrict__ out_src)
+    double4 *__restrict__ out_pa, double4 *__restrict__ out_src)
 {
     __shared__ rec_t<T> tile[128];
     __shared__ c2<T> qtile[128];
     const SoaRec<T> rec{pos, gam, (T)alpha};
     at_backward_unit<T, SRC>(units[blockIdx.x], tile, qtile, cell, range, u_off, u_idx, tile_start, tile_box, rec, qt,
-                             x0, y0, side, alpha, cut, lambda, out_pa, out_b, out_src);
+                             x0, y0, side, alpha, cut, lambda, out_pa, out_src);
 }
 
 // The adjoint's near field over the pair force (dl_dxy without its two parts), over the
@@ -689,7 +687,7 @@ __global__ __launch_bounds__(256) void at_finalize_backward_kernel(
     const double2 *__restrict__ xy, const int *__restrict__ w_off, const int *__restrict__ w_idx,
     const double2 *__restrict__ mp, const double2 *__restrict__ lo, const double2 *__restrict__ mp2,
     const double2 *__restrict__ lo2, int p, double x0, double y0, double side, const double4 *__restrict__ near_pa,
-    const double *__restrict__ near_b, const double4 *__restrict__ near_src, const double2 *__restrict__ adj,
+    const double4 *__restrict__ near_src, const double2 *__restrict__ adj,
     const double *__restrict__ gamma, double alpha, double lambda, AdjointOut out)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -697,16 +695,15 @@ __global__ __launch_bounds__(256) void at_finalize_backward_kernel(
     // the per-particle loads first, in flight during the far-field work
     const int64_t o = perm[i];
     const double4 a = near_pa[i];
-    const double sb = near_b[i];
     const int A = leaf_of[i];
     const int4 c = cell[A];
     const double2 z = xy[i];
     double2 dw, phi, dphi;
     far_adjoint(A, c, z, w_off, w_idx, cell, mp, lo, mp2, lo2, p, x0, y0, side, dw, phi, dphi);
     const double ka = alpha * alpha * kInv2Pi;
-    const double Ar = ka * (-2.0 * a.w), Ai = -ka * a.z;
-    const double Bi = -ka * lambda * sb;
-    const double g = -(alpha * a.y + phi.y) * kInv2Pi;
+    const double Ar = ka * (-2.0 * a.z), Ai = -ka * a.y;
+    const double Bi = -ka * lambda * a.w;
+    const double g = -(alpha * a.x + phi.y) * kInv2Pi;
     double ex = 0.0, ey = 0.0, sx = 0.0, sy = 0.0;
     if (out.dxe || out.dxy) {
         const double2 q = adj[i];
@@ -987,13 +984,13 @@ void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t s)
         k<<<g, 64, 0, s>>>(d.bwd_units, d.cell, d.range, d.u_off, d.u_idx, d.tile_start, d.tile_box,
                            (const double2 *)t->d_pos[1], (const double *)w.gam, (const double2 *)w.qt, t->x0,
                            t->y0, t->side, c.alpha, cut, 1.0,
-                           w.pa, w.pb, src ? w.psrc : nullptr);
+                           w.pa, src ? w.psrc : nullptr);
     } else {
         auto k = src ? at_backward_kernel<float, true> : at_backward_kernel<float, false>;
         k<<<g, 64, 0, s>>>(d.bwd_units, d.cell, d.range, d.u_off, d.u_idx, d.tile_start, d.tile_box,
                            (const float2 *)t->d_pos[0], (const float *)w.gam, (const float2 *)w.qt, t->x0,
                            t->y0, t->side, c.alpha, cut,
-                           0.69314718055994530942f, w.pa, w.pb, src ? w.psrc : nullptr);
+                           0.69314718055994530942f, w.pa, src ? w.psrc : nullptr);
     }
 }
 
@@ -1042,7 +1039,7 @@ void launch_atree_finalize_backward(const AtreeCall &c, const AdjointOut &out, h
     const AtreeWs &w = *t->wsp;
     auto k = (out.dxs || out.dxy) ? at_finalize_backward_kernel<true> : at_finalize_backward_kernel<false>;
     k<<<blocks(n, 256), 256, 0, s>>>(n, d.perm, d.leaf_of, d.cell, d.xy, d.w_off, d.w_idx, w.mp, w.lo, w.mp2, w.lo2,
-                                     c.p, t->x0, t->y0, t->side, w.pa, w.pb, w.psrc, w.adj, w.gamma, c.alpha, lambda,
+                                     c.p, t->x0, t->y0, t->side, w.pa, w.psrc, w.adj, w.gamma, c.alpha, lambda,
                                      out);
 }
 

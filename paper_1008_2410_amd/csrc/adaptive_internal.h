@@ -102,11 +102,10 @@ struct AtreeWs {
     double2 *mp = nullptr;      // multipoles a_m / w^m, cells x p
     double2 *lo = nullptr;      // locals b_l w^(l+1), cells x p
     // adjoint: expansions of the adjoint charges q, the charges (sorted, FP64, and in the
-    // records' precision), the near sums {Phi, A (Re, Im / -2)}, B, and the source sums
+    // records' precision), the near sums {Im Phi, A (Re, Im / -2), B}, and the source sums
     double2 *mp2 = nullptr, *lo2 = nullptr, *adj = nullptr;
     void *qt = nullptr;
     double4 *pa = nullptr, *psrc = nullptr;
-    double *pb = nullptr;
     // the pair force: slots of Phi (9 x n in the records' precision), the charges' range
     void *phi_slots = nullptr;
     double2 *range = nullptr;

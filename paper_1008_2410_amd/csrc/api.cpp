@@ -214,16 +214,15 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
         ws.owner = t->serial;  // zeroed just now
     }
     if (!ws.sums) {
-        // the mutual slots, or the adjoint sums at 256-byte aligned offsets 0, A(32n), A(A(32n) + 8n)
+        // the mutual slots, or the adjoint sums at 256-byte aligned offsets 0, A(32n)
         auto a256 = [](size_t b) { return (b + 255) / 256 * 256; };
         const size_t nn = (size_t)n;
-        const size_t o_b = a256(32 * nn), o_src = a256(o_b + 8 * nn);
+        const size_t o_src = a256(32 * nn);
         const size_t bytes = std::max(9 * nn * (precision == FMM_FP64 ? 16 : 8), o_src + 32 * nn);
         if ((rc = dev_alloc_block((char **)&ws.sums, bytes, "near-field sums"))) return rc;
         ws.sums_bytes = bytes;
         ws.slots = ws.sums;
         ws.bwd_near = (double4 *)ws.sums;
-        ws.bwd_b = (double *)((char *)ws.sums + o_b);
         ws.bwd_src = (double4 *)((char *)ws.sums + o_src);
     }
     if (backward && !ws.adj) {
@@ -939,7 +938,7 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
         return FMM_OK;
     }
     launch_p2p_backward(t, pos, ws.gam, qv, is_double, alpha, ws.bwd_near,
-                        ws.bwd_b, need_src ? ws.bwd_src : nullptr, ms);
+                        need_src ? ws.bwd_src : nullptr, ms);
     tm.mark(5, ms);
     tm.mark(6, ms);
     // once the outputs fill the last-level cache they reach user order through staging slots, kept in
@@ -951,7 +950,7 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     double *st_g = !staged ? nullptr : is_double ? (double *)ws.gam : (double *)ws.rec2;
     double *st_x = staged ? (double *)ws.stage : nullptr;
     double *st_s = staged ? (double *)ws.near : nullptr;
-    launch_finalize_backward(t, fc, fq, ws.bwd_near, ws.bwd_b, ws.adj, ws.bwd_src, is_double, alpha, out, st_g, st_x,
+    launch_finalize_backward(t, fc, fq, ws.bwd_near, ws.adj, ws.bwd_src, is_double, alpha, out, st_g, st_x,
                              st_s, ms);
     tm.mark(7, ms);
     HIP_TRY(hipGetLastError());

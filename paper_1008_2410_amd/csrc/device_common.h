@@ -908,17 +908,18 @@ template <typename T> __device__ __forceinline__ T series_cut();
 template <> __device__ __forceinline__ float series_cut<float>() { return 0.125f; }
 template <> __device__ __forceinline__ double series_cut<double>() { return 1e-3; }
 
-// acc: Phi (2); A as its real part and its imaginary part divided by -2 (the factor is
-// applied in finalize); B; with SRC also the source-position sums with the adjoint
-// charges, At = sum q_j conj(dz')^2 (lambda e s' - g)/s'^2 (2) and Bt = sum q_j e (2).
+// acc: Im Phi (its real part enters no output); A as its real part and its imaginary part divided
+// by -2 (the factor is applied in finalize); B; with SRC also the source-position sums with the
+// adjoint charges, At = sum q_j conj(dz')^2 (lambda e s' - g)/s'^2 (2) and Bt = sum q_j e (2).
 // conj(dz')^2 = (dx'^2 - dy'^2) - 2i dx' dy' reuses dy'^2 from s'.  SERIES false: the
 // pair is known to lie beyond the series cut (its tile's bounding boxes say so), and the
-// test is left out.
+// test is left out.  (With the real part of Phi summed too, two operations and 8 B per particle
+// more: 2^22 patch particles, mixed, 3.75 ms, now 3.50; 700001, FP64, 1.32, now 1.20.)
 template <typename T, bool FAR, bool SRC, bool SERIES = true>
 __device__ __forceinline__ void p2p_bwd_pair(const rec_t<T> &rj, const c2<T> qj, T tx, T ty, T lambda,
-                                             T (&acc)[SRC ? 9 : 5])
+                                             T (&acc)[SRC ? 8 : 4])
 {
-    T &fpr = acc[0], &fpi = acc[1], &far_r = acc[2], &far_ih = acc[3], &fb = acc[4];
+    T &fpi = acc[0], &far_r = acc[1], &far_ih = acc[2], &fb = acc[3];
     const T ddx = tx - rj.x;
     const T ddy = ty - rj.y;
     const T dy2 = fma(ddy, ddy, tiny<T>());
@@ -930,8 +931,6 @@ __device__ __forceinline__ void p2p_bwd_pair(const rec_t<T> &rj, const c2<T> qj,
         // Re(-w^2) = d = cy^2 - cx^2 and Im(-w^2)/-2 = cx cy; the source-position sum takes
         // q_j (d - 2i cx cy).  (Three operations fewer than the general form below.)
         const T cx = r * ddx, cy = -r * ddy;
-        fpr = fma(qj.x, cx, fpr);
-        fpr = fma(-qj.y, cy, fpr);
         fpi = fma(qj.x, cy, fpi);
         fpi = fma(qj.y, cx, fpi);
         const T d = fma(cy, cy, -cx * cx);
@@ -940,10 +939,10 @@ __device__ __forceinline__ void p2p_bwd_pair(const rec_t<T> &rj, const c2<T> qj,
         far_ih = fma(rj.z, m, far_ih);
         if constexpr (SRC) {
             const T wi = (T)-2 * m;
-            acc[5] = fma(qj.x, d, acc[5]);
-            acc[5] = fma(-qj.y, wi, acc[5]);
-            acc[6] = fma(qj.x, wi, acc[6]);
-            acc[6] = fma(qj.y, d, acc[6]);
+            acc[4] = fma(qj.x, d, acc[4]);
+            acc[4] = fma(-qj.y, wi, acc[4]);
+            acc[5] = fma(qj.x, wi, acc[5]);
+            acc[5] = fma(qj.y, d, acc[5]);
         }
         return;
     }
@@ -968,13 +967,11 @@ __device__ __forceinline__ void p2p_bwd_pair(const rec_t<T> &rj, const c2<T> qj,
     }
     fb = fma(rj.z, e, fb);  // B: Gamma_j e
     if constexpr (SRC) {
-        acc[7] = fma(qj.x, e, acc[7]);
-        acc[8] = fma(qj.y, e, acc[8]);
+        acc[6] = fma(qj.x, e, acc[6]);
+        acc[7] = fma(qj.y, e, acc[7]);
     }
     // Phi: q_j (g/s') conj(dz')
     const T cx = gr * ddx, cy = -gr * ddy;
-    fpr = fma(qj.x, cx, fpr);
-    fpr = fma(-qj.y, cy, fpr);
     fpi = fma(qj.x, cy, fpi);
     fpi = fma(qj.y, cx, fpi);
     // A: Gamma_j conj(dz')^2 (lambda e s' - g)/s'^2
@@ -985,16 +982,16 @@ __device__ __forceinline__ void p2p_bwd_pair(const rec_t<T> &rj, const c2<T> qj,
     far_ih = fma(hg, zh, far_ih);
     if constexpr (SRC) {
         const T wr = h * zr, wi = ((T)-2 * h) * zh;
-        acc[5] = fma(qj.x, wr, acc[5]);
-        acc[5] = fma(-qj.y, wi, acc[5]);
-        acc[6] = fma(qj.x, wi, acc[6]);
-        acc[6] = fma(qj.y, wr, acc[6]);
+        acc[4] = fma(qj.x, wr, acc[4]);
+        acc[4] = fma(-qj.y, wi, acc[4]);
+        acc[5] = fma(qj.x, wi, acc[5]);
+        acc[5] = fma(qj.y, wr, acc[5]);
     }
 }
 
 template <typename T, int K, bool FAR, bool SRC, bool SERIES = true>
 __device__ __forceinline__ void p2p_bwd_tile(const rec_t<T> *tile, const c2<T> *qtile, int len, int k, T tx, T ty,
-                                             T lambda, T (&acc)[SRC ? 9 : 5])
+                                             T lambda, T (&acc)[SRC ? 8 : 4])
 {
     if (len == 64) {
 #pragma unroll 4
@@ -1010,7 +1007,7 @@ __device__ __forceinline__ void p2p_bwd_tile(const rec_t<T> *tile, const c2<T> *
 // which carry nearly all pairs, so the other unrolled variants stay few); 0: the full form.
 template <typename T, int K, bool SRC>
 __device__ __forceinline__ void p2p_bwd_tile_any(const rec_t<T> *tile, const c2<T> *qtile, int len, int k, T tx, T ty,
-                                                 T lambda, T (&acc)[SRC ? 9 : 5], int cls)
+                                                 T lambda, T (&acc)[SRC ? 8 : 4], int cls)
 {
     if (cls == 2) p2p_bwd_tile<T, K, true, SRC>(tile, qtile, len, k, tx, ty, lambda, acc);
     else if (K <= 2 && cls == 1) p2p_bwd_tile<T, K, false, SRC, false>(tile, qtile, len, k, tx, ty, lambda, acc);
@@ -1020,7 +1017,7 @@ __device__ __forceinline__ void p2p_bwd_tile_any(const rec_t<T> *tile, const c2<
 // Steps of one batch of the adjoint, as p2p_batch.
 template <typename T, bool FAR, bool SRC>
 __device__ __forceinline__ void p2p_bwd_batch(const rec_t<T> *tile, const c2<T> *qtile, int count, int k, int K, T tx,
-                                              T ty, T lambda, T (&acc)[SRC ? 9 : 5])
+                                              T ty, T lambda, T (&acc)[SRC ? 8 : 4])
 {
     const int steps = (count + K - 1) / K;
     const rec_t<T> *src = tile + k;

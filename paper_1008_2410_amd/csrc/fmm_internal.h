@@ -114,14 +114,13 @@ struct Workspace {
     float2 *mp_f = nullptr, *lo_f = nullptr;   // FP32 levels
     // backward pass
     double2 *adj = nullptr;       // per sorted particle: adjoint charge q (sorted order)
-    double4 *bwd_near = nullptr;  // per sorted particle: near sums of Phi (2) and A (2)
-    double *bwd_b = nullptr;      // per sorted particle: near sum of B
+    double4 *bwd_near = nullptr;  // per sorted particle: near sums of Im Phi, A (2) and B
     double2 *mp2_d = nullptr, *lo2_d = nullptr;  // mp2_* = mp_* (the charges q reuse the multipoles)
     float2 *mp2_f = nullptr, *lo2_f = nullptr;
     void *rec2 = nullptr;         // adjoint charges q in FP32 for the mixed near field
     double4 *bwd_src = nullptr;   // per sorted particle: near sums of the source-position terms
     // One region for the per-particle sums of either call: the forward's mutual near-field
-    // slots (9 x n float2 or double2) or the adjoint's near sums (bwd_near, bwd_b, bwd_src),
+    // slots (9 x n float2 or double2) or the adjoint's near sums (bwd_near, bwd_src),
     // never live in the same call.
     void *sums = nullptr;
     size_t sums_bytes = 0;
@@ -290,9 +289,9 @@ void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const
 void launch_finalize_force(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double2 *adj,
                            const ForceNear &near, int is_double, double alpha, const AdjointOut &out, hipStream_t s);
 void launch_p2p_backward(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double,
-                         double alpha, double4 *out_pa, double *out_b, double4 *out_src, hipStream_t s);
+                         double alpha, double4 *out_pa, double4 *out_src, hipStream_t s);
 void launch_finalize_backward(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double4 *near_pa,
-                              const double *near_b, const double2 *adj, const double4 *near_src, int is_double,
+                              const double2 *adj, const double4 *near_src, int is_double,
                               double alpha, const AdjointOut &out, double *stage_g, double *stage_x,
                               double *stage_s, hipStream_t s);
 

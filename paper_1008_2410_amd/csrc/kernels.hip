@@ -599,10 +599,10 @@ __device__ __forceinline__ void p2p_backward_unit(const int4 u, rec_t<T> *tile, 
                                                   const int *__restrict__ tile_start,
                                                   const float4 *__restrict__ tile_box, int nside, T step,
                                                   float cut_leaf2, float series_leaf2, T lambda,
-                                                  double4 *__restrict__ out_pa, double *__restrict__ out_b,
+                                                  double4 *__restrict__ out_pa,
                                                   double4 *__restrict__ out_src)
 {
-    constexpr int NA = SRC ? 9 : 5;
+    constexpr int NA = SRC ? 8 : 4;
     const int lane = threadIdx.x;
     const int logtp = u.w;
     const int ix = (int)morton_x((uint32_t)u.x), iy = (int)morton_y((uint32_t)u.x);
@@ -667,8 +667,7 @@ __device__ __forceinline__ void p2p_backward_unit(const int4 u, rec_t<T> *tile, 
         for (int c = 0; c < NA; ++c) sum[c] = ul.reduce(sum[c]);
         if (lane < u.z) {
             out_pa[i] = make_double4(sum[0], sum[1], sum[2], sum[3]);
-            out_b[i] = sum[4];
-            if constexpr (SRC) out_src[i] = make_double4(sum[5], sum[6], sum[7], sum[8]);
+            if constexpr (SRC) out_src[i] = make_double4(sum[4], sum[5], sum[6], sum[7]);
         }
         return;
     }
@@ -720,8 +719,7 @@ __device__ __forceinline__ void p2p_backward_unit(const int4 u, rec_t<T> *tile, 
         for (int c = 0; c < NA; ++c) sum[c] += __shfl_xor(sum[c], o);
     if (k == 0 && t < u.z) {
         out_pa[i] = make_double4(sum[0], sum[1], sum[2], sum[3]);
-        out_b[i] = sum[4];
-        if constexpr (SRC) out_src[i] = make_double4(sum[5], sum[6], sum[7], sum[8]);
+        if constexpr (SRC) out_src[i] = make_double4(sum[4], sum[5], sum[6], sum[7]);
     }
 }
 
@@ -731,13 +729,13 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void p2p_ba
     const int4 *__restrict__ units, const c2<T> *__restrict__ pos, const T *__restrict__ gam,
     const c2<T> *__restrict__ qv, const int *__restrict__ leaf_start, const int *__restrict__ tile_start,
     const float4 *__restrict__ tile_box, int nside, T step, float cut_leaf2, float series_leaf2, T lambda,
-    double4 *__restrict__ out_pa, double *__restrict__ out_b, double4 *__restrict__ out_src)
+    double4 *__restrict__ out_pa, double4 *__restrict__ out_src)
 {
     __shared__ rec_t<T> tile[128];
     __shared__ c2<T> qtile[128];
     const SoaRec<T> rec{pos, gam, step};
     p2p_backward_unit<T, SRC>(units[blockIdx.x], tile, qtile, rec, qv, leaf_start, tile_start, tile_box, nside, step,
-                              cut_leaf2, series_leaf2, lambda, out_pa, out_b, out_src);
+                              cut_leaf2, series_leaf2, lambda, out_pa, out_src);
 }
 
 // Adjoint finalize: far parts from the q-field locals (Phi_far, by L2P) and the c-field
@@ -787,7 +785,7 @@ __device__ __forceinline__ AdjointFar adjoint_far(uint32_t leaf, int i, const do
 template <typename TL>
 __global__ __launch_bounds__(256) void finalize_backward_kernel(
     int n, const int *__restrict__ perm, const int *__restrict__ leaf_of, const double2 *__restrict__ xy,
-    const double4 *__restrict__ near_pa, const double *__restrict__ near_b, const double2 *__restrict__ adj,
+    const double4 *__restrict__ near_pa, const double2 *__restrict__ adj,
     const c2<TL> *__restrict__ loc_c, const c2<TL> *__restrict__ loc_q, const c2<TL> *__restrict__ pos, int p,
     int has_far, double x0, double y0,
     double w, double alpha, double lambda, AdjointOut out, const double4 *__restrict__ near_src,
@@ -801,13 +799,12 @@ __global__ __launch_bounds__(256) void finalize_backward_kernel(
     // the user row, or with stage the staging slot inside the window of the sorted bucket
     const int64_t o = stage ? gpos2[i] : perm[i];  // issued with the first loads
     const double4 a = near_pa[i];
-    const double sb = near_b[i];
-    double phi = alpha * a.y;  // only Im(Phi) enters dL/dGamma
+    double phi = alpha * a.x;  // only Im(Phi) enters dL/dGamma
     const double ka = alpha * alpha * kInv2Pi;
-    // A = -i ka (a.z + i a.w') with a.w' = -2 a.w (the near sums hold Im A / -2):
-    // A = ka (a.w', -a.z);  B = -i ka lambda sb
-    double Ar = ka * (-2.0 * a.w), Ai = -ka * a.z;
-    const double Bi = -ka * lambda * sb;
+    // A = -i ka (a.y + i a.z') with a.z' = -2 a.z (the near sums hold Im A / -2):
+    // A = ka (a.z', -a.y);  B = -i ka lambda a.w
+    double Ar = ka * (-2.0 * a.z), Ai = -ka * a.y;
+    const double Bi = -ka * lambda * a.w;
     double dwr = 0.0, dwi = 0.0, dpr = 0.0, dpi = 0.0;
     if (has_far) {
         const AdjointFar f =
@@ -1356,7 +1353,7 @@ void launch_pack_adjoint(const fmm_tree *t, const double *dl_duv, double scale, 
 
 void launch_p2p_backward(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double,
                          double alpha,
-                         double4 *out_pa, double *out_b, double4 *out_src, hipStream_t s)
+                         double4 *out_pa, double4 *out_src, hipStream_t s)
 {
     if (t->nunits == 0) return;
     const int nside = 1 << t->depth;
@@ -1374,22 +1371,22 @@ void launch_p2p_backward(const fmm_tree *t, const void *pos, const void *gam, co
         if (out_src)
             p2p_backward_kernel<double, true><<<grid, 64, 0, s>>>(
                 t->d_units, (const double2 *)pos, (const double *)gam, (const double2 *)qv, t->d_leaf_start,
-                t->d_tile_start, t->d_tile_box, nside, step, cut_leaf2, series_leaf2, 1.0, out_pa, out_b, out_src);
+                t->d_tile_start, t->d_tile_box, nside, step, cut_leaf2, series_leaf2, 1.0, out_pa, out_src);
         else
             p2p_backward_kernel<double, false><<<grid, 64, 0, s>>>(
                 t->d_units, (const double2 *)pos, (const double *)gam, (const double2 *)qv, t->d_leaf_start,
-                t->d_tile_start, t->d_tile_box, nside, step, cut_leaf2, series_leaf2, 1.0, out_pa, out_b, nullptr);
+                t->d_tile_start, t->d_tile_box, nside, step, cut_leaf2, series_leaf2, 1.0, out_pa, nullptr);
     } else {
         if (out_src)
             p2p_backward_kernel<float, true><<<grid, 64, 0, s>>>(
                 t->d_units, (const float2 *)pos, (const float *)gam, (const float2 *)qv, t->d_leaf_start,
                 t->d_tile_start, t->d_tile_box, nside, (float)step, cut_leaf2, series_leaf2, (float)ln2, out_pa,
-                out_b, out_src);
+                out_src);
         else
             p2p_backward_kernel<float, false><<<grid, 64, 0, s>>>(
                 t->d_units, (const float2 *)pos, (const float *)gam, (const float2 *)qv, t->d_leaf_start,
                 t->d_tile_start, t->d_tile_box, nside, (float)step, cut_leaf2, series_leaf2, (float)ln2, out_pa,
-                out_b, nullptr);
+                nullptr);
     }
 }
 
@@ -1420,7 +1417,7 @@ void launch_finalize_force(const fmm_tree *t, const FarArgs &fc, const FarArgs &
 }
 
 void launch_finalize_backward(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double4 *near_pa,
-                              const double *near_b, const double2 *adj, const double4 *near_src, int is_double,
+                              const double2 *adj, const double4 *near_src, int is_double,
                               double alpha, const AdjointOut &out, double *stage_g, double *stage_x,
                               double *stage_s, hipStream_t s)
 {
@@ -1432,13 +1429,13 @@ void launch_finalize_backward(const fmm_tree *t, const FarArgs &fc, const FarArg
     const double lambda = is_double ? 1.0 : 0.69314718055994530942;
     if (!has_far || L <= fc.split)
         finalize_backward_kernel<double><<<g, 256, 0, s>>>(
-            n, t->d_perm, t->d_leaf_of, t->d_xy, near_pa, near_b, adj,
+            n, t->d_perm, t->d_leaf_of, t->d_xy, near_pa, adj,
             has_far ? level_ptr<double>(fc, L, true) : nullptr, has_far ? level_ptr<double>(fq, L, true) : nullptr,
             fc.rec_is_double ? (const double2 *)fc.pos : nullptr, fc.p, has_far, t->x0, t->y0, w, alpha, lambda, out, near_src, t->d_gpos2, fc.gamma, stage_g, stage_x,
             stage_s, kXcds);
     else
         finalize_backward_kernel<float><<<g, 256, 0, s>>>(
-            n, t->d_perm, t->d_leaf_of, t->d_xy, near_pa, near_b, adj, level_ptr<float>(fc, L, true),
+            n, t->d_perm, t->d_leaf_of, t->d_xy, near_pa, adj, level_ptr<float>(fc, L, true),
             level_ptr<float>(fq, L, true), fc.rec_is_double ? nullptr : (const float2 *)fc.pos, fc.p, has_far, t->x0, t->y0, w, alpha, lambda, out, near_src, t->d_gpos2,
             fc.gamma, stage_g, stage_x, stage_s, kXcds);
     if (stage_x) gather_adjoint_kernel<<<g, 256, 0, s>>>(n, kXcds, t->d_gpos1, stage_g, stage_x, stage_s, out);
