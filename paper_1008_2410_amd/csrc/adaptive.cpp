@@ -22,8 +22,7 @@ namespace {
 void free_ws(AtreeWs &w)
 {
     for (void *p : {w.gam, (void *)w.stage, (void *)w.gamma, (void *)w.near, w.slots, (void *)w.mp, (void *)w.lo,
-                    (void *)w.mp2, (void *)w.lo2, (void *)w.adj, w.qt, (void *)w.pa, (void *)w.psrc, w.phi_slots,
-                    (void *)w.range})
+                    (void *)w.mp2, (void *)w.lo2, (void *)w.adj, w.qt, (void *)w.pa, (void *)w.psrc, (void *)w.phi_slots})
         block_free(p);
     w = AtreeWs{};
 }
@@ -279,14 +278,10 @@ int ensure_ws_backward(fmm_atree *t, bool src)
         }
     }
     if (src && !w.psrc && (rc = dev_alloc_block(&w.psrc, n, "adjoint source-position sums"))) return rc;
-    if (src && !w.range) {  // the pair force; without it the separate sums serve
-        if (block_alloc((void **)&w.range, (kRangeBlocks + 1) * sizeof(double2)) != hipSuccess ||
-            block_alloc(&w.phi_slots, 9 * n * (w.precision == FMM_FP64 ? sizeof(double) : sizeof(float))) != hipSuccess) {
-            block_free(w.range);
-            w.range = nullptr;
-            w.phi_slots = nullptr;
-        }
-    }
+    // the pair force; without it the separate sums serve
+    if (src && w.precision == FMM_FP64 && !w.phi_slots &&
+        block_alloc((void **)&w.phi_slots, 9 * n * sizeof(double)) != hipSuccess)
+        w.phi_slots = nullptr;
     return FMM_OK;
 }
 
@@ -351,11 +346,10 @@ int choose_occupancy(const fmm_atree *t, int precision, bool concurrent)
 // The same for the adjoint's pair force, whose kernels hold fewer wavefronts, beside its two far
 // chains, as for the uniform tree (1000001 clustered particles, FP64: 0.897 ms at two, 0.930 at
 // three).
-int choose_force_occupancy(const fmm_atree *t, int precision, bool concurrent, bool phi)
+int choose_force_occupancy(const fmm_atree *t, bool concurrent)
 {
-    const int cap = choose_occupancy(t, precision, concurrent);
-    if (t->near_occupancy >= 0) return cap;
-    return precision == FMM_FP64 ? (cap > 2 ? cap - 1 : cap) : std::min(cap, phi ? 4 : 5);
+    const int cap = choose_occupancy(t, FMM_FP64, concurrent);
+    return t->near_occupancy < 0 && cap > 2 ? cap - 1 : cap;
 }
 
 // The translations' operator tables (shared) and the tree's M2L plan (made on the first
@@ -423,18 +417,22 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     if ((rc = ensure_ws(t, p, precision)) || (rc = ensure_ws_backward(t, src)) ||
         (rc = ensure_coords(t, precision, ms)) || (rc = ensure_m2l_plan(t, p, ms, tabs)))
         return rc;
-    // the pair force for dl_dxy without its two parts, as for the uniform tree
+    // the pair force for dl_dxy without its two parts, as for the uniform tree, in FP64.  In FP32 a
+    // position gradient over small sigma can be as large as the result it is added to (clusters
+    // in leaves of 8 sigma: lambda + h J^T lambda, h J of order 1 and more), so that a roundoff of
+    // another order of summation is one of the result (2e-7): there the order stays, leaf by leaf.
+    // (1000001 clustered particles at depth 13: 0.774 ms, 0.662 with the pair force.)
     const AtreeWs &w = *t->wsp;
-    const bool force = out.dxy && !out.dxe && !out.dxs && w.range;
+    const bool force = precision == FMM_FP64 && out.dxy && !out.dxe && !out.dxs && w.phi_slots;
     if (!force && t->nbwd_units < 0) {
         std::string err;
         if ((rc = build_atree_adjoint_units(t, ms, err))) return fail(rc, err);
     }
     if (!force) ss = ms;
     const AtreeCall c{t, p, precision == FMM_FP64, record_alpha(sigma, precision),
-                      choose_force_occupancy(t, precision, ss != ms, out.dg != nullptr), tabs};
+                      force ? choose_force_occupancy(t, ss != ms) : 0, tabs};
     launch_atree_pack(c, gamma, ms);
-    launch_atree_pack_adjoint(c, gamma, dl_duv, scale, force, ms);
+    launch_atree_pack_adjoint(c, dl_duv, scale, ms);
     // The two far chains (charges c: the derivative W' at the particles; charges q: the transpose
     // pass) go through the same launches, beside the pair force; the separate sums, which hold
     // every wavefront slot, follow them.
@@ -453,7 +451,6 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
             near.phi = (double *)w.stage;
             near.phi_slots = w.phi_slots;
         }
-        near.qscale = c.is_double ? nullptr : (const double *)(w.range + kRangeBlocks);
         launch_atree_force(c, near, ms);
         if (ss != ms) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
         launch_atree_finalize_force(c, near, out, ms);

@@ -348,17 +348,14 @@ __global__ __launch_bounds__(256) void at_finalize_kernel(int n, const int *__re
 template <typename T>
 __global__ __launch_bounds__(256) void at_pack_adjoint_kernel(int n, int nxcd, const int *__restrict__ gpos2,
                                                                const double2 *__restrict__ dl_st, double scale,
-                                                               double2 *__restrict__ adj, c2<T> *__restrict__ qt,
-                                                               const double2 *__restrict__ bounds,
-                                                               double *__restrict__ qscale)
+                                                               double2 *__restrict__ adj, c2<T> *__restrict__ qt)
 {
-    const double qs = charge_scale(bounds, qscale);
     const int i = xcd_block(nxcd) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double2 d = dl_st[gpos2[i]];  // the cotangent staged by bucket
     const double2 q = make_double2(scale * d.x, scale * d.y);
     adj[i] = q;
-    qt[i] = mk<T>((T)(qs * q.x), (T)(qs * q.y));
+    qt[i] = mk<T>((T)q.x, (T)q.y);
 }
 
 // Adjoint near field of one unit {leaf A, first, count <= 64, log2 TP}: every source leaf
@@ -387,7 +384,8 @@ __device__ __forceinline__ void at_backward_unit(const int4 u, rec_t<T> *tile, c
     const int ebegin = u_off[A], eend = u_off[A + 1];
     int longest = 0;
     for (int e = ebegin + lane; e < eend; e += 64) longest = max(longest, range[u_idx[e]].y);
-    if (!__any(longest > 64)) {  // every source leaf is one tile: staged together, in A's frame
+    // FP64, every source leaf one tile: staged together, in A's frame (FP32: see run_backward)
+    if (sizeof(T) == 8 && !__any(longest > 64)) {
         const UnitLanes ul(lane, u.z, logtp);
         const int i = u.y + min(ul.t, u.z - 1);
         const rec_t<T> ri = rec(i);
@@ -521,7 +519,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void at_bac
 // The adjoint's near field over the pair force (dl_dxy without its two parts), over the
 // forward's work list: its units, and its mutual items with each pair evaluated once.
 template <typename T, int KIND>
-__global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 3) void at_force_kernel(
+__global__ __launch_bounds__(64, 3) void at_force_kernel(
     const int4 *__restrict__ work, const int4 *__restrict__ cell, const int2 *__restrict__ range,
     const int *__restrict__ u_off, const int *__restrict__ u_idx, const int *__restrict__ tile_start,
     const double4 *__restrict__ tile_box, const int *__restrict__ leaf_start, const int *__restrict__ leaf_tile,
@@ -725,7 +723,6 @@ __global__ __launch_bounds__(256) void at_finalize_backward_kernel(
 }
 
 // Adjoint finalize of the pair force: the near sums combined, the far parts as above.
-template <typename TS>
 __global__ __launch_bounds__(256) void at_finalize_force_kernel(
     int n, const int *__restrict__ perm, const int *__restrict__ leaf_of, const int4 *__restrict__ cell,
     const double2 *__restrict__ xy, const int *__restrict__ w_off, const int *__restrict__ w_idx,
@@ -742,14 +739,13 @@ __global__ __launch_bounds__(256) void at_finalize_force_kernel(
     const double2 z = xy[i], q = adj[i];
     const double G = gamma[i] * kInv2Pi;
     const int m = near.mask[A];
-    const double uq = near.qscale ? 1.0 / *near.qscale : 1.0;
-    const double2 nr = near_from_slots<TS>(i, n, m, near.near, (const c2<TS> *)near.slots, alpha * alpha * kInv2Pi);
+    const double2 nr = near_from_slots<double>(i, n, m, near.near, (const double2 *)near.slots, alpha * alpha * kInv2Pi);
     double nphi = 0.0;
-    if (out.dg) nphi = alpha * uq * phi_from_slots<TS>(i, n, m, near.phi, (const TS *)near.phi_slots);
+    if (out.dg) nphi = alpha * phi_from_slots<double>(i, n, m, near.phi, (const double *)near.phi_slots);
     double2 dw, phi, dphi;
     far_adjoint(A, c, z, w_off, w_idx, cell, mp, lo, mp2, lo2, p, x0, y0, side, dw, phi, dphi);
-    store_adjoint(out, o, -(nphi + phi.y) * kInv2Pi, uq * nr.x + (q.x * dw.x - q.y * dw.y),
-                  uq * nr.y - (q.x * dw.y + q.y * dw.x), -G * dphi.y, -G * dphi.x);
+    store_adjoint(out, o, -(nphi + phi.y) * kInv2Pi, nr.x + (q.x * dw.x - q.y * dw.y),
+                  nr.y - (q.x * dw.y + q.y * dw.x), -G * dphi.y, -G * dphi.x);
 }
 
 inline unsigned blocks(int64_t work, int per) { return (unsigned)((work + per - 1) / per); }
@@ -948,8 +944,7 @@ void launch_atree_finalize(const AtreeCall &c, double *uv, double *uv_near, doub
     else if (staged) scatter_rows_kernel<<<blocks(n, 256), 256, 0, s>>>(n, t->d.perm, staged, uv, base, h);
 }
 
-void launch_atree_pack_adjoint(const AtreeCall &c, const double *gamma, const double *dl_duv, double scale,
-                               bool force, hipStream_t s)
+void launch_atree_pack_adjoint(const AtreeCall &c, const double *dl_duv, double scale, hipStream_t s)
 {
     const fmm_atree *t = c.t;
     const int n = (int)t->n;
@@ -960,15 +955,12 @@ void launch_atree_pack_adjoint(const AtreeCall &c, const double *gamma, const do
     const int *idx = direct ? t->d.perm : t->d.gpos2;
     const double2 *rows = direct ? (const double2 *)dl_duv : st;
     const unsigned g = xcd_grid(n, 256, kXcds);
-    double2 *bounds = force && !c.is_double ? t->wsp->range : nullptr;
-    if (bounds)
-        adjoint_range_kernel<<<kRangeBlocks, 256, 0, s>>>(n, gamma, (const double2 *)dl_duv, scale, bounds);
     if (c.is_double)
         at_pack_adjoint_kernel<double><<<g, 256, 0, s>>>(n, kXcds, idx, rows, scale, t->wsp->adj,
-                                                         (double2 *)t->wsp->qt, nullptr, nullptr);
+                                                         (double2 *)t->wsp->qt);
     else
         at_pack_adjoint_kernel<float><<<g, 256, 0, s>>>(n, kXcds, idx, rows, scale, t->wsp->adj,
-                                                        (float2 *)t->wsp->qt, bounds, (double *)(bounds + kRangeBlocks));
+                                                        (float2 *)t->wsp->qt);
 }
 
 void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t s)
@@ -1014,8 +1006,7 @@ template <typename T, int KIND> void force_launch(const AtreeCall &c, const Forc
 void launch_atree_force(const AtreeCall &c, const ForceNear &near, hipStream_t s)
 {
     if (c.t->nwork == 0) return;
-    auto k = c.is_double ? (near.phi ? force_launch<double, kForcePhi> : force_launch<double, kForce>)
-                         : (near.phi ? force_launch<float, kForcePhi> : force_launch<float, kForce>);
+    auto k = near.phi ? force_launch<double, kForcePhi> : force_launch<double, kForce>;
     k(c, near, s);
 }
 
@@ -1025,8 +1016,8 @@ void launch_atree_finalize_force(const AtreeCall &c, const ForceNear &near, cons
     const int n = (int)t->n;
     const AtreeDev &d = t->d;
     const AtreeWs &w = *t->wsp;
-    auto k = c.is_double ? at_finalize_force_kernel<double> : at_finalize_force_kernel<float>;
-    k<<<blocks(n, 256), 256, 0, s>>>(n, d.perm, d.leaf_of, d.cell, d.xy, d.w_off, d.w_idx, w.mp, w.lo, w.mp2, w.lo2,
+    at_finalize_force_kernel<<<blocks(n, 256), 256, 0, s>>>(
+        n, d.perm, d.leaf_of, d.cell, d.xy, d.w_off, d.w_idx, w.mp, w.lo, w.mp2, w.lo2,
                                      c.p, t->x0, t->y0, t->side, near, w.adj, w.gamma, c.alpha, out);
 }
 

@@ -106,9 +106,7 @@ struct AtreeWs {
     double2 *mp2 = nullptr, *lo2 = nullptr, *adj = nullptr;
     void *qt = nullptr;
     double4 *pa = nullptr, *psrc = nullptr;
-    // the pair force: slots of Phi (9 x n in the records' precision), the charges' range
-    void *phi_slots = nullptr;
-    double2 *range = nullptr;
+    double *phi_slots = nullptr;  // the pair force (FP64): slots of Phi, 9 x n
 };
 
 }  // namespace fmm
@@ -172,8 +170,7 @@ void launch_atree_coords(const fmm_atree *t, int is_double, void *pos, hipStream
 // q (mp2, lo2)
 // both: the adjoint's two sets of expansions (charges c and q) in the same launches
 void launch_atree_far(const AtreeCall &c, hipStream_t s, bool both = false);
-void launch_atree_pack_adjoint(const AtreeCall &c, const double *gamma, const double *dl_duv, double scale,
-                               bool force, hipStream_t s);
+void launch_atree_pack_adjoint(const AtreeCall &c, const double *dl_duv, double scale, hipStream_t s);
 void launch_atree_force(const AtreeCall &c, const ForceNear &near, hipStream_t s);
 void launch_atree_finalize_force(const AtreeCall &c, const ForceNear &near, const AdjointOut &out, hipStream_t s);
 void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t s);
