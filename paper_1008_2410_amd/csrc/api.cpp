@@ -387,16 +387,29 @@ int choose_occupancy(const fmm_tree *t, int precision, bool overlap)
 }
 
 // The same for the adjoint's pair force, whose kernels hold fewer wavefronts (FP32 six per SIMD,
-// five with Phi; FP64 four and three), beside its two far chains: mixed at most five, four with
-// Phi (adjoint of 2^22 patch particles at depth 9: 3.04 ms at five, 3.09 at six; with dl_dgamma
-// 3.73 at four, 3.82; uniform 2^22 at depth 9: 1.48 at five, 1.53), FP64 one less than the forward
-// (700001 patches at depth 8: 1.02 ms at three, 1.05 at four; 1024^2 lattice: 0.619 at two, 0.658
-// at three).
+// five with Phi; FP64 four and three) and take longer, beside its two far chains: mixed at most five,
+// four with Phi (adjoint of 2^22 patch particles at depth 9: 3.66 ms at five, 3.71 at six; with
+// dl_dgamma 4.50 at four, 4.59 at five), and one more than the forward where that is less (2^20
+// uniform at depth 8: 0.397 ms at four, 0.420 at three; 2^19: 0.295 at three, 0.340 at two), FP64 one
+// less than the forward (700001 patches at depth 8: 1.02 ms at three, 1.05 at four; 1024^2 lattice:
+// 0.619 at two, 0.658 at three).
 int choose_force_occupancy(const fmm_tree *t, int precision, bool overlap, bool phi)
 {
     const int cap = choose_occupancy(t, precision, overlap);
-    if (t->near_occupancy >= 0) return cap;
-    return precision == FMM_FP64 ? (cap > 2 ? cap - 1 : cap) : std::min(cap, phi ? 4 : 5);
+    if (t->near_occupancy >= 0 || cap == 0) return cap;
+    if (precision == FMM_FP64) return cap > 2 ? cap - 1 : cap;
+    return cap < 4 ? cap + 1 : std::min(cap, phi ? 4 : 5);
+}
+
+// Whether the pair force's FP32 sums are at least as near to 64-bit sums as the separate sums
+// (see p2p_force_kernel): not where the option makes smaller leaves dense than by default (up to
+// 1.55 times their error at 4 particles per leaf, 1.04 at 24, 0.98 at 32), nor where target-centric
+// units meet leaves of several tiles, whose sums the separate ones fold leaf by leaf (1.03).  FP64:
+// always.
+constexpr int kForceDense = 32;
+bool force_accurate(const fmm_tree *t, int precision)
+{
+    return precision == FMM_FP64 || (use_mutual(t) ? t->dense_leaf >= kForceDense : t->max_leaf <= 64);
 }
 
 struct Timing {
@@ -892,7 +905,7 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     // has the bits of velocity_backward's parts added up, and callers compare the two.
     ForceNear near;
     const bool force = out.dxy && !out.dxe && !out.dxs && !outputs_windowed(t->n, kForceRow) &&
-                       force_arrays(t, ws, out.dg != nullptr, near);
+                       force_accurate(t, precision) && force_arrays(t, ws, out.dg != nullptr, near);
     // The two far chains (the charges c: the derivative of their local expansion; the charges q:
     // the transpose pass A^T q = -A q) go through the same launches.  The pair force runs beside
     // them; the separate sums, which hold every wavefront slot, follow them.
@@ -927,7 +940,7 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     tm.mark(4, ms);
     const void *qv = is_double ? (const void *)ws.adj : ws.rec2;
     if (force) {
-        launch_p2p_force(t, pos, ws.gam, qv, is_double, alpha, near, ms);
+        launch_p2p_force(t, pos, ws.gam, qv, ws.adj, fc.gamma, is_double, alpha, near, ms);
         tm.mark(5, ms);
         if (overlap) HIP_TRY(hipStreamWaitEvent(ms, t->aux.join, 0));
         tm.mark(6, ms);

@@ -751,15 +751,18 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
                         for (int j = 0; j < 16; ++j) p2p_pair<T, false>(lds.b[c * 32 + j], bx, by, f[0], f[1]);
                     }
                 } else {
+                    T fc[NS] = {};
                     if (far) {
 #pragma unroll 2
                         for (int j = 0; j < 16; ++j)
-                            force_pair<T, KIND, 2>(lds.b[c * 32 + j], lds.qb[c * 32 + j], rb, qyb, bx, by, f);
+                            force_pair<T, KIND, 2>(lds.b[c * 32 + j], lds.qb[c * 32 + j], rb, qyb, bx, by, fc);
                     } else {
 #pragma unroll 4
                         for (int j = 0; j < 16; ++j)
-                            force_pair<T, KIND, 0>(lds.b[c * 32 + j], lds.qb[c * 32 + j], rb, qyb, bx, by, f);
+                            force_pair<T, KIND, 0>(lds.b[c * 32 + j], lds.qb[c * 32 + j], rb, qyb, bx, by, fc);
                     }
+#pragma unroll
+                    for (int m = 0; m < NS; ++m) f[m] += fc[m];
                 }
             continue;
         }
@@ -805,10 +808,13 @@ __device__ __forceinline__ void mutual_resident_tile(const int4 it, NearLds<T, K
                 if (far) mutual_chunk<true>(src + at, px, py, back, r[0], r[1], cs[0], cs[1]);
                 else mutual_chunk<false>(src + at, px, py, back, r[0], r[1], cs[0], cs[1]);
             } else {
-                if (far) force_chunk<T, KIND, 2>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, r, cs);
+                T rc[NS] = {};  // the chunk's terms apart from the running sums: see p2p_force_kernel
+                if (far) force_chunk<T, KIND, 2>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, rc, cs);
                 else if (sizeof(T) == 8 || gap2 >= mt.series_leaf2)
-                    force_chunk<T, KIND, 1>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, r, cs);
-                else force_chunk<T, KIND, 0>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, r, cs);
+                    force_chunk<T, KIND, 1>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, rc, cs);
+                else force_chunk<T, KIND, 0>(src + at, qsrc + at, px, py, -pgn, pqx, pqy, rc, cs);
+#pragma unroll
+                for (int m = 0; m < NS; ++m) r[m] += rc[m];
             }
 #pragma unroll
             for (int m = 0; m < NS; ++m) cs[m] += __shfl_xor(cs[m], 16);
@@ -1025,6 +1031,20 @@ __device__ __forceinline__ void p2p_bwd_batch(const rec_t<T> *tile, const c2<T> 
 #pragma unroll 2
     for (int it = 0; it < steps; ++it, src += K, qsrc += K)
         p2p_bwd_pair<T, FAR, SRC>(*src, *qsrc, tx, ty, lambda, acc);
+}
+
+// The same over staged records that carry the adjoint charge (load_rec), source-position sums
+// included: the FP32 units of the pair force.
+template <typename T, bool FAR>
+__device__ __forceinline__ void force_sums_batch(const rec_t<T> *tile, const T *qtile, int count, int k, int K, T tx,
+                                                 T ty, T (&acc)[8])
+{
+    const int steps = (count + K - 1) / K;
+    const rec_t<T> *src = tile + k;
+    const T *qsrc = qtile + k;
+#pragma unroll 2
+    for (int it = 0; it < steps; ++it, src += K, qsrc += K)
+        p2p_bwd_pair<T, FAR, true>(*src, mk<T>(src->w, *qsrc), tx, ty, exponent_base_log<T>(), acc);
 }
 
 // The pair force multiplies Gamma_j q_i in the records' precision.  So that FP32 neither

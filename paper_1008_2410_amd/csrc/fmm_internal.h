@@ -284,8 +284,8 @@ void launch_adjoint_range(int64_t n, const double *gamma, const double *dl_duv, 
                           hipStream_t s);
 void launch_pack_adjoint(const fmm_tree *t, const double *dl_duv, double scale, double2 *adj, void *qt, int is_double,
                          double2 *staging, const double2 *range, double *qscale, hipStream_t s);
-void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double, double alpha,
-                      const ForceNear &near, hipStream_t s);
+void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const void *qv, const double2 *adj,
+                      const GammaRows &gamma, int is_double, double alpha, const ForceNear &near, hipStream_t s);
 void launch_finalize_force(const fmm_tree *t, const FarArgs &fc, const FarArgs &fq, const double2 *adj,
                            const ForceNear &near, int is_double, double alpha, const AdjointOut &out, hipStream_t s);
 void launch_p2p_backward(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double,

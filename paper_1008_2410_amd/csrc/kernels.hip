@@ -295,14 +295,24 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? 8 : 5) void p2p_near_kernel(
                             near);
 }
 
+// The target's own factors in FP64, for the FP32 units: adjoint charges and circulations, and the
+// power of two the FP32 charges carry.
+struct ForceTargets {
+    const double2 *__restrict__ adj;
+    GammaRows gamma;
+    const double *__restrict__ qscale;
+};
+
 // The adjoint's target-centric unit over the pair force: the forward's, with every source
 // leaf in the concatenation (a leaf of one tile beyond the cut skips the exponential).
 template <typename T, int KIND>
 __device__ __forceinline__ void p2p_force_unit(const int4 u, rec_t<T> *tile, T *qtile, const SoaRec<T> &rec,
-                                               const MutualTree &mt, int nside, T step, double scale, int dense,
-                                               double2 *__restrict__ near, double *__restrict__ near_phi)
+                                               const ForceTargets &own, const MutualTree &mt, int nside, T step,
+                                               double scale, int dense, double2 *__restrict__ near,
+                                               double *__restrict__ near_phi)
 {
-    constexpr int NS = kSums<KIND>;
+    // FP64: the sums of the pair force; FP32: the separate sums (see p2p_force_kernel)
+    constexpr int NS = sizeof(T) == 4 ? 8 : kSums<KIND>;
     const int lane = threadIdx.x;
     const bool skip_dense = (u.w >> 4) != 0;  // pairs with dense leaves go to the mutual form
     const int ix = (int)morton_x((uint32_t)u.x), iy = (int)morton_y((uint32_t)u.x);
@@ -337,17 +347,30 @@ __device__ __forceinline__ void p2p_force_unit(const int4 u, rec_t<T> *tile, T *
     };
     source_batches<16>(far ? 0 : len, stage, [&](int count) {
         T f[NS] = {};
-        force_batch<T, KIND, 0>(tile, qtile, count, ul.k, ul.K, ti, tiqy, f);
+        if constexpr (sizeof(T) == 4) force_sums_batch<T, false>(tile, qtile, count, ul.k, ul.K, ti.x, ti.y, f);
+        else force_batch<T, KIND, 0>(tile, qtile, count, ul.k, ul.K, ti, tiqy, f);
         for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
     });
     if (__any(far))
         source_batches<16>(far ? len : 0, stage, [&](int count) {
             T f[NS] = {};
-            force_batch<T, KIND, 2>(tile, qtile, count, ul.k, ul.K, ti, tiqy, f);
+            if constexpr (sizeof(T) == 4) force_sums_batch<T, true>(tile, qtile, count, ul.k, ul.K, ti.x, ti.y, f);
+            else force_batch<T, KIND, 2>(tile, qtile, count, ul.k, ul.K, ti, tiqy, f);
             for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
         });
     for (int m = 0; m < NS; ++m) sum[m] = ul.reduce(sum[m]);
-    if (lane < u.z) {
+    if (lane >= u.z) return;
+    if constexpr (sizeof(T) == 4) {
+        // as finalize_backward_kernel: q (A, B) and -Gamma (At, Bt), the latter of charges that
+        // carry qscale, which the sum takes on as a whole
+        constexpr double lam = 0.69314718055994530942;
+        const double2 q = own.adj[i];
+        const double qs = *own.qscale, g = scale * own.gamma.rows[own.gamma.idx[i]];
+        const double Ar = scale * (-2.0 * sum[2]), Ai = -scale * sum[1], Bi = -scale * lam * sum[3];
+        near[i] = make_double2(qs * (q.x * Ar - q.y * (Ai + Bi)) - g * (sum[5] + lam * sum[7]),
+                               -qs * (q.x * (Ai - Bi) + q.y * Ar) - g * (sum[4] - lam * sum[6]));
+        if constexpr (KIND == kForcePhi) near_phi[i] = sum[0];
+    } else {
         near[i] = make_double2(-scale * sum[0], scale * sum[1]);
         if constexpr (KIND == kForcePhi) near_phi[i] = sum[2];
     }
@@ -357,16 +380,26 @@ __device__ __forceinline__ void p2p_force_unit(const int4 u, rec_t<T> *tile, T *
 // vector operations per unordered pair (42 with the series, 41 with Phi) against 36 per ordered
 // pair of the separate sums: 2^22 patch particles at depth 9, FP32, 3.6 -> 2.1 ms; 700001 at
 // depth 8 in FP64 with Phi, whose exponential alone is some 25 operations, 1.2 -> 0.74 ms.
+//
+// The position derivative is what is left of two larger sums, so the rounding of FP32 running sums
+// shows in it.  Errors of dl_dx against the FP64 call, in units of the separate sums' (uniform
+// particles, sigma of 0.05 to 1 leaf, smooth and random circulations and cotangents, worst of 16):
+//  - mutual items with running sums over a whole tile: 1.15 at 32 particles per leaf, 1.05 at 48, 1.07
+//    at 64, 0.91 at 250; with each chunk's 16 terms added up apart 0.98, 0.97, 0.96 and 0.81 (2^22
+//    patch particles: 3.63 ms either way);
+//  - target-centric units over the pair force 1.54 at 4 particles per leaf, 1.45 at 10, 1.40 at 16 and
+//    24.  In FP32 they take the separate sums, whose terms meet the target's own FP64 factors after
+//    the sums: 1.00 at each (2^20 uniform particles at depth 8: 0.373 -> 0.397 ms).
 template <typename T, int KIND>
 __global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 3) void p2p_force_kernel(
-    const int4 *__restrict__ work, const SoaRec<T> rec, const MutualTree mt, int nside, T step, double scale,
-    int dense, int64_t n, double2 *__restrict__ near, double *__restrict__ near_phi, c2<T> *__restrict__ slots,
-    T *__restrict__ phi_slots, const MutualParts parts)
+    const int4 *__restrict__ work, const SoaRec<T> rec, const ForceTargets own, const MutualTree mt, int nside, T step,
+    double scale, int dense, int64_t n, double2 *__restrict__ near, double *__restrict__ near_phi,
+    c2<T> *__restrict__ slots, T *__restrict__ phi_slots, const MutualParts parts)
 {
     __shared__ NearLds<T, KIND> lds;
     const int4 u = work[blockIdx.x];
     if (u.w & kMutualItem) mutual_item<KIND>(u, lds, rec, mt, parts, step, n, slots, phi_slots);
-    else p2p_force_unit<T, KIND>(u, lds.a, lds.qa, rec, mt, nside, step, scale, dense, near, near_phi);
+    else p2p_force_unit<T, KIND>(u, lds.a, lds.qa, rec, own, mt, nside, step, scale, dense, near, near_phi);
 }
 
 // Stage 4, P2M: a_m / w^m = sum_j c_j xi_j^m, G lanes per leaf (64/G leaves per wavefront),
@@ -1089,8 +1122,8 @@ void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int
 namespace {
 
 template <typename T, int KIND>
-void force_launch(const fmm_tree *t, const void *pos, const void *gam, const void *qv, double alpha,
-                  const ForceNear &near, hipStream_t s)
+void force_launch(const fmm_tree *t, const void *pos, const void *gam, const void *qv, const double2 *adj,
+                  const GammaRows &gamma, double alpha, const ForceNear &near, hipStream_t s)
 {
     const bool mutual = near.slots != nullptr;
     const int64_t nwork = mutual ? t->nnear_work : t->nunits;
@@ -1102,19 +1135,19 @@ void force_launch(const fmm_tree *t, const void *pos, const void *gam, const voi
     const MutualParts parts = mutual_parts(t, mutual);
     p2p_force_kernel<T, KIND><<<(unsigned)nwork, 64, near_lds_reserve(t, sizeof(NearLds<T, KIND>)), s>>>(
         mutual ? t->d_near_work : t->d_units, SoaRec<T>{(const c2<T> *)pos, (const T *)gam, (T)step, (const c2<T> *)qv},
-        mt, nside, (T)step, alpha * alpha * kInv2Pi, t->dense_leaf, t->n, near.near, near.phi, (c2<T> *)near.slots,
+        ForceTargets{adj, gamma, near.qscale}, mt, nside, (T)step, alpha * alpha * kInv2Pi, t->dense_leaf, t->n, near.near, near.phi, (c2<T> *)near.slots,
         (T *)near.phi_slots, parts);
     if (parts.list) fold_launch<T, KIND>(t, parts, near.slots, near.phi_slots, s);
 }
 
 }  // namespace
 
-void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const void *qv, int is_double, double alpha,
-                      const ForceNear &near, hipStream_t s)
+void launch_p2p_force(const fmm_tree *t, const void *pos, const void *gam, const void *qv, const double2 *adj,
+                      const GammaRows &gamma, int is_double, double alpha, const ForceNear &near, hipStream_t s)
 {
     auto k = is_double ? (near.phi ? force_launch<double, kForcePhi> : force_launch<double, kForce>)
                        : (near.phi ? force_launch<float, kForcePhi> : force_launch<float, kForce>);
-    k(t, pos, gam, qv, alpha, near, s);
+    k(t, pos, gam, qv, adj, gamma, alpha, near, s);
 }
 
 namespace {
