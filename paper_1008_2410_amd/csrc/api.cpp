@@ -226,9 +226,10 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
         ws.bwd_src = (double4 *)((char *)ws.sums + o_src);
     }
     if (backward && !ws.adj) {
-        if ((rc = dev_alloc_block(&ws.adj, n, "adjoint charges"))) return rc;
-        if (precision != FMM_FP64 && (rc = dev_alloc_block((float2 **)&ws.rec2, n, "adjoint charges (FP32)"))) return rc;
-        if (L >= 2) {
+        auto adjoint_arrays = [&]() -> int {
+            if ((rc = dev_alloc_block(&ws.adj, n, "adjoint charges"))) return rc;
+            if (precision != FMM_FP64 && (rc = dev_alloc_block((float2 **)&ws.rec2, n, "adjoint charges (FP32)"))) return rc;
+            if (L < 2) return FMM_OK;
             // the far field of the charges q, computed beside that of the charges c
             if ((rc = dev_alloc_block(&ws.mp2_d, cells_d * p + kCoefPad, "adjoint multipoles"))) return rc;
             if ((rc = dev_alloc_block(&ws.lo2_d, cells_d * p + kCoefPad, "adjoint locals"))) return rc;
@@ -238,6 +239,22 @@ int ensure_workspace(fmm_tree *t, int p, int precision, bool backward, hipStream
                 if ((rc = dev_alloc_block(&ws.lo2_f, cells_f * p + kCoefPad, "adjoint locals"))) return rc;
                 HIP_TRY(hipMemsetAsync(ws.mp2_f, 0, (cells_f * p + kCoefPad) * sizeof(float2), s));
             }
+            return FMM_OK;
+        };
+        // whole or not at all (ws.adj tells the next call that the group is there)
+        if ((rc = adjoint_arrays())) {
+            (void)hipStreamSynchronize(s);
+            auto drop = [](auto *&q) {
+                block_free(q);
+                q = nullptr;
+            };
+            drop(ws.adj);
+            drop(ws.rec2);
+            drop(ws.mp2_d);
+            drop(ws.lo2_d);
+            drop(ws.mp2_f);
+            drop(ws.lo2_f);
+            return rc;
         }
         // with them what the pair force needs beside the forward's arrays; without it the
         // separate sums serve

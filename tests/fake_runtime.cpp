@@ -1,0 +1,397 @@
+// The library's host code (api.cpp, adaptive.cpp, device_cache.cpp, host_tree.cpp) over a HIP
+// runtime of this file's own: device memory is host memory, allocations can be made to fail,
+// kernel launchers check the arrays they are handed and compute nothing.  Each check runs in a
+// child process of its own and names what it found.
+//
+// Usage: fake_runtime CHECK
+#include <sys/wait.h>
+#include <unistd.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../include/fmm2d.h"
+#include "../include/fmm2d_adaptive.h"
+#include "../paper_1008_2410_amd/csrc/adaptive_internal.h"
+#include "../paper_1008_2410_amd/csrc/fmm_internal.h"
+
+#define REQUIRE(cond)                                                                  \
+    do {                                                                               \
+        if (!(cond)) {                                                                 \
+            printf("%s:%d: %s\n", __FILE__, __LINE__, #cond);                          \
+            fflush(stdout);                                                            \
+            _exit(1);                                                                  \
+        }                                                                              \
+    } while (0)
+
+// ---------------------------------------------------------------------------------
+// The runtime
+// ---------------------------------------------------------------------------------
+namespace {
+std::map<char *, size_t> g_live;  // device allocations
+size_t g_used = 0;
+int64_t g_allocs = 0, g_frees = 0, g_waits = 0;  // calls that a stream capture refuses
+int64_t g_fail_from = -1;                        // allocations from this one on fail
+size_t g_capacity = SIZE_MAX;                    // so do those that would exceed this
+
+hipError_t take(void **p, size_t bytes)
+{
+    *p = nullptr;
+    const int64_t number = g_allocs++;
+    if ((g_fail_from >= 0 && number >= g_fail_from) || g_used + bytes > g_capacity) return hipErrorOutOfMemory;
+    *p = calloc(1, bytes ? bytes : 1);
+    g_live[(char *)*p] = bytes;
+    g_used += bytes;
+    return hipSuccess;
+}
+
+hipError_t give(void *p)
+{
+    if (!p) return hipSuccess;
+    ++g_frees;
+    auto it = g_live.find((char *)p);
+    REQUIRE(it != g_live.end());  // freed twice, or not device memory
+    g_used -= it->second;
+    g_live.erase(it);
+    free(p);
+    return hipSuccess;
+}
+
+bool on_device(const void *p, size_t bytes)
+{
+    auto it = g_live.upper_bound((char *)p);
+    if (it == g_live.begin()) return false;
+    --it;
+    return (char *)p + bytes <= it->first + it->second;
+}
+}  // namespace
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) { return take(p, n); }
+hipError_t hipFree(void *p) { return give(p); }
+hipError_t hipMallocAsync(void **p, size_t n, hipStream_t) { return take(p, n); }
+hipError_t hipFreeAsync(void *p, hipStream_t) { return give(p); }
+hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t *p, int) { *p = nullptr; return hipSuccess; }
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { ++g_waits; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { ++g_waits; return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
+{
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemset(void *d, int v, size_t n)
+{
+    REQUIRE(on_device(d, n));
+    memset(d, v, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free((void *)s); return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { free((void *)e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "error"; }
+}
+
+// ---------------------------------------------------------------------------------
+// The device builds and the launchers
+// ---------------------------------------------------------------------------------
+namespace fmm {
+
+static bool g_mutual = true;  // whether the trees' plans have mutual items
+
+int build_tree_device(fmm_tree *, const double *, const double *, hipStream_t, std::string &, int64_t &,
+                      const std::function<void()> &)
+{
+    return FMM_EDEVICE;
+}
+int build_near_plan_device(fmm_tree *t, hipStream_t, std::string &)
+{
+    t->nmut = g_mutual ? 1 : 0;
+    t->nnear_work = 1;
+    return FMM_OK;
+}
+int build_atree_device(fmm_atree *, const double *, const double *, hipStream_t, std::string &, int64_t &)
+{
+    return FMM_EDEVICE;
+}
+// (a list of the tree's own, made with an allocation and a wait)
+static int make_list(int **p, int64_t count)
+{
+    if (hipMalloc((void **)p, (size_t)count * sizeof(int)) != hipSuccess) return FMM_ENOMEM;
+    return hipStreamSynchronize(nullptr) == hipSuccess ? FMM_OK : FMM_EDEVICE;
+}
+static std::vector<int *> g_lists;
+int build_atree_adjoint_units(fmm_atree *t, hipStream_t, std::string &)
+{
+    int *p = nullptr;
+    if (int rc = make_list(&p, t->ntiles)) return rc;
+    g_lists.push_back(p);
+    t->nbwd_units = t->ntiles;
+    return FMM_OK;
+}
+int build_atree_m2l_plan(fmm_atree *t, const int4 *, hipStream_t, std::string &)
+{
+    int *p = nullptr;
+    if (int rc = make_list(&p, 1)) return rc;
+    g_lists.push_back(p);
+    t->m2l_plan = true;
+    return FMM_OK;
+}
+int shared_tables(int, int p, const Tables **out, std::string &, bool)
+{
+    static Tables tb;
+    tb.p = p;
+    *out = &tb;
+    return 0;
+}
+int static_workspace(int, char **base)
+{
+    static char *scratch = nullptr;
+    if (!scratch) {
+        scratch = (char *)calloc(1, kStaticWorkspaceBytes);
+        g_live[scratch] = kStaticWorkspaceBytes;
+    }
+    *base = scratch;
+    return 0;
+}
+
+static size_t real_bytes(int is_double) { return is_double ? sizeof(double) : sizeof(float); }
+
+static void check_far(const FarArgs &a)
+{
+    const int L = a.t->depth;
+    if (L < 2) return;
+    const int64_t d = level_base(std::min(a.split, L) + 1), f = level_base(L + 1) - d;
+    REQUIRE(on_device(a.mp_d, d * a.p * sizeof(double2)) && on_device(a.lo_d, d * a.p * sizeof(double2)));
+    if (f > 0) REQUIRE(on_device(a.mp_f, f * a.p * sizeof(float2)) && on_device(a.lo_f, f * a.p * sizeof(float2)));
+    if (a.charge_kind) REQUIRE(on_device(a.adj, a.t->n * sizeof(double2)));
+}
+
+void launch_zero(void *p, size_t bytes, hipStream_t) { REQUIRE(on_device(p, bytes)); }
+void launch_widen_perm(const fmm_tree *, int64_t *, int32_t *, hipStream_t) {}
+GammaRows launch_stage_in(const fmm_tree *t, const double *gamma, int64_t row, hipStream_t)
+{
+    if (direct_rows(t->n, row)) return GammaRows{t->d_perm, gamma};
+    return GammaRows{t->d_gpos2, t->d_st1};
+}
+void launch_pack(const fmm_tree *t, const GammaRows &, int is_double, void *gam, hipStream_t)
+{
+    REQUIRE(on_device(gam, t->n * real_bytes(is_double)));
+}
+void launch_leaf_coords(const fmm_tree *t, int is_double, void *pos, hipStream_t)
+{
+    REQUIRE(on_device(pos, t->n * 2 * real_bytes(is_double)));
+}
+void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int is_double, double, double2 *near,
+                        void *slots, hipStream_t)
+{
+    REQUIRE(on_device(pos, t->n * 2 * real_bytes(is_double)) && on_device(gam, t->n * real_bytes(is_double)));
+    REQUIRE(on_device(near, t->n * sizeof(double2)));
+    if (slots) REQUIRE(on_device(slots, 18 * t->n * real_bytes(is_double)));
+}
+void launch_far_chain(const FarArgs &a, hipStream_t, const FarArgs *b)
+{
+    check_far(a);
+    if (b) check_far(*b);
+}
+void launch_finalize(const fmm_tree *t, const FarArgs &, const double2 *near, const void *, int, double, double *,
+                     double *, double *, void *stage, const double *, double, hipStream_t)
+{
+    REQUIRE(on_device(near, t->n * sizeof(double2)) && on_device(stage, t->n * sizeof(double2)));
+}
+void launch_adjoint_range(int64_t, const double *, const double *, double, double2 *range, hipStream_t)
+{
+    REQUIRE(on_device(range, (kRangeBlocks + 1) * sizeof(double2)));
+}
+void launch_pack_adjoint(const fmm_tree *t, const double *, double, double2 *adj, void *qt, int is_double, double2 *,
+                         const double2 *, double *, hipStream_t)
+{
+    REQUIRE(on_device(adj, t->n * sizeof(double2)));
+    if (!is_double) REQUIRE(on_device(qt, t->n * sizeof(float2)));
+}
+void launch_p2p_force(const fmm_tree *t, const void *, const void *, const void *qv, const double2 *adj,
+                      const GammaRows &, int is_double, double, const ForceNear &near, hipStream_t)
+{
+    REQUIRE(on_device(qv, t->n * 2 * real_bytes(is_double)) && on_device(adj, t->n * sizeof(double2)));
+    REQUIRE(on_device(near.near, t->n * sizeof(double2)));
+    if (near.slots) REQUIRE(on_device(near.slots, 18 * t->n * real_bytes(is_double)));
+    if (near.phi_slots) REQUIRE(on_device(near.phi_slots, 9 * t->n * real_bytes(is_double)));
+}
+void launch_finalize_force(const fmm_tree *, const FarArgs &c, const FarArgs &q, const double2 *, const ForceNear &,
+                           int, double, const AdjointOut &, hipStream_t)
+{
+    check_far(c);
+    check_far(q);
+}
+void launch_p2p_backward(const fmm_tree *t, const void *, const void *, const void *qv, int is_double, double,
+                         double4 *pa, double4 *src, hipStream_t)
+{
+    REQUIRE(on_device(qv, t->n * 2 * real_bytes(is_double)) && on_device(pa, t->n * sizeof(double4)));
+    if (src) REQUIRE(on_device(src, t->n * sizeof(double4)));
+}
+void launch_finalize_backward(const fmm_tree *, const FarArgs &c, const FarArgs &q, const double4 *, const double2 *,
+                              const double4 *, int, double, const AdjointOut &, double *, double *, double *,
+                              hipStream_t)
+{
+    check_far(c);
+    check_far(q);
+}
+hipError_t find_nonfinite(const double *, int64_t, int, int *, hipStream_t, int64_t &bad)
+{
+    bad = -1;
+    return hipSuccess;
+}
+
+static void check_atree(const AtreeCall &c, bool adjoint)
+{
+    const AtreeWs &w = *c.t->wsp;
+    const size_t coef = (size_t)c.t->ncells * c.p * sizeof(double2);
+    REQUIRE(on_device(w.mp, coef) && on_device(w.lo, coef));
+    if (adjoint) REQUIRE(on_device(w.mp2, coef) && on_device(w.lo2, coef) && on_device(w.adj, c.t->n * sizeof(double2)));
+}
+void launch_atree_pack(const AtreeCall &c, const double *, hipStream_t)
+{
+    REQUIRE(on_device(c.t->wsp->gam, c.t->n * real_bytes(c.is_double)));
+}
+void launch_atree_coords(const fmm_atree *t, int is_double, void *pos, hipStream_t)
+{
+    REQUIRE(on_device(pos, t->n * 2 * real_bytes(is_double)));
+}
+void launch_atree_far(const AtreeCall &c, hipStream_t, bool both) { check_atree(c, both); }
+void launch_atree_pack_adjoint(const AtreeCall &c, const double *, double, hipStream_t)
+{
+    REQUIRE(on_device(c.t->wsp->qt, c.t->n * 2 * real_bytes(c.is_double)));
+}
+void launch_atree_force(const AtreeCall &c, const ForceNear &near, hipStream_t)
+{
+    REQUIRE(on_device(near.slots, 18 * c.t->n * sizeof(double)));
+    if (near.phi) REQUIRE(on_device(near.phi_slots, 9 * c.t->n * sizeof(double)));
+}
+void launch_atree_finalize_force(const AtreeCall &c, const ForceNear &, const AdjointOut &, hipStream_t)
+{
+    check_atree(c, true);
+}
+void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t)
+{
+    REQUIRE(c.t->nbwd_units > 0 && on_device(c.t->wsp->pa, c.t->n * sizeof(double4)));
+    if (src) REQUIRE(on_device(c.t->wsp->psrc, c.t->n * sizeof(double4)));
+}
+void launch_atree_finalize_backward(const AtreeCall &c, const AdjointOut &, hipStream_t) { check_atree(c, true); }
+void launch_atree_near(const AtreeCall &c, hipStream_t)
+{
+    REQUIRE(on_device(c.t->wsp->near, c.t->n * sizeof(double2)));
+}
+void launch_atree_finalize(const AtreeCall &c, double *, double *, double *, const double *, double, hipStream_t)
+{
+    check_atree(c, false);
+}
+
+}  // namespace fmm
+
+// ---------------------------------------------------------------------------------
+// The checks
+// ---------------------------------------------------------------------------------
+namespace {
+
+// Runs f in a child process; whether it ended well.
+bool child(const std::function<void()> &f)
+{
+    fflush(stdout);
+    const pid_t pid = fork();
+    if (pid == 0) {
+        f();
+        fflush(stdout);
+        _exit(0);
+    }
+    int status = 0;
+    waitpid(pid, &status, 0);
+    return WIFEXITED(status) && WEXITSTATUS(status) == 0;
+}
+
+std::vector<double> points(int64_t n)
+{
+    std::vector<double> xy(2 * (size_t)n);
+    uint64_t s = 12345;
+    for (double &v : xy) {
+        s = s * 6364136223846793005ull + 1442695040888963407ull;
+        v = (double)(s >> 11) / 9007199254740992.0;
+    }
+    return xy;
+}
+const double kUnit[3] = {0.0, 0.0, 1.0};
+
+fmm_tree *uniform_tree(int64_t n, int depth)
+{
+    const std::vector<double> xy = points(n);
+    fmm_tree *t = nullptr;
+    REQUIRE(fmm_build_tree_host(xy.data(), n, depth, kUnit, nullptr, &t) == FMM_OK);
+    return t;
+}
+fmm_atree *adaptive_tree(int64_t n)
+{
+    const std::vector<double> xy = points(n);
+    fmm_atree *t = nullptr;
+    REQUIRE(fmm_atree_build_host(xy.data(), n, 20, 8, kUnit, nullptr, &t) == FMM_OK);
+    return t;
+}
+
+// A call out of memory at its k-th allocation fails cleanly: the next one has every array.
+void call_memory()
+{
+    bool bad = false;
+    for (int kind = 0; kind < 2; ++kind)
+        for (int precision : {FMM_FP64, FMM_MIXED})
+            for (int adjoint = 0; adjoint < 2; ++adjoint)
+                for (int k = 0; k < 12; ++k)
+                    bad |= !child([&] {
+                        const int64_t n = 3000;
+                        std::vector<double> g(n, 1.0), dl(2 * n, 1.0), dg(n), dx(2 * n), uv(2 * n);
+                        auto check = [&](auto t, auto velocity, auto vjp) {
+                            auto call = [&](int which) {
+                                return which ? vjp(t, g.data(), 0.01, 9, precision, dl.data(), 1.0, 0, nullptr, nullptr,
+                                                   dg.data(), dx.data())
+                                             : velocity(t, g.data(), 0.01, 9, precision, nullptr, nullptr, uv.data());
+                            };
+                            if (adjoint) REQUIRE(call(0) == FMM_OK);
+                            g_fail_from = g_allocs + k;
+                            const int rc = call(adjoint);
+                            REQUIRE(rc == FMM_OK || rc == FMM_ENOMEM);
+                            g_fail_from = -1;
+                            printf("kind %d precision %d adjoint %d allocation %d: ", kind, precision, adjoint, k);
+                            REQUIRE(call(adjoint) == FMM_OK && call(!adjoint) == FMM_OK);
+                            printf("ok\n");
+                        };
+                        if (kind == 0) check(uniform_tree(n, 7), fmm_velocity, fmm_transport_vjp);
+                        else check(adaptive_tree(n), fmm_atree_velocity, fmm_atree_transport_vjp);
+                    });
+    REQUIRE(!bad);
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}};
+    const auto it = checks.find(argc > 1 ? argv[1] : "");
+    REQUIRE(it != checks.end());
+    REQUIRE(child(it->second));
+    printf("%s passed\n", argv[1]);
+    return 0;
+}
