@@ -413,6 +413,11 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     hipStream_t ms = (hipStream_t)main_stream;
     hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
     if ((rc = validate_inputs(t, gamma, dl_duv, ms))) return rc;
+    // made by the first adjoint call of either route, so that later calls of the other can be captured
+    if (t->nbwd_units < 0) {
+        std::string err;
+        if ((rc = build_atree_adjoint_units(t, ms, err))) return fail(rc, err);
+    }
     const Tables *tabs = nullptr;
     if ((rc = ensure_ws(t, p, precision)) || (rc = ensure_ws_backward(t, src)) ||
         (rc = ensure_coords(t, precision, ms)) || (rc = ensure_m2l_plan(t, p, ms, tabs)))
@@ -424,10 +429,6 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     // (1000001 clustered particles at depth 13: 0.774 ms, 0.662 with the pair force.)
     const AtreeWs &w = *t->wsp;
     const bool force = precision == FMM_FP64 && out.dxy && !out.dxe && !out.dxs && w.phi_slots;
-    if (!force && t->nbwd_units < 0) {
-        std::string err;
-        if ((rc = build_atree_adjoint_units(t, ms, err))) return fail(rc, err);
-    }
     if (!force) ss = ms;
     const AtreeCall c{t, p, precision == FMM_FP64, record_alpha(sigma, precision),
                       force ? choose_force_occupancy(t, ss != ms) : 0, tabs};

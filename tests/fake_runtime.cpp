@@ -384,11 +384,59 @@ void call_memory()
     REQUIRE(!bad);
 }
 
+// After one adjoint call for the position derivative, of either route, every other call of that
+// precision allocates nothing and waits for nothing: it can be captured.
+void warm_calls()
+{
+    bool bad = false;
+    for (int kind = 0; kind < 2; ++kind)
+        for (int precision : {FMM_FP64, FMM_MIXED})
+            for (int first = 0; first < 3; ++first)
+                for (int k = -1; k < 0; ++k)
+                    bad |= !child([&] {
+                        const int64_t n = 3000;
+                        std::vector<double> g(n, 1.0), dl(2 * n, 1.0), dg(n), dx(2 * n), ds(2 * n), uv(2 * n);
+                        auto check = [&](auto t, auto velocity, auto backward, auto vjp) {
+                            auto call = [&](int which) {
+                                double *const o = nullptr;
+                                if (which == 0)
+                                    return vjp(t, g.data(), 0.01, 9, precision, dl.data(), 1.0, 0, nullptr, nullptr, o,
+                                               dx.data());
+                                if (which == 1)
+                                    return vjp(t, g.data(), 0.01, 9, precision, dl.data(), 1.0, 0, nullptr, nullptr,
+                                               dg.data(), dx.data());
+                                if (which == 2)
+                                    return backward(t, g.data(), 0.01, 9, precision, dl.data(), nullptr, nullptr,
+                                                    dg.data(), dx.data(), ds.data(), o);
+                                if (which == 3)
+                                    return backward(t, g.data(), 0.01, 9, precision, dl.data(), nullptr, nullptr,
+                                                    dg.data(), o, o, o);
+                                return velocity(t, g.data(), 0.01, 9, precision, nullptr, nullptr, uv.data());
+                            };
+                            REQUIRE(call(4) == FMM_OK);
+                            if (k >= 0) g_fail_from = g_allocs + k;
+                            if (call(first) != FMM_OK) return;  // (memory needed by every route)
+                            const int64_t a = g_allocs, f = g_frees, w = g_waits;
+                            for (int which = 0; which < 5; ++which) {
+                                printf("kind %d precision %d first %d without %d, call %d: ", kind, precision, first, k, which);
+                                REQUIRE(call(which) == FMM_OK && g_allocs == a && g_frees == f && g_waits == w);
+                                printf("ok\n");
+                            }
+                        };
+                        if (kind == 0)
+                            check(uniform_tree(n, 7), fmm_velocity, fmm_velocity_backward, fmm_transport_vjp);
+                        else
+                            check(adaptive_tree(n), fmm_atree_velocity, fmm_atree_velocity_backward,
+                                  fmm_atree_transport_vjp);
+                    });
+    REQUIRE(!bad);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
-    const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}};
+    const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     REQUIRE(it != checks.end());
     REQUIRE(child(it->second));
