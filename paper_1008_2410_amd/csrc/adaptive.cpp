@@ -278,10 +278,11 @@ int ensure_ws_backward(fmm_atree *t, bool src)
         }
     }
     if (src && !w.psrc && (rc = dev_alloc_block(&w.psrc, n, "adjoint source-position sums"))) return rc;
-    // the pair force; without it the separate sums serve
-    if (src && w.precision == FMM_FP64 && !w.phi_slots &&
-        block_alloc((void **)&w.phi_slots, 9 * n * sizeof(double)) != hipSuccess)
-        w.phi_slots = nullptr;
+    // the pair force; without it the separate sums serve (asked for once: a call may be captured)
+    if (src && w.precision == FMM_FP64 && !w.phi_asked) {
+        if (block_alloc((void **)&w.phi_slots, 9 * n * sizeof(double)) != hipSuccess) w.phi_slots = nullptr;
+        w.phi_asked = true;
+    }
     return FMM_OK;
 }
 

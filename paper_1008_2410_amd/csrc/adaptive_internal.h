@@ -107,6 +107,7 @@ struct AtreeWs {
     void *qt = nullptr;
     double4 *pa = nullptr, *psrc = nullptr;
     double *phi_slots = nullptr;  // the pair force (FP64): slots of Phi, 9 x n
+    bool phi_asked = false;       // its memory was asked for (and there was none, if NULL)
 };
 
 }  // namespace fmm
