@@ -45,6 +45,7 @@ void free_atree(fmm_atree *t)
     }
     if (t->wsp.use_count() == 1) free_ws(*t->wsp);
     if (t->d_flag) hipFree(t->d_flag);
+    bound_idle(t->device);
     side_stream_give(t->device, t->aux);
     delete t;
 }
@@ -967,6 +968,5 @@ extern "C" void fmm_atree_destroy(fmm_atree *t)
 {
     if (!t) return;
     hipSetDevice(t->device);
-    const int dev = t->device;
     free_atree(t);
 }

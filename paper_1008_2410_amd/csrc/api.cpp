@@ -136,6 +136,7 @@ void free_tree(fmm_tree *t)
     hipFree(t->d_flag);
     if (t->wsp.use_count() == 1) free_workspace(*t->wsp);
     if (fs) hipStreamSynchronize(fs);  // the frees are in its order
+    bound_idle(t->device);
     side_stream_give(t->device, t->aux);
     for (auto &evs : t->pending_timing)
         for (auto e : evs) hipEventDestroy(e);
@@ -668,6 +669,7 @@ int build_device(const double *xy, int64_t n, int depth, const double *root_box,
         free_tree(t);
         return rc;
     }
+    bound_idle(t->device);  // (arrays that had to grow)
     *out = t;
     return FMM_OK;
 }
@@ -1150,19 +1152,6 @@ int fmm::fail(int code, const std::string &msg)
 }
 
 void fmm::clear_last_error() { g_last_error.clear(); }
-
-void fmm::retain_pool(int device)
-{
-    static std::atomic<uint64_t> done{0};
-    if (device < 0 || device >= 64 || ((done.load() >> device) & 1)) return;
-    hipMemPool_t pool;
-    if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess) {
-        uint64_t threshold = UINT64_MAX;
-        (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &threshold);
-    }
-    (void)hipGetLastError();
-    done.fetch_or(uint64_t(1) << device);
-}
 
 double fmm::record_alpha(double sigma, int precision)
 {

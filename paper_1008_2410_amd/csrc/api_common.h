@@ -39,7 +39,7 @@ int dev_alloc(T **p, size_t count, const char *what)
     return FMM_OK;
 }
 
-// Stream-ordered allocation from the device's default pool (see retain_pool).
+// Stream-ordered allocation from the device's default pool (the uniform trees' arrays).
 template <typename T>
 int dev_alloc_async(T **p, size_t count, const char *what, hipStream_t s)
 {
@@ -62,11 +62,6 @@ int dev_alloc_block(T **p, size_t count, const char *what)
     *p = nullptr;
     return fail(FMM_ENOMEM, std::string("device allocation failed: ") + what);
 }
-
-// Keep freed blocks of the device's default memory pool (the uniform trees' arrays) for
-// reuse instead of returning them at every synchronisation.  Once per device.  (The runtime
-// still returns them once more is free than in use.)
-void retain_pool(int device);
 
 template <typename T>
 int upload(T **p, const std::vector<T> &h, const char *what)

@@ -1,5 +1,7 @@
 #include "device_cache.h"
 
+#include <atomic>
+#include <cstdint>
 #include <deque>
 #include <map>
 #include <mutex>
@@ -117,6 +119,42 @@ void block_free(void *p)
         }
     }
     for (void *q : drop) (void)hipFree(q);
+}
+
+void retain_pool(int device)
+{
+    static std::atomic<uint64_t> done{0};
+    if (device < 0 || device >= 64 || ((done.load() >> device) & 1)) return;
+    hipMemPool_t pool;
+    if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess) {
+        uint64_t threshold = UINT64_MAX;
+        (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &threshold);
+    }
+    (void)hipGetLastError();
+    done.fetch_or(uint64_t(1) << device);
+}
+
+void bound_idle(int device)
+{
+    size_t idle;
+    {
+        Cache &c = cache();
+        std::lock_guard<std::mutex> lock(c.mu);
+        idle = c.idle_bytes[device];
+    }
+    const uint64_t rest = kIdleBytes > idle ? kIdleBytes - idle : 0;
+    hipMemPool_t pool;
+    uint64_t used = 0, reserved = 0;
+    auto excess = [&]() {
+        return hipMemPoolGetAttribute(pool, hipMemPoolAttrUsedMemCurrent, &used) == hipSuccess &&
+               hipMemPoolGetAttribute(pool, hipMemPoolAttrReservedMemCurrent, &reserved) == hipSuccess &&
+               reserved > used + rest;
+    };
+    if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess && excess()) {
+        (void)hipMemPoolTrimTo(pool, used + rest);
+        if (excess()) (void)hipMemPoolTrimTo(pool, rest);
+    }
+    (void)hipGetLastError();
 }
 
 hipError_t side_stream_take(int device, SideStream &s)

@@ -11,6 +11,9 @@
 //    any stream and any thread may take it.
 //  - Idle blocks of a device are bounded by kIdleBytes; beyond it the oldest go back to the
 //    device at once, and all of them do when an allocation fails.
+//  - The uniform trees' own arrays come from the device's stream-ordered pool, whose release
+//    threshold is lifted so that they are not unmapped at every synchronisation.  What lies idle
+//    there counts towards the same bound (bound_idle).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,6 +30,12 @@ constexpr size_t kIdleStreams = 8;              // per device
 hipError_t block_alloc(void **p, size_t bytes);
 // Gives a block back; the device work that used it has completed.  NULL is a no-op.
 void block_free(void *p);
+
+// Keeps blocks that the device's default memory pool has taken back (once per device).
+void retain_pool(int device);
+// Returns to the device what the pool holds idle beyond kIdleBytes less the idle blocks.  Called
+// where trees have been built or destroyed, the work that used their arrays completed.
+void bound_idle(int device);
 
 // A tree's side stream (default priority, non-blocking) and its fork and join events.
 struct SideStream {

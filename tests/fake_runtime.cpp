@@ -7,6 +7,7 @@
 #include <sys/wait.h>
 #include <unistd.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -38,12 +39,13 @@ size_t g_used = 0;
 int64_t g_allocs = 0, g_frees = 0, g_waits = 0;  // calls that a stream capture refuses
 int64_t g_fail_from = -1;                        // allocations from this one on fail
 size_t g_capacity = SIZE_MAX;                    // so do those that would exceed this
+size_t g_pool_used = 0, g_pool_idle = 0;         // of the stream-ordered pool
 
 hipError_t take(void **p, size_t bytes)
 {
     *p = nullptr;
     const int64_t number = g_allocs++;
-    if ((g_fail_from >= 0 && number >= g_fail_from) || g_used + bytes > g_capacity) return hipErrorOutOfMemory;
+    if ((g_fail_from >= 0 && number >= g_fail_from) || g_used + g_pool_idle + bytes > g_capacity) return hipErrorOutOfMemory;
     *p = calloc(1, bytes ? bytes : 1);
     g_live[(char *)*p] = bytes;
     g_used += bytes;
@@ -77,10 +79,38 @@ hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipMalloc(void **p, size_t n) { return take(p, n); }
 hipError_t hipFree(void *p) { return give(p); }
-hipError_t hipMallocAsync(void **p, size_t n, hipStream_t) { return take(p, n); }
-hipError_t hipFreeAsync(void *p, hipStream_t) { return give(p); }
-hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t *p, int) { *p = nullptr; return hipSuccess; }
+// The stream-ordered pool: what is given back stays reserved until it is trimmed (a release
+// threshold without limit).
+hipError_t hipMallocAsync(void **p, size_t n, hipStream_t)
+{
+    const size_t reuse = std::min(n, g_pool_idle);
+    g_pool_idle -= reuse;
+    const hipError_t e = take(p, n);
+    if (e != hipSuccess) g_pool_idle += reuse;
+    else g_pool_used += n;
+    return e;
+}
+hipError_t hipFreeAsync(void *p, hipStream_t)
+{
+    const size_t n = g_live.count((char *)p) ? g_live[(char *)p] : 0;
+    g_pool_used -= n;
+    g_pool_idle += n;
+    return give(p);
+}
+hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t *p, int) { *p = (hipMemPool_t)&g_pool_idle; return hipSuccess; }
 hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipMemPoolGetAttribute(hipMemPool_t, hipMemPoolAttr a, void *v)
+{
+    if (a == hipMemPoolAttrUsedMemCurrent) *(uint64_t *)v = g_pool_used;
+    else if (a == hipMemPoolAttrReservedMemCurrent) *(uint64_t *)v = g_pool_used + g_pool_idle;
+    else return hipErrorInvalidValue;
+    return hipSuccess;
+}
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t keep)
+{
+    g_pool_idle = std::min(g_pool_idle, keep > g_pool_used ? keep - g_pool_used : 0);
+    return hipSuccess;
+}
 hipError_t hipDeviceSynchronize() { ++g_waits; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { ++g_waits; return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
@@ -116,10 +146,13 @@ namespace fmm {
 
 static bool g_mutual = true;  // whether the trees' plans have mutual items
 
-int build_tree_device(fmm_tree *, const double *, const double *, hipStream_t, std::string &, int64_t &,
+// A tree that cannot be evaluated, with arrays of g_tree_bytes from where the device build takes them.
+static size_t g_tree_bytes = 1 << 20;
+int build_tree_device(fmm_tree *t, const double *, const double *, hipStream_t s, std::string &, int64_t &,
                       const std::function<void()> &)
 {
-    return FMM_EDEVICE;
+    t->pooled = true;
+    return hipMallocAsync((void **)&t->slab, g_tree_bytes, s) == hipSuccess ? FMM_OK : FMM_ENOMEM;
 }
 int build_near_plan_device(fmm_tree *t, hipStream_t, std::string &)
 {
@@ -127,9 +160,10 @@ int build_near_plan_device(fmm_tree *t, hipStream_t, std::string &)
     t->nnear_work = 1;
     return FMM_OK;
 }
-int build_atree_device(fmm_atree *, const double *, const double *, hipStream_t, std::string &, int64_t &)
+int build_atree_device(fmm_atree *t, const double *, const double *, hipStream_t, std::string &, int64_t &)
 {
-    return FMM_EDEVICE;
+    t->pooled = true;
+    return block_alloc((void **)&t->d.perm, g_tree_bytes) == hipSuccess ? FMM_OK : FMM_ENOMEM;
 }
 // (a list of the tree's own, made with an allocation and a wait)
 static int make_list(int **p, int64_t count)
@@ -433,11 +467,35 @@ void warm_calls()
     REQUIRE(!bad);
 }
 
+// What stays reserved after trees are destroyed is bounded, whatever they were and in any order.
+void held_memory()
+{
+    const size_t MiB = size_t(1) << 20;
+    for (const std::vector<int> &sizes : {std::vector<int>{3000}, {-3000}, {900, -900}, {-900, 900}, {700, -700, 700, -200},
+                                          {500, 500, -500, 500}})
+        REQUIRE(child([&] {
+            const double xy[2] = {0.5, 0.5};
+            for (int pass = 0; pass < 2; ++pass)
+                for (int size : sizes) {
+                    fmm::g_tree_bytes = (size_t)std::abs(size) * MiB;
+                    fmm_tree *t = nullptr;
+                    fmm_atree *a = nullptr;
+                    if (size > 0) REQUIRE(fmm_build_tree(xy, 1, 4, kUnit, nullptr, &t) == FMM_OK);
+                    else REQUIRE(fmm_atree_build(xy, 1, 4, 4, kUnit, nullptr, &a) == FMM_OK);
+                    fmm_destroy_tree(t);
+                    fmm_atree_destroy(a);
+                    printf("after %d MiB: %zu MiB held, %zu in the pool\n", size, (g_used + g_pool_idle) / MiB,
+                           g_pool_idle / MiB);
+                    REQUIRE(g_used + g_pool_idle <= fmm::kIdleBytes + 64 * MiB);  // (and the caller's tables)
+                }
+        }));
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
-    const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}};
+    const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}, {"held_memory", held_memory}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     REQUIRE(it != checks.end());
     REQUIRE(child(it->second));
