@@ -30,13 +30,8 @@ int dev_alloc(T **p, size_t count, const char *what)
 {
     *p = nullptr;
     if (count == 0) count = 1;
-    hipError_t e = hipMalloc((void **)p, count * sizeof(T));
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
-        return fail(FMM_ENOMEM, std::string("device allocation failed: ") + what);
-    }
-    return FMM_OK;
+    if (device_malloc((void **)p, count * sizeof(T)) == hipSuccess) return FMM_OK;
+    return fail(FMM_ENOMEM, std::string("device allocation failed: ") + what);
 }
 
 // Stream-ordered allocation from the device's default pool (the uniform trees' arrays).
@@ -45,13 +40,8 @@ int dev_alloc_async(T **p, size_t count, const char *what, hipStream_t s)
 {
     *p = nullptr;
     if (count == 0) count = 1;
-    hipError_t e = hipMallocAsync((void **)p, count * sizeof(T), s);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
-        return fail(FMM_ENOMEM, std::string("device allocation failed: ") + what);
-    }
-    return FMM_OK;
+    if (pool_malloc((void **)p, count * sizeof(T), s) == hipSuccess) return FMM_OK;
+    return fail(FMM_ENOMEM, std::string("device allocation failed: ") + what);
 }
 
 // From the library's block cache.

@@ -42,7 +42,55 @@ size_t rounded(size_t bytes)
     return (bytes + step - 1) / step * step;
 }
 
+// Returns everything held idle on the current device: the cache's blocks, and what the pool has
+// taken back.
+void release_idle()
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    Cache &c = cache();
+    std::vector<void *> drop;
+    {
+        std::lock_guard<std::mutex> lock(c.mu);
+        std::deque<Idle> rest;
+        for (const Idle &b : c.idle)
+            if (b.device == dev) drop.push_back(b.p);
+            else rest.push_back(b);
+        c.idle.swap(rest);
+        c.idle_bytes[dev] = 0;
+    }
+    for (void *q : drop) (void)hipFree(q);
+    hipMemPool_t pool;
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+    (void)hipGetLastError();
+}
+
+template <typename Alloc> hipError_t again_without_idle(void **p, Alloc alloc)
+{
+    hipError_t e = alloc();
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        release_idle();
+        e = alloc();
+    }
+    if (e != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
+    }
+    return e;
+}
+
 }  // namespace
+
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    return again_without_idle(p, [&] { return hipMalloc(p, bytes); });
+}
+
+hipError_t pool_malloc(void **p, size_t bytes, hipStream_t s)
+{
+    return again_without_idle(p, [&] { return hipMallocAsync(p, bytes, s); });
+}
 
 hipError_t block_alloc(void **p, size_t bytes)
 {
@@ -68,27 +116,8 @@ hipError_t block_alloc(void **p, size_t bytes)
             return hipSuccess;
         }
     }
-    e = hipMalloc(p, want);
-    if (e == hipErrorOutOfMemory) {  // idle blocks first
-        (void)hipGetLastError();
-        std::vector<void *> drop;
-        {
-            std::lock_guard<std::mutex> lock(c.mu);
-            std::deque<Idle> rest;
-            for (const Idle &b : c.idle)
-                if (b.device == dev) drop.push_back(b.p);
-                else rest.push_back(b);
-            c.idle.swap(rest);
-            c.idle_bytes[dev] = 0;
-        }
-        for (void *q : drop) (void)hipFree(q);
-        e = hipMalloc(p, want);
-    }
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
-        return e;
-    }
+    e = device_malloc(p, want);
+    if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(c.mu);
     c.live.emplace(*p, Idle{*p, want, dev});
     return hipSuccess;

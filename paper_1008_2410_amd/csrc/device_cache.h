@@ -10,7 +10,7 @@
 //  - A block enters the cache idle: no queued work uses it (its owner has synchronised), so
 //    any stream and any thread may take it.
 //  - Idle blocks of a device are bounded by kIdleBytes; beyond it the oldest go back to the
-//    device at once, and all of them do when an allocation fails.
+//    device at once, and all of them do when an allocation of the library's fails.
 //  - The uniform trees' own arrays come from the device's stream-ordered pool, whose release
 //    threshold is lifted so that they are not unmapped at every synchronisation.  What lies idle
 //    there counts towards the same bound (bound_idle).
@@ -24,6 +24,11 @@ namespace fmm {
 
 constexpr size_t kIdleBytes = size_t(1) << 30;  // per device (of 288 GiB)
 constexpr size_t kIdleStreams = 8;              // per device
+
+// hipMalloc, and hipMallocAsync on stream s, on the current device; where memory is short, again
+// after everything held idle has gone back.  (NULL on failure, the runtime's error cleared.)
+hipError_t device_malloc(void **p, size_t bytes);
+hipError_t pool_malloc(void **p, size_t bytes, hipStream_t s);
 
 // A block of at least `bytes` on the current device: an idle one (at most half of it
 // unused), else new memory.

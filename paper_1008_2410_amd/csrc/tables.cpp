@@ -109,9 +109,9 @@ int upload_tables(Tables &tb, int p, std::string &err)
     for (int q = 0; q < 4; ++q) ent.push_back(make_int4(q, 0, 53 + q, 2));
     int rc = 0;
     {
-        if (hipMalloc((void **)&tb.mfma_f, mf.size() * sizeof(float)) != hipSuccess ||
-            hipMalloc((void **)&tb.mfma_d, md.size() * sizeof(double)) != hipSuccess) {
-            err = "hipMalloc failed for operator tables";
+        if (device_malloc((void **)&tb.mfma_f, mf.size() * sizeof(float)) != hipSuccess ||
+            device_malloc((void **)&tb.mfma_d, md.size() * sizeof(double)) != hipSuccess) {
+            err = "device allocation failed: operator tables";
             rc = -2;
         } else if (hipMemcpy(tb.mfma_f, mf.data(), mf.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
                    hipMemcpy(tb.mfma_d, md.data(), md.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess) {
@@ -120,8 +120,8 @@ int upload_tables(Tables &tb, int p, std::string &err)
         }
     }
     if (!rc) {
-        if (hipMalloc((void **)&tb.mfma_entries, ent.size() * sizeof(int4)) != hipSuccess) {
-            err = "hipMalloc failed for operator tables";
+        if (device_malloc((void **)&tb.mfma_entries, ent.size() * sizeof(int4)) != hipSuccess) {
+            err = "device allocation failed: operator tables";
             rc = -2;
         } else if (hipMemcpy(tb.mfma_entries, ent.data(), ent.size() * sizeof(int4), hipMemcpyHostToDevice) !=
                    hipSuccess) {
@@ -130,7 +130,7 @@ int upload_tables(Tables &tb, int p, std::string &err)
         }
     }
     if (!rc) {
-        if (hipMalloc((void **)&tb.zero_row, 128 * sizeof(double)) != hipSuccess ||
+        if (device_malloc((void **)&tb.zero_row, 128 * sizeof(double)) != hipSuccess ||
             hipMemset(tb.zero_row, 0, 128 * sizeof(double)) != hipSuccess) {
             err = "allocation of the zero row failed";
             rc = -2;

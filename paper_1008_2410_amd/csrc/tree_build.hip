@@ -938,12 +938,8 @@ template <typename T> hipError_t pool_array(T *&p, int64_t &cap, int64_t count, 
     if (p) (void)hipFreeAsync((void *)p, s);
     p = nullptr;
     cap = std::max<int64_t>(count + count / 8, 64);
-    const hipError_t e = hipMallocAsync((void **)&p, (size_t)cap * sizeof(T), s);
-    if (e != hipSuccess) {
-        p = nullptr;
-        cap = 0;
-        (void)hipGetLastError();
-    }
+    const hipError_t e = pool_malloc((void **)&p, (size_t)cap * sizeof(T), s);
+    if (e != hipSuccess) cap = 0;
     return e;
 }
 
@@ -963,12 +959,8 @@ hipError_t alloc_slab(fmm_tree *t, hipStream_t s)
                  g1 = take(n * sizeof(int)), g2 = take(n * sizeof(int)), lo = take(n * sizeof(int)),
                  ls = take((nleaf + 1) * sizeof(int)), ts = take((nleaf + 1) * sizeof(int)),
                  co = take((size_t)level_base(t->depth + 1) * sizeof(int)), ma = take(nleaf * sizeof(uint16_t));
-    const hipError_t e = hipMallocAsync((void **)&t->slab, off, s);
-    if (e != hipSuccess) {
-        t->slab = nullptr;
-        (void)hipGetLastError();
-        return e;
-    }
+    const hipError_t e = pool_malloc((void **)&t->slab, off, s);
+    if (e != hipSuccess) return e;
     char *b = t->slab;
     t->d_xy = (double2 *)(b + xy);
     t->d_st1 = (double *)(b + st1);
@@ -1189,7 +1181,7 @@ int build_near_plan_device(fmm_tree *t, hipStream_t s, std::string &err)
     Buf<uint32_t> nent;
     Buf<unsigned long long> plan;
     if ((!t->d_leaf_mask &&
-         !st.check(hipMallocAsync((void **)&t->d_leaf_mask, nleaf * sizeof(uint16_t), s), "near-field plan")) ||
+         !st.check(pool_malloc((void **)&t->d_leaf_mask, nleaf * sizeof(uint16_t), s), "near-field plan")) ||
         !st.check(plan.alloc(kPlanFacts, s), "near-field plan") ||
         !st.check(hipMemsetAsync(plan.p, 0, kPlanFacts * sizeof(unsigned long long), s), "near-field plan") ||
         !plan_count(t, nent, plan.p, s, st))

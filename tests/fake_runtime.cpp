@@ -1,4 +1,4 @@
-// The library's host code (api.cpp, adaptive.cpp, device_cache.cpp, host_tree.cpp) over a HIP
+// The library's host code (api.cpp, adaptive.cpp, device_cache.cpp, tables.cpp, host_tree.cpp) over a HIP
 // runtime of this file's own: device memory is host memory, allocations can be made to fail,
 // kernel launchers check the arrays they are handed and compute nothing.  Each check runs in a
 // child process of its own and names what it found.
@@ -152,7 +152,7 @@ int build_tree_device(fmm_tree *t, const double *, const double *, hipStream_t s
                       const std::function<void()> &)
 {
     t->pooled = true;
-    return hipMallocAsync((void **)&t->slab, g_tree_bytes, s) == hipSuccess ? FMM_OK : FMM_ENOMEM;
+    return pool_malloc((void **)&t->slab, g_tree_bytes, s) == hipSuccess ? FMM_OK : FMM_ENOMEM;
 }
 int build_near_plan_device(fmm_tree *t, hipStream_t, std::string &)
 {
@@ -187,13 +187,6 @@ int build_atree_m2l_plan(fmm_atree *t, const int4 *, hipStream_t, std::string &)
     g_lists.push_back(p);
     t->m2l_plan = true;
     return FMM_OK;
-}
-int shared_tables(int, int p, const Tables **out, std::string &, bool)
-{
-    static Tables tb;
-    tb.p = p;
-    *out = &tb;
-    return 0;
 }
 int static_workspace(int, char **base)
 {
@@ -491,11 +484,50 @@ void held_memory()
         }));
 }
 
+// Where memory is short, what the library holds idle goes back before a call fails.
+void idle_released()
+{
+    const size_t MiB = size_t(1) << 20;
+    bool bad = false;
+    for (int pool = 0; pool < 2; ++pool)
+        for (int what = 0; what < 5; ++what)
+            bad |= !child([&] {
+                const double one[2] = {0.5, 0.5};
+                const int64_t n = 100000;
+                std::vector<double> g(n, 1.0), uv(2 * n);
+                fmm_tree *kept = uniform_tree(n, 6), *t = nullptr;
+                REQUIRE(fmm_velocity(kept, g.data(), 0.01, 9, FMM_MIXED, nullptr, nullptr, uv.data()) == FMM_OK);
+                fmm::g_tree_bytes = 600 * MiB;
+                fmm_atree *a = nullptr;
+                if (pool) REQUIRE(fmm_build_tree(one, 1, 4, kUnit, nullptr, &t) == FMM_OK);
+                else REQUIRE(fmm_atree_build(one, 1, 4, 4, kUnit, nullptr, &a) == FMM_OK);
+                fmm_destroy_tree(t);
+                fmm_atree_destroy(a);
+                REQUIRE(g_pool_idle > 0 || !pool);
+                // room for the trees' small arrays only
+                g_capacity = g_used + g_pool_idle;
+                printf("idle in the %s, allocation %d: ", pool ? "pool" : "cache", what);
+                int rc = FMM_OK;
+                if (what == 0) rc = fmm_velocity(kept, g.data(), 0.01, 31, FMM_MIXED, nullptr, nullptr, uv.data());  // tables
+                if (what == 1) rc = fmm_velocity(kept, g.data(), 0.01, 9, FMM_FP64, nullptr, nullptr, uv.data());
+                if (what == 2) uniform_tree(n, 5);
+                if (what == 3) rc = fmm_set_option(kept, FMM_OPT_VALIDATE, 1) != FMM_OK ? FMM_EINVAL
+                                    : fmm_velocity(kept, g.data(), 0.01, 9, FMM_MIXED, nullptr, nullptr, uv.data());
+                fmm::g_tree_bytes = 100 * MiB;
+                if (what == 4) rc = pool ? fmm_atree_build(one, 1, 4, 4, kUnit, nullptr, &a)
+                                         : fmm_build_tree(one, 1, 4, kUnit, nullptr, &t);
+                REQUIRE(rc == FMM_OK);
+                printf("ok\n");
+            });
+    REQUIRE(!bad);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
-    const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}, {"held_memory", held_memory}};
+    const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}, {"held_memory", held_memory},
+                                                              {"idle_released", idle_released}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     REQUIRE(it != checks.end());
     REQUIRE(child(it->second));

@@ -9,7 +9,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCES = ["tests/fake_runtime.cpp"] + [f"paper_1008_2410_amd/csrc/{f}.cpp"
-                                        for f in ("api", "adaptive", "device_cache", "host_tree")]
+                                        for f in ("api", "adaptive", "device_cache", "tables", "host_tree")]
 
 
 @pytest.fixture(scope="module")
@@ -27,7 +27,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["call_memory", "warm_calls", "held_memory"])
+@pytest.mark.parametrize("check", ["call_memory", "warm_calls", "held_memory", "idle_released"])
 def test_host_runtime(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and f"{check} passed" in r.stdout, r.stdout[-3000:] + r.stderr[-1000:]
