@@ -1118,41 +1118,64 @@ int most_parts(int64_t n)
 }
 
 // The plan's counts: entries per leaf (scanned into offsets, nleaf + 1), the leaf masks, and the
-// first of plan[] (device, zeroed), see PlanFact.
-bool plan_count(fmm_tree *t, Buf<uint32_t> &nent, unsigned long long *plan, hipStream_t s, Status &st)
+// first of plan[] (device, zeroed), see PlanFact.  most: parts of an item.
+bool plan_count(fmm_tree *t, Buf<uint32_t> &nent, int most, unsigned long long *plan, hipStream_t s, Status &st)
 {
     const int64_t nleaf = int64_t(1) << (2 * t->depth);
-    if (!st.check(nent.alloc(nleaf + 1, s), "near-field plan")) return false;
+    if (!nent.p && !st.check(nent.alloc(nleaf + 1, s), "near-field plan")) return false;
     k_plan_cost<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, t->d_leaf_mask, plan);
     k_plan_count<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, t->d_leaf_mask,
-                                                           most_parts(t->n), plan, nent.p);
+                                                           most, plan, nent.p);
     return scan_on(nent.p, nent.p, nleaf + 1, nullptr, s, st);
 }
 
+// The arrays of the split items; none of them if memory does not hold them.
+bool part_arrays(fmm_tree *t, const unsigned long long *h, hipStream_t s)
+{
+    if (pool_array(t->d_split, t->cap_split, (int64_t)h[kPlanSplit], s) == hipSuccess &&
+        pool_array(t->d_parts, t->cap_parts, (int64_t)h[kPlanParts], s) == hipSuccess &&
+        pool_array(t->d_part_sums, t->cap_part_sums, 3 * (int64_t)h[kPlanSums], s) == hipSuccess)
+        return true;
+    auto drop = [s](auto *&p, int64_t &cap) {
+        if (p) (void)hipFreeAsync((void *)p, s);
+        p = nullptr;
+        cap = 0;
+    };
+    drop(t->d_split, t->cap_split);
+    drop(t->d_parts, t->cap_parts);
+    drop(t->d_part_sums, t->cap_part_sums);
+    return false;
+}
+
 // The work list of `total` entries, heaviest first, and the parts of the split items; plan as the
-// host read it and on the device.
-bool plan_fill(fmm_tree *t, const Buf<uint32_t> &nent, uint32_t total, const unsigned long long *h,
+// host read it and on the device.  Where the parts' arrays do not fit, the items stay whole.
+bool plan_fill(fmm_tree *t, Buf<uint32_t> &nent, uint32_t total, const unsigned long long *h,
                unsigned long long *plan, hipStream_t s, Status &st)
 {
     const int64_t nleaf = int64_t(1) << (2 * t->depth);
+    int most = most_parts(t->n);
+    if (h[kPlanSplit] > 0 && !part_arrays(t, h, s)) {
+        most = 1;
+        if (!st.check(hipMemsetAsync(plan, 0, kPlanFacts * sizeof(unsigned long long), s), "near-field plan") ||
+            !plan_count(t, nent, most, plan, s, st) ||
+            !st.check(hipMemcpyAsync(&total, nent.p + nleaf, sizeof total, hipMemcpyDeviceToHost, s), "near-field plan") ||
+            !st.check(hipStreamSynchronize(s), "near-field plan"))
+            return false;
+    }
     Buf<int4> work;
     Buf<uint64_t> key;
     Buf<uint32_t> val;
     if (!st.check(pool_array(t->d_near_work, t->cap_near_work, total, s), "near-field plan") ||
-        (h[kPlanSplit] > 0 &&
-         (!st.check(pool_array(t->d_split, t->cap_split, (int64_t)h[kPlanSplit], s), "near-field plan") ||
-          !st.check(pool_array(t->d_parts, t->cap_parts, (int64_t)h[kPlanParts], s), "near-field plan") ||
-          !st.check(pool_array(t->d_part_sums, t->cap_part_sums, 3 * (int64_t)h[kPlanSums], s), "near-field plan"))) ||
         !st.check(work.alloc(total, s), "near-field plan") || !st.check(key.alloc(total, s), "near-field plan") ||
         !st.check(val.alloc(total, s), "near-field plan"))
         return false;
-    k_plan_fill<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, most_parts(t->n), plan,
-                                                      nent.p, PlanOut{work.p, key.p, val.p, t->d_split, t->d_parts});
+    k_plan_fill<<<grid_for(nleaf, 256), 256, 0, s>>>(t->d_leaf_start, t->depth, t->dense_leaf, most, plan, nent.p,
+                                                      PlanOut{work.p, key.p, val.p, t->d_split, t->d_parts});
     if (!st.check(hipGetLastError(), "near-field plan") || !radix_sort(key, val, total, 8, s, st)) return false;
     k_gather<int4><<<grid_for(total, 256), 256, 0, s>>>(work.p, val.p, total, t->d_near_work);
     t->nnear_work = total;
-    t->nsplit = (int64_t)h[kPlanSplit];
-    t->npart_sums = (int64_t)h[kPlanSums];
+    t->nsplit = most > 1 ? (int64_t)h[kPlanSplit] : 0;
+    t->npart_sums = most > 1 ? (int64_t)h[kPlanSums] : 0;
     return st.check(hipGetLastError(), "near-field plan");
 }
 
@@ -1184,7 +1207,7 @@ int build_near_plan_device(fmm_tree *t, hipStream_t s, std::string &err)
          !st.check(pool_malloc((void **)&t->d_leaf_mask, nleaf * sizeof(uint16_t), s), "near-field plan")) ||
         !st.check(plan.alloc(kPlanFacts, s), "near-field plan") ||
         !st.check(hipMemsetAsync(plan.p, 0, kPlanFacts * sizeof(unsigned long long), s), "near-field plan") ||
-        !plan_count(t, nent, plan.p, s, st))
+        !plan_count(t, nent, most_parts(t->n), plan.p, s, st))
         return failed();
     unsigned long long hs[kPlanFacts];
     uint32_t total = 0;
@@ -1275,7 +1298,7 @@ int build_tree_device(fmm_tree *t, const double *xy, const double *root_box, hip
         if (!scan_on(pos.p, pos.p, nflags + 1, nullptr, s, st)) return failed();
     }
     t->nunits_tc = t->nmut = t->nnear_work = t->nsplit = t->npart_sums = t->mutual_pairs = 0;
-    if (t->near_mutual && !plan_count(t, nent, facts.p->plan, s, st)) return failed();
+    if (t->near_mutual && !plan_count(t, nent, most_parts(t->n), facts.p->plan, s, st)) return failed();
     k_sizes<<<1, 64, 0, s>>>(tstart, pos.p, nent.p, nleaf, L, facts.p);
     if (!st.check(hipGetLastError(), "tree build") || !read_facts()) return failed();
     const uint32_t ntiles = h.ntiles;
