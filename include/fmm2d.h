@@ -66,7 +66,8 @@ enum {
                                  second stream, and in the mixed form when the far field is
                                  predicted more than 4 times the near field; concurrent otherwise */
     FMM_OPT_COARSE_LEVEL = 2, /* L_c: in the mixed form levels <= max(L_c, 5) of the up/down
-                                 sweeps run in FP64 (default 3, range 1..depth) */
+                                 sweeps run in FP64 (default 3, range 1..depth); levels <= L_c in
+                                 a call of fmm_velocity_noalloc that does not fit otherwise */
     FMM_OPT_TIMING = 3,       /* 1: record HIP events around each stage of every call for
                                  fmm_get_timings (default 0) */
                               /* keys 4 and 5 (a persistent near-field grid, a cap on the far-field

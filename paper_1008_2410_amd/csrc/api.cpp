@@ -464,43 +464,48 @@ int ensure_positions(fmm_tree *t, int precision, hipStream_t s)
 // The per-call arrays of an evaluation carved from the static workspace (no allocation):
 // circulations, staged velocities, near field, leaf-unit coordinates (in `sums`, when the
 // tree has none yet), slots (mutual form), then the multipoles and locals of every level,
-// each 256-byte aligned.  FMM_EINVAL when they do not fit, naming both sizes.
+// each 256-byte aligned.  A mixed call for which they do not fit with levels 2..5 in FP64 (20 KiB
+// per term) takes L_c as it stands.  FMM_EINVAL when that does not fit, naming both sizes.
 int static_ws(const fmm_tree *t, int p, int precision, Workspace &ws)
 {
     char *base = nullptr;
     const int e = static_workspace(t->device, &base);
     if (e != 0) return hip_fail((hipError_t)e, "looking up the static workspace");
-    const int split = split_level(t, precision);
     const int L = t->depth;
     const int64_t n = t->n;
-    const int64_t cells_d = L >= 2 ? level_base(std::min(split, L) + 1) * p + kCoefPad : 0;
-    const int64_t cells_f = L >= 2 && level_base(L + 1) > level_base(std::min(split, L) + 1)
-                                ? (level_base(L + 1) - level_base(std::min(split, L) + 1)) * p + kCoefPad
-                                : 0;
     const size_t real = precision == FMM_FP64 ? sizeof(double) : sizeof(float);
     const size_t slot = precision == FMM_FP64 ? sizeof(double2) : sizeof(float2);
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        const size_t at = off;
-        off += (bytes + 255) / 256 * 256;
-        return base + at;
+    auto carve = [&](int split) {
+        const int64_t cells_d = L >= 2 ? level_base(std::min(split, L) + 1) * p + kCoefPad : 0;
+        const int64_t cells_f = L >= 2 && level_base(L + 1) > level_base(std::min(split, L) + 1)
+                                    ? (level_base(L + 1) - level_base(std::min(split, L) + 1)) * p + kCoefPad
+                                    : 0;
+        size_t off = 0;
+        auto take = [&](size_t bytes) {
+            const size_t at = off;
+            off += (bytes + 255) / 256 * 256;
+            return base + at;
+        };
+        ws = Workspace{};
+        ws.p = p;
+        ws.precision = precision;
+        ws.split = split;
+        ws.gam = take((size_t)n * real);
+        ws.stage = (double2 *)take((size_t)n * sizeof(double2));
+        ws.near = (double2 *)take((size_t)n * sizeof(double2));
+        // the tree's leaf-unit coordinates when an allocating evaluation has not made them yet
+        if (!t->d_pos[precision == FMM_FP64]) ws.sums = take((size_t)n * 2 * real);
+        if (use_mutual(t)) ws.slots = take((size_t)9 * n * slot);
+        ws.mp_d = (double2 *)take((size_t)cells_d * sizeof(double2));
+        ws.lo_d = (double2 *)take((size_t)cells_d * sizeof(double2));
+        ws.mp_f = (float2 *)take((size_t)cells_f * sizeof(float2));
+        ws.lo_f = (float2 *)take((size_t)cells_f * sizeof(float2));
+        return off;
     };
-    ws = Workspace{};
-    ws.p = p;
-    ws.precision = precision;
-    ws.split = split;
-    ws.gam = take((size_t)n * real);
-    ws.stage = (double2 *)take((size_t)n * sizeof(double2));
-    ws.near = (double2 *)take((size_t)n * sizeof(double2));
-    // the tree's leaf-unit coordinates when an allocating evaluation has not made them yet
-    if (!t->d_pos[precision == FMM_FP64]) ws.sums = take((size_t)n * 2 * real);
-    if (use_mutual(t)) ws.slots = take((size_t)9 * n * slot);
-    ws.mp_d = (double2 *)take((size_t)cells_d * sizeof(double2));
-    ws.lo_d = (double2 *)take((size_t)cells_d * sizeof(double2));
-    ws.mp_f = (float2 *)take((size_t)cells_f * sizeof(float2));
-    ws.lo_f = (float2 *)take((size_t)cells_f * sizeof(float2));
-    if (off > kStaticWorkspaceBytes)
-        return fail(FMM_EINVAL, "this evaluation needs " + std::to_string(off) + " bytes of device workspace, more "
+    size_t bytes = carve(split_level(t, precision));
+    if (bytes > kStaticWorkspaceBytes && precision != FMM_FP64) bytes = carve(std::min(t->lc, L));
+    if (bytes > kStaticWorkspaceBytes)
+        return fail(FMM_EINVAL, "this evaluation needs " + std::to_string(bytes) + " bytes of device workspace, more "
                                 "than the " + std::to_string(kStaticWorkspaceBytes) + " bytes of the static workspace");
     return FMM_OK;
 }
