@@ -1049,8 +1049,9 @@ __device__ __forceinline__ void force_sums_batch(const rec_t<T> *tile, const T *
 
 // The pair force multiplies Gamma_j q_i in the records' precision.  So that FP32 neither
 // overflows nor underflows where the separate sums (linear in each) did not, the FP32 charges
-// carry the power of two that brings max|q| max|Gamma| near 1: the maxima of every block here,
-// reduced by every block of the pack kernel, which leaves the factor for the finalize kernel.
+// carry the power of two that brings max|q| max|Gamma| near 1 (charge_scale): the maxima of every
+// block here, reduced by every block of the pack kernel, which leaves the factor for the finalize
+// kernel.
 static __global__ __launch_bounds__(256) void adjoint_range_kernel(int64_t n, const double *__restrict__ gamma,
                                                             const double2 *__restrict__ dl, double scale,
                                                             double2 *__restrict__ range)
@@ -1099,8 +1100,9 @@ __device__ __forceinline__ double charge_scale(const double2 *__restrict__ range
         g = fmax(g, part[k].x);
         q = fmax(q, part[k].y);
     }
-    // (a zero, infinite or NaN maximum counts as 1; FP32's own range bounds Gamma's exponent)
-    const int eg = g > 0.0 && g < 1e300 ? max(-120, min(120, ilogb(g))) : 0;
+    // (a zero, infinite or NaN maximum counts as 1.  Half of Gamma's exponent range in FP32: Phi
+    // sums the charges themselves, and 2^60 of them and products down to 2^-66 both leave room)
+    const int eg = g > 0.0 && g < 1e300 ? max(-60, min(60, ilogb(g))) : 0;
     const int eq = q > 0.0 && q < 1e300 ? ilogb(q) : 0;
     const double s = ldexp(1.0, -max(-900, min(900, eg + eq)));
     if (blockIdx.x == 0 && threadIdx.x == 0) *qscale = s;
