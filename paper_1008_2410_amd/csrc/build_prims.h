@@ -100,8 +100,11 @@ inline void build_free(void *p, size_t bytes, hipStream_t s)
 {
     if (!p) return;
     if (t_build_scope && t_build_scope->s == s) {
-        t_build_scope->freed.emplace_back(p, bytes);
-        return;
+        try {
+            t_build_scope->freed.emplace_back(p, bytes);
+            return;
+        } catch (...) {  // (called from destructors) no host memory: given back at once
+        }
     }
     (void)hipStreamSynchronize(s);
     block_free(p);

@@ -2,27 +2,33 @@
 
 #include <atomic>
 #include <cstdint>
-#include <deque>
-#include <map>
+#include <list>
 #include <mutex>
 #include <unordered_map>
-#include <vector>
 
 namespace fmm {
 namespace {
 
-struct Idle {
+constexpr int kDevices = 64;
+
+struct Block {
     void *p;
     size_t bytes;
     int device;
 };
 
+// A block keeps its list node and its place in `where` from the allocation to the release of its
+// memory: giving blocks back, here and to the device, allocates no host memory and cannot throw.
 struct Cache {
     std::mutex mu;
-    std::unordered_map<void *, Idle> live;     // blocks handed out
-    std::deque<Idle> idle;                     // oldest first
-    std::map<int, size_t> idle_bytes;          // per device
-    std::map<int, std::vector<SideStream>> streams;
+    std::list<Block> live;  // handed out
+    std::list<Block> idle;  // oldest first
+    std::unordered_map<void *, std::list<Block>::iterator> where;
+    size_t idle_bytes[kDevices] = {};
+    struct {
+        SideStream s[kIdleStreams];
+        size_t count = 0;
+    } streams[kDevices];
 };
 
 // Never destroyed: trees may outlive static destruction order, and the runtime releases
@@ -31,6 +37,22 @@ Cache &cache()
 {
     static Cache *c = new Cache();
     return *c;
+}
+
+// Takes the device's oldest idle blocks out of the cache until at most `keep` bytes are idle.
+std::list<Block> take_oldest(Cache &c, int device, size_t keep)
+{
+    std::list<Block> out;
+    for (auto k = c.idle.begin(); c.idle_bytes[device] > keep && k != c.idle.end();) {
+        const auto next = std::next(k);
+        if (k->device == device) {
+            c.idle_bytes[device] -= k->bytes;
+            c.where.erase(k->p);
+            out.splice(out.end(), c.idle, k);
+        }
+        k = next;
+    }
+    return out;
 }
 
 // Sizes in steps of an eighth of the power of two below, so that slightly different trees
@@ -47,19 +69,14 @@ size_t rounded(size_t bytes)
 void release_idle()
 {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return;
     Cache &c = cache();
-    std::vector<void *> drop;
+    std::list<Block> drop;
     {
         std::lock_guard<std::mutex> lock(c.mu);
-        std::deque<Idle> rest;
-        for (const Idle &b : c.idle)
-            if (b.device == dev) drop.push_back(b.p);
-            else rest.push_back(b);
-        c.idle.swap(rest);
-        c.idle_bytes[dev] = 0;
+        drop = take_oldest(c, dev, 0);
     }
-    for (void *q : drop) (void)hipFree(q);
+    for (const Block &b : drop) (void)hipFree(b.p);
     hipMemPool_t pool;
     if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
     (void)hipGetLastError();
@@ -98,6 +115,7 @@ hipError_t block_alloc(void **p, size_t bytes)
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kDevices) return hipErrorInvalidDevice;
     const size_t want = rounded(bytes ? bytes : 1);
     Cache &c = cache();
     {
@@ -108,18 +126,28 @@ hipError_t block_alloc(void **p, size_t bytes)
                 (best == c.idle.end() || it->bytes < best->bytes))
                 best = it;
         if (best != c.idle.end()) {
-            const Idle b = *best;
-            c.idle.erase(best);
-            c.idle_bytes[dev] -= b.bytes;
-            c.live.emplace(b.p, b);
-            *p = b.p;
+            c.idle_bytes[dev] -= best->bytes;
+            c.live.splice(c.live.end(), c.idle, best);
+            *p = best->p;
             return hipSuccess;
         }
     }
     e = device_malloc(p, want);
     if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lock(c.mu);
-    c.live.emplace(*p, Idle{*p, want, dev});
+    try {
+        std::lock_guard<std::mutex> lock(c.mu);
+        c.live.push_back(Block{*p, want, dev});
+        try {
+            c.where.emplace(*p, std::prev(c.live.end()));
+        } catch (...) {
+            c.live.pop_back();
+            throw;
+        }
+    } catch (...) {  // no host memory for its entry
+        (void)hipFree(*p);
+        *p = nullptr;
+        return hipErrorOutOfMemory;
+    }
     return hipSuccess;
 }
 
@@ -127,33 +155,23 @@ void block_free(void *p)
 {
     if (!p) return;
     Cache &c = cache();
-    std::vector<void *> drop;
+    std::list<Block> drop;
     {
         std::lock_guard<std::mutex> lock(c.mu);
-        auto it = c.live.find(p);
-        if (it == c.live.end()) return;
-        const Idle b = it->second;
-        c.live.erase(it);
-        c.idle.push_back(b);
-        size_t &sum = c.idle_bytes[b.device];
-        sum += b.bytes;
-        for (auto k = c.idle.begin(); sum > kIdleBytes && k != c.idle.end();) {
-            if (k->device != b.device) {
-                ++k;
-                continue;
-            }
-            sum -= k->bytes;
-            drop.push_back(k->p);
-            k = c.idle.erase(k);
-        }
+        const auto it = c.where.find(p);
+        if (it == c.where.end()) return;
+        const auto b = it->second;
+        c.idle.splice(c.idle.end(), c.live, b);
+        c.idle_bytes[b->device] += b->bytes;
+        drop = take_oldest(c, b->device, kIdleBytes);
     }
-    for (void *q : drop) (void)hipFree(q);
+    for (const Block &b : drop) (void)hipFree(b.p);
 }
 
 void retain_pool(int device)
 {
     static std::atomic<uint64_t> done{0};
-    if (device < 0 || device >= 64 || ((done.load() >> device) & 1)) return;
+    if (device < 0 || device >= kDevices || ((done.load() >> device) & 1)) return;
     hipMemPool_t pool;
     if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess) {
         uint64_t threshold = UINT64_MAX;
@@ -166,6 +184,7 @@ void retain_pool(int device)
 void bound_idle(int device)
 {
     size_t idle;
+    if (device < 0 || device >= kDevices) return;
     {
         Cache &c = cache();
         std::lock_guard<std::mutex> lock(c.mu);
@@ -188,13 +207,12 @@ void bound_idle(int device)
 
 hipError_t side_stream_take(int device, SideStream &s)
 {
-    Cache &c = cache();
-    {
+    if (device >= 0 && device < kDevices) {
+        Cache &c = cache();
         std::lock_guard<std::mutex> lock(c.mu);
         auto &v = c.streams[device];
-        if (!v.empty()) {
-            s = v.back();
-            v.pop_back();
+        if (v.count > 0) {
+            s = v.s[--v.count];
             return hipSuccess;
         }
     }
@@ -207,12 +225,12 @@ hipError_t side_stream_take(int device, SideStream &s)
 
 void side_stream_give(int device, SideStream &s)
 {
-    if (s.stream && s.fork && s.join) {
+    if (s.stream && s.fork && s.join && device >= 0 && device < kDevices) {
         Cache &c = cache();
         std::lock_guard<std::mutex> lock(c.mu);
         auto &v = c.streams[device];
-        if (v.size() < kIdleStreams) {
-            v.push_back(s);
+        if (v.count < kIdleStreams) {
+            v.s[v.count++] = s;
             s = SideStream{};
             return;
         }

@@ -13,12 +13,14 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
 #include "../include/fmm2d.h"
 #include "../include/fmm2d_adaptive.h"
 #include "../paper_1008_2410_amd/csrc/adaptive_internal.h"
+#include "../paper_1008_2410_amd/csrc/build_prims.h"
 #include "../paper_1008_2410_amd/csrc/fmm_internal.h"
 
 #define REQUIRE(cond)                                                                  \
@@ -29,6 +31,17 @@
             _exit(1);                                                                  \
         }                                                                              \
     } while (0)
+
+// Host allocations fail from this one on (-1: none does).
+static int64_t g_new_left = -1;
+void *operator new(size_t n)
+{
+    if (g_new_left == 0) throw std::bad_alloc();
+    if (g_new_left > 0) --g_new_left;
+    return malloc(n ? n : 1);
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 // ---------------------------------------------------------------------------------
 // The runtime
@@ -47,7 +60,10 @@ hipError_t take(void **p, size_t bytes)
     const int64_t number = g_allocs++;
     if ((g_fail_from >= 0 && number >= g_fail_from) || g_used + g_pool_idle + bytes > g_capacity) return hipErrorOutOfMemory;
     *p = calloc(1, bytes ? bytes : 1);
+    const int64_t left = g_new_left;  // (this runtime's own entries are not the library's)
+    g_new_left = -1;
     g_live[(char *)*p] = bytes;
+    g_new_left = left;
     g_used += bytes;
     return hipSuccess;
 }
@@ -522,12 +538,47 @@ void idle_released()
     REQUIRE(!bad);
 }
 
+// Without host memory the cache hands out nothing or a block, gives back what it is given and
+// throws nothing (it is called from destructors and behind the C interface).
+void host_memory()
+{
+    bool bad = false;
+    for (int k = 0; k < 12; ++k)
+        bad |= !child([&] {
+            const size_t MiB = size_t(1) << 20;
+            std::vector<void *> kept, got(8, nullptr);
+            for (int j = 0; j < 6; ++j) {
+                void *p = nullptr;
+                REQUIRE(fmm::block_alloc(&p, (200 + j) * MiB) == hipSuccess);
+                kept.push_back(p);
+            }
+            fmm::SideStream side;
+            REQUIRE(fmm::side_stream_take(0, side) == hipSuccess);
+            fmm::BuildScope *scope = new fmm::BuildScope(nullptr);
+            void *step = nullptr;
+            REQUIRE(fmm::build_alloc(&step, MiB, nullptr) == hipSuccess);
+            g_new_left = k;
+            fmm::side_stream_give(0, side);
+            fmm::build_free(step, MiB, nullptr);
+            for (void *p : kept) fmm::block_free(p);
+            for (size_t j = 0; j < got.size(); ++j)
+                REQUIRE((fmm::block_alloc(&got[j], (300 + j) * MiB) == hipSuccess) == (got[j] != nullptr));
+            for (void *p : got) fmm::block_free(p);
+            g_new_left = -1;
+            delete scope;
+            printf("allocation %d: %zu MiB held\n", k, g_used / MiB);
+            REQUIRE(g_used <= fmm::kIdleBytes);
+        });
+    REQUIRE(!bad);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}, {"held_memory", held_memory},
-                                                              {"idle_released", idle_released}};
+                                                              {"idle_released", idle_released},
+                                                              {"host_memory", host_memory}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     REQUIRE(it != checks.end());
     REQUIRE(child(it->second));
