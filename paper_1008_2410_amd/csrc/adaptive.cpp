@@ -12,6 +12,7 @@
 #include "../../include/fmm2d_adaptive.h"
 #include "adaptive_internal.h"
 #include "api_common.h"
+#include "cost_order.h"
 #include "fmm_internal.h"
 
 using namespace fmm;
@@ -770,7 +771,8 @@ extern "C" int fmm_atree_build_host(const double *xy, int64_t n, int max_leaf, i
         }
         std::vector<int> worder(work.size());
         for (size_t u = 0; u < work.size(); ++u) worder[u] = (int)u;
-        std::stable_sort(worder.begin(), worder.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+        for (int64_t &c : cost) c = (int64_t)cost_order((uint64_t)c);
+        std::stable_sort(worder.begin(), worder.end(), [&](int a, int b) { return cost[a] < cost[b]; });
         std::vector<int4> swork(work.size());
         for (size_t u = 0; u < work.size(); ++u) swork[u] = work[worder[u]];
         t->ntiles = (int64_t)boxes.size();

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/fmm2d.h"
+#include "cost_order.h"
 #include "device_cache.h"
 
 namespace fmm {
@@ -183,16 +184,6 @@ bool scan_exclusive(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tota
 // Stable LSD sort of (keys, vals) by the low `bits` bits of the keys, 8-bit digits; the
 // result is in keys and vals (whose buffers may be swapped with the sort's own).
 bool radix_sort(Buf<uint64_t> &keys, Buf<uint32_t> &vals, int64_t n, int bits, hipStream_t s, Status &st);
-
-// Order key of a work entry of a near-field list by its estimated cost, heaviest first, in
-// 8 bits: the cost's binary exponent and its next two bits (within 25%, which is what an
-// order of dispatch needs).  One sort pass instead of four or five over the whole number.
-__host__ __device__ inline uint64_t cost_order(uint64_t cost)
-{
-    const int msb = 63 - __builtin_clzll(cost | 1);
-    const int e = msb > 2 ? msb - 2 : 0;  // cost >> e < 8
-    return 255 - (4 * (uint64_t)e + (cost >> e));
-}
 
 // The sums of v[0..NV) over a workgroup of 256 threads (all of them), added to dst by one thread
 // each: an atomic per wavefront and value had every wavefront of the launch wait in line for the

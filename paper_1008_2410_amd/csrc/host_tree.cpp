@@ -7,6 +7,7 @@
 #include <numeric>
 
 #include "../../include/fmm2d.h"
+#include "cost_order.h"
 #include "morton.h"
 
 namespace fmm {
@@ -172,7 +173,7 @@ int build_host_tree(const double *xy, int64_t n, int depth, const double *root_b
     int64_t pairs = 0, nonempty = 0, maxleaf = 0;
     // Stage 9 work units: target chunks of <= 64 in each non-empty leaf.
     std::vector<HostI4> units;
-    std::vector<int64_t> cost;
+    std::vector<uint64_t> cost;
     for (int64_t c = 0; c < nleaf; ++c) {
         const int nt = leaf_start[c + 1] - leaf_start[c];
         if (nt == 0) continue;
@@ -194,7 +195,7 @@ int build_host_tree(const double *xy, int64_t n, int depth, const double *root_b
             u.z = cnt;
             u.w = logtp;
             units.push_back(u);
-            cost.push_back((nsrc + kstride - 1) / kstride);
+            cost.push_back(cost_order((uint64_t)((nsrc + kstride - 1) / kstride)));
         }
     }
     t.p2p_pairs = pairs - n;
@@ -220,7 +221,7 @@ int build_host_tree(const double *xy, int64_t n, int depth, const double *root_b
     // Heaviest units first so the tail of the launch is short.
     std::vector<int64_t> order(units.size());
     std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return cost[a] > cost[b]; });
+    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return cost[a] < cost[b]; });
     t.units.resize(units.size());
     for (size_t k = 0; k < order.size(); ++k) t.units[k] = units[order[k]];
 

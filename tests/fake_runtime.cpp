@@ -21,6 +21,7 @@
 #include "../include/fmm2d_adaptive.h"
 #include "../paper_1008_2410_amd/csrc/adaptive_internal.h"
 #include "../paper_1008_2410_amd/csrc/build_prims.h"
+#include "../paper_1008_2410_amd/csrc/cost_order.h"
 #include "../paper_1008_2410_amd/csrc/fmm_internal.h"
 
 #define REQUIRE(cond)                                                                  \
@@ -353,6 +354,8 @@ void launch_atree_finalize(const AtreeCall &c, double *, double *, double *, con
 // ---------------------------------------------------------------------------------
 namespace {
 
+using namespace fmm;
+
 // Runs f in a child process; whether it ended well.
 bool child(const std::function<void()> &f)
 {
@@ -572,13 +575,66 @@ void host_memory()
     REQUIRE(!bad);
 }
 
+// The host builds order their work by the device builds' key (cost_order), ties in the order of
+// the leaves.
+void work_order()
+{
+    std::vector<double> xy = points(9000);
+    for (size_t k = 0; k < 4000; ++k) xy[k] = 0.3 + 0.05 * xy[k];
+    fmm_tree *t = nullptr;
+    REQUIRE(fmm_build_tree_host(xy.data(), 9000, 5, kUnit, nullptr, &t) == FMM_OK);
+    std::vector<std::pair<uint64_t, int>> keys;
+    for (int64_t k = 0; k < t->nunits; ++k) {
+        const int4 u = t->d_units[k];
+        int64_t nsrc = 0;
+        const int x = (int)morton_x((uint32_t)u.x), y = (int)morton_y((uint32_t)u.x);
+        for (int dy = -1; dy <= 1; ++dy)
+            for (int dx = -1; dx <= 1; ++dx)
+                if (x + dx >= 0 && y + dy >= 0 && x + dx < 32 && y + dy < 32) {
+                    const uint32_t c = morton_encode((uint32_t)(x + dx), (uint32_t)(y + dy));
+                    nsrc += t->d_leaf_start[c + 1] - t->d_leaf_start[c];
+                }
+        const int64_t stride = 64 >> u.w;
+        keys.emplace_back(cost_order((uint64_t)((nsrc + stride - 1) / stride)), u.y);
+    }
+    REQUIRE(std::is_sorted(keys.begin(), keys.end()) && keys.front().first < keys.back().first);
+
+    fmm_atree *a = nullptr;
+    REQUIRE(fmm_atree_build_host(xy.data(), 9000, 60, 8, kUnit, nullptr, &a) == FMM_OK);
+    uint64_t last = 0;
+    int units = 0, items = 0;
+    for (int64_t k = 0; k < a->nwork; ++k) {
+        const int4 u = a->d.work[k];
+        int64_t cost = 0;
+        if (u.w & kMutualItem) {
+            ++items;
+            const int64_t s = a->d.leaf_start[u.x + 1] - a->d.leaf_start[u.x];
+            const int64_t r = a->d.leaf_start[u.y + 1] - a->d.leaf_start[u.y];
+            cost = u.x == u.y ? at_self_cost(s) : 3 * at_pair_steps(s, r);
+        } else {
+            ++units;
+            const int4 c = a->d.cell[u.x];
+            int64_t nsrc = 0;
+            for (int e = a->d.u_off[u.x]; e < a->d.u_off[u.x + 1]; ++e) {
+                const int S = a->d.u_idx[e];
+                if (!((u.w >> 4) && a->d.cell[S].x == c.x && a->d.range[S].y >= a->dense_leaf)) nsrc += a->d.range[S].y;
+            }
+            cost = at_unit_cost(nsrc, u.z);
+        }
+        REQUIRE(cost_order((uint64_t)cost) >= last);
+        last = cost_order((uint64_t)cost);
+    }
+    REQUIRE(units > 0 && items > 0);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}, {"held_memory", held_memory},
                                                               {"idle_released", idle_released},
-                                                              {"host_memory", host_memory}};
+                                                              {"host_memory", host_memory},
+                                                              {"work_order", work_order}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     REQUIRE(it != checks.end());
     REQUIRE(child(it->second));
