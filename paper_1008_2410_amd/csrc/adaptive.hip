@@ -517,33 +517,33 @@ __global__ __launch_bounds__(64, sizeof(T) == 4 ? (SRC ? 5 : 6) : 2) void at_bac
 }
 
 // The adjoint's near field over the pair force (dl_dxy without its two parts), over the
-// forward's work list: its units, and its mutual items with each pair evaluated once.
-template <typename T, int KIND>
+// forward's work list: its units, and its mutual items with each pair evaluated once.  FP64 alone
+// (see run_backward).
+template <int KIND>
 __global__ __launch_bounds__(64, 3) void at_force_kernel(
     const int4 *__restrict__ work, const int4 *__restrict__ cell, const int2 *__restrict__ range,
     const int *__restrict__ u_off, const int *__restrict__ u_idx, const int *__restrict__ tile_start,
     const double4 *__restrict__ tile_box, const int *__restrict__ leaf_start, const int *__restrict__ leaf_tile,
-    const float4 *__restrict__ tile_box_leaf, const SoaRec<T> rec, double x0, double y0, double side, double alpha,
+    const float4 *__restrict__ tile_box_leaf, const SoaRec<double> rec, double x0, double y0, double side, double alpha,
     double cut, int dense, int64_t n, double2 *__restrict__ near, double *__restrict__ near_phi,
-    c2<T> *__restrict__ slots, T *__restrict__ phi_slots)
+    double2 *__restrict__ slots, double *__restrict__ phi_slots)
 {
     constexpr int NS = kSums<KIND>;
-    __shared__ NearLds<T, KIND> lds;
+    __shared__ NearLds<double, KIND> lds;
     const int4 u = work[blockIdx.x];
     if (u.w & kMutualItem) {
         const double step = alpha * ldexp(side, -(u.w >> 9));
         mutual_item<KIND>(u, lds, rec,
-                          MutualTree{leaf_start, leaf_tile, tile_box_leaf, (float)(cut / (step * step)),
-                                     force_series_leaf2(step)},
-                          MutualParts{}, (T)step, n, slots, phi_slots);
+                          MutualTree{leaf_start, leaf_tile, tile_box_leaf, (float)(cut / (step * step)), 0.0f},
+                          MutualParts{}, step, n, slots, phi_slots);
         return;
     }
     const int lane = threadIdx.x;
     const bool skip_dense = (u.w >> 4) != 0;
     const UnitLanes ul(lane, u.z, u.w & 15);
     const int i = u.y + min(ul.t, u.z - 1);
-    T tiqy;
-    const rec_t<T> ti = load_rec<KIND>(rec, i, tiqy);
+    double tiqy;
+    const double4 ti = load_rec<KIND>(rec, i, tiqy);
     const int A = u.x;
     const int4 cla = cell[A];
     const double2 ca = cell_centre(x0, y0, side, cla);
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(64, 3) void at_force_kernel(
         // lane k: the k-th source leaf of this group of U(A)
         int s0 = 0, len = 0;
         bool far = false;
-        T ox = 0, oy = 0;
+        double ox = 0, oy = 0;
         if (e0 + lane < eend) {
             const int S = u_idx[e0 + lane];
             const int4 cls = cell[S];
@@ -562,8 +562,8 @@ __global__ __launch_bounds__(64, 3) void at_force_kernel(
             s0 = r.x;
             len = skip_dense && cls.x == cla.x && r.y >= dense ? 0 : r.y;  // else in a mutual item
             const double2 cs = cell_centre(x0, y0, side, cls);
-            ox = (T)(alpha * (cs.x - ca.x));  // moved into the frame of A
-            oy = (T)(alpha * (cs.y - ca.y));
+            ox = alpha * (cs.x - ca.x);  // moved into the frame of A
+            oy = alpha * (cs.y - ca.y);
             if (len > 0 && len <= 64) {  // one tile (a larger leaf takes the general form)
                 const double4 sb = tile_box[tile_start[S]];
                 const double gx = fmax(0.0, fmax(sb.x - tb.z, tb.x - sb.z));
@@ -573,19 +573,19 @@ __global__ __launch_bounds__(64, 3) void at_force_kernel(
         }
         auto stage = [&](int e, int j) {
             const int from = __shfl(s0, e);
-            const T sx = __shfl(ox, e), sy = __shfl(oy, e);
+            const double sx = __shfl(ox, e), sy = __shfl(oy, e);
             stage_source<KIND>(lds.a, lds.qa, rec, j >= 0 ? from + j : -1, sx, sy);
         };
         source_batches<64>(far ? 0 : len, stage, [&](int count) {
-            T f[NS] = {};
-            force_batch<T, KIND, 0>(lds.a, lds.qa, count, ul.k, ul.K, ti, tiqy, f);
-            for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
+            double f[NS] = {};
+            force_batch<double, KIND, 0>(lds.a, lds.qa, count, ul.k, ul.K, ti, tiqy, f);
+            for (int m = 0; m < NS; ++m) sum[m] += f[m];
         });
         if (__any(far))
             source_batches<64>(far ? len : 0, stage, [&](int count) {
-                T f[NS] = {};
-                force_batch<T, KIND, 2>(lds.a, lds.qa, count, ul.k, ul.K, ti, tiqy, f);
-                for (int m = 0; m < NS; ++m) sum[m] += (double)f[m];
+                double f[NS] = {};
+                force_batch<double, KIND, 2>(lds.a, lds.qa, count, ul.k, ul.K, ti, tiqy, f);
+                for (int m = 0; m < NS; ++m) sum[m] += f[m];
             });
     }
     for (int m = 0; m < NS; ++m) sum[m] = ul.reduce(sum[m]);
@@ -988,17 +988,16 @@ void launch_atree_backward_near(const AtreeCall &c, bool src, hipStream_t s)
 
 namespace {
 
-template <typename T, int KIND> void force_launch(const AtreeCall &c, const ForceNear &near, hipStream_t s)
+template <int KIND> void force_launch(const AtreeCall &c, const ForceNear &near, hipStream_t s)
 {
     const fmm_atree *t = c.t;
     const AtreeDev &d = t->d;
-    const double cut = c.is_double ? 39.0 : 27.0;  // as for the forward near field
-    at_force_kernel<T, KIND><<<(unsigned)t->nwork, 64, near_lds_reserve(c, sizeof(NearLds<T, KIND>)), s>>>(
+    at_force_kernel<KIND><<<(unsigned)t->nwork, 64, near_lds_reserve(c, sizeof(NearLds<double, KIND>)), s>>>(
         d.work, d.cell, d.range, d.u_off, d.u_idx, d.tile_start, d.tile_box, d.leaf_start, d.leaf_tile,
         d.tile_box_leaf,
-        SoaRec<T>{(const c2<T> *)t->d_pos[c.is_double], (const T *)t->wsp->gam, (T)c.alpha, (const c2<T> *)t->wsp->qt},
-        t->x0, t->y0, t->side, c.alpha, cut, t->dense_leaf, t->n, near.near, near.phi, (c2<T> *)near.slots,
-        (T *)near.phi_slots);
+        SoaRec<double>{(const double2 *)t->d_pos[1], (const double *)t->wsp->gam, c.alpha, (const double2 *)t->wsp->qt},
+        t->x0, t->y0, t->side, c.alpha, 39.0, t->dense_leaf, t->n, near.near, near.phi, (double2 *)near.slots,
+        (double *)near.phi_slots);  // (the cut as for the forward near field)
 }
 
 }  // namespace
@@ -1006,7 +1005,7 @@ template <typename T, int KIND> void force_launch(const AtreeCall &c, const Forc
 void launch_atree_force(const AtreeCall &c, const ForceNear &near, hipStream_t s)
 {
     if (c.t->nwork == 0) return;
-    auto k = near.phi ? force_launch<double, kForcePhi> : force_launch<double, kForce>;
+    auto k = near.phi ? force_launch<kForcePhi> : force_launch<kForce>;
     k(c, near, s);
 }
 

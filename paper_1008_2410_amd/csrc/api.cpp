@@ -324,7 +324,6 @@ FarArgs far_args(const fmm_tree *t, const Workspace &ws, int p, int precision, b
     a.pos = t->d_pos[precision == FMM_FP64];
     a.gam = ws.gam;
     a.rec_is_double = precision == FMM_FP64;
-    a.charge_kind = adjoint ? 1 : 0;
     a.adj = adjoint ? ws.adj : nullptr;
     return a;
 }

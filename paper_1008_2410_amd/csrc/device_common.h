@@ -179,7 +179,6 @@ template <> __device__ __forceinline__ double tiny<double>() { return 1e-300; }
 // f = Gamma (1 - e)/s evaluated as q - e q with q = Gamma/s (one fused multiply-add);
 // on a far tile e rounds to 0 against 1 and f = q.
 __device__ __forceinline__ float exp_neg_scaled(float s) { return __builtin_amdgcn_exp2f(-s); }
-__device__ __forceinline__ double exp_neg_scaled(double s) { return exp(-s); }
 
 template <typename T, bool FAR>
 __device__ __forceinline__ void p2p_pair(const rec_t<T> &rj, T tx, T ty, T &fu, T &fv)
@@ -190,7 +189,7 @@ __device__ __forceinline__ void p2p_pair(const rec_t<T> &rj, T tx, T ty, T &fu, 
     const T q = recip(s) * rj.z;
     T f;
     if (FAR) f = q;
-    else if (sizeof(T) == 4) f = fma(-exp_neg_scaled(s), q, q);
+    else if constexpr (sizeof(T) == 4) f = fma(-exp_neg_scaled(s), q, q);
     else f = one_minus_exp(s) * q;
     fu = fma(f, ddy, fu);
     fv = fma(f, ddx, fv);

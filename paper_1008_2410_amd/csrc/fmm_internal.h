@@ -238,8 +238,7 @@ struct FarArgs {
     const void *pos;           // the tree's leaf-unit coordinates in the records' precision (or null)
     const void *gam;           // circulations in tree order in that precision (null: P2M reads `gamma`)
     int rec_is_double;
-    int charge_kind;           // 0: real Gamma in rec.z -> c = -i Gamma/(2 pi); 1: complex q from adj array
-    const double2 *adj;        // complex charges in sorted order (charge_kind 1)
+    const double2 *adj;        // complex charges in sorted order (null: real circulations, c = -i Gamma/(2 pi))
     GammaRows gamma{};         // the circulations
     bool no_lds = false;       // beside a capped near field, which holds the LDS: kernels without any
 };

@@ -225,7 +225,7 @@ static void check_far(const FarArgs &a)
     const int64_t d = level_base(std::min(a.split, L) + 1), f = level_base(L + 1) - d;
     REQUIRE(on_device(a.mp_d, d * a.p * sizeof(double2)) && on_device(a.lo_d, d * a.p * sizeof(double2)));
     if (f > 0) REQUIRE(on_device(a.mp_f, f * a.p * sizeof(float2)) && on_device(a.lo_f, f * a.p * sizeof(float2)));
-    if (a.charge_kind) REQUIRE(on_device(a.adj, a.t->n * sizeof(double2)));
+    if (a.adj) REQUIRE(on_device(a.adj, a.t->n * sizeof(double2)));
 }
 
 void launch_zero(void *p, size_t bytes, hipStream_t) { REQUIRE(on_device(p, bytes)); }
@@ -253,7 +253,10 @@ void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int
 void launch_far_chain(const FarArgs &a, hipStream_t, const FarArgs *b)
 {
     check_far(a);
-    if (b) check_far(*b);
+    if (b) {
+        REQUIRE(b->adj);
+        check_far(*b);
+    }
 }
 void launch_finalize(const fmm_tree *t, const FarArgs &, const double2 *near, const void *, int, double, double *,
                      double *, double *, void *stage, const double *, double, hipStream_t)
