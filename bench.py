@@ -164,8 +164,8 @@ def cpu_baseline_leg(w, sample_frac_log4=0):
 
 
 def lattice_overlap_leg(torch, dev, workloads, steps):
-    """The jittered 1024^2 lattice as configured (FP64, depth 8, p = 12, coarse levels <= 5
-    in the one-workgroup kernel on the second stream): the evaluation overlapped and
+    """The jittered 1024^2 lattice as configured (FP64, depth 8, p = 12, coarse levels <= 5,
+    the far chain on the second stream): the evaluation overlapped and
     serialised, and the overlap fraction (T_P2P + T_far - T_both) / min(T_P2P, T_far) from
     the serialised stage times and the overlapped span between the pack and final stages."""
     from paper_1008_2410_amd import _lib, fmm

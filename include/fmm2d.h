@@ -241,6 +241,11 @@ int fmm_velocity_parts(fmm_tree *tree, const double *gamma, double sigma, int p,
  *              expansion;
  *   dl_dxy     device, (n, 2) FP64: dl_dxeval + dl_dxsrc, the derivative for particles
  *              moving as a whole (source and evaluation point, the tree's cells held fixed).
+ *              With either part asked for it is their sum bit for bit.  By itself (and in
+ *              fmm_transport_vjp) its near field may come from one sum per pair of particles
+ *              and agrees with theirs to rounding: in FMM_MIXED the particle's own Gamma and
+ *              dL/du enter that sum in FP32 where both leaves are dense, and no error against
+ *              64-bit sums was measured above that of the two parts.
  * Any output may be NULL to skip it.  Other arguments as fmm_velocity.  The paper has no
  * backward pass; this is the transpose of the discrete operator defined by stages 4-10.
  */

@@ -425,11 +425,11 @@ int run_backward(fmm_atree *t, const double *gamma, double sigma, int p, int pre
     if ((rc = ensure_ws(t, p, precision)) || (rc = ensure_ws_backward(t, src)) ||
         (rc = ensure_coords(t, precision, ms)) || (rc = ensure_m2l_plan(t, p, ms, tabs)))
         return rc;
-    // the pair force for dl_dxy without its two parts, as for the uniform tree, in FP64.  In FP32 a
-    // position gradient over small sigma can be as large as the result it is added to (clusters
-    // in leaves of 8 sigma: lambda + h J^T lambda, h J of order 1 and more), so that a roundoff of
-    // another order of summation is one of the result (2e-7): there the order stays, leaf by leaf.
-    // (1000001 clustered particles at depth 13: 0.774 ms, 0.662 with the pair force.)
+    // The pair force for dl_dxy without its two parts, as for the uniform tree, in FP64.  In FP32 its
+    // target-centric units are further from 64-bit sums than the separate sums (see p2p_force_kernel),
+    // and an adaptive tree has units of several levels throughout: 20001 uniform and patch particles,
+    // max_leaf 48, random cotangents, 1.04 to 1.16 times their error.  So mixed calls take the separate
+    // sums, leaf by leaf (1000001 clustered particles at depth 13: 0.774 ms, 0.662 with the pair force).
     const AtreeWs &w = *t->wsp;
     const bool force = precision == FMM_FP64 && out.dxy && !out.dxe && !out.dxs && w.phi_slots;
     if (!force) ss = ms;

@@ -1,5 +1,5 @@
 // Stages 1-3 of the adaptive tree on the GPU: keys on the finest grid, the stable sort,
-// the cells level by level (a cell splits while it holds more than max_leaf particles
+// the cells of all levels at once (a cell splits while it holds more than max_leaf particles
 // and lies above max_depth), the same-level neighbours of every cell, the U, V, W and X
 // lists, the leaves in sorted order with their 64-particle tiles and tile boxes, and
 // the near-field plan.
@@ -10,9 +10,8 @@
 // arithmetic (not contracted); and the sorts are stable on the same keys.  So the two
 // builds give bit-identical evaluations.
 //
-// Neighbours come from the tree itself: the cell at (ix + dx, iy + dy) on level l is a
-// child of the parent or of one of the parent's same-level neighbours, so each cell's
-// eight neighbour slots follow from its parent's, level by level, without a search.
+// The cells of a level are in Morton order, so the neighbour at (ix + dx, iy + dy) is found by
+// a binary search for its Morton code among them.
 #include <algorithm>
 #include <cmath>
 #include <string>

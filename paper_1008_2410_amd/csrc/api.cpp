@@ -1,5 +1,5 @@
-// C ABI of the gfx950 FMM library (include/fmm2d.h): argument checks, the host-side
-// tree build (stages 1-3 of Fig. fmmStages), workspace management and the two-stream
+// C ABI of the gfx950 FMM library (include/fmm2d.h): argument checks, the trees' lifetime
+// (built by tree_build.hip or host_tree.cpp), workspace management and the two-stream
 // schedule of stages 4-10.
 #include <algorithm>
 #include <cmath>
@@ -362,7 +362,8 @@ double far_near_ratio(const fmm_tree *t)
 //  - In the mixed form calls beyond a far/near ratio of kSerialRatio are serialised: there is
 //    too little near field to run beside.  Up to 2.4 the best cap still gained (uniform 2^22,
 //    depth 10: 2.44 against 2.56 ms).
-//  - FP64 calls overlap (1024^2 lattice: 0.416 against 0.454 ms).
+//  - FP64 calls overlap (1024^2 lattice: 0.347 against 0.390 ms in a row of calls, 0.40 against 0.41
+//    alone and in the first twenty after a pause; 2^21 uniform, depth 9: 0.91 against 1.03).
 constexpr double kSerialRatio = 4.0, kSerialNear = 0.020;
 bool call_overlaps(const fmm_tree *t, int precision)
 {
@@ -923,9 +924,12 @@ int run_backward(fmm_tree *t, const double *gamma, double sigma, int p, int prec
     hipStream_t ss = side_stream ? (hipStream_t)side_stream : t->aux.stream;
     const double alpha = record_alpha(sigma, precision);
     const int is_double = precision == FMM_FP64;
-    // The pair force gives dl_dxy without its two parts, in half the near field's time.  Where
-    // the outputs outgrow the last-level cache the separate sums stay: there a step's adjoint
-    // has the bits of velocity_backward's parts added up, and callers compare the two.
+    // The pair force gives dl_dxy without its two parts, in half the near field's time over dense
+    // leaves.  Where the outputs outgrow the last-level cache the separate sums stay, for their bits
+    // and not for their time: there a step's adjoint has the bits of velocity_backward's parts added
+    // up, which callers compare.  It costs 2^23 patch particles 18.4 against 11.7 ms at depth 9 and
+    // 7.4 against 5.3 at depth 10, 2^24 at depth 10 23.4 against 15.9 (with dl_dgamma 23.7 against
+    // 19.4), 2^24 uniform 7.10 against 6.76.
     ForceNear near;
     const bool force = out.dxy && !out.dxe && !out.dxs && !outputs_windowed(t->n, kForceRow) &&
                        force_accurate(t, precision) && force_arrays(t, ws, out.dg != nullptr, near);

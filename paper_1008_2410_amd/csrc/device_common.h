@@ -224,9 +224,10 @@ __device__ __forceinline__ void p2p_tile_any(const rec_t<T> *tile, int len, int 
 // the gradient of (v_y dx' - v_x dy') g/s', and the sum of the evaluation part Gamma_j (q_i A, B)
 // and the source part Gamma_i (q_j ..) of the separate sums below.  (As a turned product of v with
 // h conj(dz')^2 +- lambda e a step took three operations more, 28 in FP32 instead of 25, 62 in FP64
-// with Phi instead of 60: adjoint of 2^22 patch particles, mixed, 2.90 -> 2.77 ms, of 2^20 uniform
-// 0.395 -> 0.372.)  Two sums per particle in place of seven, and both particles of a pair
-// are served by one evaluation of the weights.  The sums kept are -dL/dx/ka and dL/dy/ka, the
+// with Phi instead of 60: adjoint of 2^22 patch particles, mixed, 2.90 -> 2.77 ms; the errors are
+// the same.)  Two sums per particle in place of seven, and both particles of a pair
+// are served by one evaluation of the weights.  In FP32 it serves the mutual items; the
+// target-centric units take the separate sums there (p2p_force_kernel says why).  The sums kept are -dL/dx/ka and dL/dy/ka, the
 // signs of the velocity's.  Phi_i = alpha sum_j q_j (g/s') conj(dz') enters by its imaginary
 // part alone.
 //
@@ -689,7 +690,7 @@ struct MutualTree {
 };
 
 // The tiles of R that an item takes (the particles from a0 to a1), and where its sums for the
-// particles of S go: their slot, or for a part of an item (see MutualPart) an array of the part's
+// particles of S go: their slot, or for a part of an item (see MutualParts) an array of the part's
 // own.
 template <typename T, int KIND> struct MutualRange {
     int a0, a1;

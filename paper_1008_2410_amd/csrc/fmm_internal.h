@@ -115,7 +115,7 @@ struct Workspace {
     // backward pass
     double2 *adj = nullptr;       // per sorted particle: adjoint charge q (sorted order)
     double4 *bwd_near = nullptr;  // per sorted particle: near sums of Im Phi, A (2) and B
-    double2 *mp2_d = nullptr, *lo2_d = nullptr;  // mp2_* = mp_* (the charges q reuse the multipoles)
+    double2 *mp2_d = nullptr, *lo2_d = nullptr;  // the expansions of the charges q
     float2 *mp2_f = nullptr, *lo2_f = nullptr;
     void *rec2 = nullptr;         // adjoint charges q in FP32 for the mixed near field
     double4 *bwd_src = nullptr;   // per sorted particle: near sums of the source-position terms
@@ -262,7 +262,7 @@ void launch_pack(const fmm_tree *t, const GammaRows &gamma, int is_double, void 
 void launch_leaf_coords(const fmm_tree *t, int is_double, void *pos, hipStream_t s);
 void launch_p2p_forward(const fmm_tree *t, const void *pos, const void *gam, int is_double, double alpha,
                         double2 *near, void *slots, hipStream_t s);
-// Stages 4-7 (P2M, M2M, M2L, L2L), or 5-7 without P2M when it was launched on its own.
+// Stages 4-7 (P2M, M2M, M2L, L2L).
 // b: a second set of expansions (its own storage and charges, the rest as a's), in the same launches.
 void launch_far_chain(const FarArgs &a, hipStream_t s, const FarArgs *b = nullptr);
 // uv alone is written through `stage` (a buffer of n double2); with base, uv = base + h u.

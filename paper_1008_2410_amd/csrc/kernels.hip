@@ -1,7 +1,7 @@
 // gfx950 kernels of the FMM evaluation phase (stages 4-10 of Fig. fmmStages of
 // Knepley, arXiv:1008.2410) and their host launchers.
 //
-// Conventions (shared with the host code in api.cpp / tree.cpp):
+// Conventions (shared with api.cpp, host_tree.cpp and tree_build.hip):
 //  - Particles are in leaf-Morton order ("sorted"); d_perm maps a sorted slot to the
 //    user index, d_leaf_of to its leaf.
 //  - Complex charge c_j = -i Gamma_j / (2 pi) (the factor of the multipole

@@ -2,9 +2,9 @@
 // offsets, per-level occupancy, interaction-list cell lists, near-field work lists and
 // the statistics of fmm_tree_info.
 //
-// The arrays equal those of the host build of api.cpp element for element (same
-// arithmetic for the binning and tile boxes, stable sorts with the same keys), so either
-// build gives bit-identical evaluations.  The building blocks are a stable LSD radix
+// The arrays equal those of the host build (host_tree.cpp) element for element (same
+// arithmetic for the binning and tile boxes, stable sorts with the same keys, the cost
+// orders included), so either build gives bit-identical evaluations.  The building blocks are a stable LSD radix
 // sort of (64-bit key, 32-bit value) pairs with 8-bit digits and a device-wide
 // exclusive scan, both written here.
 #include <algorithm>
@@ -727,7 +727,7 @@ __global__ __launch_bounds__(256) void k_gpos2(const int *__restrict__ gpos1, co
 }
 
 // ---------------------------------------------------------------------------------
-// Near-field plan (the mutual form; see build_near_plan in api.cpp for its meaning).
+// Near-field plan (the mutual form; see build_near_plan_device for its meaning).
 // Per leaf: its entries (target-centric units, then the self item, then the items of
 // its dense upper neighbours), their costs, the slot mask; then a stable sort by cost.
 // ---------------------------------------------------------------------------------
