@@ -384,12 +384,12 @@ __device__ __forceinline__ void p2p_force_unit(const int4 u, rec_t<T> *tile, T *
 // The position derivative is what is left of two larger sums, so the rounding of FP32 running sums
 // shows in it.  Errors of dl_dx against the FP64 call, in units of the separate sums' (uniform
 // particles, sigma of 0.05 to 1 leaf, smooth and random circulations and cotangents, worst of 16):
-//  - mutual items with running sums over a whole tile: 1.15 at 32 particles per leaf, 1.05 at 48, 1.07
-//    at 64, 0.91 at 250; with each chunk's 16 terms added up apart 0.98, 0.97, 0.96 and 0.81 (2^22
-//    patch particles: 3.63 ms either way);
+//  - mutual items with running sums over a whole tile: 1.04 at 32 particles per leaf, 1.05 at 48, 1.07
+//    at 64, 0.91 at 250; with each chunk's 16 terms added up apart 0.98, 0.97, 0.96 and 0.81 (2^20
+//    uniform particles at depth 7: 0.433 -> 0.431 ms);
 //  - target-centric units over the pair force 1.54 at 4 particles per leaf, 1.45 at 10, 1.40 at 16 and
 //    24.  In FP32 they take the separate sums, whose terms meet the target's own FP64 factors after
-//    the sums: 1.00 at each (2^20 uniform particles at depth 8: 0.373 -> 0.397 ms).
+//    the sums: 1.00 at each (2^20 uniform particles at depth 8: 0.373 -> 0.400 ms).
 template <typename T, int KIND>
 __global__ __launch_bounds__(64, sizeof(T) == 4 ? (KIND == kForcePhi ? 5 : 6) : 3) void p2p_force_kernel(
     const int4 *__restrict__ work, const SoaRec<T> rec, const ForceTargets own, const MutualTree mt, int nside, T step,
