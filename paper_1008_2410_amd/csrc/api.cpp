@@ -159,7 +159,8 @@ int split_level(const fmm_tree *t, int precision)
 
 // A workspace last used by another tree (a rebuild's hand-over, or a tree sharing it):
 // multipoles of cells that are empty in this tree must read as zero (the M2L kernels
-// read them unconditionally), so the multipole arrays are cleared.  Locals and
+// read them unconditionally), so the multipole arrays are cleared, by a kernel: the call
+// may be captured, and memset nodes of a graph are not relied on.  Locals and
 // per-particle arrays are written in full by every call before they are read.
 int clear_multipoles(const fmm_tree *t, hipStream_t s)
 {
@@ -169,9 +170,10 @@ int clear_multipoles(const fmm_tree *t, hipStream_t s)
     const int64_t cells_f = level_base(t->depth + 1) - cells_d;
     const size_t bd = (cells_d * ws.p + kCoefPad) * sizeof(double2), bf = (cells_f * ws.p + kCoefPad) * sizeof(float2);
     for (double2 *m : {ws.mp_d, ws.mp2_d})
-        if (m) HIP_TRY(hipMemsetAsync(m, 0, bd, s));
+        if (m) launch_zero(m, bd, s);
     for (float2 *m : {ws.mp_f, ws.mp2_f})
-        if (m && cells_f > 0) HIP_TRY(hipMemsetAsync(m, 0, bf, s));
+        if (m && cells_f > 0) launch_zero(m, bf, s);
+    HIP_TRY(hipGetLastError());
     return FMM_OK;
 }
 

@@ -51,6 +51,7 @@ namespace {
 std::map<char *, size_t> g_live;  // device allocations
 size_t g_used = 0;
 int64_t g_allocs = 0, g_frees = 0, g_waits = 0;  // calls that a stream capture refuses
+int64_t g_memsets = 0;                           // and that must not become nodes of a graph
 int64_t g_fail_from = -1;                        // allocations from this one on fail
 size_t g_capacity = SIZE_MAX;                    // so do those that would exceed this
 size_t g_pool_used = 0, g_pool_idle = 0;         // of the stream-ordered pool
@@ -142,7 +143,11 @@ hipError_t hipMemset(void *d, int v, size_t n)
     memset(d, v, n);
     return hipSuccess;
 }
-hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t)
+{
+    ++g_memsets;
+    return hipMemset(d, v, n);
+}
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free((void *)s); return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
@@ -228,7 +233,11 @@ static void check_far(const FarArgs &a)
     if (a.adj) REQUIRE(on_device(a.adj, a.t->n * sizeof(double2)));
 }
 
-void launch_zero(void *p, size_t bytes, hipStream_t) { REQUIRE(on_device(p, bytes)); }
+void launch_zero(void *p, size_t bytes, hipStream_t)
+{
+    REQUIRE(on_device(p, bytes) && bytes % 8 == 0);
+    memset(p, 0, bytes);
+}
 void launch_widen_perm(const fmm_tree *, int64_t *, int32_t *, hipStream_t) {}
 GammaRows launch_stage_in(const fmm_tree *t, const double *gamma, int64_t row, hipStream_t)
 {
@@ -630,6 +639,34 @@ void work_order()
     REQUIRE(units > 0 && items > 0);
 }
 
+// Trees that take turns with one workspace: a call clears what the other tree left in the multipoles,
+// with a kernel (a call may be captured, and a memset is not to become a node of a graph).
+void shared_workspace()
+{
+    for (int precision : {FMM_FP64, FMM_MIXED}) {
+        const int64_t n = 3000;
+        std::vector<double> g(n, 1.0), dl(2 * n, 1.0), dx(2 * n), uv(2 * n);
+        fmm_tree *t[2] = {uniform_tree(n, 7), uniform_tree(n, 7)};
+        REQUIRE(fmm_share_workspace(t[1], t[0]) == FMM_OK);
+        auto calls = [&](fmm_tree *tree) {
+            REQUIRE(fmm_velocity(tree, g.data(), 0.01, 9, precision, nullptr, nullptr, uv.data()) == FMM_OK);
+            REQUIRE(fmm_transport_vjp(tree, g.data(), 0.01, 9, precision, dl.data(), 1.0, 0, nullptr, nullptr, nullptr,
+                                      dx.data()) == FMM_OK);
+        };
+        for (fmm_tree *tree : t) calls(tree);
+        const int64_t a = g_allocs, w = g_waits, m = g_memsets;
+        Workspace &ws = *t[0]->wsp;
+        for (int k = 0; k < 4; ++k) {
+            auto *left = (double *)(precision == FMM_FP64 ? (void *)ws.mp_d : (void *)ws.mp_f);
+            left[100] = 1.0;  // (a cell that the next tree leaves empty)
+            ws.mp2_d[50].x = 1.0;
+            calls(t[k % 2]);
+            REQUIRE(left[100] == 0.0 && ws.mp2_d[50].x == 0.0);
+            REQUIRE(g_allocs == a && g_waits == w && g_memsets == m);
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -637,7 +674,8 @@ int main(int argc, char **argv)
     const std::map<std::string, void (*)()> checks = {{"call_memory", call_memory}, {"warm_calls", warm_calls}, {"held_memory", held_memory},
                                                               {"idle_released", idle_released},
                                                               {"host_memory", host_memory},
-                                                              {"work_order", work_order}};
+                                                              {"work_order", work_order},
+                                                              {"shared_workspace", shared_workspace}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     REQUIRE(it != checks.end());
     REQUIRE(child(it->second));

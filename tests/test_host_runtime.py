@@ -28,7 +28,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["call_memory", "warm_calls", "held_memory", "idle_released",
-                                   "host_memory", "work_order"])
+                                   "host_memory", "work_order", "shared_workspace"])
 def test_host_runtime(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and f"{check} passed" in r.stdout, r.stdout[-3000:] + r.stderr[-1000:]
